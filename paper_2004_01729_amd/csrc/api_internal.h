@@ -98,6 +98,7 @@ struct ftcc_ctx {
   std::vector<Instance> inst;
   std::vector<void*> allocs;
   Program prog;
+  std::vector<InstMomentum> one_block;        // small dense problems: labels that put everything into one block
   std::unique_ptr<Executor> ex_main, ex_d, ex_g;   // ex_g: integral gradients (built on first use)
   std::map<std::pair<int, int>, double*> g_derived, g_cgrad;   // (tensor, problem) buffers of ex_g
   bool built = false, solved = false, have_lambda = false;

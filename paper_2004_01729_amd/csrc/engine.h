@@ -92,13 +92,16 @@ struct Launch {
   int min_k = 0;                    // smallest K of the launch's GEMM problems
   void* d_tasks = nullptr;          // SGEMM / ELEM: task list
   int n_tasks = 0;
+  int n_tile = 0;                   // SGEMM: leading tasks that are block tiles
+  bool narrow = false;              // SGEMM: some of them are not 64 x 64
   void* d_bfirst = nullptr;         // ELEM / DOTB: per 256-element block, the task of its first element
   void* d_red = nullptr;            // SGEMM: reductions of split inner ranges
   int n_red = 0;
-  bool zero_fill = false;           // ELEM with alpha = beta = 0 (host copies kept for merging)
-  std::vector<ElemProblem> eprobs;
+  std::vector<ElemProblem> eprobs;  // ELEM: host copies of the descriptors, kept until the lists are fused
+  std::vector<ElemSource> esrcs;
   std::vector<ElemTask> etasks;
-  long long n_elem = 0;             // ELEM: allowed elements
+  void* d_src = nullptr;            // ELEM: source list
+  long long n_elem = 0;             // ELEM: elements, problems padded to whole blocks
   int dot_blocks = 0;
   void* d_desc = nullptr;
   int* d_prefix = nullptr;
@@ -255,6 +258,32 @@ class Executor {
   bool elem_blocked(std::vector<Launch>& dst, const PerProb& X, const std::string& xi, const PerProb& Y,
                     const std::string& yi, double alpha, double beta, int t_y, int t_x, const std::string& tag,
                     const std::vector<const double*>* scale = nullptr, int xp = -1, int yp = -1);
+  // one source of a blocked elementwise sum: alpha * scale * X[xi]
+  struct SumTerm {
+    PerProb X;
+    std::string xi;
+    int t_x;
+    double alpha;
+    std::vector<const double*> scale;   // empty: no device scalar
+    int xp = -1;                        // storage of X (-1: as its tensor)
+  };
+  // Y[yi] = beta Y + sum of the terms over Y's allowed elements
+  bool sum_blocked(std::vector<Launch>& dst, const std::vector<SumTerm>& terms, const PerProb& Y,
+                   const std::string& yi, double beta, int t_y, const std::string& tag, int yp = -1);
+  // One op of a launch list before lowering: out[oi] (+)= alpha A[ai] (B[bi]); the keys
+  // name the buffers (a tensor's values or its gradient) for the order of writes and reads.
+  struct OpInst {
+    int okey, akey, bkey;
+    const PerProb *out, *A, *B;
+    std::string oi, ai, bi;
+    double alpha;
+    bool acc;
+    int a_const, b_const, a_val, b_val, t_out, t_a, t_b;
+    std::string tag;
+  };
+  void lower(std::vector<Launch>& dst, const std::vector<OpInst>& ops, const std::vector<int>& zeroed,
+             const std::vector<PerProb>& zero_bufs);
+  void lower_one(std::vector<Launch>& dst, const OpInst& o, const PerProb& out, bool acc);
   PerProb const_permuted(int tensor, const PerProb& X, const std::string& xi, const std::string& yi);
   void* upload(const void* host, size_t bytes);
   void dump_plan() const;
@@ -263,14 +292,14 @@ class Executor {
   std::vector<ProblemRef> probs_;
   Scratch* scratch_ = nullptr;
   bool inline_setup_ = false;
-  // consecutive zero fills write disjoint buffers: one launch serves them all
-  void merge_fills(std::vector<Launch>& L);
   // Momentum-blocked lists: every launch moves to the earliest dependency level
   // its byte ranges allow, and the blocked contractions (and the blocked
   // elementwise ops) of one level become one launch each.  Every buffer sees its
   // writes in program order, so results are unchanged.
   void fuse_levels(std::vector<Launch>& L);
   Launch merge_sgemm(const std::vector<Launch*>& parts);
+  void upload_sgemm(Launch& L);
+  void upload_elem(Launch& L);
   Launch merge_elem(const std::vector<Launch*>& parts);
   void release(const std::vector<void*>& dev);
   std::function<double*(int, size_t)> const_alloc_;
@@ -308,6 +337,7 @@ class Executor {
                                 const std::string& yi, bool yp, const std::vector<int>& signs);
   std::vector<char> packed_;               // per tensor: stored packed (n^(rank-1) doubles)
   bool pack_on_ = false;                   // packing applies to this executor's problems
+  bool one_per_label_ = false;             // every orbital of every instance has its own label
   void plan_packing(bool want_backward);
   // constants (and derived constants) read through packed copies: no gradient asked
   // for them, and every op that reads them lowers to blocked kernels

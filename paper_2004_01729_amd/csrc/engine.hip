@@ -702,10 +702,12 @@ int Executor::n_packed() const {
 void Executor::plan_packing(bool want_backward) {
   const int nt = (int)prog_->t.size();
   packed_.assign(nt, 0);
-  pack_on_ = false;
-  if (mom_.empty() || !packing_enabled()) return;
+  pack_on_ = one_per_label_ = false;
+  if (mom_.empty()) return;
   for (const ProblemRef& p : probs_)
     if (p.inst < 0 || p.inst >= (int)mom_.size() || !mom_[p.inst] || !labels_distinct(*mom_[p.inst])) return;
+  one_per_label_ = true;
+  if (!packing_enabled()) return;
   pack_on_ = true;
   for (int k = 0; k < nt; ++k) {
     const TensorDecl& d = prog_->t[k];
@@ -905,8 +907,28 @@ static int sgemm_shape(int ml, int nl, int kl, long cap) {
 
 constexpr long kSgemmThinSteps = 16;
 
-// wave latencies of a task by the same count (the order of a merged task list)
+// Block-tile shape of one block of a blocked contraction, or 0 (wave tiles).  A
+// block tile pays when both its sides exceed one 16-wide MFMA tile and it is long on
+// one side (27-orbital step 515 ms with wave tiles only, 265 with block tiles) or over
+// the inner range (33 x 33 outputs over 33^3: 100 us in wave tiles of 64 indices plus
+// 60 us to add them, 20 us together in block tiles); a narrow side of at most 32 takes
+// the 128-long tiles.
+constexpr int kTileMin = 64;
+constexpr int kTileSpread = 144;
+static int sgemm_tile_shape(int ml, int nl, int kl) {
+  if (std::min(ml, nl) <= 16 || (std::max(ml, nl) < kTileMin && kl < 512)) return 0;
+  if (nl <= 32 && ml > 64) return kTile128x32;
+  if (ml <= 32 && nl > 64) return kTile32x128;
+  return kTile64x64;
+}
+
+// workspace units (256 doubles) of one part of a split tile
+static int part_units(int shape) { return shape >= kTile64x64 ? 16 : 1; }
+
+// wave latencies of a task by the same count (the order of a merged task list);
+// block tiles stand before every wave task, longest first
 static long sgemm_task_cost(const SgemmTask& t) {
+  if (t.shape >= kTile64x64) return 1000000L + t.klen;
   const long per = t.shape ? (8L << ((t.shape >> 6) & 7)) : 32L;
   return 3 + 2 * std::max(1L, (t.klen + per - 1) / per);
 }
@@ -920,6 +942,15 @@ bool Executor::contract_blocked(std::vector<Launch>& dst, const PerProb& out, co
                                 bool acc, const std::string& tag, int t_out, int t_a, int t_b) {
   if (mom_.empty() || t_out < 0 || t_a < 0 || t_b < 0) return false;
   if (!law_ok_[t_out] || !law_ok_[t_a] || !law_ok_[t_b]) return false;
+  // the letter along which a tensor is contiguous (a packed tensor drops its last axis)
+  auto unit_letter = [&](const std::string& idx, int t) {
+    return is_packed(t) ? (idx.size() >= 2 ? idx[idx.size() - 2] : '\0') : idx.back();
+  };
+  // columns of C are the index group that holds its contiguous letter: the other
+  // way round, compute the transpose (with one orbital per momentum the blocks are
+  // a few elements wide and the order does not matter)
+  if (!one_per_label_ && !has(bi, unit_letter(oi, t_out)) && has(ai, unit_letter(oi, t_out)))
+    return contract_blocked(dst, out, oi, alpha, B, bi, A, ai, acc, tag, t_out, t_b, t_a);
   const std::vector<int>&la = law_[t_a], &lb = law_[t_b];
   auto sa = [&](char c) { return la[ai.find(c)]; };
   auto sb = [&](char c) { return lb[bi.find(c)]; };
@@ -979,6 +1010,8 @@ bool Executor::contract_blocked(std::vector<Launch>& dst, const PerProb& out, co
     P.alpha = alpha;
     P.beta = acc ? 1.0 : 0.0;
     P.active = gate_for(dst, p);
+    P.a_inner = has(K, unit_letter(ai, t_a)) ? 1 : 0;
+    P.b_inner = has(K, unit_letter(bi, t_b)) ? 1 : 0;
     pinst[p] = inst;
     const InstMomentum& Mm = *mom_[inst];
     for (const auto& blk : TM.blocks) {
@@ -1000,11 +1033,22 @@ bool Executor::contract_blocked(std::vector<Launch>& dst, const PerProb& out, co
       if (kl == 0 && acc) continue;   // nothing to add; a set writes its zeros
       const int m0 = blk.second.first, ml = blk.second.second;
       const int n0 = nb->second.first, nl = nb->second.second;
-      const int shape = thin_ok ? sgemm_shape(ml, nl, kl, thin_cap) : 0;
-      const int R = shape ? 1 << (shape & 7) : 16, C = shape ? 1 << ((shape >> 3) & 7) : 16;
-      for (int r = 0; r < ml; r += R)
+      int shape = sgemm_tile_shape(ml, nl, kl);
+      int R, C;
+      if (shape) {
+        R = sgemm_tile_rows(shape);
+        C = 4096 / R;
+      } else {
+        shape = thin_ok ? sgemm_shape(ml, nl, kl, thin_cap) : 0;
+        R = shape ? 1 << (shape & 7) : 16;
+        C = shape ? 1 << ((shape >> 3) & 7) : 16;
+      }
+      // bands of 8 tile rows, down the rows first, so that neighbouring tiles share both
+      // operands' panels (see upload_sgemm)
+      for (int band = 0; band < ml; band += 8 * R)
         for (int c = 0; c < nl; c += C)
-          tiles.push_back(Tile{p, m0 + r, std::min(R, ml - r), k0, kl, n0 + c, std::min(C, nl - c), shape});
+          for (int r = band; r < std::min(ml, band + 8 * R); r += R)
+            tiles.push_back(Tile{p, m0 + r, std::min(R, ml - r), k0, kl, n0 + c, std::min(C, nl - c), shape});
       pf[p] += 2.0 * ml * (double)nl * kl;
       bytes += sizeof(double) * ((double)ml * kl + (double)kl * nl + (double)ml * nl * (acc ? 2 : 1));
     }
@@ -1014,26 +1058,50 @@ bool Executor::contract_blocked(std::vector<Launch>& dst, const PerProb& out, co
   // dependent gathers: its range is cut into chunks whose partial tiles a
   // second kernel adds in order.  The chunk grows (powers of two) until every
   // partial tile fits the workspace.
+  // Block tiles: chunks of at least 16 steps, sized so that one problem alone makes
+  // about kTileSpread tasks (by the problem's own tiles only, so that a batch and a
+  // single instance add in the same order).
   const long ws_tiles = scratch_ && scratch_->tail_ws ? (long)(scratch_->tail_ws_doubles / 256) : 0;
-  int chunk = kSgemmChunk;
-  auto parts_needed = [&](int ch) {
+  auto is_tile = [](const Tile& t) { return t.shape >= kTile64x64; };
+  auto steps_of = [](int kl) { return (kl + kTileBK - 1) / kTileBK; };
+  std::vector<long> prob_steps(np, 0);
+  for (const Tile& t : tiles)
+    if (is_tile(t)) prob_steps[t.p] += steps_of(t.kl);
+  int chunk = kSgemmChunk, grow = 1;
+  auto chunk_of = [&](const Tile& t) {   // inner indices per part; kl: not split
+    if (!is_tile(t)) return t.shape || t.kl <= chunk + chunk / 2 ? t.kl : chunk;
+    const long per = grow * std::max(16L, (prob_steps[t.p] + kTileSpread - 1) / kTileSpread);
+    const long st = steps_of(t.kl);
+    if (st <= per + per / 2) return t.kl;
+    const long parts = (st + per - 1) / per;
+    return (int)((st + parts - 1) / parts) * kTileBK;
+  };
+  auto units_needed = [&] {
     long n = 0;
-    for (const Tile& t : tiles)
-      if (!t.shape && t.kl > ch + ch / 2) n += (t.kl + ch - 1) / ch;
+    for (const Tile& t : tiles) {
+      const int ch = chunk_of(t);
+      if (ch < t.kl) n += (long)part_units(t.shape) * ((t.kl + ch - 1) / ch);
+    }
     return n;
   };
-  while (ws_tiles > 0 && parts_needed(chunk) > ws_tiles) chunk *= 2;
+  while (ws_tiles > 0 && units_needed() > ws_tiles) {
+    chunk *= 2;
+    grow *= 2;
+  }
   std::vector<SgemmReduce> reds;
-  int parts = 0;
+  int units = 0;
   for (const Tile& t : tiles) {
-    if (t.shape || ws_tiles == 0 || t.kl <= chunk + chunk / 2) {
+    const int ch = ws_tiles == 0 ? t.kl : chunk_of(t);
+    if (ch >= t.kl) {
       tasks.push_back(SgemmTask{t.p, t.m0, t.ml, t.k0, t.kl, t.n0, t.nl, -1, t.shape});
       continue;
     }
-    const int first = parts;
-    for (int k = 0; k < t.kl; k += chunk)
-      tasks.push_back(SgemmTask{t.p, t.m0, t.ml, t.k0 + k, std::min(chunk, t.kl - k), t.n0, t.nl, parts++, 0});
-    reds.push_back(SgemmReduce{t.p, t.m0, t.ml, t.n0, t.nl, first, parts - first});
+    const int first = units, pu = part_units(t.shape);
+    for (int k = 0; k < t.kl; k += ch) {
+      tasks.push_back(SgemmTask{t.p, t.m0, t.ml, t.k0 + k, std::min(ch, t.kl - k), t.n0, t.nl, units, t.shape});
+      units += pu;
+    }
+    reds.push_back(SgemmReduce{t.p, t.m0, t.ml, t.n0, t.nl, first, (units - first) / pu, t.shape, 0});
   }
   Launch L;
   for (int p = 0; p < np; ++p) {
@@ -1044,22 +1112,11 @@ bool Executor::contract_blocked(std::vector<Launch>& dst, const PerProb& out, co
   }
   L.ranged = true;
   L.bytes = bytes;
-  if (&dst != &setup_) {
-    L.sprobs = ps;
-    L.stasks = tasks;
-    L.sreds = reds;
-  }
+  L.sprobs = ps;
+  L.stasks = tasks;
+  L.sreds = reds;
   L.kind = Launch::SGEMM;
-  L.n_prob = np;
-  L.d_desc = upload(ps.data(), sizeof(SgemmProblem) * np);
-  L.n_tasks = (int)tasks.size();
-  L.d_tasks = upload(tasks.data(), sizeof(SgemmTask) * std::max<size_t>(tasks.size(), 1));
-  L.n_red = (int)reds.size();
-  if (L.n_red > 0) {
-    L.d_red = upload(reds.data(), sizeof(SgemmReduce) * reds.size());
-    L.d_partial = scratch_->tail_ws;
-  }
-  L.total = (L.n_tasks + 3) / 4;
+  upload_sgemm(L);
   L.flops = flops;
   if (&dst != &setup_) {
     L.prob_flops = pf;
@@ -1070,48 +1127,75 @@ bool Executor::contract_blocked(std::vector<Launch>& dst, const PerProb& out, co
   return true;
 }
 
-// Y[yi] = alpha X[xi] + beta Y over the allowed elements of Y (its law known):
-// Y's letters split into two halves whose momentum blocks q and -q pair up.
-// Returns false (dense lowering) when a law is unknown.
+// Y[yi] = alpha X[xi] + beta Y over the allowed elements of Y (its law known).
 bool Executor::elem_blocked(std::vector<Launch>& dst, const PerProb& X, const std::string& xi, const PerProb& Y,
                             const std::string& yi, double alpha, double beta, int t_y, int t_x,
                             const std::string& tag, const std::vector<const double*>* scale, int xp, int yp) {
-  const bool xpk = xp >= 0 ? xp != 0 : is_packed(t_x), ypk = yp >= 0 ? yp != 0 : is_packed(t_y);
-  if (mom_.empty() || t_y < 0 || t_x < 0 || !law_ok_[t_y] || !law_ok_[t_x] || yi.empty()) return false;
+  std::vector<SumTerm> terms;
+  if (alpha != 0.0) {
+    SumTerm t{X, xi, t_x, alpha, {}, xp};
+    if (scale) t.scale = *scale;
+    terms.push_back(t);
+  }
+  return sum_blocked(dst, terms, Y, yi, beta, t_y, tag, yp);
+}
+
+// Y[yi] = beta Y + sum_s alpha_s X_s[xi_s] over the allowed elements of Y (its law known):
+// Y's letters split into two halves whose momentum blocks q and -q pair up.
+// Returns false (dense lowering) when a law is unknown.
+bool Executor::sum_blocked(std::vector<Launch>& dst, const std::vector<SumTerm>& terms, const PerProb& Y,
+                           const std::string& yi, double beta, int t_y, const std::string& tag, int yp) {
+  const bool ypk = yp >= 0 ? yp != 0 : is_packed(t_y);
+  if (mom_.empty() || t_y < 0 || !law_ok_[t_y] || yi.empty()) return false;
   const std::vector<int>& ly = law_[t_y];
-  const std::vector<int>& lx = law_[t_x];
-  // the operand's law must describe the same allowed set (equal or opposite signs)
-  int rel = 0;
-  for (size_t a = 0; a < yi.size(); ++a) {
-    const int r = ly[a] * lx[xi.find(yi[a])];
-    if (rel == 0) rel = r;
-    else if (r != rel) return false;
+  // every operand's law must describe the same allowed set (equal or opposite signs)
+  for (const SumTerm& s : terms) {
+    if (s.t_x < 0 || !law_ok_[s.t_x]) return false;
+    int rel = 0;
+    for (size_t a = 0; a < yi.size(); ++a) {
+      const int r = ly[a] * law_[s.t_x][s.xi.find(yi[a])];
+      if (rel == 0) rel = r;
+      else if (r != rel) return false;
+    }
   }
   const std::string G1 = yi.substr(0, yi.size() / 2), G2 = yi.substr(yi.size() / 2);
-  std::vector<int> s1, s2;
-  for (size_t a = 0; a < G1.size(); ++a) s1.push_back(ly[a]);
-  for (size_t a = 0; a < G2.size(); ++a) s2.push_back(ly[G1.size() + a]);
+  const std::vector<int> s1(ly.begin(), ly.begin() + G1.size()), s2(ly.begin() + G1.size(), ly.end());
   const int np = (int)probs_.size();
-  std::vector<ElemProblem> ps(np);
-  std::vector<ElemTask> tasks;
-  long long total = 0;
+  Launch L;
+  double elements = 0.0;
   for (int p = 0; p < np; ++p) {
     const int inst = probs_[p].inst;
     const long n = probs_[p].n;
     if (ipow(n, (int)yi.size()) >= (1L << 32)) throw std::runtime_error("tensor exceeds 2^32 elements: " + tag);
-    const GroupTable& T1 = group_table(inst, n, G1, xi, xpk, yi, ypk, s1);
-    const GroupTable& T2 = group_table(inst, n, G2, xi, xpk, yi, ypk, s2);
-    ElemProblem& P = ps[p];
-    P.X = X[p];
+    const GroupTable& T1 = group_table(inst, n, G1, yi, ypk, yi, ypk, s1);
+    const GroupTable& T2 = group_table(inst, n, G2, yi, ypk, yi, ypk, s2);
+    ElemProblem P;
     P.Y = Y[p];
-    P.ox1 = (const unsigned*)T1.off1;
     P.oy1 = (const unsigned*)T1.off2;
-    P.ox2 = (const unsigned*)T2.off1;
     P.oy2 = (const unsigned*)T2.off2;
-    P.alpha = alpha;
     P.beta = beta;
     P.active = gate_for(dst, p);
-    P.scale = scale ? (*scale)[p] : nullptr;
+    P.src = (int)L.esrcs.size();
+    P.n_src = (int)terms.size();
+    const size_t ey = sizeof(double) * (size_t)ipow_l(n, (int)yi.size() - (ypk ? 1 : 0));
+    if (beta != 0.0) add_range(L.rd, Y[p], ey);
+    add_range(L.wr, Y[p], ey);
+    for (const SumTerm& s : terms) {
+      const bool xpk = s.xp >= 0 ? s.xp != 0 : is_packed(s.t_x);
+      ElemSource q;
+      q.X = s.X[p];
+      q.ox1 = q.ox2 = nullptr;
+      if (s.xi != yi || xpk != ypk) {   // the same tuples in the same order, X's offsets
+        q.ox1 = (const unsigned*)group_table(inst, n, G1, s.xi, xpk, yi, ypk, s1).off1;
+        q.ox2 = (const unsigned*)group_table(inst, n, G2, s.xi, xpk, yi, ypk, s2).off1;
+      }
+      q.scale = s.scale.empty() ? nullptr : s.scale[p];
+      q.alpha = s.alpha;
+      L.esrcs.push_back(q);
+      add_range(L.rd, q.X, sizeof(double) * (size_t)ipow_l(n, (int)yi.size() - (xpk ? 1 : 0)));
+      if (q.scale) add_range(L.rd, q.scale, sizeof(double));
+    }
+    L.n_elem = (L.n_elem + 255) / 256 * 256;   // every problem starts on a block boundary
     const InstMomentum& Mm = *mom_[inst];
     for (const auto& blk : T1.blocks) {
       std::vector<int> q(Mm.dims);
@@ -1121,41 +1205,31 @@ bool Executor::elem_blocked(std::vector<Launch>& dst, const PerProb& X, const st
       }
       auto b2 = T2.blocks.find(pack_momentum(q));
       if (b2 == T2.blocks.end()) continue;
-      tasks.push_back(ElemTask{total, p, blk.second.first, blk.second.second, b2->second.first, b2->second.second});
-      total += (long long)blk.second.second * b2->second.second;
+      L.etasks.push_back(
+          ElemTask{L.n_elem, p, blk.second.first, blk.second.second, b2->second.first, b2->second.second});
+      L.n_elem += (long long)blk.second.second * b2->second.second;
+      elements += (double)blk.second.second * b2->second.second;
     }
-  }
-  Launch L;
-  for (int p = 0; p < np; ++p) {
-    const long n = probs_[p].n;
-    if (alpha != 0.0 && scale) add_range(L.rd, (*scale)[p], sizeof(double));
-    const size_t ex = (size_t)ipow_l(n, (int)xi.size() - (xpk ? 1 : 0));
-    const size_t ey = (size_t)ipow_l(n, (int)yi.size() - (ypk ? 1 : 0));
-    if (alpha != 0.0) add_range(L.rd, X[p], sizeof(double) * ex);
-    if (beta != 0.0) add_range(L.rd, Y[p], sizeof(double) * ey);
-    add_range(L.wr, Y[p], sizeof(double) * ey);
+    L.eprobs.push_back(P);
   }
   L.ranged = true;
   L.kind = Launch::ELEM;
-  L.n_prob = np;
-  L.d_desc = upload(ps.data(), sizeof(ElemProblem) * np);
-  L.n_tasks = (int)tasks.size();
-  L.d_tasks = upload(tasks.data(), sizeof(ElemTask) * std::max<size_t>(tasks.size(), 1));
-  {
-    const std::vector<int> bf = block_first_tasks(tasks, total);
-    L.d_bfirst = upload(bf.data(), sizeof(int) * bf.size());
-  }
-  L.n_elem = total;
-  L.bytes = sizeof(double) * (double)total * ((alpha != 0.0) + (beta != 0.0) + 1);
-  L.zero_fill = alpha == 0.0 && beta == 0.0;
-  if (&dst != &setup_) {
-    L.eprobs = ps;
-    L.etasks = tasks;
-  }
-  L.total = (int)std::min<long long>((total + 255) / 256, 1 << 30);
+  L.bytes = sizeof(double) * elements * ((double)terms.size() + (beta != 0.0) + 1);
   L.tag = tag + "(blocked)";
+  upload_elem(L);
   dst.push_back(L);
   return true;
+}
+
+void Executor::upload_elem(Launch& L) {
+  L.n_prob = (int)L.eprobs.size();
+  L.d_desc = upload(L.eprobs.data(), sizeof(ElemProblem) * L.eprobs.size());
+  L.d_src = upload(L.esrcs.data(), sizeof(ElemSource) * L.esrcs.size());
+  L.n_tasks = (int)L.etasks.size();
+  L.d_tasks = upload(L.etasks.data(), sizeof(ElemTask) * L.etasks.size());
+  const std::vector<int> bf = block_first_tasks(L.etasks, L.n_elem);
+  L.d_bfirst = upload(bf.data(), sizeof(int) * bf.size());
+  L.total = (int)std::min<long long>((L.n_elem + 255) / 256, 1 << 30);
 }
 
 bool Executor::dot_blocked(std::vector<Launch>& dst, const PerProb& A, const std::string& ai, const PerProb& B,
@@ -1230,48 +1304,64 @@ bool Executor::dot_blocked(std::vector<Launch>& dst, const PerProb& A, const std
   return true;
 }
 
-void Executor::merge_fills(std::vector<Launch>& L) {
-  std::vector<Launch> out;
-  std::vector<bool> merged;
-  for (Launch& l : L) {
-    if (l.kind == Launch::ELEM && l.zero_fill && !out.empty() && out.back().kind == Launch::ELEM &&
-        out.back().zero_fill) {
-      Launch& m = out.back();
-      const int po = (int)m.eprobs.size();
-      m.eprobs.insert(m.eprobs.end(), l.eprobs.begin(), l.eprobs.end());
-      for (ElemTask t : l.etasks) {
-        t.prob += po;
-        t.first += m.n_elem;
-        m.etasks.push_back(t);
-      }
-      m.n_elem += l.n_elem;
-      m.bytes += l.bytes;
-      m.tag += "+" + l.tag;
-      merged.back() = true;
-      continue;
-    }
-    out.push_back(std::move(l));
-    merged.push_back(false);
-  }
-  for (size_t k = 0; k < out.size(); ++k) {
-    if (!merged[k]) continue;
-    Launch& m = out[k];
-    m.n_prob = (int)m.eprobs.size();
-    m.d_desc = upload(m.eprobs.data(), sizeof(ElemProblem) * m.eprobs.size());
-    m.n_tasks = (int)m.etasks.size();
-    m.d_tasks = upload(m.etasks.data(), sizeof(ElemTask) * std::max<size_t>(m.etasks.size(), 1));
-    const std::vector<int> bf = block_first_tasks(m.etasks, m.n_elem);
-    m.d_bfirst = upload(bf.data(), sizeof(int) * bf.size());
-    m.total = (int)std::min<long long>((m.n_elem + 255) / 256, 1 << 30);
-  }
-  L = std::move(out);
-}
-
 double Executor::sgemm_flops_forward() const {
   double f = 0.0;
   for (const Launch& l : fwd_)
     if (l.kind == Launch::SGEMM) f += l.flops;
   return f;
+}
+
+// Order of the first n (block tile) tasks over the chip: block b runs on XCD b % 8,
+// and each XCD has its own L2, so every run of equally long tasks is cut into eight
+// contiguous pieces, one per XCD (neighbouring tiles share operand panels), while
+// the list as a whole stays longest first.
+static void xcd_order(std::vector<SgemmTask>& tasks, int n) {
+  constexpr int X = 8;
+  std::vector<SgemmTask> q[X];
+  for (int i = 0, turn = 0; i < n; ++turn) {
+    int j = i;
+    while (j < n && tasks[j].klen == tasks[i].klen) ++j;
+    for (int x = 0; x < X; ++x) {
+      const int lo = i + (int)((long)(j - i) * x / X), hi = i + (int)((long)(j - i) * (x + 1) / X);
+      std::vector<SgemmTask>& t = q[(x + turn) % X];
+      t.insert(t.end(), tasks.begin() + lo, tasks.begin() + hi);
+    }
+    i = j;
+  }
+  size_t at[X] = {};
+  for (int i = 0; i < n; ++i) {
+    int x = i % X;
+    for (int k = 0; k < X && at[x] >= q[x].size(); ++k) x = (x + 1) % X;   // that XCD's share is used up
+    tasks[i] = q[x][at[x]++];
+  }
+}
+
+// Device lists of an SGEMM launch: block tiles first, longest tasks first (so that
+// the last wave of the launch holds short ones), one reduction entry per 256 outputs.
+void Executor::upload_sgemm(Launch& L) {
+  std::stable_sort(L.stasks.begin(), L.stasks.end(),
+                   [](const SgemmTask& a, const SgemmTask& b) { return sgemm_task_cost(a) > sgemm_task_cost(b); });
+  L.n_prob = (int)L.sprobs.size();
+  L.d_desc = upload(L.sprobs.data(), sizeof(SgemmProblem) * L.sprobs.size());
+  L.n_tasks = (int)L.stasks.size();
+  L.n_tile = 0;
+  L.narrow = false;
+  for (const SgemmTask& t : L.stasks) {
+    L.n_tile += t.shape >= kTile64x64;
+    L.narrow = L.narrow || t.shape > kTile64x64;
+  }
+  xcd_order(L.stasks, L.n_tile);
+  L.d_tasks = upload(L.stasks.data(), sizeof(SgemmTask) * std::max<size_t>(L.stasks.size(), 1));
+  std::vector<SgemmReduce> slices;
+  for (const SgemmReduce& r : L.sreds)
+    for (int k = 0; k < part_units(r.shape); ++k) {
+      slices.push_back(r);
+      slices.back().slice = k;
+    }
+  L.n_red = (int)slices.size();
+  if (L.n_red > 0) L.d_red = upload(slices.data(), sizeof(SgemmReduce) * slices.size());
+  L.d_partial = scratch_->tail_ws;
+  L.total = L.n_tile + (L.n_tasks - L.n_tile + 3) / 4;
 }
 
 Launch Executor::merge_sgemm(const std::vector<Launch*>& parts) {
@@ -1291,7 +1381,7 @@ Launch Executor::merge_sgemm(const std::vector<Launch*>& parts) {
     for (SgemmReduce r : l->sreds) {
       r.prob += po;
       r.first += part_base;
-      n_parts += r.count;
+      n_parts += r.count * part_units(r.shape);
       M.sreds.push_back(r);
     }
     part_base += n_parts;
@@ -1303,21 +1393,9 @@ Launch Executor::merge_sgemm(const std::vector<Launch*>& parts) {
     M.wr.insert(M.wr.end(), l->wr.begin(), l->wr.end());
     M.tag += (M.tag.empty() ? "" : "+") + l->tag;
   }
-  // longest tasks first, so that the last wave of the launch holds short ones
-  std::stable_sort(M.stasks.begin(), M.stasks.end(),
-                   [](const SgemmTask& a, const SgemmTask& b) { return sgemm_task_cost(a) > sgemm_task_cost(b); });
   normalize(M.rd);
   normalize(M.wr);
-  M.n_prob = (int)M.sprobs.size();
-  M.d_desc = upload(M.sprobs.data(), sizeof(SgemmProblem) * M.sprobs.size());
-  M.n_tasks = (int)M.stasks.size();
-  M.d_tasks = upload(M.stasks.data(), sizeof(SgemmTask) * std::max<size_t>(M.stasks.size(), 1));
-  M.n_red = (int)M.sreds.size();
-  if (M.n_red > 0) {
-    M.d_red = upload(M.sreds.data(), sizeof(SgemmReduce) * M.sreds.size());
-    M.d_partial = scratch_->tail_ws;
-  }
-  M.total = (M.n_tasks + 3) / 4;
+  upload_sgemm(M);
   return M;
 }
 
@@ -1325,10 +1403,14 @@ Launch Executor::merge_elem(const std::vector<Launch*>& parts) {
   Launch M;
   M.kind = Launch::ELEM;
   M.ranged = true;
-  M.zero_fill = true;
   for (const Launch* l : parts) {
-    const int po = (int)M.eprobs.size();
-    M.eprobs.insert(M.eprobs.end(), l->eprobs.begin(), l->eprobs.end());
+    const int po = (int)M.eprobs.size(), so = (int)M.esrcs.size();
+    M.n_elem = (M.n_elem + 255) / 256 * 256;
+    for (ElemProblem q : l->eprobs) {
+      q.src += so;
+      M.eprobs.push_back(q);
+    }
+    M.esrcs.insert(M.esrcs.end(), l->esrcs.begin(), l->esrcs.end());
     for (ElemTask t : l->etasks) {
       t.prob += po;
       t.first += M.n_elem;
@@ -1336,20 +1418,13 @@ Launch Executor::merge_elem(const std::vector<Launch*>& parts) {
     }
     M.n_elem += l->n_elem;
     M.bytes += l->bytes;
-    M.zero_fill = M.zero_fill && l->zero_fill;
     M.rd.insert(M.rd.end(), l->rd.begin(), l->rd.end());
     M.wr.insert(M.wr.end(), l->wr.begin(), l->wr.end());
     M.tag += (M.tag.empty() ? "" : "+") + l->tag;
   }
   normalize(M.rd);
   normalize(M.wr);
-  M.n_prob = (int)M.eprobs.size();
-  M.d_desc = upload(M.eprobs.data(), sizeof(ElemProblem) * M.eprobs.size());
-  M.n_tasks = (int)M.etasks.size();
-  M.d_tasks = upload(M.etasks.data(), sizeof(ElemTask) * std::max<size_t>(M.etasks.size(), 1));
-  const std::vector<int> bf = block_first_tasks(M.etasks, M.n_elem);
-  M.d_bfirst = upload(bf.data(), sizeof(int) * bf.size());
-  M.total = (int)std::min<long long>((M.n_elem + 255) / 256, 1 << 30);
+  upload_elem(M);
   return M;
 }
 
@@ -1375,7 +1450,7 @@ void Executor::fuse_levels(std::vector<Launch>& L) {
   std::vector<Launch> out;
   std::vector<void*> freed;
   auto retire = [&](Launch& l) {
-    for (void* d : {l.d_desc, l.d_tasks, l.d_red, l.d_bfirst})
+    for (void* d : {l.d_desc, l.d_tasks, l.d_red, l.d_bfirst, l.d_src})
       if (d) freed.push_back(d);
   };
   for (const std::vector<int>& lv : at) {
@@ -1399,7 +1474,7 @@ void Executor::fuse_levels(std::vector<Launch>& L) {
       long parts = 0;
       for (; k < sg.size(); ++k) {
         long np = 0;
-        for (const SgemmReduce& r : sg[k]->sreds) np += r.count;
+        for (const SgemmReduce& r : sg[k]->sreds) np += r.count * part_units(r.shape);
         if (!grp.empty() && parts + np > ws_tiles) break;
         grp.push_back(sg[k]);
         parts += np;
@@ -1418,9 +1493,171 @@ void Executor::fuse_levels(std::vector<Launch>& L) {
     std::vector<SgemmTask>().swap(l.stasks);
     std::vector<SgemmReduce>().swap(l.sreds);
     std::vector<ElemProblem>().swap(l.eprobs);
+    std::vector<ElemSource>().swap(l.esrcs);
     std::vector<ElemTask>().swap(l.etasks);
   }
   L = std::move(out);
+}
+
+// ------------------------------------------------------------------ lowering: op lists
+void Executor::lower_one(std::vector<Launch>& dst, const OpInst& o, const PerProb& out, bool acc) {
+  contract(dst, out, o.oi, o.alpha, *o.A, o.ai, o.a_const, o.B, o.bi, o.b_const, acc, o.tag, o.a_val, o.b_val,
+           o.t_out, o.t_a, o.t_b);
+  if (&dst == &fwd_) version_[o.t_out]++;
+}
+
+// Lower a list of ops; the buffers of `zeroed` (gradients, key number of tensors + k)
+// start at zero.
+//
+// Without momentum laws: one launch (or GEMM and permute) per op, in order.
+// With them the launches later run by dependency level, and the ops that accumulate
+// into one buffer would stand in one level each, since its writes keep their order:
+// 11 for the doubles residual.  Instead every run of writes with no read in between
+// is taken together: contractions write private copies (the first one the buffer
+// itself), and one elementwise sum adds the copies and the elementwise terms in op
+// order.  A contraction whose operands are ready later than everything else
+// accumulates in place after that sum.  27 -> 13 dispatches per forward pass of the
+// restricted program, 40 -> 21 per reverse pass.  Copies are taken only while memory
+// is plentiful (cache_alloc); without them the writes are serial.
+void Executor::lower(std::vector<Launch>& dst, const std::vector<OpInst>& ops, const std::vector<int>& zeroed,
+                     const std::vector<PerProb>& zero_bufs) {
+  const int nt = (int)prog_->t.size(), np = (int)probs_.size();
+  auto rank_of = [&](int t) { return prog_->t[t].rank; };
+  std::map<int, int> fresh;   // key -> index in zeroed, until its first write
+  for (size_t k = 0; k < zeroed.size(); ++k) fresh[nt + zeroed[k]] = (int)k;
+  if (mom_.empty()) {
+    for (size_t k = 0; k < zeroed.size(); ++k)
+      fill(dst, zero_bufs[k], rank_of(zeroed[k]), "zero:" + prog_->t[zeroed[k]].name, zeroed[k]);
+    for (const OpInst& o : ops) lower_one(dst, o, *o.out, o.acc);
+    return;
+  }
+  // the elementwise form of an op with one operand, or one operand and a scalar
+  auto unary = [](const OpInst& o) { return !o.B || o.ai.empty() || o.bi.empty(); };
+  auto term_of = [&](const OpInst& o) {   // letters renamed by their place in the output
+    const bool sa = o.B && o.ai.empty(), sb = o.B && o.bi.empty();
+    SumTerm t{sa ? *o.B : *o.A, sa ? o.bi : o.ai, sa ? o.t_b : o.t_a, o.alpha, {}, -1};
+    if (sa) t.scale.assign(o.A->begin(), o.A->end());
+    if (sb) t.scale.assign(o.B->begin(), o.B->end());
+    for (char& c : t.xi) c = (char)('A' + o.oi.find(c));
+    return t;
+  };
+  std::map<int, int> level;   // of a buffer's last write
+  auto lv = [&](int key) {
+    auto it = level.find(key);
+    return it == level.end() ? 0 : it->second;
+  };
+  auto ready = [&](const OpInst& o) { return std::max(lv(o.akey), o.bkey >= 0 ? lv(o.bkey) : 0) + 1; };
+  std::map<int, std::vector<const OpInst*>> open;
+  auto close = [&](int key) {
+    auto it = open.find(key);
+    if (it == open.end()) {
+      auto f = fresh.find(key);   // read before any write: zero
+      if (f == fresh.end()) return;
+      const int k = f->second;
+      fresh.erase(f);
+      fill(dst, zero_bufs[k], rank_of(zeroed[k]), "zero:" + prog_->t[zeroed[k]].name, zeroed[k]);
+      level[key] = 1;
+      return;
+    }
+    const std::vector<const OpInst*> seg = std::move(it->second);
+    open.erase(it);
+    const PerProb& out = *seg[0]->out;
+    const int t_out = seg[0]->t_out, r = rank_of(t_out);
+    const bool acc0 = fresh.count(key) ? false : seg[0]->acc;
+    fresh.erase(key);
+    std::vector<const OpInst*> un, con;
+    for (const OpInst* o : seg) (unary(*o) ? un : con).push_back(o);
+    std::string yi;
+    for (int k = 0; k < r; ++k) yi.push_back((char)('A' + k));
+    // the contraction to accumulate in place, last: the only one ready strictly after the others and their sum
+    const OpInst* last = nullptr;
+    int top = 0, rest = 0;
+    for (const OpInst* o : con) top = std::max(top, ready(*o));
+    int at_top = 0;
+    for (const OpInst* o : con)
+      if (ready(*o) == top) {
+        ++at_top;
+        last = o;
+      } else {
+        rest = std::max(rest, ready(*o));
+      }
+    for (const OpInst* o : un) rest = std::max(rest, ready(*o) - 1);
+    if (at_top != 1 || (con.size() > 1 && rest + 1 >= top)) last = nullptr;
+    if (last) con.erase(std::find(con.begin(), con.end(), last));
+    bool acc = acc0;
+    // private copies of every contraction but the first
+    std::vector<SumTerm> copies;
+    bool serial = false;
+    for (size_t k = 1; k < con.size() && !serial; ++k) {
+      size_t total = 0;
+      for (int p = 0; p < np; ++p) total += (elems(t_out, probs_[p].n, r) + 31) / 32 * 32;
+      double* q = cache_alloc_ ? cache_alloc_(total) : nullptr;
+      if (!q) {
+        serial = true;
+        break;
+      }
+      cache_bytes_ += sizeof(double) * total;
+      SumTerm t{PerProb(np), yi, t_out, 1.0, {}, -1};
+      for (int p = 0; p < np; ++p) {
+        t.X[p] = q;
+        q += (elems(t_out, probs_[p].n, r) + 31) / 32 * 32;
+      }
+      copies.push_back(t);
+    }
+    if (serial) copies.clear();
+    if (!con.empty() && !serial) {
+      lower_one(dst, *con[0], out, acc);
+      acc = true;
+      for (size_t k = 1; k < con.size(); ++k) lower_one(dst, *con[k], copies[k - 1].X, false);
+    }
+    std::vector<SumTerm> terms;
+    {
+      size_t c = 0;
+      for (const OpInst* o : seg) {
+        if (unary(*o)) terms.push_back(term_of(*o));
+        else if (o != last && !serial && o != con[0]) terms.push_back(copies[c++]);
+      }
+    }
+    if (!terms.empty()) {
+      if (!sum_blocked(dst, terms, out, yi, acc ? 1.0 : 0.0, t_out, seg[0]->tag)) {
+        for (const OpInst* o : un) {   // no common law: one dense pass each
+          lower_one(dst, *o, out, acc);
+          acc = true;
+        }
+        for (const SumTerm& t : copies) {
+          dense_guard(seg[0]->tag, {t_out});
+          perm(dst, t.X, yi, out, yi, 1.0, 1.0, nullptr, seg[0]->tag);
+        }
+      }
+      acc = true;
+    }
+    if (serial)
+      for (const OpInst* o : con) {
+        lower_one(dst, *o, out, acc);
+        acc = true;
+      }
+    if (last) lower_one(dst, *last, out, acc);
+    int done = rest;   // of the others, then their sum, then the contraction in place
+    if (!last && !con.empty()) done = std::max(done, top);
+    if (!terms.empty()) ++done;
+    if (last) done = std::max(top, done + 1);
+    level[key] = std::max(done, 1);
+  };
+  for (const OpInst& o : ops) {
+    close(o.akey);
+    if (o.bkey >= 0) close(o.bkey);
+    if (o.oi.empty()) {   // a full contraction: a dot, in order
+      auto f = fresh.find(o.okey);
+      const bool acc = f == fresh.end() && o.acc;
+      fresh.erase(o.okey);
+      lower_one(dst, o, *o.out, acc);
+      level[o.okey] = std::max(lv(o.okey), ready(o));
+      continue;
+    }
+    open[o.okey].push_back(&o);
+  }
+  while (!open.empty()) close(open.begin()->first);
+  while (!fresh.empty()) close(fresh.begin()->first);
 }
 
 // ------------------------------------------------------------------ build
@@ -1550,12 +1787,15 @@ void Executor::build(const Program* prog, const std::vector<ProblemRef>& probs, 
     if (prog->t[k].kind == T_INPUT) move_packed(fwd_, dense_f[k], fwd[k], k, true, "gather:");
   version_.assign(nt, 0);
   auto vidx = [&](int k) { return (k >= 0 && cidx(k) < 0) ? k : -1; };
+  // buffer keys of the op lists: a tensor's values k, its gradient nt + k
+  std::vector<OpInst> ops;
   for (const SymOp& o : prog->ops) {
     if (o.setup && !inline_setup_) continue;
-    contract(fwd_, fwd[o.out], o.oi, o.alpha, fwd[o.a], o.ai, cidx(o.a), o.b >= 0 ? &fwd[o.b] : nullptr, o.bi,
-             cidx(o.b), o.accumulate, prog->t[o.out].name, vidx(o.a), vidx(o.b), o.out, o.a, o.b);
-    version_[o.out]++;
+    ops.push_back(OpInst{o.out, o.a, o.b, &fwd[o.out], &fwd[o.a], o.b >= 0 ? &fwd[o.b] : nullptr, o.oi, o.ai, o.bi,
+                         o.alpha, o.accumulate, cidx(o.a), cidx(o.b), vidx(o.a), vidx(o.b), o.out, o.a, o.b,
+                         prog->t[o.out].name});
   }
+  lower(fwd_, ops, {}, {});
   for (int k : io)
     if (prog->t[k].kind == T_OUTPUT) move_packed(fwd_, fwd[k], dense_f[k], k, false, "scatter:");
   if (!want_backward) {
@@ -1564,29 +1804,31 @@ void Executor::build(const Program* prog, const std::vector<ProblemRef>& probs, 
     dump_plan();
     return;
   }
-  // zero every gradient buffer except the cotangents of the outputs
-  for (int k = 0; k < nt; ++k)
-    if (need_grad[k] && prog->t[k].kind != T_OUTPUT)
-      fill(bwd_, grd[k], prog->t[k].rank, "zero:" + prog->t[k].name, k);
   for (int k : io)
     if (need_grad[k] && prog->t[k].kind == T_OUTPUT) move_packed(bwd_, dense_g[k], grd[k], k, true, "gather:d");
+  // every gradient buffer except the cotangents of the outputs starts at zero
+  std::vector<int> zeroed;
+  std::vector<PerProb> zero_bufs;
+  for (int k = 0; k < nt; ++k)
+    if (need_grad[k] && prog->t[k].kind != T_OUTPUT) {
+      zeroed.push_back(k);
+      zero_bufs.push_back(grd[k]);
+    }
+  ops.clear();
   for (int i = (int)prog->ops.size() - 1; i >= 0; --i) {
     const SymOp& o = prog->ops[i];
     if (o.setup && !inline_setup_) continue;
     const std::string tag = "bwd:" + prog->t[o.out].name;
-    if (o.b < 0) {
-      if (need_grad[o.a])
-        contract(bwd_, grd[o.a], o.ai, o.alpha, grd[o.out], o.oi, -1, nullptr, "", -1, true, tag, -1, -1, o.a, o.out,
-                 -1);
-      continue;
-    }
+    const bool one = o.b < 0;
     if (need_grad[o.a])
-      contract(bwd_, grd[o.a], o.ai, o.alpha, grd[o.out], o.oi, -1, &fwd[o.b], o.bi, cidx(o.b), true, tag + ":dA",
-               -1, vidx(o.b), o.a, o.out, o.b);
-    if (need_grad[o.b])
-      contract(bwd_, grd[o.b], o.bi, o.alpha, fwd[o.a], o.ai, cidx(o.a), &grd[o.out], o.oi, -1, true, tag + ":dB",
-               vidx(o.a), -1, o.b, o.a, o.out);
+      ops.push_back(OpInst{nt + o.a, nt + o.out, o.b, &grd[o.a], &grd[o.out], one ? nullptr : &fwd[o.b], o.ai, o.oi,
+                           o.bi, o.alpha, true, -1, cidx(o.b), -1, vidx(o.b), o.a, o.out, o.b,
+                           one ? tag : tag + ":dA"});
+    if (!one && need_grad[o.b])
+      ops.push_back(OpInst{nt + o.b, o.a, nt + o.out, &grd[o.b], &fwd[o.a], &grd[o.out], o.bi, o.ai, o.oi, o.alpha,
+                           true, cidx(o.a), -1, vidx(o.a), -1, o.b, o.a, o.out, tag + ":dB"});
   }
+  lower(bwd_, ops, zeroed, zero_bufs);
   for (int k : io)
     if (need_grad[k] && prog->t[k].kind == T_INPUT) move_packed(bwd_, grd[k], dense_g[k], k, false, "scatter:d");
   // FTCC_FUSE=0 keeps the program order, one launch per contraction (diagnostics)
@@ -1594,8 +1836,6 @@ void Executor::build(const Program* prog, const std::vector<ProblemRef>& probs, 
   if (!mom_.empty() && !(fz && fz[0] == '0')) {
     fuse_levels(fwd_);
     fuse_levels(bwd_);
-  } else {
-    merge_fills(bwd_);
   }
   dump_plan();
 }
@@ -1723,7 +1963,8 @@ void Executor::run(const std::vector<Launch>& L, hipStream_t s) const {
         launch_dot((const DotProblem*)l.d_desc, l.n_prob, l.dot_blocks, l.d_partial, s);
         break;
       case Launch::SGEMM:
-        launch_sgemm((const SgemmProblem*)l.d_desc, (const SgemmTask*)l.d_tasks, l.n_tasks, l.d_partial,
+        launch_sgemm((const SgemmProblem*)l.d_desc, (const SgemmTask*)l.d_tasks, l.n_tile, l.narrow, l.n_tasks,
+                     l.d_partial,
                      (const SgemmReduce*)l.d_red, l.n_red, s);
         break;
       case Launch::DOTB:
@@ -1732,8 +1973,8 @@ void Executor::run(const std::vector<Launch>& L, hipStream_t s) const {
                     l.d_partial, s);
         break;
       case Launch::ELEM:
-        launch_elem((const ElemProblem*)l.d_desc, (const ElemTask*)l.d_tasks, (const int*)l.d_bfirst, l.n_tasks,
-                    l.n_elem, s);
+        launch_elem((const ElemProblem*)l.d_desc, (const ElemSource*)l.d_src, (const ElemTask*)l.d_tasks,
+                    (const int*)l.d_bfirst, l.n_tasks, l.n_elem, s);
         break;
     }
   }
@@ -1792,7 +2033,7 @@ long Executor::dispatches(const std::vector<Launch>& L) const {
         k += (l.total > 0) + (t.splits > 1 && t.dp_tiles < l.total) + (l.splitk_blocks > 0);
         break;
       }
-      case Launch::SGEMM: k += (l.n_tasks > 0) + (l.n_tasks > 0 && l.n_red > 0); break;
+      case Launch::SGEMM: k += (l.n_tile > 0) + (l.n_tasks > l.n_tile) + (l.n_tasks > 0 && l.n_red > 0); break;
       case Launch::DOT: k += 2; break;
       case Launch::DOTB: k += 1 + (l.n_elem > 0 && l.n_tasks > 0); break;
       case Launch::ELEM: k += (l.n_tasks > 0 && l.n_elem > 0); break;

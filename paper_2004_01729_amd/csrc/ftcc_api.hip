@@ -931,18 +931,38 @@ void build(ftcc_ctx* c) {
   };
   // reuse budget for permuted operand copies: a quarter of the memory still available
   // (the blocked contractions address their operands in place: no permuted copies)
-  const size_t budget = mom ? 0 : (size_t)(c->available() / 4);
+  // Small dense problems take the blocked executor's path as well, everything in one
+  // block: no operand or output is permuted and independent contractions share
+  // launches.  Four nodes' residuals, GEMM path against this one: n = 8 0.401 / 0.106
+  // ms, 16 0.646 / 0.248, 24 1.40 / 0.80, 32 3.23 / 2.68, 40 8.81 / 8.77, 44 13.7 /
+  // 15.2, 57 50.7 / 64.5: beyond 40 the 128 x 128 tiles of the GEMM path win.
+  // FTCC_DENSE_LEVELS=N: up to n = N (diagnostics; 0: never).
+  int nmax = 0;
+  for (const Instance& I : c->inst) nmax = std::max(nmax, I.n);
+  const char* lenv = std::getenv("FTCC_DENSE_LEVELS");
+  const bool trivial = !mom && nmax <= (lenv ? std::atoi(lenv) : 40);
+  if (trivial)
+    for (const Instance& I : c->inst) {
+      InstMomentum t;
+      t.dims = 1;
+      t.modulus = {1};
+      t.labels.assign(I.n, 0);
+      c->one_block.push_back(t);
+    }
+  const size_t budget = (mom || trivial) ? 0 : (size_t)(c->available() / 4);
   std::vector<const InstMomentum*> by_inst;
   if (mom)
     for (const Instance& I : c->inst) by_inst.push_back(&I.mom);
+  else
+    for (const InstMomentum& t : c->one_block) by_inst.push_back(&t);
   c->ex_main.reset(new Executor());
   c->ex_main->set_gate(c->d_run, c->run_host.data());
-  if (mom) c->ex_main->set_momentum(by_inst);
+  if (mom || trivial) c->ex_main->set_momentum(by_inst);
   c->ex_main->build(&prog, probs, bind_main, &c->scratch, calloc_, true, ugrads, vcache, budget);
   c->ex_main->set_profiler(&c->prof);
   trace_executor(c, "main", *c->ex_main);
   c->ex_d.reset(new Executor());
-  if (mom) c->ex_d->set_momentum(by_inst);
+  if (mom || trivial) c->ex_d->set_momentum(by_inst);
   c->ex_d->build(&prog, probs, bind_d, &c->scratch, calloc_, false, {}, vcache, budget / 2);
   c->ex_d->set_profiler(&c->prof);
   trace_executor(c, "derivative", *c->ex_d);

@@ -16,6 +16,11 @@ namespace ftcc {
 template <class T>
 using gptr = __attribute__((address_space(1))) T*;
 
+// Constant address space: for tables no kernel writes, read at wave-uniform
+// indices through scalar loads.
+template <class T>
+using cptr = __attribute__((address_space(4))) T*;
+
 template <class T>
 __device__ __forceinline__ gptr<const T> gview(const T* p) {
   return (gptr<const T>)p;

@@ -101,6 +101,7 @@ struct SgemmProblem {
   const unsigned* offCN;
   double alpha, beta;
   const int* active;     // optional run flag (0: skip)
+  int a_inner, b_inner;  // the operand's stride-1 letter is an inner index (else a row / column)
 };
 struct SgemmTask {
   int prob;
@@ -110,49 +111,62 @@ struct SgemmTask {
   int part;              // -1: write C; else the 16 x 16 partial tile goes to ws[part * 256 ...]
   int shape;             // 0: one 16 x 16 MFMA tile (rows, columns <= 16); else a lane-mapped tile of
                          // 2^lr rows x 2^lc columns whose inner range is split over 2^ls lanes
-                         // (lr | lc << 3 | ls << 6, lr + lc + ls = 6; never split into parts)
+                         // (lr | lc << 3 | ls << 6, lr + lc + ls = 6; never split into parts); or a
+                         // kTile* code: a tile of 4096 outputs computed by one block through LDS
 };
+// block tiles (rows x columns); part counts units of 256 doubles, a block tile takes 16
+constexpr int kTile64x64 = 1 << 12, kTile128x32 = 2 << 12, kTile32x128 = 3 << 12;
+constexpr int sgemm_tile_rows(int shape) { return shape == kTile64x64 ? 64 : shape == kTile128x32 ? 128 : 32; }
+constexpr int kTileBK = 16;   // inner indices of one step of a block tile
 // shape code of a lane-mapped tile
 constexpr int sgemm_thin_shape(int lr, int lc, int ls) { return lr | (lc << 3) | (ls << 6); }
-// A tile whose inner range was split into `count` consecutive partial tiles
-// ws[first .. first + count - 1]: C = alpha * (their sum, in order) + beta * C.
+// A tile whose inner range was split into `count` consecutive partial tiles from
+// unit `first` of the workspace: C = alpha * (their sum, in a fixed order) + beta * C.
 struct SgemmReduce {
   int prob;
   int mb, mlen;
   int nb, nlen;
-  int first, count;
+  int first, count;      // first part (units of 256 doubles), number of parts
+  int shape;             // 0: 16 x 16 tile (parts of 1 unit); kTile*: block tile (parts of 16)
+  int slice;             // which 256 outputs of the tile (one entry per slice on the device)
 };
 // Inner ranges longer than this are split into chunks of kSgemmChunk (or a
 // power-of-two multiple of it when the partial tiles would not fit the workspace).
 constexpr int kSgemmChunk = 64;
-void launch_sgemm(const SgemmProblem* d_probs, const SgemmTask* d_tasks, int n_tasks, double* ws,
-                  const SgemmReduce* d_red, int n_red, hipStream_t s);
+// tasks [0, n_tile) are block tiles (one block each; narrow: not all of them 64 x 64),
+// the rest one wave each
+void launch_sgemm(const SgemmProblem* d_probs, const SgemmTask* d_tasks, int n_tile, bool narrow, int n_tasks,
+                  double* ws, const SgemmReduce* d_red, int n_red, hipStream_t s);
 
-// Momentum-blocked elementwise op over the allowed elements of Y only:
-// Y[oy1[u] + oy2[v]] = alpha * s * X[ox1[u] + ox2[v]] + beta * Y[oy1[u] + oy2[v]] for
-// every pair (u, v) of a matched pair of index-group blocks, s = *scale (a device
-// scalar) or 1 (alpha = beta = 0: zero fill, nothing read).  Forbidden elements
-// are never touched.
-struct ElemProblem {
+// Momentum-blocked elementwise sum over the allowed elements of Y only:
+// Y[y] = sum_s alpha_s * f_s * X_s[x_s] + beta * Y[y],  y = oy1[u] + oy2[v],
+// x_s = ox1_s[u] + ox2_s[v], for every pair (u, v) of a matched pair of index-group
+// blocks; f_s = *scale_s (a device scalar) or 1.  No source and beta = 0: zero fill.
+// Forbidden elements are never touched.
+struct ElemSource {
   const double* X;
-  double* Y;
-  const unsigned* ox1;
-  const unsigned* oy1;
+  const unsigned* ox1;   // null: X has Y's layout
   const unsigned* ox2;
+  const double* scale;   // optional device scalar factor
+  double alpha;
+};
+struct ElemProblem {
+  double* Y;
+  const unsigned* oy1;
   const unsigned* oy2;
-  double alpha, beta;
+  double beta;
   const int* active;
-  const double* scale;   // optional device scalar factor of X
+  int src, n_src;        // the problem's entries of the source list
 };
 struct ElemTask {
-  long long first;       // elements of the tasks before this one
+  long long first;       // elements of the tasks before this one (each problem starts at a multiple of 256)
   int prob;
   int u0, ulen, v0, vlen;
 };
 // d_bfirst: per 256-element block the task of its first element, then the last
 // task (total / 256 rounded up, plus one entries)
-void launch_elem(const ElemProblem* d_probs, const ElemTask* d_tasks, const int* d_bfirst, int n_tasks,
-                 long long total, hipStream_t s);
+void launch_elem(const ElemProblem* d_probs, const ElemSource* d_src, const ElemTask* d_tasks, const int* d_bfirst,
+                 int n_tasks, long long total, hipStream_t s);
 
 // Momentum-blocked full contraction: out = alpha * sum X[ox1[u] + ox2[v]] * Y[oy1[u] + oy2[v]]
 // + beta * out over the allowed elements (task list as for elem_kernel).  Each

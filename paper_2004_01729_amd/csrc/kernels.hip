@@ -462,10 +462,10 @@ __global__ void __launch_bounds__(256) sgemm_kernel(const SgemmProblem* __restri
 #pragma unroll
     for (int u = 0; u < G; ++u) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a[u], b[u], acc, 0, 0, 0);
   }
-  if (T.part >= 0) {   // one chunk of a split inner range: the whole tile, lane-major
+  if (T.part >= 0) {   // one chunk of a split inner range: the whole tile, row-major
     const gptr<double> w = gview(ws) + (size_t)T.part * 256;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) w[i * 64 + lane] = acc[i];
+    for (int i = 0; i < 4; ++i) w[i * 64 + lane] = acc[i];   // (4 i + q) * 16 + r
     return;
   }
   // the offsets of the lane's four elements (clamped into the tile), then the
@@ -486,63 +486,301 @@ __global__ void __launch_bounds__(256) sgemm_kernel(const SgemmProblem* __restri
     if (4 * i + q < T.mlen && r < T.nlen) C[cm[i] + cn] = P.alpha * acc[i] + P.beta * cv[i];
 }
 
-// Sum of the partial tiles of a split inner range, in chunk order (deterministic).
-__global__ void __launch_bounds__(256) sgemm_reduce_kernel(const SgemmProblem* __restrict__ probs,
-                                                           const SgemmReduce* __restrict__ red, int n_red,
-                                                           const double* __restrict__ ws) {
-  const int lane = threadIdx.x & 63;
-  const int ti = __builtin_amdgcn_readfirstlane(blockIdx.x * 4 + (threadIdx.x >> 6));
-  if (ti >= n_red) return;
-  const SgemmReduce R = red[ti];
-  const SgemmProblem& P = probs[R.prob];
-  if (P.active && *gview(P.active) == 0) return;
-  const int r = lane & 15, q = lane >> 4;
-  // chunk partials added in chunk order per element (deterministic); offsets,
-  // target loads and stores batched over the lane's four elements
-  double acc[4] = {0.0, 0.0, 0.0, 0.0};
-  for (int c = 0; c < R.count; ++c)
+// Large blocks: one 256-thread block per tile of 4096 outputs (64 x 64, 128 x 32 or
+// 32 x 128; four waves of 32 x 32), operands gathered through the offset lists into
+// LDS (double-buffered steps of kTileBK inner indices), so each operand element is
+// read once per tile and no operand is permuted.  Lanes run along whichever index
+// of the operand has stride 1 (IN: the inner index, else rows / columns), so the
+// loads are coalesced for every index order.  The inner offsets are fetched one step
+// before the operand loads that use them, the operands one step before their MFMAs.
+// The LDS pitch 4 (mod 32) makes the stores of both lane maps conflict-free; the
+// fragment reads then meet two-way conflicts, a quarter of the MFMA time they
+// overlap with.
+constexpr int tile_smem(int bm, int bn) { return 2 * kTileBK * (bm + 4 + bn + 4); }   // doubles
+
+template <int BM, bool IN>
+struct TileOperand {
+  static constexpr int NL = BM * kTileBK / 256;   // elements per thread and step
+  static constexpr int PITCH = BM + 4;
+  static constexpr int NR = IN ? NL : 1, NK = IN ? 1 : NL;
+  gptr<const double> X;
+  gptr<const unsigned> offK;
+  unsigned row[NR], ko[NK];
+  double v[NL];
+  int klen, rlen;
+  // element j of this thread: row r, inner index k
+  static __device__ __forceinline__ int rj(int j) {
+    const int t = threadIdx.x;
+    return IN ? (t >> 4) + 16 * j : (t & (BM - 1));
+  }
+  static __device__ __forceinline__ int kj(int j) {
+    const int t = threadIdx.x;
+    // with 64 or more rows a wave holds one inner index: a scalar, scalar offset loads
+    const int k0 = BM >= 64 ? __builtin_amdgcn_readfirstlane(t / BM) : t / BM;
+    return IN ? (t & 15) : k0 + (256 / BM) * j;
+  }
+  __device__ __forceinline__ void init(const double* x, const unsigned* off_row, const unsigned* off_k, int r0,
+                                       int rl, int k0, int kl) {
+    X = gview(x);
+    offK = gview(off_k) + k0;
+    klen = kl;
+    rlen = rl;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) acc[i] += gview(ws)[(size_t)(R.first + c) * 256 + i * 64 + lane];
-  const size_t cn = gview(P.offCN)[R.nb + max(min(r, R.nlen - 1), 0)];
-  size_t cm[4];
+    for (int j = 0; j < NR; ++j) row[j] = gview(off_row)[r0 + min(rj(j), rl - 1)];
+  }
+  // (offsets and operands past the step's range are clamped to the last inner index:
+  // valid addresses, zeroed on their way into LDS)
+  __device__ __forceinline__ void fetch_k(int k) {
 #pragma unroll
-  for (int i = 0; i < 4; ++i) cm[i] = gview(P.offCM)[R.mb + max(min(4 * i + q, R.mlen - 1), 0)];
+    for (int j = 0; j < NK; ++j) {
+      const int i = min(k + kj(j), klen - 1);
+      if constexpr (!IN && BM >= 64) ko[j] = ((cptr<const unsigned>)offK)[i];   // wave-uniform: a scalar load
+      else ko[j] = offK[i];
+    }
+  }
+  __device__ __forceinline__ void load() {
+#pragma unroll
+    for (int j = 0; j < NL; ++j) v[j] = X[row[IN ? j : 0] + ko[IN ? 0 : j]];
+  }
+  __device__ __forceinline__ void store(double* s, int k) const {
+#pragma unroll
+    for (int j = 0; j < NL; ++j)
+      s[kj(j) * PITCH + rj(j)] = ((int)(rj(j) < rlen) & (int)(k + kj(j) < klen)) ? v[j] : 0.0;   // no branch
+  }
+};
+
+template <int BM, int BN, bool AIN, bool BIN>
+__device__ __forceinline__ void tile_task(const SgemmProblem& P, const SgemmTask& T, double* __restrict__ ws,
+                                          double* smem) {
+  constexpr int WC = BN / 32;                    // waves along the columns
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wm = (wave / WC) * 32, wn = (wave % WC) * 32;
+  TileOperand<BM, AIN> a;
+  TileOperand<BN, BIN> b;
+  constexpr int PA = BM + 4, PB = BN + 4;
+  constexpr int BUF = kTileBK * (PA + PB);
+  const int steps = (T.klen + kTileBK - 1) / kTileBK;
+  double4_t acc[2][2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j) acc[i][j] = (double4_t){0.0, 0.0, 0.0, 0.0};
+  const int fr = lane & 15, fk = lane >> 4;
+  // a 32 x 32 part wholly outside the tile's rows or columns multiplies nothing
+  const bool live = wm < T.mlen && wn < T.nlen;
+  // step `it` from LDS buffer CUR (compile-time, so that the stores into the other
+  // buffer are known not to alias this step's fragment reads): the next step's loads
+  // after the first MFMAs, its stores among the last ones, a barrier
+  auto kstep = [&](auto cur_c, auto live_c, int it) {
+    constexpr int CUR = decltype(cur_c)::value;
+    double* sa = smem + CUR * BUF;
+    double* na = smem + (CUR ^ 1) * BUF;
+    a.load();
+    b.load();
+    a.fetch_k((it + 2) * kTileBK);
+    b.fetch_k((it + 2) * kTileBK);
+    if constexpr (decltype(live_c)::value) {
+      const double* fa = sa + fk * PA + wm + fr;
+      const double* fb = sa + kTileBK * PA + fk * PB + wn + fr;
+#pragma unroll
+      for (int kq = 0; kq < kTileBK / 4; ++kq) {
+        const double a0 = fa[kq * 4 * PA], a1 = fa[kq * 4 * PA + 16];
+        const double b0 = fb[kq * 4 * PB], b1 = fb[kq * 4 * PB + 16];
+        acc[0][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(a0, b0, acc[0][0], 0, 0, 0);
+        acc[0][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(a0, b1, acc[0][1], 0, 0, 0);
+        acc[1][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(a1, b0, acc[1][0], 0, 0, 0);
+        acc[1][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(a1, b1, acc[1][1], 0, 0, 0);
+      }
+    }
+    a.store(na, (it + 1) * kTileBK);
+    b.store(na + kTileBK * PA, (it + 1) * kTileBK);
+    if constexpr (decltype(live_c)::value) {
+      constexpr int NV = decltype(a)::NL + decltype(b)::NL;                     // operand loads, LDS stores
+      constexpr int NO = (AIN || BM < 64 ? decltype(a)::NK : 0) + (BIN || BN < 64 ? decltype(b)::NK : 0);
+      __builtin_amdgcn_sched_group_barrier(0x100, 4, 0);
+#pragma unroll
+      for (int u = 0; u < 16; ++u) {
+        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+        if (u < NV + NO) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
+        if (u < 12) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+        if (u >= 16 - NV) __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);
+      }
+    }
+    __syncthreads();
+  };
+  auto march = [&](auto live_c) {
+    for (int it = 0; it < steps; it += 2) {
+      kstep(std::integral_constant<int, 0>{}, live_c, it);
+      if (it + 1 < steps) kstep(std::integral_constant<int, 1>{}, live_c, it + 1);
+    }
+  };
+  if (steps > 0) {
+    a.init(P.A, P.offAM, P.offAK, T.mb, T.mlen, T.kb, T.klen);
+    b.init(P.B, P.offBN, P.offBK, T.nb, T.nlen, T.kb, T.klen);
+    a.fetch_k(0);
+    b.fetch_k(0);
+    a.load();
+    b.load();
+    a.fetch_k(kTileBK);
+    b.fetch_k(kTileBK);
+    a.store(smem, 0);
+    b.store(smem + kTileBK * PA, 0);
+    __syncthreads();
+    // both marches pass the same barriers; a wave runs exactly one of them
+    if (__builtin_amdgcn_readfirstlane(live ? 1 : 0)) march(std::true_type{});
+    else march(std::false_type{});
+  }
+  if (T.part >= 0) {   // one chunk of a split inner range: the whole tile, row-major
+    const gptr<double> w = gview(ws) + (size_t)T.part * 256;
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) w[(wm + 16 * i + 4 * r + fk) * BN + wn + 16 * j + fr] = acc[i][j][r];
+    return;
+  }
+  if (!live) return;
+  // offsets clamped into the tile, the target loads together, then the stores
+  size_t cn[2], cm[2][4];
+#pragma unroll
+  for (int j = 0; j < 2; ++j) cn[j] = gview(P.offCN)[T.nb + min(wn + 16 * j + fr, T.nlen - 1)];
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) cm[i][r] = gview(P.offCM)[T.mb + min(wm + 16 * i + 4 * r + fk, T.mlen - 1)];
   const gptr<double> C = gview(P.C);
-  double cv[4] = {0.0, 0.0, 0.0, 0.0};
+  double cv[2][2][4] = {};
   if (P.beta != 0.0) {
 #pragma unroll
-    for (int i = 0; i < 4; ++i) cv[i] = C[cm[i] + cn];
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) cv[i][j][r] = C[cm[i][r] + cn[j]];
   }
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
-    if (4 * i + q < R.mlen && r < R.nlen) C[cm[i] + cn] = P.alpha * acc[i] + P.beta * cv[i];
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        if (wm + 16 * i + 4 * r + fk < T.mlen && wn + 16 * j + fr < T.nlen)
+          C[cm[i][r] + cn[j]] = P.alpha * acc[i][j][r] + P.beta * cv[i][j][r];
+}
+
+template <int BM, int BN>
+__device__ __forceinline__ void tile_dispatch(const SgemmProblem& P, const SgemmTask& T, double* ws, double* smem) {
+  if (P.a_inner) {
+    if (P.b_inner) tile_task<BM, BN, true, true>(P, T, ws, smem);
+    else tile_task<BM, BN, true, false>(P, T, ws, smem);
+  } else {
+    if (P.b_inner) tile_task<BM, BN, false, true>(P, T, ws, smem);
+    else tile_task<BM, BN, false, false>(P, T, ws, smem);
+  }
+}
+
+// NARROW: the launch also holds 128 x 32 or 32 x 128 tiles (a fifth more LDS, three
+// instead of four blocks per CU)
+template <bool NARROW>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NARROW ? 3 : 4, 4)))
+sgemm_tile_kernel(const SgemmProblem* __restrict__ probs, const SgemmTask* __restrict__ tasks,
+                  double* __restrict__ ws) {
+  __shared__ double smem[NARROW ? tile_smem(128, 32) : tile_smem(64, 64)];
+  const SgemmTask T = tasks[blockIdx.x];
+  const SgemmProblem& P = probs[T.prob];
+  if (P.active && *gview(P.active) == 0) return;   // the whole block, before any barrier
+  if constexpr (NARROW) {
+    if (T.shape == kTile128x32) {
+      tile_dispatch<128, 32>(P, T, ws, smem);
+      return;
+    }
+    if (T.shape == kTile32x128) {
+      tile_dispatch<32, 128>(P, T, ws, smem);
+      return;
+    }
+  }
+  tile_dispatch<64, 64>(P, T, ws, smem);
+}
+
+// Sum of the partial tiles of a split inner range: one block per 256 outputs of a
+// tile, 8 partials in flight per thread, four interleaved sums joined in a fixed
+// order (deterministic).
+__global__ void __launch_bounds__(256) sgemm_reduce_kernel(const SgemmProblem* __restrict__ probs,
+                                                           const SgemmReduce* __restrict__ red,
+                                                           const double* __restrict__ ws) {
+  const SgemmReduce R = red[blockIdx.x];
+  const int bn = R.shape ? 4096 / sgemm_tile_rows(R.shape) : 16;
+  const int unit = R.shape ? 4096 : 256;
+  const SgemmProblem& P = probs[R.prob];
+  if (P.active && *gview(P.active) == 0) return;
+  const int e = R.slice * 256 + threadIdx.x;
+  const int m = e / bn, n = e % bn;
+  if (m >= R.mlen || n >= R.nlen) return;
+  const gptr<const double> w = gview(ws) + (size_t)R.first * 256 + e;
+  double s[4] = {0.0, 0.0, 0.0, 0.0};
+  int c = 0;
+  for (; c + 8 <= R.count; c += 8) {
+    double v[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) v[u] = w[(size_t)(c + u) * unit];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) s[u & 3] += v[u];
+  }
+  for (; c < R.count; ++c) s[c & 3] += w[(size_t)c * unit];
+  const double acc = (s[0] + s[1]) + (s[2] + s[3]);
+  const gptr<double> C = gview(P.C) + (size_t)gview(P.offCM)[R.mb + m] + gview(P.offCN)[R.nb + n];
+  double v = P.alpha * acc;
+  if (P.beta != 0.0) v += P.beta * (*C);
+  *C = v;
 }
 
 // One thread per allowed element; the task is found by binary search over the
-// element prefix, between the tasks of this block's first element and of the
-// next block's (a few steps instead of a search of the whole list).
+// element prefix, between the tasks of this block's first element and of the next
+// block's (a few steps instead of a search of the whole list).  A block belongs to one
+// problem, so the problem and its sources come in through scalar loads; the sources
+// are added in list order, four of them in flight at a time.
 __global__ void __launch_bounds__(256) elem_kernel(const ElemProblem* __restrict__ probs,
+                                                   const ElemSource* __restrict__ srcs,
                                                    const ElemTask* __restrict__ tasks,
                                                    const int* __restrict__ bfirst, long long total) {
   const long long e = (long long)blockIdx.x * 256 + threadIdx.x;
   if (e >= total) return;
-  int lo = gview(bfirst)[blockIdx.x], hi = gview(bfirst)[blockIdx.x + 1];
+  int lo = bfirst[blockIdx.x], hi = bfirst[blockIdx.x + 1];
+  const ElemProblem& P = probs[tasks[lo].prob];
+  if (P.active && *gview(P.active) == 0) return;
   while (lo < hi) {
     const int mid = (lo + hi + 1) >> 1;
     if (tasks[mid].first <= e) lo = mid; else hi = mid - 1;
   }
-  const ElemTask& T = tasks[lo];
-  const ElemProblem& P = probs[T.prob];
-  if (P.active && *gview(P.active) == 0) return;
+  const ElemTask T = tasks[lo];
   const int r = (int)(e - T.first);
-  const int u = T.u0 + r / T.vlen, v = T.v0 + r % T.vlen;
-  const gptr<double> y = gview(P.Y) + gview(P.oy1)[u] + gview(P.oy2)[v];
+  const int row = r / T.vlen;
+  if (row >= T.ulen) return;   // padding up to the next problem
+  const int u = T.u0 + row, v = T.v0 + r - row * T.vlen;
+  const unsigned yo = gview(P.oy1)[u] + gview(P.oy2)[v];
+  const gptr<double> y = gview(P.Y) + yo;
   double val = 0.0;
-  if (P.alpha != 0.0) {
-    const double a = P.scale ? P.alpha * *gview(P.scale) : P.alpha;
-    val = a * gview(P.X)[gview(P.ox1)[u] + gview(P.ox2)[v]];
+  if (P.beta != 0.0) val = P.beta * (*y);
+  const ElemSource* S = srcs + P.src;
+  const int n = P.n_src;
+  for (int k = 0; k < n; k += 4) {
+    unsigned x[4];
+    double xv[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const ElemSource& q = S[min(k + j, n - 1)];
+      x[j] = q.ox1 ? gview(q.ox1)[u] + gview(q.ox2)[v] : yo;
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j) xv[j] = k + j < n ? gview(S[min(k + j, n - 1)].X)[x[j]] : 0.0;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      if (k + j >= n) break;
+      const ElemSource& q = S[k + j];
+      val += (q.scale ? q.alpha * *gview(q.scale) : q.alpha) * xv[j];
+    }
   }
-  if (P.beta != 0.0) val += P.beta * (*y);
   *y = val;
 }
 
@@ -839,20 +1077,25 @@ void launch_splitk_reduce(const GemmProblem* d_probs, const int* d_prefix, int n
                      total_blocks);
 }
 
-void launch_sgemm(const SgemmProblem* d_probs, const SgemmTask* d_tasks, int n_tasks, double* ws,
-                  const SgemmReduce* d_red, int n_red, hipStream_t s) {
+void launch_sgemm(const SgemmProblem* d_probs, const SgemmTask* d_tasks, int n_tile, bool narrow, int n_tasks,
+                  double* ws, const SgemmReduce* d_red, int n_red, hipStream_t s) {
   if (n_tasks <= 0) return;
-  hipLaunchKernelGGL(sgemm_kernel, dim3((n_tasks + 3) / 4), dim3(256), 0, s, d_probs, d_tasks, n_tasks, ws);
+  if (n_tile > 0 && narrow)
+    hipLaunchKernelGGL(sgemm_tile_kernel<true>, dim3(n_tile), dim3(256), 0, s, d_probs, d_tasks, ws);
+  else if (n_tile > 0)
+    hipLaunchKernelGGL(sgemm_tile_kernel<false>, dim3(n_tile), dim3(256), 0, s, d_probs, d_tasks, ws);
+  const int waves = n_tasks - n_tile;
+  if (waves > 0)
+    hipLaunchKernelGGL(sgemm_kernel, dim3((waves + 3) / 4), dim3(256), 0, s, d_probs, d_tasks + n_tile, waves, ws);
   if (n_red > 0)
-    hipLaunchKernelGGL(sgemm_reduce_kernel, dim3((n_red + 3) / 4), dim3(256), 0, s, d_probs, d_red, n_red,
-                       (const double*)ws);
+    hipLaunchKernelGGL(sgemm_reduce_kernel, dim3(n_red), dim3(256), 0, s, d_probs, d_red, (const double*)ws);
 }
 
-void launch_elem(const ElemProblem* d_probs, const ElemTask* d_tasks, const int* d_bfirst, int n_tasks,
-                 long long total, hipStream_t s) {
+void launch_elem(const ElemProblem* d_probs, const ElemSource* d_src, const ElemTask* d_tasks, const int* d_bfirst,
+                 int n_tasks, long long total, hipStream_t s) {
   if (n_tasks <= 0 || total <= 0) return;
-  hipLaunchKernelGGL(elem_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s, d_probs, d_tasks, d_bfirst,
-                     total);
+  hipLaunchKernelGGL(elem_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s, d_probs, d_src, d_tasks,
+                     d_bfirst, total);
 }
 
 void launch_dotb(const DotbProblem* d_probs, int n_prob, const ElemTask* d_tasks, const int* d_bfirst, int n_tasks,
