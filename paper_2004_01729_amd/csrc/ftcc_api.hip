@@ -1126,6 +1126,7 @@ int tau_problems(ftcc_ctx* c, int mode, int panel, double* partial_base, std::ve
                  std::vector<int>& prefix) {
   const int B = c->B, m = c->m;
   int total = 0;
+  const long per = tau_block_elements(mode);
   ps.clear();
   prefix.clear();
     for (int i = 0; i < B; ++i) {
@@ -1179,7 +1180,7 @@ int tau_problems(ftcc_ctx* c, int mode, int panel, double* partial_base, std::ve
         if (mode == TAU_APREV) t.out = I.abuf[panel] + off;
         if (mode == TAU_BETA || mode == TAU_DEPS) t.lam_a = I.abuf[panel + 1] + off;
         if (mode == TAU_DEPS) t.out = I.deps_delta + off;
-        const int nb = (int)((t.len + 1023) / 1024);
+        const int nb = (int)((t.len + per - 1) / per);
         t.partial = partial_base + (long)total;
         prefix.push_back(total);
         total += nb;
@@ -1454,7 +1455,6 @@ int ftcc_create(ftcc_ctx** out, int device, int n_instances, const ftcc_options*
     FTCC_HIP(hipGetDeviceProperties(&prop, device));
     if (std::string(prop.gcnArchName).rfind("gfx950", 0) != 0)
       fail(FTCC_EDEVICE, std::string("device is ") + prop.gcnArchName + ", this library is built for gfx950");
-    FTCC_HIP(init_tau_constants());
     noalloc_setup(device);
     std::unique_ptr<ftcc_ctx> c(new ftcc_ctx());
     c->device = device;

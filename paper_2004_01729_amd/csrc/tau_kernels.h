@@ -53,10 +53,10 @@ struct TauProblem {
                                 // nullptr: every element 0..len-1
 };
 
-// blocks: 1024 elements each, per problem; d_rule is a device copy of the rule
+// elements per block of a launch (per problem); d_rule is a device copy of the rule
+inline long tau_block_elements(int mode) { return mode == TAU_BETA ? 1024 : 256; }
 void launch_tau(const PanelRule* d_rule, int m, int mode, const TauProblem* d_probs, const int* d_prefix, int n_prob,
                 int total_blocks, hipStream_t s);
-hipError_t init_tau_constants();
 
 // Explicit Runge-Kutta march of the differential form (Algorithm alg:diff,
 // eqn:smud: ds/dtau = -(Delta s + S[s])) and its reverse: one combination per

@@ -23,15 +23,17 @@
 
 namespace ftcc {
 
-__constant__ double c_inv_fact[48];
-
-// 1/k! table; must be uploaded on each device before the first propagator launch
-hipError_t init_tau_constants() {
+// 1/k!, compile-time so that the series' coefficients are literals: read from a table
+// they were a chain of scalar loads that cost more than the series' arithmetic
+// (2-block launch of a 6-site ring, 1024 elements a block: 32 us a sweep before).
+struct InvFact {
   double f[48];
-  f[0] = 1.0;
-  for (int k = 1; k < 48; ++k) f[k] = f[k - 1] / k;
-  return hipMemcpyToSymbol(HIP_SYMBOL(c_inv_fact), f, sizeof(f));
-}
+  constexpr InvFact() : f() {
+    f[0] = 1.0;
+    for (int k = 1; k < 48; ++k) f[k] = f[k - 1] / k;
+  }
+};
+constexpr InvFact kInvFact;
 
 // phi[k] = phi_k(z) for k = 1..kmax.  Small |z|: phi_kmax by its Taylor series,
 // then downward phi_k = z phi_{k+1} + 1/k! (stable there: |z| <= 4 and every term
@@ -39,16 +41,18 @@ hipError_t init_tau_constants() {
 template <int kmax>
 __device__ __forceinline__ void phi_all(double z, double* phi) {
   if (fabs(z) <= 4.0) {
-    double acc = c_inv_fact[kmax + 34];
-#pragma unroll 4
-    for (int j = 33; j >= 0; --j) acc = fma(acc, z, c_inv_fact[j + kmax]);
+    double acc = kInvFact.f[kmax + 34];
+#pragma unroll
+    for (int j = 33; j >= 0; --j) acc = fma(acc, z, kInvFact.f[j + kmax]);
     phi[kmax] = acc;
-    for (int k = kmax - 1; k >= 1; --k) phi[k] = fma(z, phi[k + 1], c_inv_fact[k]);
+#pragma unroll
+    for (int k = kmax - 1; k >= 1; --k) phi[k] = fma(z, phi[k + 1], kInvFact.f[k]);
   } else {
     double p = expm1(z) / z;
     phi[1] = p;
+#pragma unroll
     for (int k = 1; k < kmax; ++k) {
-      p = (p - c_inv_fact[k]) / z;
+      p = (p - kInvFact.f[k]) / z;
       phi[k + 1] = p;
     }
   }
@@ -68,6 +72,7 @@ __device__ void weights(const PanelRule& R, double D, double h, Weights<M>& w, i
   // R is the rule in global memory (uniform across the grid: scalar loads)
   constexpr int m = M;
   double phi[M + 2];
+#pragma unroll
   for (int x = 0; x <= m; ++x) {
     if (x == m && !need_end) break;
     const double cx = (x < m) ? R.c[x] : 1.0;
@@ -77,6 +82,7 @@ __device__ void weights(const PanelRule& R, double D, double h, Weights<M>& w, i
     else if (deriv == 2) e = -h * cx * e;       // dE/dD
     if (x < m) w.E[x] = e; else w.Ee = e;
     if (R.lawson) {
+#pragma unroll
       for (int y = 0; y < m; ++y) {
         const double arg = D * h * (R.c[y] - cx);
         const double a = (x < m) ? R.A[x][y] : R.b[y];
@@ -88,11 +94,13 @@ __device__ void weights(const PanelRule& R, double D, double h, Weights<M>& w, i
     }
     if (deriv == 2) phi_all<M + 1>(z, phi);
     else phi_all<M>(z, phi);
+#pragma unroll
     for (int y = 0; y < m; ++y) {
       double acc = 0.0;
+#pragma unroll
       for (int k = 0; k < m; ++k) {
         const double g = R.gc[x][y][k];
-        if (deriv == 1) acc += g * ((z - k) * phi[k + 1] + c_inv_fact[k]);
+        if (deriv == 1) acc += g * ((z - k) * phi[k + 1] + kInvFact.f[k]);
         else if (deriv == 2) acc += g * (phi[k + 1] - (k + 1) * phi[k + 2]);
         else acc += g * phi[k + 1];
       }
@@ -107,16 +115,15 @@ __device__ void weights(const PanelRule& R, double D, double h, Weights<M>& w, i
 // (rank 4, [i][j][a][b]) segment
 __device__ __forceinline__ double seg_delta(const double* eps_ptr, int n, int rank, long e) {
   const gptr<const double> eps = gview(eps_ptr);
-  if (rank == 2) {
-    const int a = (int)(e % n), i = (int)(e / n);
-    return eps[a] - eps[i];
-  }
-  const int b = (int)(e % n);
-  long r = e / n;
-  const int a = (int)(r % n);
-  r /= n;
-  const int j = (int)(r % n);
-  const int i = (int)(r / n);
+  // element offsets are below 2^32 (n <= 256)
+  const unsigned un = (unsigned)n, ue = (unsigned)e;
+  if (rank == 2) return eps[ue % un] - eps[ue / un];
+  unsigned r = ue / un;
+  const unsigned b = ue - r * un;
+  unsigned q = r / un;
+  const unsigned a = r - q * un;
+  const unsigned i = q / un;
+  const unsigned j = q - i * un;
   return eps[a] + eps[b] - eps[i] - eps[j];
 }
 
@@ -129,11 +136,18 @@ __device__ __forceinline__ double nan_max(double a, double b) {
 }
 
 __device__ __forceinline__ void atomic_max_pos(unsigned long long* p, double v) {
-  // non-negative doubles order like their bit patterns
+  // non-negative doubles order like their bit patterns; the maximum only grows, so a
+  // block whose value is not above a (possibly old) reading of it has nothing to add
+  if ((unsigned long long)__double_as_longlong(v) <= __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+    return;
   atomicMax(p, (unsigned long long)__double_as_longlong(v));
 }
 
-template <int M>
+// One element per thread (IT = 1); TAU_BETA four (IT = 4), its partial sums being one
+// per 1024 elements.  A loop over a thread's elements would queue them up behind each
+// other where the chip is not full, and the compiler would keep the series' 35
+// coefficients in registers across it (245 VGPRs).
+template <int M, int IT>
 __global__ void __launch_bounds__(256) tau_kernel(const PanelRule* __restrict__ rule, int mode,
                                                   const TauProblem* __restrict__ probs,
                                                   const int* __restrict__ prefix, int n_prob) {
@@ -147,9 +161,9 @@ __global__ void __launch_bounds__(256) tau_kernel(const PanelRule* __restrict__ 
   if (P.active && *gview(P.active) == 0) return;   // converged instance of a batch: left unchanged
   const PanelRule& R = *rule;
   constexpr int m = M;
-  const long base = (long)(b - prefix[lo]) * 1024;
+  const long base = (long)(b - prefix[lo]) * (256 * IT);
   double mchg = 0.0, mval = 0.0, acc = 0.0;
-  for (int u = 0; u < 4; ++u) {
+  for (int u = 0; u < IT; ++u) {
     const long ei = base + u * 256 + threadIdx.x;
     if (ei >= P.len) break;
     const long e = P.idx ? (long)gview(P.idx)[ei] : ei;   // element offset in the segment
@@ -169,7 +183,7 @@ __global__ void __launch_bounds__(256) tau_kernel(const PanelRule* __restrict__ 
       }
       continue;
     }
-    if (mode == TAU_BETA || mode == TAU_DEPS) {
+    if ((IT == 4 && mode == TAU_BETA) || (IT == 1 && mode == TAU_DEPS)) {
       double Rv[M];
       bool anyb = any || (P.lam_a && gview(P.lam_a)[e] != 0.0);
       for (int y = 0; y < m; ++y) {
@@ -196,6 +210,7 @@ __global__ void __launch_bounds__(256) tau_kernel(const PanelRule* __restrict__ 
       else gview(P.out)[e] += val;
       continue;
     }
+    if (IT == 4) continue;   // TAU_BETA only
     if (!any) {
       // structurally zero (dropped slots, or zero start): outputs stay zero
       if (mode == TAU_INIT || mode == TAU_LAMT) {
@@ -259,7 +274,7 @@ __global__ void __launch_bounds__(256) tau_kernel(const PanelRule* __restrict__ 
       atomic_max_pos(P.maxbits, r0[0]);
       atomic_max_pos(P.maxbits + 1, r1[0]);
     }
-  } else if (mode == TAU_BETA) {
+  } else if (IT == 4 && mode == TAU_BETA) {
     r0[threadIdx.x] = acc;
     __syncthreads();
     for (int s = 128; s > 0; s >>= 1) {
@@ -273,9 +288,14 @@ __global__ void __launch_bounds__(256) tau_kernel(const PanelRule* __restrict__ 
 void launch_tau(const PanelRule* d_rule, int m, int mode, const TauProblem* d_probs, const int* d_prefix, int n_prob,
                 int total_blocks, hipStream_t s) {
   if (total_blocks <= 0) return;
-#define FTCC_TAU(MM)                                                                                              \
-  case MM:                                                                                                        \
-    hipLaunchKernelGGL(tau_kernel<MM>, dim3(total_blocks), dim3(256), 0, s, d_rule, mode, d_probs, d_prefix, n_prob); \
+#define FTCC_TAU(MM)                                                                                            \
+  case MM:                                                                                                      \
+    if (mode == TAU_BETA)                                                                                       \
+      hipLaunchKernelGGL((tau_kernel<MM, 4>), dim3(total_blocks), dim3(256), 0, s, d_rule, mode, d_probs,       \
+                         d_prefix, n_prob);                                                                     \
+    else                                                                                                        \
+      hipLaunchKernelGGL((tau_kernel<MM, 1>), dim3(total_blocks), dim3(256), 0, s, d_rule, mode, d_probs,       \
+                         d_prefix, n_prob);                                                                     \
     break;
   switch (m) {
     FTCC_TAU(1)
