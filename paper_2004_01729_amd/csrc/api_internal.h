@@ -82,9 +82,8 @@ struct Instance {
   double* gacc[12] = {};                    // two-body density: accumulated gradients of the 12 weighted blocks
   double* rk_hbar = nullptr;                // d Omega_CC / d(step) at fixed integrals
   // orbital-energy response (allocated on first request): per-orbital accumulators of
-  // the thermal-integral part, dL/dDelta of every amplitude element, the direction
-  // du = -e_q e_q^T and the assembled vector
-  double *deps_acc = nullptr, *deps_delta = nullptr, *deps_dh = nullptr, *deps_out = nullptr;
+  // the thermal-integral part, dL/dDelta of every amplitude element and the assembled vector
+  double *deps_acc = nullptr, *deps_delta = nullptr, *deps_out = nullptr;
 };
 
 struct ftcc_ctx {
@@ -102,6 +101,25 @@ struct ftcc_ctx {
   std::unique_ptr<Executor> ex_main, ex_d, ex_g;   // ex_g: integral gradients (built on first use)
   std::map<std::pair<int, int>, double*> g_derived, g_cgrad;   // (tensor, problem) buffers of ex_g
   bool built = false, solved = false, have_lambda = false;
+  // thermal set-up of all instances in one launch per stage
+  SetupProblem* d_setup = nullptr;            // [B]
+  int* d_setup_prefix = nullptr;              // [B] first block of each instance, [B] a 0
+  std::vector<int> setup_blocks;              // blocks of each instance
+  double* d_mubeta = nullptr;                 // [B][2]
+  std::vector<double> mubeta;
+  const double** d_dirs = nullptr;            // [B][2] response directions
+  int n_max = 0;
+  // grouped copies of node states, (kind, panel) -> descriptors, their block prefix, counts
+  struct StateCopies {
+    StateCopy* d = nullptr;
+    int* prefix = nullptr;
+    int n = 0, blocks = 0;
+  };
+  std::map<std::pair<int, int>, StateCopies> state_copies;
+  double *e_all = nullptr, *de_all = nullptr;   // node energies of all instances, contiguous
+  int* d_beta_off = nullptr;                    // [B + 1] first TAU_BETA partial of each instance
+  double* d_dh_out = nullptr;                   // assembled dOmega/dh of all instances
+  double* d_acc_all = nullptr;                  // [B][13] response accumulators and mean-field sums
   // per node (instance * m + x): amplitudes, residuals, energies, gradients, cotangents
   std::vector<double*> amp, S, e, gr, cot, ebar, dS, de;
   // per executor slot (instance * slots + slot); the same pointers as the node
@@ -129,8 +147,9 @@ struct ftcc_ctx {
   double* d_partial = nullptr;                // TAU_BETA partial sums
   std::vector<int> tau_prefix_host;
   int* d_active = nullptr;                    // [B] propagator step flags
-  int* d_run = nullptr;                       // [B] residual-program run flags (executor gate)
-  std::vector<int> run_host;                  // host copy of d_run
+  int* d_run = nullptr;                       // [B slots] residual-program run flags (executor gate)
+  std::vector<int> run_host;                  // [B] which instances run
+  std::vector<int> run_slots;                 // host copy of d_run
   KernelProfiler prof;
   hipGraphExec_t g_fwd = nullptr, g_bwd = nullptr;
   std::vector<int> beta_part_off;             // first TAU_BETA partial of each instance
@@ -184,6 +203,18 @@ struct ftcc_ctx {
     bytes += nb;
     allocs.push_back(p);
     return (double*)p;
+  }
+
+  // launch descriptors and other small tables: the library's own, outside the caller's
+  // allocator and the cap, kept until the context is destroyed
+  std::vector<void*> descs;
+  void* desc(const void* host, size_t nbytes) {
+    void* p = nullptr;
+    FTCC_HIP(hipMalloc(&p, std::max<size_t>(nbytes, 8)));
+    descs.push_back(p);
+    if (host) FTCC_HIP(hipMemcpy(p, host, nbytes, hipMemcpyHostToDevice));
+    else FTCC_HIP(hipMemset(p, 0, nbytes));
+    return p;
   }
 
   // device memory this context may still take: free memory, bounded by the cap
@@ -258,10 +289,15 @@ void trace(ftcc_ctx* c, const char* phase, int panel, int n_panels, const std::v
 void trace_mem(ftcc_ctx* c, const char* stage);
 void trace_executor(ftcc_ctx* c, const char* which, const Executor& ex);
 void sync(ftcc_ctx* c);
-void thermal_setup(ftcc_ctx* c, int i);
-void deriv_setup(ftcc_ctx* c, int i, int which, const double* d_dh, const double* d_deri);
-void deriv_setup_eps(ftcc_ctx* c, int i, int q);
+// thermal quantities of every instance, or of one (i >= 0), at its mu and beta
+void thermal_setup(ftcc_ctx* c, int i = -1);
+// derivative blocks of every instance along `which` (SetupDeriv; SETUP_DIR: the directions of
+// set_directions; SETUP_EPS: orbital q)
+void deriv_setup(ftcc_ctx* c, int which, int q = 0);
+void set_directions(ftcc_ctx* c, const std::vector<double*>& d_dh, const std::vector<double*>& d_deri);
 long node_len_of(long n);
+// with momentum labels a dot of two node states runs over the allowed elements (the others are zero)
+void list_allowed(const ftcc_ctx* c, int i, DotProblem& d);
 void check_momentum(ftcc_ctx* c, int i, const double* x, int rank, const char* what);
 bool momentum_on(const ftcc_ctx* c);
 void allowed_elements(ftcc_ctx* c, int i);
@@ -273,6 +309,11 @@ void run_bwd_slots(ftcc_ctx* c);
 long node_len(ftcc_ctx* c, int i);
 void dcopy(ftcc_ctx* c, double* dst, const double* src, long count);
 void node_copy(ftcc_ctx* c, int i, double* dst, const double* src);
+// one launch for a set of whole node states: (instance, dst, src or null for zero) per entry, fixed
+// per (kind, panel) once the context is built
+enum StateSet { ST_SAVE = 0, ST_LOAD = 1, ST_ZERO_COT = 2, ST_ZERO_START = 3, ST_ZERO_END = 4 };
+void state_set(ftcc_ctx* c, int kind, int panel,
+               const std::function<void(std::function<void(int, double*, const double*)>)>& list);
 void forward(ftcc_ctx* c);
 void backward(ftcc_ctx* c);
 void d_forward(ftcc_ctx* c);

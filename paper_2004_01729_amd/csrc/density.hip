@@ -91,10 +91,16 @@ void build_gamma_executor(ftcc_ctx* c) {
   for (int k = 0; k < (int)prog.t.size(); ++k)
     if (prog.t[k].kind == T_CONST) cgrads.push_back(k);
   auto calloc_ = [c](int, size_t count) { return c->dalloc(count); };
-  auto vcache = [c](size_t count) { return c->dalloc(count); };
+  // private copies of accumulated outputs are optional: only while memory is plentiful
+  double reserve = 1073741824.0;
+  for (const Instance& I : c->inst) reserve += 16.0 * std::pow((double)I.n, 4) * sizeof(double);
+  auto vcache = [c, reserve](size_t count) -> double* {
+    if (c->opt.mem_cap_bytes || c->available() < 4.0 * reserve + (double)count * sizeof(double)) return nullptr;
+    return c->dalloc(count);
+  };
   std::unique_ptr<Executor> ex(new Executor());
   ex->set_inline_setup(true);
-  ex->set_gate(c->d_run, c->run_host.data());
+  ex->set_gate(c->d_run, c->run_slots.data());
   if (momentum_on(c)) {
     std::vector<const InstMomentum*> by_inst;
     for (const Instance& I : c->inst) by_inst.push_back(&I.mom);

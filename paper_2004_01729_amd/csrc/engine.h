@@ -109,7 +109,8 @@ struct Launch {
   double* d_partial = nullptr;
   double flops = 0.0;
   std::vector<double> prob_flops;   // per problem (GEMM), for gated accounting
-  std::vector<int> prob_inst;
+  std::vector<int> prob_gate;       // the problems' run flags
+  std::vector<int> prob_total, prob_total2;   // PERM / FILL / GEMM: blocks of each problem (and of its split-K reduce)
   float tuned_ms = 0.f;
   std::string tag;
   std::vector<Launch> alts;         // GEMM: other descriptor sets of the same contraction (tile
@@ -206,11 +207,15 @@ class Executor {
   void autotune(hipStream_t s);
   void run_setup(hipStream_t s) const { run(setup_, s); }
   void run_forward(hipStream_t s) const { run(fwd_, s); }
+  // One problem's forward pass (GEMM path): its blocks alone, so that it has the chip
+  // to itself, where a launch over all problems would leave the others' share idle.
+  // false: this executor's launches are not per problem (use the run flags).
+  bool run_forward_one(int prob, hipStream_t s) const;
   void run_backward(hipStream_t s) const { run(bwd_, s); }
 
   void set_profiler(KernelProfiler* p) { prof_ = p; }
-  // Per-instance run flags (device int array indexed by instance, read when the
-  // kernels run): forward and backward launches of an instance whose flag is 0
+  // Per-problem run flags (device int array indexed by problem, read when the
+  // kernels run): forward and backward launches of a problem whose flag is 0
   // return at once.  Set before build(); set-up launches are never gated.
   // h_flags mirrors the device flags on the host (flop accounting of the profiler).
   void set_gate(const int* d_flags, const int* h_flags) {
@@ -316,6 +321,7 @@ class Executor {
   std::vector<void*> owned_;
   KernelProfiler* prof_ = nullptr;
   const int* gate_ = nullptr;
+  int* d_zero_ = nullptr;                  // a device 0: block prefix of a single problem
   const int* gate_host_ = nullptr;
   // momentum blocking
   std::vector<const InstMomentum*> mom_;
@@ -359,7 +365,7 @@ class Executor {
                           scratch_ ? scratch_->tail_ws_doubles : 0);
   }
   const int* gate_for(const std::vector<Launch>& dst, int p) const {
-    return (gate_ && &dst != &setup_) ? gate_ + probs_[p].inst : nullptr;
+    return (gate_ && &dst != &setup_) ? gate_ + p : nullptr;
   }
 };
 

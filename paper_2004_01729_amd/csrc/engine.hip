@@ -225,6 +225,7 @@ void Executor::perm(std::vector<Launch>& dst, const PerProb& X, const std::strin
   Launch L;
   L.kind = Launch::PERM;
   L.n_prob = np;
+  for (int p = 0; p < np; ++p) L.prob_total.push_back((p + 1 < np ? prefix[p + 1] : total) - prefix[p]);
   L.total = total;
   L.d_desc = upload(ps.data(), sizeof(PermProblem) * np);
   L.d_prefix = (int*)upload(prefix.data(), sizeof(int) * np);
@@ -277,6 +278,7 @@ void Executor::fill(std::vector<Launch>& dst, const PerProb& Y, int rank, const 
   L.ranged = true;
   L.kind = Launch::FILL;
   L.n_prob = np;
+  for (int p = 0; p < np; ++p) L.prob_total.push_back((p + 1 < np ? prefix[p + 1] : total) - prefix[p]);
   L.total = total;
   L.d_desc = upload(ps.data(), sizeof(PermProblem) * np);
   L.d_prefix = (int*)upload(prefix.data(), sizeof(int) * np);
@@ -616,18 +618,22 @@ void Executor::contract(std::vector<Launch>& dst, const PerProb& out, const std:
     Launch L;
     for (int p = 0; p < np; ++p) {
       pf[p] = 2.0 * gs[p].M * (double)gs[p].N * gs[p].K;
-      pinst[p] = probs_[p].inst;
+      pinst[p] = p;
       L.bytes += sizeof(double) * ((double)gs[p].M * gs[p].K + (double)gs[p].K * gs[p].N +
                                    (double)gs[p].M * gs[p].N * (beta != 0.0 ? 2 : 1));
     }
     L.kind = Launch::GEMM;
     L.n_prob = np;
+    for (int p = 0; p < np; ++p) {
+      L.prob_total.push_back((p + 1 < np ? prefix[p + 1] : total) - prefix[p]);
+      L.prob_total2.push_back((p + 1 < np ? prefix2[p + 1] : total2) - prefix2[p]);
+    }
     L.total = total;
     L.min_k = np > 0 ? gs[0].K : 0;
     for (int p = 1; p < np; ++p) L.min_k = std::min(L.min_k, gs[p].K);
     if (&dst != &setup_) {
       L.prob_flops = pf;
-      L.prob_inst = pinst;
+      L.prob_gate = pinst;
     }
     L.cfg = gcfg;
     L.ta = ta;
@@ -1012,7 +1018,7 @@ bool Executor::contract_blocked(std::vector<Launch>& dst, const PerProb& out, co
     P.active = gate_for(dst, p);
     P.a_inner = has(K, unit_letter(ai, t_a)) ? 1 : 0;
     P.b_inner = has(K, unit_letter(bi, t_b)) ? 1 : 0;
-    pinst[p] = inst;
+    pinst[p] = p;
     const InstMomentum& Mm = *mom_[inst];
     for (const auto& blk : TM.blocks) {
       std::vector<int> q(Mm.dims), qk(Mm.dims), qn(Mm.dims);
@@ -1120,7 +1126,7 @@ bool Executor::contract_blocked(std::vector<Launch>& dst, const PerProb& out, co
   L.flops = flops;
   if (&dst != &setup_) {
     L.prob_flops = pf;
-    L.prob_inst = pinst;
+    L.prob_gate = pinst;
   }
   L.tag = tag + "(blocked)";
   dst.push_back(L);
@@ -1388,7 +1394,7 @@ Launch Executor::merge_sgemm(const std::vector<Launch*>& parts) {
     M.flops += l->flops;
     M.bytes += l->bytes;
     M.prob_flops.insert(M.prob_flops.end(), l->prob_flops.begin(), l->prob_flops.end());
-    M.prob_inst.insert(M.prob_inst.end(), l->prob_inst.begin(), l->prob_inst.end());
+    M.prob_gate.insert(M.prob_gate.end(), l->prob_gate.begin(), l->prob_gate.end());
     M.rd.insert(M.rd.end(), l->rd.begin(), l->rd.end());
     M.wr.insert(M.wr.end(), l->wr.begin(), l->wr.end());
     M.tag += (M.tag.empty() ? "" : "+") + l->tag;
@@ -1674,6 +1680,8 @@ void Executor::build(const Program* prog, const std::vector<ProblemRef>& probs, 
   const_alloc_ = const_alloc;
   if (!mom_.empty()) infer_laws();
   plan_packing(want_backward);
+  const int zero = 0;
+  d_zero_ = (int*)upload(&zero, sizeof(int));
   const int np = (int)probs.size();
   const int nt = (int)prog->t.size();
   std::vector<PerProb> fwd(nt, PerProb(np)), grd(nt, PerProb(np));
@@ -1716,12 +1724,34 @@ void Executor::build(const Program* prog, const std::vector<ProblemRef>& probs, 
     firsts_scratch.dot_partial = scratch->dot_partial;
     probs_ = firsts;
     scratch_ = &firsts_scratch;
+    // with momentum laws: one elementwise sum per derived constant (its ops are elementwise)
+    std::map<int, std::vector<const SymOp*>> by_out;
+    std::vector<int> order;
     for (const SymOp& o : prog->ops) {
       if (!o.setup) continue;
-      PerProb ob;
-      if (o.b >= 0) ob = sub(fwd[o.b]);
-      contract(setup_, sub(fwd[o.out]), o.oi, o.alpha, sub(fwd[o.a]), o.ai, -1, o.b >= 0 ? &ob : nullptr, o.bi,
-               -1, o.accumulate, "setup:" + prog->t[o.out].name, -1, -1, o.out, o.a, o.b);
+      if (by_out[o.out].empty()) order.push_back(o.out);
+      by_out[o.out].push_back(&o);
+    }
+    for (int out : order) {
+      std::vector<SumTerm> terms;
+      const std::vector<const SymOp*>& list = by_out[out];
+      for (const SymOp* o : list)
+        if (o->b < 0) {
+          SumTerm t{sub(fwd[o->a]), o->ai, o->a, o->alpha, {}, -1};
+          for (char& ch : t.xi) ch = (char)('A' + o->oi.find(ch));
+          terms.push_back(t);
+        }
+      std::string yi;
+      for (int k = 0; k < prog->t[out].rank; ++k) yi.push_back((char)('A' + k));
+      if (terms.size() == list.size() && !list[0]->accumulate &&
+          sum_blocked(setup_, terms, sub(fwd[out]), yi, 0.0, out, "setup:" + prog->t[out].name))
+        continue;
+      for (const SymOp* o : list) {
+        PerProb ob;
+        if (o->b >= 0) ob = sub(fwd[o->b]);
+        contract(setup_, sub(fwd[o->out]), o->oi, o->alpha, sub(fwd[o->a]), o->ai, -1, o->b >= 0 ? &ob : nullptr,
+                 o->bi, -1, o->accumulate, "setup:" + prog->t[o->out].name, -1, -1, o->out, o->a, o->b);
+      }
     }
     // Packed copies of the constants the blocked ops read, gathered from the dense
     // blocks (after the derived ones are made) each time the set-up list runs; the
@@ -1800,7 +1830,10 @@ void Executor::build(const Program* prog, const std::vector<ProblemRef>& probs, 
     if (prog->t[k].kind == T_OUTPUT) move_packed(fwd_, fwd[k], dense_f[k], k, false, "scatter:");
   if (!want_backward) {
     const char* fz = std::getenv("FTCC_FUSE");
-    if (!mom_.empty() && !(fz && fz[0] == '0')) fuse_levels(fwd_);
+    if (!mom_.empty() && !(fz && fz[0] == '0')) {
+      fuse_levels(setup_);
+      fuse_levels(fwd_);
+    }
     dump_plan();
     return;
   }
@@ -1834,6 +1867,7 @@ void Executor::build(const Program* prog, const std::vector<ProblemRef>& probs, 
   // FTCC_FUSE=0 keeps the program order, one launch per contraction (diagnostics)
   const char* fz = std::getenv("FTCC_FUSE");
   if (!mom_.empty() && !(fz && fz[0] == '0')) {
+    fuse_levels(setup_);
     fuse_levels(fwd_);
     fuse_levels(bwd_);
   }
@@ -1896,6 +1930,8 @@ void Executor::autotune(hipStream_t s) {
         l.d_prefix2 = w.d_prefix2;
         l.total = w.total;
         l.splitk_blocks = w.splitk_blocks;
+        l.prob_total = w.prob_total;
+        l.prob_total2 = w.prob_total2;
         l.min_k = w.min_k;
       }
       l.cfg = best_cfg;
@@ -1938,7 +1974,7 @@ double Executor::run_flops(const Launch& l) const {
   if (!gate_host_ || l.prob_flops.empty()) return l.flops;
   double f = 0.0;
   for (size_t p = 0; p < l.prob_flops.size(); ++p)
-    if (gate_host_[l.prob_inst[p]]) f += l.prob_flops[p];
+    if (gate_host_[l.prob_gate[p]]) f += l.prob_flops[p];
   return f;
 }
 
@@ -1978,6 +2014,32 @@ void Executor::run(const std::vector<Launch>& L, hipStream_t s) const {
         break;
     }
   }
+}
+
+bool Executor::run_forward_one(int prob, hipStream_t s) const {
+  for (const Launch& l : fwd_)
+    if (l.kind != Launch::PERM && l.kind != Launch::FILL && l.kind != Launch::GEMM && l.kind != Launch::DOT) return false;
+  for (const Launch& l : fwd_) {
+    switch (l.kind) {
+      case Launch::PERM:
+      case Launch::FILL:
+        launch_permute((const PermProblem*)l.d_desc + prob, d_zero_, 1, l.prob_total[prob], s);
+        break;
+      case Launch::GEMM: {
+        const GemmProblem* d = (const GemmProblem*)l.d_desc + prob;
+        const int total = l.prob_total[prob];
+        launch_gemm(l.cfg, l.ta, l.tb, d, d_zero_, 1, total,
+                    plan_gemm_tail(l.cfg, total, l.min_k, l.splitk_blocks > 0, scratch_->tail_ws,
+                                   scratch_->tail_ws_doubles),
+                    s);
+        if (l.splitk_blocks > 0) launch_splitk_reduce(d, d_zero_, 1, l.prob_total2[prob], s);
+        break;
+      }
+      default:
+        launch_dot((const DotProblem*)l.d_desc + prob, 1, l.dot_blocks, l.d_partial, s);
+    }
+  }
+  return true;
 }
 
 // ------------------------------------------------------------------ profiler

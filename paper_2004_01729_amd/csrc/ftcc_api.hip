@@ -36,9 +36,14 @@ thread_local std::string g_err;
 // g = electrons per orbital and occupation (2 spatial restricted, 1 spin orbitals):
 //   Omega_0 = -(g/beta) sum ln(1 + e^{-beta(eps-mu)}),
 //   Omega_1 = g sum (h_pp - eps_p) n_p + (g/2) sum_pq (g <pq|pq> - <pq|qp>) n_p n_q.
-__global__ void meanfield_kernel(int n, const double* eps, const double* h, const double* eri, const double* occ,
-                                 const double* fock, double mu, double beta, const double* dh, const double* deri,
-                                 double g, double* out) {
+__global__ void meanfield_kernel(const SetupProblem* probs, const double* mubeta, const double* const* dirs, double g) {
+  const SetupProblem& P = probs[blockIdx.x];   // one block per instance
+  const int n = P.n;
+  const double *eps = P.eps, *h = P.h, *eri = P.eri, *occ = P.occ, *fock = P.fock;
+  const double mu = mubeta[2 * blockIdx.x], beta = mubeta[2 * blockIdx.x + 1];
+  const double* dh = dirs ? dirs[2 * blockIdx.x] : nullptr;
+  const double* deri = dirs ? dirs[2 * blockIdx.x + 1] : nullptr;
+  double* out = P.mf;
   __shared__ double red[5][256];
   double a0 = 0, a1 = 0, a2 = 0, a3 = 0, a4 = 0;
   const long nn = (long)n * n;
@@ -90,19 +95,6 @@ __global__ void meanfield_kernel(int n, const double* eps, const double* h, cons
 }
 
 // dn/dmu = beta n (1-n), dn/dbeta = -(eps - mu) n (1-n); dw = dn / (2 w) on kept slots
-__global__ void occ_deriv_kernel(int n, const double* eps, const double* occ, const double* wo, const double* wv,
-                                 double mu, double beta, int which, double* dn, double* dwo, double* dwv) {
-  const int p = blockIdx.x * blockDim.x + threadIdx.x;
-  if (p >= n) return;
-  const double x = beta * (eps[p] - mu);
-  const double nvir = (x > 0.0) ? 1.0 / (1.0 + exp(-x)) : exp(x) / (1.0 + exp(x));
-  const double nn1 = occ[p] * nvir;
-  const double d = (which == 0) ? beta * nn1 : -(eps[p] - mu) * nn1;
-  dn[p] = d;
-  dwo[p] = (wo[p] > 0.0) ? d / (2.0 * wo[p]) : 0.0;
-  dwv[p] = (wv[p] > 0.0) ? -d / (2.0 * wv[p]) : 0.0;
-}
-
 // dO/dh_pq = g n_p delta_pq + sum_XY w^X_p w^Y_q G^XY_pq
 __global__ void dh_assemble_kernel(int n, const double* occ, const double* wo, const double* wv, const double* goo,
                                    const double* gov, const double* gvo, const double* gvv, double g, double* out) {
@@ -112,27 +104,6 @@ __global__ void dh_assemble_kernel(int n, const double* occ, const double* wo, c
   double v = (p == q) ? g * occ[p] : 0.0;
   v += wo[p] * wo[q] * goo[e] + wo[p] * wv[q] * gov[e] + wv[p] * wo[q] * gvo[e] + wv[p] * wv[q] * gvv[e];
   out[e] = v;
-}
-
-// Direction of the orbital energy eps_q at a frozen reference: dn_p = dn_p/deps_q =
-// -beta n_q (1 - n_q) delta_pq (the weights follow, dw = dn / (2 w) on kept slots),
-// and the explicit dependence of u = f - diag(eps): du = -e_q e_q^T (in dh).
-__global__ void occ_deriv_eps_kernel(int n, int q, const double* eps, const double* occ, const double* wo,
-                                     const double* wv, double mu, double beta, double* dn, double* dwo, double* dwv,
-                                     double* dh) {
-  const long e = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (e < (long)n * n) dh[e] = (e == (long)q * n + q) ? -1.0 : 0.0;
-  if (e >= n) return;
-  const int p = (int)e;
-  double d = 0.0;
-  if (p == q) {
-    const double x = beta * (eps[p] - mu);
-    const double nvir = (x > 0.0) ? 1.0 / (1.0 + exp(-x)) : exp(x) / (1.0 + exp(x));
-    d = -beta * occ[p] * nvir;
-  }
-  dn[p] = d;
-  dwo[p] = (wo[p] > 0.0) ? d / (2.0 * wo[p]) : 0.0;
-  dwv[p] = (wv[p] > 0.0) ? -d / (2.0 * wv[p]) : 0.0;
 }
 
 // Mean-field part of dOmega/deps_q: Omega_0 gives g n_q and the explicit -eps_q n_q of
@@ -227,6 +198,14 @@ __global__ void resp_combine_kernel(int B, int m, const double* vals, const doub
   for (int x = 0; x < m; ++x) s = vals[i * m + x] + s;
   for (int x = 0; x < m; ++x) s = w[x] * de[i * m + x][0] + s;
   acc[i][slot] = s;
+}
+
+// out[13 i ..]: the 8 response accumulators and the 5 mean-field sums of instance i
+__global__ void gather_acc_kernel(int B, double* const* acc, const SetupProblem* probs, double* out) {
+  const int t = blockIdx.x * blockDim.x + threadIdx.x;
+  if (t >= 13 * B) return;
+  const int i = t / 13, k = t % 13;
+  out[t] = k < 8 ? acc[i][k] : probs[i].mf[k - 8];
 }
 
 __global__ void zero_u64_kernel(unsigned long long* p, int count) {
@@ -415,143 +394,94 @@ void sync(ftcc_ctx* c) {
 }
 
 // ------------------------------------------------------------------ thermal set-up
+void setup_tables(ftcc_ctx* c) {
+  std::vector<SetupProblem> ps;
+  std::vector<int> prefix;
+  int total = 0;
+  for (Instance& I : c->inst) {
+    SetupProblem p{};
+    p.n = I.n;
+    p.eps = I.eps;
+    p.h = I.h;
+    p.eri = I.eri;
+    p.occ = I.occ;
+    p.wo = I.wo;
+    p.wv = I.wv;
+    p.fock = I.fock;
+    p.u_raw = I.u_raw;
+    p.dn = I.dn;
+    p.dwo = I.dwo;
+    p.dwv = I.dwv;
+    p.du_raw = I.du_raw;
+    for (int k = 0; k < 4; ++k) {
+      p.u[k] = I.blk[kU[k]];
+      p.du[k] = I.dblk[kU[k]];
+    }
+    for (int k = 0; k < 12; ++k) {
+      p.g[k] = I.blk[kG[k]];
+      p.dg[k] = I.dblk[kG[k]];
+    }
+    p.idx = I.d_allowed[1];   // with momentum labels: the allowed elements (the law of t2)
+    p.count = I.n_allowed[1];
+    p.mf = I.mf;
+    ps.push_back(p);
+    prefix.push_back(total);
+    c->setup_blocks.push_back((int)((setup_elements(p) + 255) / 256));
+    total += c->setup_blocks.back();
+    c->n_max = std::max(c->n_max, I.n);
+  }
+  prefix.push_back(0);
+  c->d_setup = (SetupProblem*)c->desc(ps.data(), sizeof(SetupProblem) * ps.size());
+  c->d_setup_prefix = (int*)c->desc(prefix.data(), sizeof(int) * prefix.size());
+  c->d_mubeta = (double*)c->desc(nullptr, sizeof(double) * 2 * ps.size());
+  c->d_dirs = (const double**)c->desc(nullptr, sizeof(double*) * 2 * ps.size());
+  c->mubeta.assign(2 * ps.size(), 0.0);
+}
+
+static int setup_total(const ftcc_ctx* c) {
+  int t = 0;
+  for (int b : c->setup_blocks) t += b;
+  return t;
+}
+
 void thermal_setup(ftcc_ctx* c, int i) {
-  Instance& I = c->inst[i];
-  const int n = I.n;
-  ThermalProblem tp;
-  tp.n = n;
-  tp.eps = I.eps;
-  tp.h = I.h;
-  tp.eri = I.eri;
-  tp.mu = I.mu;
-  tp.beta = I.beta;
-  tp.thr = c->opt.occ_thresh;
-  tp.g = c->gdeg;
-  tp.occ = I.occ;
-  tp.wo = I.wo;
-  tp.wv = I.wv;
-  tp.fock = I.fock;
-  launch_thermal(tp, c->stream);
-  launch_u_from_fock(n, I.fock, I.eps, I.u_raw, c->stream);
-  for (int k = 0; k < 4; ++k) {
-    BlockSpec b;
-    b.n = n;
-    b.rank = 2;
-    b.pat[0] = kU[k][2];
-    b.pat[1] = kU[k][3];
-    b.base = I.u_raw;
-    b.dbase = I.u_raw;
-    b.wo = I.wo;
-    b.wv = I.wv;
-    b.dwo = b.dwv = nullptr;
-    b.out = I.blk[kU[k]];
-    launch_block(b, c->stream);
+  for (int k = 0; k < c->B; ++k) {
+    c->mubeta[2 * k] = c->inst[k].mu;
+    c->mubeta[2 * k + 1] = c->inst[k].beta;
   }
-  for (int k = 0; k < 12; ++k) {
-    BlockSpec b;
-    b.n = n;
-    b.rank = 4;
-    for (int s = 0; s < 4; ++s) b.pat[s] = kG[k][2 + s];
-    b.base = I.eri;
-    b.dbase = I.eri;
-    b.wo = I.wo;
-    b.wv = I.wv;
-    b.dwo = b.dwv = nullptr;
-    b.out = I.blk[kG[k]];
-    b.idx = I.d_allowed[1];   // with momentum labels: the allowed elements (the law of t2)
-    b.count = I.n_allowed[1];
-    launch_block(b, c->stream);
-  }
-  hipLaunchKernelGGL(meanfield_kernel, dim3(1), dim3(256), 0, c->stream, n, I.eps, I.h, I.eri, I.occ, I.fock, I.mu,
-                     I.beta, nullptr, nullptr, c->gdeg, I.mf);
+  FTCC_HIP(hipMemcpyAsync(c->d_mubeta, c->mubeta.data(), sizeof(double) * c->mubeta.size(), hipMemcpyHostToDevice,
+                          c->stream));
+  const int first = i < 0 ? 0 : i, count = i < 0 ? c->B : 1;
+  launch_thermal(c->d_setup + first, c->d_mubeta + 2 * first, i < 0 ? c->d_setup_prefix : c->d_setup_prefix + c->B,
+                 count, c->n_max, i < 0 ? setup_total(c) : c->setup_blocks[i], c->opt.occ_thresh, c->gdeg, c->stream);
+  hipLaunchKernelGGL(meanfield_kernel, dim3(count), dim3(256), 0, c->stream, (const SetupProblem*)c->d_setup + first,
+                     (const double*)c->d_mubeta + 2 * first, (const double* const*)nullptr, c->gdeg);
   FTCC_HIP(hipGetLastError());
 }
 
-// derivative blocks for theta: which = 0 (mu), 1 (beta), 2 (direction dh, deri)
-void deriv_setup(ftcc_ctx* c, int i, int which, const double* d_dh, const double* d_deri) {
-  Instance& I = c->inst[i];
-  const int n = I.n;
-  if (which < 2) {
-    hipLaunchKernelGGL(occ_deriv_kernel, dim3((n + 63) / 64), dim3(64), 0, c->stream, n, I.eps, I.occ, I.wo, I.wv,
-                       I.mu, I.beta, which, I.dn, I.dwo, I.dwv);
-    launch_fock_deriv(n, I.eri, nullptr, nullptr, I.occ, I.dn, c->gdeg, I.du_raw, c->stream);
-  } else {
-    launch_fock_deriv(n, I.eri, d_deri, d_dh, I.occ, nullptr, c->gdeg, I.du_raw, c->stream);
+void set_directions(ftcc_ctx* c, const std::vector<double*>& d_dh, const std::vector<double*>& d_deri) {
+  std::vector<const double*> d;
+  for (int i = 0; i < c->B; ++i) {
+    d.push_back(d_dh[i]);
+    d.push_back(d_deri[i]);
   }
-  for (int k = 0; k < 4; ++k) {
-    BlockSpec b;
-    b.n = n;
-    b.rank = 2;
-    b.pat[0] = kU[k][2];
-    b.pat[1] = kU[k][3];
-    b.base = I.u_raw;
-    b.dbase = I.du_raw;
-    b.wo = I.wo;
-    b.wv = I.wv;
-    b.dwo = (which < 2) ? I.dwo : nullptr;
-    b.dwv = (which < 2) ? I.dwv : nullptr;
-    b.out = I.dblk[kU[k]];
-    launch_block(b, c->stream);
-  }
-  for (int k = 0; k < 12; ++k) {
-    BlockSpec b;
-    b.n = n;
-    b.rank = 4;
-    for (int s = 0; s < 4; ++s) b.pat[s] = kG[k][2 + s];
-    b.base = I.eri;
-    b.dbase = (which < 2) ? nullptr : d_deri;
-    b.wo = I.wo;
-    b.wv = I.wv;
-    b.dwo = (which < 2) ? I.dwo : nullptr;
-    b.dwv = (which < 2) ? I.dwv : nullptr;
-    b.out = I.dblk[kG[k]];
-    b.idx = I.d_allowed[1];
-    b.count = I.n_allowed[1];
-    launch_block(b, c->stream);
-  }
+  FTCC_HIP(hipMemcpy(c->d_dirs, d.data(), sizeof(double*) * d.size(), hipMemcpyHostToDevice));
+}
+
+void deriv_setup(ftcc_ctx* c, int which, int q) {
+  launch_setup_deriv(c->d_setup, c->d_mubeta, c->d_dirs, c->d_setup_prefix, c->B, c->n_max, setup_total(c), which, q,
+                     c->gdeg, c->stream);
   FTCC_HIP(hipGetLastError());
 }
 
-// derivative blocks along the orbital energy eps_q (occupation and explicit u parts)
-void deriv_setup_eps(ftcc_ctx* c, int i, int q) {
-  Instance& I = c->inst[i];
-  const int n = I.n;
-  const long n2 = (long)n * n;
-  hipLaunchKernelGGL(occ_deriv_eps_kernel, dim3((unsigned)((n2 + 255) / 256)), dim3(256), 0, c->stream, n, q, I.eps,
-                     I.occ, I.wo, I.wv, I.mu, I.beta, I.dn, I.dwo, I.dwv, I.deps_dh);
-  launch_fock_deriv(n, I.eri, nullptr, I.deps_dh, I.occ, I.dn, c->gdeg, I.du_raw, c->stream);
-  for (int k = 0; k < 4; ++k) {
-    BlockSpec b;
-    b.n = n;
-    b.rank = 2;
-    b.pat[0] = kU[k][2];
-    b.pat[1] = kU[k][3];
-    b.base = I.u_raw;
-    b.dbase = I.du_raw;
-    b.wo = I.wo;
-    b.wv = I.wv;
-    b.dwo = I.dwo;
-    b.dwv = I.dwv;
-    b.out = I.dblk[kU[k]];
-    launch_block(b, c->stream);
-  }
-  for (int k = 0; k < 12; ++k) {
-    BlockSpec b;
-    b.n = n;
-    b.rank = 4;
-    for (int s = 0; s < 4; ++s) b.pat[s] = kG[k][2 + s];
-    b.base = I.eri;
-    b.dbase = nullptr;
-    b.wo = I.wo;
-    b.wv = I.wv;
-    b.dwo = I.dwo;
-    b.dwv = I.dwv;
-    b.out = I.dblk[kG[k]];
-    b.idx = I.d_allowed[1];
-    b.count = I.n_allowed[1];
-    launch_block(b, c->stream);
-  }
-  FTCC_HIP(hipGetLastError());
+void list_allowed(const ftcc_ctx* c, int i, DotProblem& d) {
+  const Instance& I = c->inst[i];
+  if (!I.d_allowed[0]) return;
+  d.ia = I.d_allowed[0];
+  d.na = I.n_allowed[0];
+  d.ib = I.d_allowed[1];
+  d.nb = I.n_allowed[1];
+  d.second = (long)I.n * I.n;
 }
 
 long node_len_of(long n) { return n * n + n * n * n * n; }
@@ -676,6 +606,7 @@ void build(ftcc_ctx* c) {
     I.sb.resize(P + 1);
     for (int p = 0; p <= P; ++p) I.sb[p] = c->dalloc(len);
   }
+  setup_tables(c);
   // Checkpointing when the stored grid (amplitudes and residuals of every node)
   // would take more than half of the capped memory.
   if (!c->opt.checkpoint && c->opt.mem_cap_bytes) {
@@ -745,6 +676,8 @@ void build(ftcc_ctx* c) {
   c->dS.resize(nn);
   c->de.resize(nn);
   c->ugrad.resize(nn);
+  c->e_all = c->dalloc(nn);
+  c->de_all = c->dalloc(nn);
   for (int i = 0; i < B; ++i)
     for (int x = 0; x < m; ++x) {
       const int p = i * m + x;
@@ -752,13 +685,13 @@ void build(ftcc_ctx* c) {
       const long n2 = (long)n * n, n4 = n2 * n2, len = n2 + n4;
       c->amp[p] = c->dalloc(len);
       c->S[p] = c->dalloc(len);
-      c->e[p] = c->dalloc(1);
+      c->e[p] = c->e_all + p;
       c->gr[p] = c->dalloc(len);
       c->cot[p] = c->dalloc(len);
       c->ebar[p] = c->dalloc(1);
       // with one slot the derivative residuals reuse the gradient buffers (never live together)
       c->dS[p] = (SL == m) ? c->dalloc(len) : c->gr[p];
-      c->de[p] = c->dalloc(1);
+      c->de[p] = c->de_all + p;
       for (int k = 0; k < 4; ++k) c->ugrad[p][k] = c->dalloc(n2);
       const double eb = c->rule.b[x] / P;   // (1/beta) g_x
       FTCC_HIP(hipMemcpy(c->ebar[p], &eb, sizeof(double), hipMemcpyHostToDevice));
@@ -822,9 +755,10 @@ void build(ftcc_ctx* c) {
   }
   c->d_maxbits = (unsigned long long*)c->dalloc(2 * B);
   c->d_active = (int*)c->dalloc(B);
-  c->d_run = (int*)c->dalloc(B);
+  c->d_run = (int*)c->dalloc(B * SL);
   c->run_host.assign(B, 1);
-  FTCC_HIP(hipMemcpy(c->d_run, c->run_host.data(), sizeof(int) * B, hipMemcpyHostToDevice));
+  c->run_slots.assign(B * SL, 1);
+  FTCC_HIP(hipMemcpy(c->d_run, c->run_slots.data(), sizeof(int) * B * SL, hipMemcpyHostToDevice));
   {
     std::vector<int> ones(2 * B, 1);
     FTCC_HIP(hipMemcpy(c->d_active, ones.data(), sizeof(int) * B, hipMemcpyHostToDevice));
@@ -914,23 +848,6 @@ void build(ftcc_ctx* c) {
     fail(FTCC_EINVAL, "unbound tensor " + d.name);
   };
   auto calloc_ = [c](int, size_t count) { return c->dalloc(count); };
-  // Reused permuted copies of value operands are optional: one is taken only while
-  // it leaves a reserve for what the executors must still allocate (the second
-  // executor's intermediates and permuted constants: 16 n^4 doubles per instance,
-  // plus 1 GiB), and an allocation that fails leaves the operand uncached.
-  double reserve = 1073741824.0;
-  for (int i = 0; i < B; ++i) reserve += 16.0 * std::pow((double)c->inst[i].n, 4) * sizeof(double);
-  auto vcache = [c, reserve](size_t count) -> double* {
-    if (c->available() < reserve + (double)count * sizeof(double)) return nullptr;
-    try {
-      return c->dalloc(count);
-    } catch (const Fail& f) {
-      if (f.code != FTCC_ENOMEM) throw;
-      return nullptr;
-    }
-  };
-  // reuse budget for permuted operand copies: a quarter of the memory still available
-  // (the blocked contractions address their operands in place: no permuted copies)
   // Small dense problems take the blocked executor's path as well, everything in one
   // block: no operand or output is permuted and independent contractions share
   // launches.  Four nodes' residuals, GEMM path against this one: n = 8 0.401 / 0.106
@@ -949,20 +866,45 @@ void build(ftcc_ctx* c) {
       t.labels.assign(I.n, 0);
       c->one_block.push_back(t);
     }
-  const size_t budget = (mom || trivial) ? 0 : (size_t)(c->available() / 4);
+  const bool blocked = mom || trivial;
+  // Optional buffers: reused permuted copies of value operands (GEMM path), private
+  // copies of accumulated outputs (blocked path).  One is taken only while it leaves a
+  // reserve for what the executors must still allocate (the second executor's
+  // intermediates and permuted constants: 16 n^4 doubles per instance, plus 1 GiB), and
+  // an allocation that fails leaves the operand uncached or the writes serial.  The
+  // blocked path's stay within an eighth of the memory available here, and a capped
+  // context takes none.
+  double reserve = 1073741824.0;
+  for (int i = 0; i < B; ++i) reserve += 16.0 * std::pow((double)c->inst[i].n, 4) * sizeof(double);
+  double copies_left = blocked ? (c->opt.mem_cap_bytes ? 0.0 : c->available() / 8.0) : INFINITY;
+  auto vcache = [c, reserve, &copies_left](size_t count) -> double* {
+    const double bytes = (double)count * sizeof(double);
+    if (bytes > copies_left || c->available() < reserve + bytes) return nullptr;
+    try {
+      double* q = c->dalloc(count);
+      copies_left -= bytes;
+      return q;
+    } catch (const Fail& f) {
+      if (f.code != FTCC_ENOMEM) throw;
+      return nullptr;
+    }
+  };
+  // reuse budget for permuted operand copies: a quarter of the memory still available
+  // (the blocked contractions address their operands in place: no permuted copies)
+  const size_t budget = blocked ? 0 : (size_t)(c->available() / 4);
   std::vector<const InstMomentum*> by_inst;
   if (mom)
     for (const Instance& I : c->inst) by_inst.push_back(&I.mom);
   else
     for (const InstMomentum& t : c->one_block) by_inst.push_back(&t);
   c->ex_main.reset(new Executor());
-  c->ex_main->set_gate(c->d_run, c->run_host.data());
-  if (mom || trivial) c->ex_main->set_momentum(by_inst);
+  c->ex_main->set_gate(c->d_run, c->run_slots.data());
+  if (blocked) c->ex_main->set_momentum(by_inst);
   c->ex_main->build(&prog, probs, bind_main, &c->scratch, calloc_, true, ugrads, vcache, budget);
   c->ex_main->set_profiler(&c->prof);
   trace_executor(c, "main", *c->ex_main);
   c->ex_d.reset(new Executor());
-  if (mom || trivial) c->ex_d->set_momentum(by_inst);
+  if (blocked) c->ex_d->set_momentum(by_inst);
   c->ex_d->build(&prog, probs, bind_d, &c->scratch, calloc_, false, {}, vcache, budget / 2);
   c->ex_d->set_profiler(&c->prof);
   trace_executor(c, "derivative", *c->ex_d);
@@ -1035,6 +977,8 @@ void node_copy(ftcc_ctx* c, int i, double* dst, const double* src) {
   FTCC_HIP(hipGetLastError());
 }
 
+constexpr int kEvalGateMinN = 12;
+
 // forward residuals of every node of the panel slots (node amplitudes -> S, E)
 void forward(ftcc_ctx* c) {
   if (c->slots == c->m) {
@@ -1051,6 +995,82 @@ void forward(ftcc_ctx* c) {
       dcopy(c, c->e[i * c->m + x], c->s_e[i], 1);
     }
   }
+}
+
+void state_set(ftcc_ctx* c, int kind, int panel,
+               const std::function<void(std::function<void(int, double*, const double*)>)>& list) {
+  const auto key = std::make_pair(kind, panel);
+  auto it = c->state_copies.find(key);
+  if (it == c->state_copies.end()) {
+    std::vector<StateCopy> cs;
+    std::vector<int> prefix;
+    int total = 0;
+    list([&](int i, double* dst, const double* src) {
+      const Instance& I = c->inst[i];
+      StateCopy k{};
+      k.src = src;
+      k.dst = dst;
+      k.len = node_len(c, i);
+      if (I.d_allowed[0] && I.d_allowed[1]) {
+        k.a = I.d_allowed[0];
+        k.na = I.n_allowed[0];
+        k.b = I.d_allowed[1];
+        k.nb = I.n_allowed[1];
+        k.second = (long)I.n * I.n;
+        k.len = k.na + k.nb;
+      }
+      prefix.push_back(total);
+      total += (int)((k.len + kStateCopyBlock - 1) / kStateCopyBlock);
+      cs.push_back(k);
+    });
+    ftcc_ctx::StateCopies t;
+    t.n = (int)cs.size();
+    t.blocks = total;
+    t.d = (StateCopy*)c->desc(cs.data(), sizeof(StateCopy) * cs.size());
+    t.prefix = (int*)c->desc(prefix.data(), sizeof(int) * prefix.size());
+    it = c->state_copies.emplace(key, t).first;
+  }
+  launch_state_copies(it->second.d, it->second.prefix, it->second.n, it->second.blocks, c->stream);
+  FTCC_HIP(hipGetLastError());
+}
+
+// Write access to every page of a caller's output buffer, contents unchanged: memory
+// fresh from the system is mapped page by page on first access, which a copy into it
+// would otherwise wait for (84 MB at n = 57: 9.4 ms, 5 ms once mapped).
+void touch_pages(void* p, size_t bytes) {
+  volatile char* c = (volatile char*)p;
+  for (size_t k = 0; k < bytes; k += 4096) c[k] = c[k];
+  if (bytes) c[bytes - 1] = c[bytes - 1];
+}
+
+// the forward residual of one node of one instance (its first), the others left as they are
+void eval_one(ftcc_ctx* c, int i) {
+  if (c->slots != c->m) {   // one slot: that node alone goes through it
+    const int q = i * c->m;
+    node_copy(c, i, c->s_amp[i], c->amp[q]);
+    std::vector<bool> only(c->B, false);
+    only[i] = true;
+    set_run(c, only);
+    run_fwd_slots(c);
+    node_copy(c, i, c->S[q], c->s_S[i]);
+    dcopy(c, c->e[q], c->s_e[i], 1);
+    run_all(c);
+    return;
+  }
+  if (!c->prof.enabled && c->ex_main->run_forward_one(i * c->m, c->stream)) return;
+  // The blocked launches hold every problem: the others' tasks return at once.  Below
+  // this size a pass of all nodes costs no more than switching the flags.
+  if (c->B == 1 && c->inst[i].n < kEvalGateMinN) {
+    run_fwd_slots(c);
+    return;
+  }
+  std::vector<int> only(c->run_slots.size(), 0);
+  only[i * c->m] = 1;
+  FTCC_HIP(hipMemcpyAsync(c->d_run, only.data(), sizeof(int) * only.size(), hipMemcpyHostToDevice, c->stream));
+  run_fwd_slots(c);
+  FTCC_HIP(hipMemcpyAsync(c->d_run, c->run_slots.data(), sizeof(int) * c->run_slots.size(), hipMemcpyHostToDevice,
+                          c->stream));
+  FTCC_HIP(hipStreamSynchronize(c->stream));   // both host arrays are read by then
 }
 
 // reverse pass of every node (cotangents cot, E weights ebar -> gradients gr, ugrad).
@@ -1229,8 +1249,12 @@ void set_run(ftcc_ctx* c, const std::vector<bool>& run) {
   bool same = true;
   for (int i = 0; i < c->B; ++i) same = same && ((c->run_host[i] != 0) == run[i]);
   if (same) return;
-  for (int i = 0; i < c->B; ++i) c->run_host[i] = run[i] ? 1 : 0;
-  FTCC_HIP(hipMemcpyAsync(c->d_run, c->run_host.data(), sizeof(int) * c->B, hipMemcpyHostToDevice, c->stream));
+  for (int i = 0; i < c->B; ++i) {
+    c->run_host[i] = run[i] ? 1 : 0;
+    for (int x = 0; x < c->slots; ++x) c->run_slots[i * c->slots + x] = c->run_host[i];
+  }
+  FTCC_HIP(hipMemcpyAsync(c->d_run, c->run_slots.data(), sizeof(int) * c->run_slots.size(), hipMemcpyHostToDevice,
+                          c->stream));
   // the host array is reused by the next call: finish this copy first
   FTCC_HIP(hipStreamSynchronize(c->stream));
 }
@@ -1509,6 +1533,7 @@ int ftcc_destroy(ftcc_ctx* c) {
     c->ex_main.reset();
     c->ex_d.reset();
     c->ex_g.reset();
+    for (void* p : c->descs) (void)hipFree(p);
     for (void* p : c->allocs) {
       if (c->ufree) c->ufree(p, c->uuser);
       else if (!c->ualloc) (void)hipFree(p);
@@ -1603,7 +1628,6 @@ int ftcc_solve_amplitudes(ftcc_ctx* c, const double* mu, const double* beta, int
     build(c);
     clear_tau_cache(c);
     const int B = c->B, m = c->m, P = c->P;
-    auto lenof = [c](int i) { const long n = c->inst[i].n; return n * n + n * n * n * n; };
     hipEvent_t e0, e1;
     FTCC_HIP(hipEventCreate(&e0));
     FTCC_HIP(hipEventCreate(&e1));
@@ -1613,11 +1637,13 @@ int ftcc_solve_amplitudes(ftcc_ctx* c, const double* mu, const double* beta, int
       Instance& I = c->inst[i];
       I.mu = mu[i];
       I.beta = beta[i];
-      thermal_setup(c, i);
-      zero_d(c, I.sb[0], lenof(i));
       I.iters = 0;
       I.status = 0;
     }
+    state_set(c, ST_ZERO_START, 0, [c](auto add) {
+      for (int i = 0; i < c->B; ++i) add(i, c->inst[i].sb[0], nullptr);
+    });
+    thermal_setup(c);
     c->ex_main->run_setup(c->stream);
     std::vector<int> status(B, 0), total(B, 0);
     std::vector<double> ebuf(B * m);
@@ -1627,17 +1653,15 @@ int ftcc_solve_amplitudes(ftcc_ctx* c, const double* mu, const double* beta, int
     for (int p = 0; p < ((c->rk || c->simpson) ? 0 : P); ++p) {
       std::vector<int> its = panel_solve(c, p, status);
       for (int i = 0; i < B; ++i) total[i] += its[i];
-      for (int i = 0; i < B; ++i) {
-        Instance& I = c->inst[i];
-        for (int x = 0; x < m; ++x) {
-          FTCC_HIP(hipMemcpyAsync(&ebuf[i * m + x], c->e[i * m + x], sizeof(double), hipMemcpyDeviceToHost,
-                                  c->stream));
-          if (!c->opt.checkpoint) {
-            copy_d(c, I.grid[p * m + x], c->amp[i * m + x], lenof(i));
-            copy_d(c, I.resid[p * m + x], c->S[i * m + x], lenof(i));
+      FTCC_HIP(hipMemcpyAsync(ebuf.data(), c->e_all, sizeof(double) * B * m, hipMemcpyDeviceToHost, c->stream));
+      if (!c->opt.checkpoint)
+        state_set(c, ST_SAVE, p, [c, p](auto add) {
+          for (int q = 0; q < c->B * c->m; ++q) {
+            Instance& I = c->inst[q / c->m];
+            add(q / c->m, I.grid[p * c->m + q % c->m], c->amp[q]);
+            add(q / c->m, I.resid[p * c->m + q % c->m], c->S[q]);
           }
-        }
-      }
+        });
       tau_run(c, TAU_END, p);
       sync(c);
       for (int i = 0; i < B; ++i)
@@ -1730,10 +1754,10 @@ void load_panel(ftcc_ctx* c, int p) {
     ok[i] = st[i] == 0;
   }
   if (!c->opt.checkpoint) {
-    for (int i = 0; i < B; ++i) {
-      const long n = c->inst[i].n, len = n * n + n * n * n * n;
-      for (int x = 0; x < m; ++x) copy_d(c, c->amp[i * m + x], c->inst[i].grid[p * m + x], len);
-    }
+    state_set(c, ST_LOAD, p, [c, p](auto add) {
+      for (int q = 0; q < c->B * c->m; ++q)
+        add(q / c->m, c->amp[q], c->inst[q / c->m].grid[p * c->m + q % c->m]);
+    });
     set_run(c, ok);
     forward(c);
   } else {
@@ -1754,11 +1778,10 @@ int ftcc_lambda(ftcc_ctx* c, int* iters_out, int* status_out) {
     if (!c->solved) fail(FTCC_ESTATE, "call ftcc_solve_amplitudes first");
     FTCC_HIP(hipSetDevice(c->device));
     const int B = c->B, m = c->m, P = c->P;
-    for (int i = 0; i < B && !c->simpson; ++i) {   // a_P = 0 (the Simpson form keeps S[s_P] there)
-      Instance& I = c->inst[i];
-      const long n = I.n, len = n * n + n * n * n * n;
-      zero_d(c, I.abuf[P], len);
-    }
+    if (!c->simpson)   // a_P = 0 (the Simpson form keeps S[s_P] there)
+      state_set(c, ST_ZERO_END, 0, [c](auto add) {
+        for (int i = 0; i < c->B; ++i) add(i, c->inst[i].abuf[c->P], nullptr);
+      });
     hipEvent_t e0, e1;
     FTCC_HIP(hipEventCreate(&e0));
     FTCC_HIP(hipEventCreate(&e1));
@@ -1776,10 +1799,9 @@ int ftcc_lambda(ftcc_ctx* c, int* iters_out, int* status_out) {
       const std::vector<int> before = total;
       load_panel(c, p);
       // lambda_x = -(g_x/beta) dE/ds : backward with zero S-cotangent
-      for (int q = 0; q < B * m; ++q) {
-        const long n = c->inst[q / m].n;
-        zero_d(c, c->cot[q], n * n + n * n * n * n);
-      }
+      state_set(c, ST_ZERO_COT, 0, [c](auto add) {
+        for (int q = 0; q < c->B * c->m; ++q) add(q / c->m, c->cot[q], nullptr);
+      });
       backward(c);
       c->vjp_evals += n_running(c) * m;
       reset_maxbits(c);
@@ -1933,13 +1955,7 @@ static void ensure_resp_groups(ftcc_ctx* c) {
       d.Y = c->dS[q];
       d.out = c->d_resp_vals + q;
       d.len = n * n + n * n * n * n;
-      if (c->inst[i].d_allowed[0]) {   // momentum labels: the allowed elements only
-        d.ia = c->inst[i].d_allowed[0];
-        d.na = c->inst[i].n_allowed[0];
-        d.ib = c->inst[i].d_allowed[1];
-        d.nb = c->inst[i].n_allowed[1];
-        d.second = n * n;
-      }
+      list_allowed(c, i, d);
       d.alpha = 1.0;
       d.beta = 0.0;
       ds[q] = d;
@@ -1959,6 +1975,14 @@ static void ensure_resp_groups(ftcc_ctx* c) {
   c->d_ug_src = (const double**)up(ugs.data(), sizeof(double*) * ugs.size());
   c->d_ug_dst = (double**)up(ugd.data(), sizeof(double*) * ugd.size());
   c->d_n2 = (long*)up(n2.data(), sizeof(long) * n2.size());
+  std::vector<int> off(B + 1, 0);
+  for (int i = 0; i < B; ++i)
+    off[i + 1] = off[i] + (int)((seg_len(c, i, 0) + 1023) / 1024 + (seg_len(c, i, 1) + 1023) / 1024);
+  c->d_beta_off = (int*)c->desc(off.data(), sizeof(int) * off.size());
+  long total_n2 = 0;
+  for (long v : n2) total_n2 += v;
+  c->d_dh_out = (double*)c->desc(nullptr, sizeof(double) * total_n2);
+  c->d_acc_all = (double*)c->desc(nullptr, sizeof(double) * 13 * B);   // the accumulators (8) and mean-field sums (5), gathered for the host
 }
 
 int ftcc_response(ftcc_ctx* c, double* dO_dmu, double* dO_dbeta, double* dO_dh, double* dO_deps,
@@ -1977,7 +2001,6 @@ int ftcc_response(ftcc_ctx* c, double* dO_dmu, double* dO_dbeta, double* dO_dh, 
         if (!I.deps_acc) {
           I.deps_acc = c->dalloc(n);
           I.deps_out = c->dalloc(n);
-          I.deps_dh = c->dalloc(n * n);
           I.deps_delta = c->dalloc(node_len(c, i));
         }
         zero_d(c, I.deps_acc, n);
@@ -2015,6 +2038,7 @@ int ftcc_response(ftcc_ctx* c, double* dO_dmu, double* dO_dbeta, double* dO_dh, 
         }
       }
     }
+    if (want_theta) set_directions(c, d_dh, d_deri);
     for (int i = 0; i < B; ++i) {
       const long n = c->inst[i].n;
       zero_d(c, c->inst[i].acc, 8);
@@ -2041,13 +2065,7 @@ int ftcc_response(ftcc_ctx* c, double* dO_dmu, double* dO_dbeta, double* dO_dh, 
           d.Y = c->dS[i * m + x];
           d.out = c->inst[i].deps_acc + q;
           d.len = n * n + n * n * n * n;
-          if (c->inst[i].d_allowed[0]) {
-            d.ia = c->inst[i].d_allowed[0];
-            d.na = c->inst[i].n_allowed[0];
-            d.ib = c->inst[i].d_allowed[1];
-            d.nb = c->inst[i].n_allowed[1];
-            d.second = n * n;
-          }
+          list_allowed(c, i, d);
           d.alpha = 1.0;
           d.beta = 1.0;
           DotProblem* dd = nullptr;
@@ -2098,7 +2116,7 @@ int ftcc_response(ftcc_ctx* c, double* dO_dmu, double* dO_dbeta, double* dO_dh, 
             if (which == 0 && !dO_dmu) continue;
             if (which == 1 && !dO_dbeta) continue;
             if (which == 2 && !want_theta) continue;
-            for (int i = 0; i < B; ++i) deriv_setup(c, i, which, d_dh[i], d_deri[i]);
+            deriv_setup(c, which);
             c->ex_d->run_setup(c->stream);
             d_forward_one(c, x);
             rk_dot(c, 2 + which, k, x, [c, x, which](int i) {
@@ -2121,8 +2139,7 @@ int ftcc_response(ftcc_ctx* c, double* dO_dmu, double* dO_dbeta, double* dO_dh, 
                                    c->inst[i].deps_delta);
               }
             for (int q = 0; q < nmax; ++q) {
-              for (int i = 0; i < B; ++i)
-                if (q < c->inst[i].n) deriv_setup_eps(c, i, q);
+              deriv_setup(c, SETUP_EPS, q);
               c->ex_d->run_setup(c->stream);
               d_forward_one(c, x);
               for (int i = 0; i < B; ++i) {
@@ -2133,6 +2150,7 @@ int ftcc_response(ftcc_ctx* c, double* dO_dmu, double* dO_dbeta, double* dO_dh, 
                 d.Y = c->dS[i * m + x];
                 d.out = c->inst[i].deps_acc + q;
                 d.len = n * n + n * n * n * n;
+                list_allowed(c, i, d);
                 d.alpha = 1.0;
                 d.beta = 1.0;
                 DotProblem* dd = nullptr;
@@ -2168,6 +2186,7 @@ int ftcc_response(ftcc_ctx* c, double* dO_dmu, double* dO_dbeta, double* dO_dh, 
           d.Y = Y ? Y : c->dS[i * m];
           d.out = out(i);
           d.len = node_len(c, i);
+          list_allowed(c, i, d);
           d.alpha = 1.0;
           d.beta = 1.0;
           DotProblem* dd = nullptr;
@@ -2197,7 +2216,7 @@ int ftcc_response(ftcc_ctx* c, double* dO_dmu, double* dO_dbeta, double* dO_dh, 
           if (which == 0 && !dO_dmu) continue;
           if (which == 1 && !dO_dbeta) continue;
           if (which == 2 && !want_theta) continue;
-          for (int i = 0; i < B; ++i) deriv_setup(c, i, which, d_dh[i], d_deri[i]);
+          deriv_setup(c, which);
           c->ex_d->run_setup(c->stream);
           d_forward_one(c, 0);
           dot_into(nullptr, nullptr, [c, which](int i) { return c->inst[i].acc + which; });
@@ -2206,8 +2225,7 @@ int ftcc_response(ftcc_ctx* c, double* dO_dmu, double* dO_dbeta, double* dO_dh, 
         }
         if (dO_deps) {
           for (int q = 0; q < nmax; ++q) {
-            for (int i = 0; i < B; ++i)
-              if (q < c->inst[i].n) deriv_setup_eps(c, i, q);
+            deriv_setup(c, SETUP_EPS, q);
             c->ex_d->run_setup(c->stream);
             d_forward_one(c, 0);
             for (int i = 0; i < B; ++i) {
@@ -2217,6 +2235,7 @@ int ftcc_response(ftcc_ctx* c, double* dO_dmu, double* dO_dbeta, double* dO_dh, 
               d.Y = c->dS[i * m];
               d.out = c->inst[i].deps_acc + q;
               d.len = node_len(c, i);
+              list_allowed(c, i, d);
               d.alpha = 1.0;
               d.beta = 1.0;
               DotProblem* dd = nullptr;
@@ -2241,6 +2260,7 @@ int ftcc_response(ftcc_ctx* c, double* dO_dmu, double* dO_dbeta, double* dO_dh, 
             d.Y = c->inst[i].rk_tmp[0];
             d.out = c->inst[i].rk_hbar;
             d.len = node_len(c, i);
+            list_allowed(c, i, d);
             d.alpha = 1.0;
             d.beta = 1.0;
             DotProblem* dd = nullptr;
@@ -2274,19 +2294,15 @@ int ftcc_response(ftcc_ctx* c, double* dO_dmu, double* dO_dbeta, double* dO_dh, 
       // beta: explicit dependence of the propagator weights (needs S at converged s)
       if (dO_dbeta) {
         tau_run(c, TAU_BETA, p);
-        // partial sums per (instance, segment) -> acc[3]
-        for (int i = 0; i < B; ++i) {
-          const long n2 = (long)c->inst[i].n * c->inst[i].n;
-          const int nb1 = (int)((seg_len(c, i, 0) + 1023) / 1024), nb2 = (int)((seg_len(c, i, 1) + 1023) / 1024);
-          launch_sum(c->d_partial + c->beta_part_off[i], nb1 + nb2, c->inst[i].acc + 4, c->stream);
-          launch_axpby(1, 1.0 / P, c->inst[i].acc + 4, 1.0, c->inst[i].acc + 3, c->stream);
-        }
+        ensure_resp_groups(c);
+        launch_partial_sums(B, c->d_partial, c->d_beta_off, 1.0 / P, c->d_acc_ptrs, 3, c->stream);
+        FTCC_HIP(hipGetLastError());
       }
       for (int which = 0; which < 3; ++which) {
         if (which == 0 && !dO_dmu) continue;
         if (which == 1 && !dO_dbeta) continue;
         if (which == 2 && !want_theta) continue;
-        for (int i = 0; i < B; ++i) deriv_setup(c, i, which, d_dh[i], d_deri[i]);
+        deriv_setup(c, which);
         c->ex_d->run_setup(c->stream);
         d_forward(c);
         accumulate(which);
@@ -2296,8 +2312,7 @@ int ftcc_response(ftcc_ctx* c, double* dO_dmu, double* dO_dbeta, double* dO_dh, 
         // derivative-integral evaluation per orbital energy
         tau_run(c, TAU_DEPS, p);
         for (int q = 0; q < nmax; ++q) {
-          for (int i = 0; i < B; ++i)
-            if (q < c->inst[i].n) deriv_setup_eps(c, i, q);
+          deriv_setup(c, SETUP_EPS, q);
           c->ex_d->run_setup(c->stream);
           d_forward(c);
           accumulate_eps(q);
@@ -2307,23 +2322,26 @@ int ftcc_response(ftcc_ctx* c, double* dO_dmu, double* dO_dbeta, double* dO_dh, 
     run_all(c);
     // mean-field parts and assembly
     std::vector<double> accs(8 * B), mfv(5 * B);
-    for (int i = 0; i < B; ++i) {
-      Instance& I = c->inst[i];
-      const long n = I.n, n2 = n * n;
-      hipLaunchKernelGGL(meanfield_kernel, dim3(1), dim3(256), 0, c->stream, (int)n, I.eps, I.h, I.eri, I.occ,
-                         I.fock, I.mu, I.beta, d_dh[i], d_deri[i], c->gdeg, I.mf);
-      FTCC_HIP(hipMemcpyAsync(&mfv[5 * i], I.mf, sizeof(double) * 5, hipMemcpyDeviceToHost, c->stream));
-      FTCC_HIP(hipMemcpyAsync(&accs[8 * i], I.acc, sizeof(double) * 8, hipMemcpyDeviceToHost, c->stream));
-      if (dO_dh) {
-        double* dd = nullptr;
-        FTCC_HIP(hipMallocAsync((void**)&dd, sizeof(double) * n2, c->stream));
+    hipLaunchKernelGGL(meanfield_kernel, dim3(B), dim3(256), 0, c->stream, (const SetupProblem*)c->d_setup,
+                       (const double*)c->d_mubeta, want_theta ? (const double* const*)c->d_dirs : nullptr, c->gdeg);
+    FTCC_HIP(hipGetLastError());
+    ensure_resp_groups(c);
+    hipLaunchKernelGGL(gather_acc_kernel, dim3((13 * B + 255) / 256), dim3(256), 0, c->stream, B, c->d_acc_ptrs,
+                       (const SetupProblem*)c->d_setup, c->d_acc_all);
+    FTCC_HIP(hipGetLastError());
+    std::vector<double> host(13 * B);
+    FTCC_HIP(hipMemcpyAsync(host.data(), c->d_acc_all, sizeof(double) * host.size(), hipMemcpyDeviceToHost, c->stream));
+    if (dO_dh) {
+      long off = 0;
+      for (int i = 0; i < B; ++i) {
+        Instance& I = c->inst[i];
+        const long n = I.n, n2 = n * n;
         hipLaunchKernelGGL(dh_assemble_kernel, dim3((n2 + 255) / 256), dim3(256), 0, c->stream, (int)n, I.occ, I.wo,
-                           I.wv, I.ugrad_acc[0], I.ugrad_acc[1], I.ugrad_acc[2], I.ugrad_acc[3], c->gdeg, dd);
-        long off = 0;
-        for (int k = 0; k < i; ++k) off += (long)c->inst[k].n * c->inst[k].n;
-        FTCC_HIP(hipMemcpyAsync(dO_dh + off, dd, sizeof(double) * n2, hipMemcpyDeviceToHost, c->stream));
-        FTCC_HIP(hipFreeAsync(dd, c->stream));
+                           I.wv, I.ugrad_acc[0], I.ugrad_acc[1], I.ugrad_acc[2], I.ugrad_acc[3], c->gdeg,
+                           c->d_dh_out + off);
+        off += n2;
       }
+      FTCC_HIP(hipMemcpyAsync(dO_dh, c->d_dh_out, sizeof(double) * off, hipMemcpyDeviceToHost, c->stream));
     }
     if (dO_deps) {
       long off = 0;
@@ -2341,6 +2359,8 @@ int ftcc_response(ftcc_ctx* c, double* dO_dmu, double* dO_dbeta, double* dO_dh, 
     }
     sync(c);
     for (int i = 0; i < B; ++i) {
+      for (int k = 0; k < 8; ++k) accs[8 * i + k] = host[13 * i + k];
+      for (int k = 0; k < 5; ++k) mfv[5 * i + k] = host[13 * i + 8 + k];
       if (dO_dmu) dO_dmu[i] = mfv[5 * i + 2] + accs[8 * i + 0];
       if (dO_dbeta) dO_dbeta[i] = mfv[5 * i + 3] + accs[8 * i + 1] + accs[8 * i + 3];
       if (want_theta) dO_dtheta[i] = mfv[5 * i + 4] + accs[8 * i + 2];
@@ -2362,17 +2382,17 @@ int ftcc_eval_residual(ftcc_ctx* c, int i, double mu, double beta, const double*
     I.beta = beta;
     thermal_setup(c, i);
     c->ex_main->run_setup(c->stream);
-    for (int x = 0; x < c->m; ++x) {
-      FTCC_HIP(hipMemcpyAsync(c->amp[i * c->m + x], t1, sizeof(double) * n2, hipMemcpyHostToDevice, c->stream));
-      FTCC_HIP(
-          hipMemcpyAsync(c->amp[i * c->m + x] + n2, t2, sizeof(double) * n4, hipMemcpyHostToDevice, c->stream));
-    }
-    if (I.d_allowed[0]) {   // the blocked path keeps every forbidden element of a state at zero
-      check_momentum(c, i, c->amp[i * c->m], 2, "t1");
-      check_momentum(c, i, c->amp[i * c->m] + n2, 4, "t2");
-    }
-    forward(c);
+    // every node slot gets the amplitudes (ftcc_time_residual evaluates them all)
     const int q = i * c->m;
+    FTCC_HIP(hipMemcpyAsync(c->amp[q], t1, sizeof(double) * n2, hipMemcpyHostToDevice, c->stream));
+    FTCC_HIP(hipMemcpyAsync(c->amp[q] + n2, t2, sizeof(double) * n4, hipMemcpyHostToDevice, c->stream));
+    for (int x = 1; x < c->m; ++x) node_copy(c, i, c->amp[q + x], c->amp[q]);
+    if (I.d_allowed[0]) {   // the blocked path keeps every forbidden element of a state at zero
+      check_momentum(c, i, c->amp[q], 2, "t1");
+      check_momentum(c, i, c->amp[q] + n2, 4, "t2");
+    }
+    eval_one(c, i);
+    if (S2) touch_pages(S2, sizeof(double) * n4);   // while the GPU works
     if (S1) FTCC_HIP(hipMemcpyAsync(S1, c->S[q], sizeof(double) * n2, hipMemcpyDeviceToHost, c->stream));
     if (S2) FTCC_HIP(hipMemcpyAsync(S2, c->S[q] + n2, sizeof(double) * n4, hipMemcpyDeviceToHost, c->stream));
     if (E) FTCC_HIP(hipMemcpyAsync(E, c->e[q], sizeof(double), hipMemcpyDeviceToHost, c->stream));

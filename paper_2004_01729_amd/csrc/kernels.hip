@@ -403,24 +403,37 @@ __global__ void __launch_bounds__(256) sgemm_kernel(const SgemmProblem* __restri
     if (ok) {
       const unsigned am = gview(P.offAM)[T.mb + tr];
       const unsigned bn = gview(P.offBN)[T.nb + tc];
-      int k = s;
-      for (; k + 7 * S < T.klen; k += 8 * S) {
-        unsigned ak[8], bk[8];
-        double a[8], b[8];
+      // N inner indices of the slice at once: their offsets, then their gathers
+      auto batch = [&](auto n_c, int k) {
+        constexpr int N = decltype(n_c)::value;
+        unsigned ak[N], bk[N];
+        double a[N], b[N];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) {
+        for (int u = 0; u < N; ++u) {
           ak[u] = offAK[k + u * S];
           bk[u] = offBK[k + u * S];
         }
 #pragma unroll
-        for (int u = 0; u < 8; ++u) {
+        for (int u = 0; u < N; ++u) {
           a[u] = A[am + ak[u]];
           b[u] = B[bk[u] + bn];
         }
 #pragma unroll
-        for (int u = 0; u < 8; ++u) acc = fma(a[u], b[u], acc);
+        for (int u = 0; u < N; ++u) acc = fma(a[u], b[u], acc);
+      };
+      int k = s;
+      for (; k + 7 * S < T.klen; k += 8 * S) batch(std::integral_constant<int, 8>{}, k);
+      // the rest in batches of 4, 2 and 1: no gather more than needed, three waits
+      // for memory at most
+      if (k + 3 * S < T.klen) {
+        batch(std::integral_constant<int, 4>{}, k);
+        k += 4 * S;
       }
-      for (; k < T.klen; k += S) acc = fma(A[am + offAK[k]], B[offBK[k] + bn], acc);
+      if (k + S < T.klen) {
+        batch(std::integral_constant<int, 2>{}, k);
+        k += 2 * S;
+      }
+      if (k < T.klen) batch(std::integral_constant<int, 1>{}, k);
     }
     for (int o = S >> 1; o > 0; o >>= 1) acc += __shfl_xor(acc, o);
     if (ok && s == 0) {
@@ -439,9 +452,12 @@ __global__ void __launch_bounds__(256) sgemm_kernel(const SgemmProblem* __restri
   // G groups of 4 inner indices per step: the offset loads of all groups are
   // issued together, then all operand gathers, then the MFMAs, so one step
   // waits for two memory latencies instead of two per group.  Loads past the
-  // end of the range read the range's first entry (in bounds) and are zeroed.
-  constexpr int G = 8;
-  for (int k0 = 0; k0 < T.klen; k0 += 4 * G) {
+  // end of the range read the range's first entry (in bounds) and are zeroed;
+  // a step has no more groups than the range needs (rounded up to 1, 2, 4 or 8:
+  // most blocks of a plane-wave gas have an inner range of 4 to 16, and the
+  // scattered gathers are what the kernel waits for).
+  auto step = [&](auto g_c, int k0) {
+    constexpr int G = decltype(g_c)::value;
     unsigned ak[G], bk[G];
     double a[G], b[G];
 #pragma unroll
@@ -461,7 +477,12 @@ __global__ void __launch_bounds__(256) sgemm_kernel(const SgemmProblem* __restri
     }
 #pragma unroll
     for (int u = 0; u < G; ++u) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a[u], b[u], acc, 0, 0, 0);
-  }
+  };
+  int k0 = 0;
+  for (; T.klen - k0 > 16; k0 += 32) step(std::integral_constant<int, 8>{}, k0);
+  if (T.klen - k0 > 8) step(std::integral_constant<int, 4>{}, k0);
+  else if (T.klen - k0 > 4) step(std::integral_constant<int, 2>{}, k0);
+  else if (T.klen - k0 > 0) step(std::integral_constant<int, 1>{}, k0);
   if (T.part >= 0) {   // one chunk of a split inner range: the whole tile, row-major
     const gptr<double> w = gview(ws) + (size_t)T.part * 256;
 #pragma unroll

@@ -116,7 +116,7 @@ int ftcc_response_noalloc(ftcc_ctx* c, double* dO_dmu, double* dO_dbeta) {
       }
       for (int which = 0; which < 2; ++which) {
         if ((which == 0 && !dO_dmu) || (which == 1 && !dO_dbeta)) continue;
-        for (int i = 0; i < B; ++i) deriv_setup(c, i, which, nullptr, nullptr);
+        deriv_setup(c, which);
         c->ex_d->run_setup(c->stream);
         d_forward(c);
         // <lamt_x, dS_x> + (g_x / beta) dE_x into acc[which], one problem at a time

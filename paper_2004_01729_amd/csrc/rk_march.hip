@@ -99,7 +99,7 @@ void rk_combine(ftcc_ctx* c, int kind, int p, int x, double sigma, bool track,
         r.sigma = sigma;
         r.out = sp.out + off;
         r.maxbits = track ? c->d_maxbits + 2 * i + 1 : nullptr;
-        r.active = c->d_run + i;
+        r.active = c->d_run + i * c->slots;
         prefix.push_back(total);
         total += (int)((r.len + 1023) / 1024);
         ps.push_back(r);
@@ -131,6 +131,7 @@ void rk_dot(ftcc_ctx* c, int kind, int p, int x, const std::function<std::array<
       d.Y = v[1];
       d.out = const_cast<double*>(v[2]);
       d.len = node_len(c, i);
+      list_allowed(c, i, d);
       d.alpha = 1.0;
       d.beta = 1.0;
       DotProblem* dd = nullptr;

@@ -62,7 +62,7 @@ void expsum_run(ftcc_ctx* c, long key, const std::function<ExpSpec(int)>& spec) 
         p.nterms = (int)sp.terms.size();
         p.out = sp.out + off;
         p.maxbits = sp.track ? c->d_maxbits + 2 * i : nullptr;
-        p.active = c->d_run + i;
+        p.active = c->d_run + i * c->slots;
         std::vector<ExpTerm> t;
         for (const auto& x : sp.terms) t.push_back(ExpTerm{std::get<0>(x) + off, std::get<1>(x), std::get<2>(x)});
         terms.push_back(t);

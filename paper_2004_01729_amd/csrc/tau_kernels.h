@@ -127,48 +127,63 @@ void launch_expsum(const ExpSumProblem* d_probs, const int* d_prefix, int n_prob
 void launch_copy_listed(const unsigned* a, long na, const unsigned* b, long nb, long second, const double* src,
                         double* dst, hipStream_t s);
 
-// Thermal quantities of one instance.
-struct ThermalProblem {
+// Many node states at once: dst = src (null: zero), over the listed elements when a is
+// set (as above), else over len contiguous doubles.
+struct StateCopy {
+  const double* src;
+  double* dst;
+  long len;
+  const unsigned* a;
+  const unsigned* b;
+  long na, nb, second;
+};
+constexpr long kStateCopyBlock = 1024;   // elements per block
+void launch_state_copies(const StateCopy* d_copies, const int* d_prefix, int n, int blocks, hipStream_t s);
+
+// One instance's thermal set-up: occupations and weights from (mu, beta), the Fock
+// operator f_pq = h_pq + sum_r (g <pr|qr> - <pr|rq>) n_r (g = 2: spin-restricted
+// spatial orbitals, 1: spin orbitals), u = f - diag(eps), the 4 one-body and 12
+// two-body weighted blocks (out = product of the slots' weights times the integral)
+// and the mean-field sums; and the same quantities' derivatives.  Every launch takes
+// a range of instances, blockIdx.y (or the block prefix) selecting one.
+struct SetupProblem {
   int n;
   const double* eps;
-  const double* h;     // n x n
-  const double* eri;   // n^4, <pq|rs>
-  double mu, beta, thr;
-  double g;            // electrons per orbital and occupation: 2 (spatial, restricted), 1 (spin orbitals)
-  double* occ;         // n_p
-  double* wo;          // sqrt(n_p) or 0 when dropped
-  double* wv;          // sqrt(1 - n_p) or 0 when dropped
-  double* fock;        // n x n
+  const double* h;      // n x n
+  const double* eri;    // n^4, <pq|rs>
+  double* occ;          // n_p
+  double* wo;           // sqrt(n_p) or 0 when dropped
+  double* wv;           // sqrt(1 - n_p) or 0 when dropped
+  double* fock;         // n x n
+  double* u_raw;        // f - diag(eps)
+  double *dn, *dwo, *dwv, *du_raw;   // derivatives
+  double* u[4];         // weighted blocks: oo, ov, vo, vv
+  double* g[12];        // in the order of kBlockHoles
+  double* du[4];        // their derivatives
+  double* dg[12];
+  const unsigned* idx;  // optional list of the two-body elements to compute (the others stay zero)
+  long count;
+  double* mf;           // mean-field sums
 };
-void launch_thermal(const ThermalProblem& p, hipStream_t s);
+// hole slots (bit k: slot k) of the 12 two-body blocks: oooo ooov oovo oovv ovov ovvo ovvv vovv vvvv vvvo ovoo vvoo
+constexpr int kBlockHoles[12] = {15, 7, 11, 3, 5, 9, 1, 2, 0, 8, 13, 12};
+constexpr int kBlockHoles1[4] = {3, 1, 2, 0};
+// elements one instance's block launch visits, and its blocks of 256
+inline long setup_elements(const SetupProblem& p) {
+  const long n2 = (long)p.n * p.n;
+  return (p.idx ? p.count : n2 * n2) + n2;
+}
+enum SetupDeriv { SETUP_MU = 0, SETUP_BETA = 1, SETUP_DIR = 2, SETUP_EPS = 3 };
 
-// out[p,q,r,s] = sum over the product rule of prod_k w_k(slot) * base:
-//   out = (prod w) * dbase + sum_k (prod_{j != k} w_j) dw_k * base
-// For plain blocks pass dbase = base and dw = nullptr.
-struct BlockSpec {
-  int n;
-  int rank;            // 2 or 4
-  char pat[4];         // 'o' or 'v' per slot
-  const double* base;  // unweighted tensor
-  const double* dbase; // derivative of the unweighted tensor (may equal base)
-  const double* wo;
-  const double* wv;
-  const double* dwo;   // may be nullptr
-  const double* dwv;
-  double* out;
-  // optional list of the elements to compute (the others stay as they are: zero);
-  // rank 4 only
-  const unsigned* idx = nullptr;
-  long count = 0;
-};
-void launch_block(const BlockSpec& b, hipStream_t s);
-
-// u = f - diag(eps) and its derivative du = dh + J[dn] + dJ[n], with the Fock
-// operator f_pq = h_pq + sum_r (g <pr|qr> - <pr|rq>) n_r (g = 2: spin-restricted
-// spatial orbitals, g = 1: spin orbitals)
-void launch_fock_deriv(int n, const double* eri, const double* deri, const double* dh, const double* occ,
-                       const double* docc, double g, double* du, hipStream_t s);
-void launch_u_from_fock(int n, const double* fock, const double* eps, double* u, hipStream_t s);
+// occupations, Fock operator, blocks and mean-field sums of n_prob instances; mubeta[2 i]
+// = mu, [2 i + 1] = beta; prefix: first block of each instance, `blocks` in all
+void launch_thermal(const SetupProblem* d_probs, const double* d_mubeta, const int* d_prefix, int n_prob, int n_max,
+                    int blocks, double thr, double g, hipStream_t s);
+// derivative blocks: along mu, beta, a direction (dirs[2 i] = dh, [2 i + 1] = d<pq|rs>, either may be
+// null) or the orbital energy q (occupations and the explicit u; instances with n <= q are left alone)
+void launch_setup_deriv(const SetupProblem* d_probs, const double* d_mubeta, const double* const* d_dirs,
+                        const int* d_prefix, int n_prob, int n_max, int blocks, int which, int q, double g,
+                        hipStream_t s);
 
 // DIIS: coefficients for every instance from its Gram matrix (ld x ld, count entries
 // valid), then the extrapolated iterate sum_j c_j (X_j + R_j) of one buffer.
@@ -183,6 +198,9 @@ void launch_diis_solve(int n_inst, const int* counts, const int* newest, const d
                        hipStream_t s);
 void launch_diis_combine(long len, const DiisTerms& t, double* out, hipStream_t s);
 
+// acc[i][slot] += scale * (sum of instance i's partials [off[i], off[i + 1])), one block per instance
+void launch_partial_sums(int n_inst, const double* partial, const int* off, double scale, double* const* acc, int slot,
+                         hipStream_t s);
 // sum of `count` doubles into *out (single block, deterministic)
 void launch_sum(const double* x, int count, double* out, hipStream_t s);
 // element-wise: y = a * x + b * y over len doubles

@@ -428,10 +428,36 @@ void launch_copy_listed(const unsigned* a, long na, const unsigned* b, long nb, 
 }
 
 // ------------------------------------------------------------------ thermal quantities
-__global__ void occ_kernel(ThermalProblem P) {
+__global__ void __launch_bounds__(256) state_copy_kernel(const StateCopy* __restrict__ copies,
+                                                         const int* __restrict__ prefix, int n) {
+  int lo = 0, hi = n - 1;
+  const int b = blockIdx.x;
+  while (lo < hi) {
+    const int mid = (lo + hi + 1) >> 1;
+    if (prefix[mid] <= b) lo = mid; else hi = mid - 1;
+  }
+  const StateCopy& C = copies[lo];
+  const long first = (long)(b - prefix[lo]) * kStateCopyBlock;
+#pragma unroll
+  for (int u = 0; u < (int)(kStateCopyBlock / 256); ++u) {
+    const long e = first + u * 256 + threadIdx.x;
+    if (e >= C.len) return;
+    long off = e;
+    if (C.a) off = e < C.na ? (long)gview(C.a)[e] : C.second + (long)gview(C.b)[e - C.na];
+    gview(C.dst)[off] = C.src ? gview(C.src)[off] : 0.0;
+  }
+}
+
+void launch_state_copies(const StateCopy* d_copies, const int* d_prefix, int n, int blocks, hipStream_t s) {
+  if (n <= 0 || blocks <= 0) return;
+  hipLaunchKernelGGL(state_copy_kernel, dim3(blocks), dim3(256), 0, s, d_copies, d_prefix, n);
+}
+
+__global__ void occ_kernel(const SetupProblem* probs, const double* mubeta, double thr) {
+  const SetupProblem& P = probs[blockIdx.y];
   const int p = blockIdx.x * blockDim.x + threadIdx.x;
   if (p >= P.n) return;
-  const double x = P.beta * (P.eps[p] - P.mu);
+  const double x = mubeta[2 * blockIdx.y + 1] * (P.eps[p] - mubeta[2 * blockIdx.y]);
   // n = 1 / (1 + e^x), 1 - n = 1 / (1 + e^-x), each without cancellation
   double nocc, nvir;
   if (x > 0.0) {
@@ -444,101 +470,180 @@ __global__ void occ_kernel(ThermalProblem P) {
     nvir = t / (1.0 + t);
   }
   P.occ[p] = nocc;
-  P.wo[p] = (nocc > P.thr) ? sqrt(nocc) : 0.0;
-  P.wv[p] = (nvir > P.thr) ? sqrt(nvir) : 0.0;
+  P.wo[p] = (nocc > thr) ? sqrt(nocc) : 0.0;
+  P.wv[p] = (nvir > thr) ? sqrt(nvir) : 0.0;
 }
 
-// f_pq = h_pq + sum_r (2 <pr|qr> - <pr|rq>) n_r
-__global__ void fock_kernel(ThermalProblem P) {
+// f_pq = h_pq + sum_r (g <pr|qr> - <pr|rq>) n_r, u = f - diag(eps)
+__global__ void fock_kernel(const SetupProblem* probs, double g) {
+  const SetupProblem& P = probs[blockIdx.z];
   const int q = blockIdx.x * blockDim.x + threadIdx.x;
   const int p = blockIdx.y;
   const int n = P.n;
-  if (q >= n) return;
+  if (q >= n || p >= n) return;
   double acc = P.h[(long)p * n + q];
+#pragma unroll 8
   for (int r = 0; r < n; ++r) {
-    const double d = P.eri[(((long)p * n + r) * n + q) * n + r];
-    const double x = P.eri[(((long)p * n + r) * n + r) * n + q];
-    acc += (P.g * d - x) * P.occ[r];
+    const double d = gview(P.eri)[(((long)p * n + r) * n + q) * n + r];
+    const double x = gview(P.eri)[(((long)p * n + r) * n + r) * n + q];
+    acc += (g * d - x) * gview(P.occ)[r];
   }
   P.fock[(long)p * n + q] = acc;
+  P.u_raw[(long)p * n + q] = acc - (p == q ? P.eps[p] : 0.0);
 }
 
-void launch_thermal(const ThermalProblem& p, hipStream_t s) {
-  hipLaunchKernelGGL(occ_kernel, dim3((p.n + 63) / 64), dim3(64), 0, s, p);
-  hipLaunchKernelGGL(fock_kernel, dim3((p.n + 63) / 64, p.n), dim3(64), 0, s, p);
+// dn, dw along mu, beta or eps_q (dn_p/deps_q = -beta n_q (1 - n_q) delta_pq)
+__global__ void occ_deriv_kernel(const SetupProblem* probs, const double* mubeta, int which, int q) {
+  const SetupProblem& P = probs[blockIdx.y];
+  const int p = blockIdx.x * blockDim.x + threadIdx.x;
+  if (p >= P.n || (which == SETUP_EPS && q >= P.n)) return;
+  const double mu = mubeta[2 * blockIdx.y], beta = mubeta[2 * blockIdx.y + 1];
+  const double x = beta * (P.eps[p] - mu);
+  const double nvir = (x > 0.0) ? 1.0 / (1.0 + exp(-x)) : exp(x) / (1.0 + exp(x));
+  const double nn1 = P.occ[p] * nvir;
+  const double d = which == SETUP_MU ? beta * nn1
+                                     : (which == SETUP_BETA ? -(P.eps[p] - mu) * nn1 : (p == q ? -beta * nn1 : 0.0));
+  P.dn[p] = d;
+  P.dwo[p] = (P.wo[p] > 0.0) ? d / (2.0 * P.wo[p]) : 0.0;
+  P.dwv[p] = (P.wv[p] > 0.0) ? -d / (2.0 * P.wv[p]) : 0.0;
 }
 
-// du_pq = dh_pq + sum_r (2 <pr|qr> - <pr|rq>) dn_r + sum_r (2 d<pr|qr> - d<pr|rq>) n_r
-__global__ void fock_deriv_kernel(int n, const double* eri, const double* deri, const double* dh,
-                                  const double* occ, const double* docc, double g, double* du) {
+// du_pq = dh_pq + sum_r (g <pr|qr> - <pr|rq>) dn_r + sum_r (g d<pr|qr> - d<pr|rq>) n_r; along
+// eps_q the explicit part of u = f - diag(eps) is -e_q e_q^T
+__global__ void fock_deriv_kernel(const SetupProblem* probs, const double* const* dirs, int which, int eq, double g) {
+  const SetupProblem& P = probs[blockIdx.z];
   const int q = blockIdx.x * blockDim.x + threadIdx.x;
   const int p = blockIdx.y;
-  if (q >= n) return;
+  const int n = P.n;
+  if (q >= n || p >= n || (which == SETUP_EPS && eq >= n)) return;
+  const double* dh = which == SETUP_DIR ? dirs[2 * blockIdx.z] : nullptr;
+  const double* deri = which == SETUP_DIR ? dirs[2 * blockIdx.z + 1] : nullptr;
   double acc = dh ? dh[(long)p * n + q] : 0.0;
-  for (int r = 0; r < n; ++r) {
-    const long id = (((long)p * n + r) * n + q) * n + r;
-    const long ix = (((long)p * n + r) * n + r) * n + q;
-    if (docc) acc += (g * eri[id] - eri[ix]) * docc[r];
-    if (deri) acc += (g * deri[id] - deri[ix]) * occ[r];
+  if (which == SETUP_EPS && p == eq && q == eq) acc = -1.0;
+  if (which != SETUP_DIR || deri) {
+    const gptr<const double> v = gview(which == SETUP_DIR ? deri : P.eri);
+    const gptr<const double> occ = gview((const double*)(which == SETUP_DIR ? P.occ : P.dn));
+#pragma unroll 8
+    for (int r = 0; r < n; ++r) {
+      const long id = (((long)p * n + r) * n + q) * n + r;
+      const long ix = (((long)p * n + r) * n + r) * n + q;
+      acc += (g * v[id] - v[ix]) * occ[r];
+    }
   }
-  du[(long)p * n + q] = acc;
-}
-
-void launch_fock_deriv(int n, const double* eri, const double* deri, const double* dh, const double* occ,
-                       const double* docc, double g, double* du, hipStream_t s) {
-  hipLaunchKernelGGL(fock_deriv_kernel, dim3((n + 63) / 64, n), dim3(64), 0, s, n, eri, deri, dh, occ, docc, g, du);
-}
-
-__global__ void u_from_fock_kernel(int n, const double* fock, const double* eps, double* u) {
-  const long e = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= (long)n * n) return;
-  const int p = (int)(e / n), q = (int)(e % n);
-  u[e] = fock[e] - (p == q ? eps[p] : 0.0);
-}
-
-void launch_u_from_fock(int n, const double* fock, const double* eps, double* u, hipStream_t s) {
-  const long len = (long)n * n;
-  hipLaunchKernelGGL(u_from_fock_kernel, dim3((len + 255) / 256), dim3(256), 0, s, n, fock, eps, u);
+  P.du_raw[(long)p * n + q] = acc;
 }
 
 // ------------------------------------------------------------------ weighted blocks
-__global__ void block_kernel(BlockSpec B) {
-  const long len = (B.rank == 4) ? (long)B.n * B.n * B.n * B.n : (long)B.n * B.n;
-  const long t = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= (B.idx ? B.count : len)) return;
-  const long e = B.idx ? (long)gview(B.idx)[t] : t;
-  int idx[4];
-  long r = e;
-  for (int k = B.rank - 1; k >= 0; --k) {
-    idx[k] = (int)(r % B.n);
-    r /= B.n;
+// Every block of every instance in one pass: an element of <pq|rs> is read once and its
+// 12 weighted copies are written (one launch per block and instance before: 12 reads
+// and, for a batch of 16 small instances, 256 launches per set-up).
+//   out = (prod w) * dX + sum_k (prod_{j != k} w_j) dw_k * X
+template <int R, bool DERIV>
+__device__ __forceinline__ double weighted(int holes, const double (&wo)[R], const double (&wv)[R],
+                                           const double (&dwo)[R], const double (&dwv)[R], bool has_d, double base,
+                                           bool has_dx, double dx) {
+  double w[R], prod = 1.0;
+#pragma unroll
+  for (int k = 0; k < R; ++k) {
+    w[k] = (holes >> k) & 1 ? wo[k] : wv[k];
+    prod *= w[k];
   }
-  double w[4], dw[4];
-  for (int k = 0; k < B.rank; ++k) {
-    const bool o = (B.pat[k] == 'o');
-    w[k] = o ? B.wo[idx[k]] : B.wv[idx[k]];
-    const double* dv = o ? B.dwo : B.dwv;
-    dw[k] = dv ? dv[idx[k]] : 0.0;
-  }
-  double prod = 1.0;
-  for (int k = 0; k < B.rank; ++k) prod *= w[k];
-  double v = B.dbase ? prod * B.dbase[e] : 0.0;
-  if (B.dwo || B.dwv) {
-    for (int k = 0; k < B.rank; ++k) {
-      if (dw[k] == 0.0) continue;
-      double pk = dw[k];
-      for (int j = 0; j < B.rank; ++j)
+  double v = has_dx ? prod * dx : 0.0;
+  if (DERIV && has_d) {
+#pragma unroll
+    for (int k = 0; k < R; ++k) {
+      double pk = (holes >> k) & 1 ? dwo[k] : dwv[k];
+      if (pk == 0.0) continue;
+#pragma unroll
+      for (int j = 0; j < R; ++j)
         if (j != k) pk *= w[j];
-      v += pk * B.base[e];
+      v += pk * base;
     }
   }
-  B.out[e] = v;
+  return v;
 }
 
-void launch_block(const BlockSpec& b, hipStream_t s) {
-  const long len = b.idx ? b.count : (b.rank == 4) ? (long)b.n * b.n * b.n * b.n : (long)b.n * b.n;
-  if (len <= 0) return;
-  hipLaunchKernelGGL(block_kernel, dim3((len + 255) / 256), dim3(256), 0, s, b);
+template <bool DERIV>
+__global__ void __launch_bounds__(256) blocks_kernel(const SetupProblem* __restrict__ probs,
+                                                     const int* __restrict__ prefix, int n_prob,
+                                                     const double* const* __restrict__ dirs, int which, int eq) {
+  int lo = 0, hi = n_prob - 1;
+  const int b = blockIdx.x;
+  while (lo < hi) {
+    const int mid = (lo + hi + 1) >> 1;
+    if (prefix[mid] <= b) lo = mid; else hi = mid - 1;
+  }
+  const SetupProblem& P = probs[lo];
+  const unsigned n = (unsigned)P.n;
+  if (DERIV && which == SETUP_EPS && eq >= P.n) return;
+  const bool has_d = DERIV && which != SETUP_DIR;
+  const long n2 = (long)n * n, cnt4 = P.idx ? P.count : n2 * n2;
+  const long t = (long)(b - prefix[lo]) * 256 + threadIdx.x;
+  const gptr<const double> wo = gview((const double*)P.wo), wv = gview((const double*)P.wv);
+  const gptr<const double> dwo = gview((const double*)P.dwo), dwv = gview((const double*)P.dwv);
+  if (t < cnt4) {
+    const unsigned e = P.idx ? gview(P.idx)[t] : (unsigned)t;   // n <= 256: below 2^32
+    unsigned i[4], r = e;
+    i[3] = r % n;
+    r /= n;
+    i[2] = r % n;
+    r /= n;
+    i[1] = r % n;
+    i[0] = r / n;
+    double a[4], v[4], da[4] = {}, dv[4] = {};
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      a[k] = wo[i[k]];
+      v[k] = wv[i[k]];
+      if (has_d) {
+        da[k] = dwo[i[k]];
+        dv[k] = dwv[i[k]];
+      }
+    }
+    const double* deri = DERIV && which == SETUP_DIR ? dirs[2 * lo + 1] : nullptr;
+    const double base = !DERIV || has_d ? gview(P.eri)[e] : 0.0;
+    const double dx = DERIV ? (deri ? gview(deri)[e] : 0.0) : base;
+#pragma unroll
+    for (int k = 0; k < 12; ++k)
+      gview(DERIV ? P.dg[k] : P.g[k])[e] =
+          weighted<4, DERIV>(kBlockHoles[k], a, v, da, dv, has_d, base, !DERIV || deri != nullptr, dx);
+    return;
+  }
+  const long e2 = t - cnt4;
+  if (e2 >= n2) return;
+  const unsigned p = (unsigned)e2 / n, q = (unsigned)e2 % n;
+  const double a[2] = {wo[p], wo[q]}, v[2] = {wv[p], wv[q]};
+  double da[2] = {}, dv[2] = {};
+  if (has_d) {
+    da[0] = dwo[p];
+    da[1] = dwo[q];
+    dv[0] = dwv[p];
+    dv[1] = dwv[q];
+  }
+  const double base = P.u_raw[e2];
+  const double dx = DERIV ? P.du_raw[e2] : base;
+#pragma unroll
+  for (int k = 0; k < 4; ++k)
+    gview(DERIV ? P.du[k] : P.u[k])[e2] = weighted<2, DERIV>(kBlockHoles1[k], a, v, da, dv, has_d, base, true, dx);
+}
+
+void launch_thermal(const SetupProblem* d_probs, const double* d_mubeta, const int* d_prefix, int n_prob, int n_max,
+                    int blocks, double thr, double g, hipStream_t s) {
+  const unsigned c = (n_max + 63) / 64;
+  hipLaunchKernelGGL(occ_kernel, dim3(c, n_prob), dim3(64), 0, s, d_probs, d_mubeta, thr);
+  hipLaunchKernelGGL(fock_kernel, dim3(c, n_max, n_prob), dim3(64), 0, s, d_probs, g);
+  hipLaunchKernelGGL(blocks_kernel<false>, dim3(blocks), dim3(256), 0, s, d_probs, d_prefix, n_prob,
+                     (const double* const*)nullptr, 0, 0);
+}
+
+void launch_setup_deriv(const SetupProblem* d_probs, const double* d_mubeta, const double* const* d_dirs,
+                        const int* d_prefix, int n_prob, int n_max, int blocks, int which, int q, double g,
+                        hipStream_t s) {
+  const unsigned c = (n_max + 63) / 64;
+  if (which != SETUP_DIR)
+    hipLaunchKernelGGL(occ_deriv_kernel, dim3(c, n_prob), dim3(64), 0, s, d_probs, d_mubeta, which, q);
+  hipLaunchKernelGGL(fock_deriv_kernel, dim3(c, n_max, n_prob), dim3(64), 0, s, d_probs, d_dirs, which, q, g);
+  hipLaunchKernelGGL(blocks_kernel<true>, dim3(blocks), dim3(256), 0, s, d_probs, d_prefix, n_prob, d_dirs, which, q);
 }
 
 // ------------------------------------------------------------------ DIIS (Anderson) extrapolation
@@ -632,6 +737,25 @@ __global__ void sum_kernel(const double* x, int count, double* out) {
     __syncthreads();
   }
   if (threadIdx.x == 0) *out = r[0];
+}
+
+__global__ void __launch_bounds__(256) partial_sums_kernel(const double* partial, const int* off, double scale,
+                                                           double* const* acc, int slot) {
+  __shared__ double r[256];
+  double a = 0.0;
+  for (int i = off[blockIdx.x] + threadIdx.x; i < off[blockIdx.x + 1]; i += 256) a += partial[i];
+  r[threadIdx.x] = a;
+  __syncthreads();
+  for (int s = 128; s > 0; s >>= 1) {
+    if (threadIdx.x < s) r[threadIdx.x] += r[threadIdx.x + s];
+    __syncthreads();
+  }
+  if (threadIdx.x == 0) acc[blockIdx.x][slot] = scale * r[0] + acc[blockIdx.x][slot];
+}
+
+void launch_partial_sums(int n_inst, const double* partial, const int* off, double scale, double* const* acc, int slot,
+                         hipStream_t s) {
+  hipLaunchKernelGGL(partial_sums_kernel, dim3(n_inst), dim3(256), 0, s, partial, off, scale, acc, slot);
 }
 
 void launch_sum(const double* x, int count, double* out, hipStream_t s) {
