@@ -92,8 +92,7 @@ struct Launch {
   int min_k = 0;                    // smallest K of the launch's GEMM problems
   void* d_tasks = nullptr;          // SGEMM / ELEM: task list
   int n_tasks = 0;
-  int n_tile = 0;                   // SGEMM: leading tasks that are block tiles
-  bool narrow = false;              // SGEMM: some of them are not 64 x 64
+  int n_square = 0, n_narrow = 0;   // SGEMM: leading tasks that are 64 x 64 block tiles, then the other block tiles
   void* d_bfirst = nullptr;         // ELEM / DOTB: per 256-element block, the task of its first element
   void* d_red = nullptr;            // SGEMM: reductions of split inner ranges
   int n_red = 0;
@@ -290,7 +289,19 @@ class Executor {
              const std::vector<PerProb>& zero_bufs);
   void lower_one(std::vector<Launch>& dst, const OpInst& o, const PerProb& out, bool acc);
   PerProb const_permuted(int tensor, const PerProb& X, const std::string& xi, const std::string& yi);
+  // Device copy of a host table.  Small ones share chunks whose host images are copied
+  // over at the end of build() (flush_uploads), one transfer per chunk.
   void* upload(const void* host, size_t bytes);
+  void flush_uploads();
+  struct Chunk {
+    char* dev = nullptr;
+    std::vector<char> host;
+    size_t flushed = 0;
+  };
+  std::vector<Chunk> chunks_;
+  bool defer_ = false;   // descriptors of lists that fuse_levels will merge are uploaded there
+  // instances whose labels (and n) agree share tuple tables: the first of them
+  std::vector<int> same_labels_;
   void dump_plan() const;
 
   const Program* prog_ = nullptr;
@@ -306,7 +317,6 @@ class Executor {
   void upload_sgemm(Launch& L);
   void upload_elem(Launch& L);
   Launch merge_elem(const std::vector<Launch*>& parts);
-  void release(const std::vector<void*>& dev);
   std::function<double*(int, size_t)> const_alloc_;
   std::map<std::pair<int, std::string>, PerProb> const_cache_;
   struct CacheEntry {
@@ -339,8 +349,12 @@ class Executor {
   bool contract_blocked(std::vector<Launch>& dst, const PerProb& out, const std::string& oi, double alpha,
                         const PerProb& A, const std::string& ai, const PerProb& B, const std::string& bi, bool acc,
                         const std::string& tag, int t_out, int t_a, int t_b);
+  // edge > 0: the tuples of a block ordered for the two tensors' contiguous letters
+  // (patches of edge x edge where they differ), else lexicographically
+  // edge > 0: the tuples of a block ordered for the two tensors' contiguous letters
+  // (patches of edge x edge where they differ), else lexicographically
   const GroupTable& group_table(int inst, long n, const std::string& letters, const std::string& xi, bool xp,
-                                const std::string& yi, bool yp, const std::vector<int>& signs);
+                                const std::string& yi, bool yp, const std::vector<int>& signs, int edge = 0);
   std::vector<char> packed_;               // per tensor: stored packed (n^(rank-1) doubles)
   bool pack_on_ = false;                   // packing applies to this executor's problems
   bool one_per_label_ = false;             // every orbital of every instance has its own label

@@ -7,6 +7,7 @@
 #include <cstdlib>
 #include <cstring>
 #include <stdexcept>
+#include <unordered_map>
 
 #include "util.h"
 
@@ -100,22 +101,39 @@ Executor::~Executor() {
 }
 
 void* Executor::upload(const void* host, size_t bytes) {
-  void* d = nullptr;
-  FTCC_HIP(hipMalloc(&d, bytes > 0 ? bytes : 8));
-  if (bytes) FTCC_HIP(hipMemcpy(d, host, bytes, hipMemcpyHostToDevice));
-  owned_.push_back(d);
-  return d;
+  constexpr size_t kChunk = (size_t)4 << 20, kAlign = 256;
+  if (bytes > kChunk / 4) {
+    void* d = nullptr;
+    FTCC_HIP(hipMalloc(&d, bytes));
+    owned_.push_back(d);
+    FTCC_HIP(hipMemcpy(d, host, bytes, hipMemcpyHostToDevice));
+    return d;
+  }
+  const size_t need = (std::max<size_t>(bytes, 8) + kAlign - 1) / kAlign * kAlign;
+  if (chunks_.empty() || chunks_.back().host.size() + need > kChunk) {
+    flush_uploads();
+    Chunk c;
+    void* d = nullptr;
+    FTCC_HIP(hipMalloc(&d, kChunk));
+    owned_.push_back(d);
+    c.dev = (char*)d;
+    c.host.reserve(kChunk);
+    chunks_.push_back(std::move(c));
+  }
+  Chunk& c = chunks_.back();
+  const size_t at = c.host.size();
+  c.host.resize(at + need);
+  if (bytes) std::memcpy(c.host.data() + at, host, bytes);
+  return c.dev + at;
 }
 
-void Executor::release(const std::vector<void*>& dev) {
-  if (dev.empty()) return;
-  std::vector<void*> keep;
-  keep.reserve(owned_.size());
-  for (void* p : owned_) {
-    if (std::find(dev.begin(), dev.end(), p) != dev.end()) FTCC_HIP(hipFree(p));
-    else keep.push_back(p);
+void Executor::flush_uploads() {
+  for (Chunk& c : chunks_) {
+    if (c.flushed < c.host.size())
+      FTCC_HIP(hipMemcpy(c.dev + c.flushed, c.host.data() + c.flushed, c.host.size() - c.flushed,
+                         hipMemcpyHostToDevice));
+    c.flushed = c.host.size();
   }
-  owned_.swap(keep);
 }
 
 using Ranges = std::vector<std::pair<uintptr_t, uintptr_t>>;
@@ -823,10 +841,12 @@ static long long pack_momentum(const std::vector<int>& q) {
 // offsets in the operands indexed by xi and yi (row-major, every axis n) and
 // the packed momentum sum_l signs[l] k(index_l) of each block.
 const Executor::GroupTable& Executor::group_table(int inst, long n, const std::string& letters,
-                                                  const std::string& xi, bool xp, const std::string& yi,
-                                                  bool yp, const std::vector<int>& signs) {
+                                                  const std::string& xi, bool xp, const std::string& yi, bool yp,
+                                                  const std::vector<int>& signs, int edge) {
+  if (one_per_label_) edge = 0;   // blocks of a few elements: nothing to gain
+  inst = same_labels_[inst];
   std::string key = std::to_string(inst) + "|" + letters + "|" + xi + (xp ? "#" : "") + "|" + yi +
-                    (yp ? "#" : "") + "|";
+                    (yp ? "#" : "") + "|" + std::to_string(edge);
   for (int v : signs) key += (v > 0 ? '+' : '-');
   auto it = group_cache_.find(key);
   if (it != group_cache_.end()) return it->second;
@@ -847,7 +867,26 @@ const Executor::GroupTable& Executor::group_table(int inst, long n, const std::s
   const long count = ipow(n, g);
   struct Row {
     long long key;
-    unsigned ox, oy;
+    unsigned ox, oy, ord;
+  };
+  // Order inside a block.  Lanes run along a tuple list, so the letter along which a
+  // tensor is contiguous should be the fastest: for rows and columns (edge 1) the
+  // operand's, which is read once per tile, before the output's; for the inner list
+  // (edge 4), where the two operands may want different letters, the tuples go in patches
+  // of edge x edge of those two and both are read in runs of `edge` (27 orbitals, a ring
+  // contraction with crossed inner letters: 165 -> 114 us).
+  int lx = edge && has(letters, xi.back()) ? (int)letters.find(xi.back()) : -1;
+  int ly = edge && has(letters, yi.back()) ? (int)letters.find(yi.back()) : -1;
+  if (edge == 1 && lx >= 0) ly = -1;
+  auto order_of = [&](const std::vector<int>& idx, long t) -> unsigned {
+    if (lx < 0 && ly < 0) return (unsigned)t;
+    unsigned long o = 0;
+    for (int l = 0; l < g; ++l)
+      if (l != lx && l != ly) o = o * n + idx[l];
+    if (lx < 0 || ly < 0 || lx == ly) return (unsigned)(o * n + idx[lx >= 0 ? lx : ly]);
+    const unsigned long nb = (n + edge - 1) / edge;
+    o = (o * nb + idx[lx] / edge) * nb + idx[ly] / edge;
+    return (unsigned)((o * edge + idx[lx] % edge) * edge + idx[ly] % edge);
   };
   std::vector<Row> rows(count);
   std::vector<int> idx(g, 0), q(D);
@@ -861,21 +900,44 @@ const Executor::GroupTable& Executor::group_table(int inst, long n, const std::s
     }
     for (int c = 0; c < D; ++c)
       if (M.modulus[c] > 0) q[c] = ((q[c] % M.modulus[c]) + M.modulus[c]) % M.modulus[c];
-    rows[t] = Row{pack_momentum(q), (unsigned)ox, (unsigned)oy};
+    rows[t] = Row{pack_momentum(q), (unsigned)ox, (unsigned)oy, order_of(idx, t)};
     for (int l = g - 1; l >= 0; --l) {   // next tuple, last letter fastest
       if (++idx[l] < n) break;
       idx[l] = 0;
     }
   }
-  std::stable_sort(rows.begin(), rows.end(), [](const Row& a, const Row& b) { return a.key < b.key; });
+  // into blocks by momentum (a counting sort over the few distinct ones), each block in its order
+  std::map<long long, std::pair<int, int>> found;
+  std::vector<std::pair<int, int>*> of(count);
+  {
+    std::unordered_map<long long, std::pair<int, int>*> seen;
+    for (long t = 0; t < count; ++t) {
+      auto it = seen.find(rows[t].key);
+      if (it == seen.end()) it = seen.emplace(rows[t].key, &found.emplace(rows[t].key, std::make_pair(0, 0)).first->second).first;
+      of[t] = it->second;
+      it->second->second++;
+    }
+  }
+  int first = 0;
+  for (auto& f : found) {
+    f.second.first = first;
+    first += f.second.second;
+    f.second.second = 0;
+  }
+  std::vector<Row> sorted(count);
+  for (long t = 0; t < count; ++t) sorted[of[t]->first + of[t]->second++] = rows[t];
+  if (lx >= 0 || ly >= 0)
+    for (const auto& f : found) {
+      auto b = sorted.begin() + f.second.first, e = b + f.second.second;
+      auto before = [](const Row& x, const Row& y) { return x.ord < y.ord; };
+      if (!std::is_sorted(b, e, before)) std::sort(b, e, before);
+    }
   GroupTable T;
+  T.blocks = std::move(found);
   std::vector<unsigned> o1(count), o2(count);
   for (long t = 0; t < count; ++t) {
-    o1[t] = rows[t].ox;
-    o2[t] = rows[t].oy;
-    auto b = T.blocks.find(rows[t].key);
-    if (b == T.blocks.end()) T.blocks[rows[t].key] = std::make_pair((int)t, 1);
-    else b->second.second++;
+    o1[t] = sorted[t].ox;
+    o2[t] = sorted[t].oy;
   }
   T.off1 = upload(o1.data(), sizeof(unsigned) * count);
   T.off2 = upload(o2.data(), sizeof(unsigned) * count);
@@ -934,7 +996,7 @@ static int part_units(int shape) { return shape >= kTile64x64 ? 16 : 1; }
 // wave latencies of a task by the same count (the order of a merged task list);
 // block tiles stand before every wave task, longest first
 static long sgemm_task_cost(const SgemmTask& t) {
-  if (t.shape >= kTile64x64) return 1000000L + t.klen;
+  if (t.shape >= kTile64x64) return (t.shape == kTile64x64 ? 2000000000L : 1000000000L) + t.klen;
   const long per = t.shape ? (8L << ((t.shape >> 6) & 7)) : 32L;
   return 3 + 2 * std::max(1L, (t.klen + per - 1) / per);
 }
@@ -1000,9 +1062,9 @@ bool Executor::contract_blocked(std::vector<Launch>& dst, const PerProb& out, co
     if (inst < 0 || inst >= (int)mom_.size() || !mom_[inst]) throw std::runtime_error("momentum labels missing");
     if (ipow(n, (int)std::max(std::max(ai.size(), bi.size()), oi.size())) >= (1L << 32))
       throw std::runtime_error("tensor exceeds 2^32 elements: " + tag);
-    const GroupTable& TM = group_table(inst, n, M, ai, is_packed(t_a), oi, is_packed(t_out), sgM);
-    const GroupTable& TK = group_table(inst, n, K, ai, is_packed(t_a), bi, is_packed(t_b), sgK);
-    const GroupTable& TN = group_table(inst, n, N, bi, is_packed(t_b), oi, is_packed(t_out), sgN);
+    const GroupTable& TM = group_table(inst, n, M, ai, is_packed(t_a), oi, is_packed(t_out), sgM, 1);
+    const GroupTable& TK = group_table(inst, n, K, ai, is_packed(t_a), bi, is_packed(t_b), sgK, 4);
+    const GroupTable& TN = group_table(inst, n, N, bi, is_packed(t_b), oi, is_packed(t_out), sgN, 1);
     SgemmProblem& P = ps[p];
     P.A = A[p];
     P.B = B[p];
@@ -1228,6 +1290,7 @@ bool Executor::sum_blocked(std::vector<Launch>& dst, const std::vector<SumTerm>&
 }
 
 void Executor::upload_elem(Launch& L) {
+  if (defer_) return;
   L.n_prob = (int)L.eprobs.size();
   L.d_desc = upload(L.eprobs.data(), sizeof(ElemProblem) * L.eprobs.size());
   L.d_src = upload(L.esrcs.data(), sizeof(ElemSource) * L.esrcs.size());
@@ -1317,16 +1380,16 @@ double Executor::sgemm_flops_forward() const {
   return f;
 }
 
-// Order of the first n (block tile) tasks over the chip: block b runs on XCD b % 8,
+// Order of n block tile tasks from `begin` over the chip: block b runs on XCD b % 8,
 // and each XCD has its own L2, so every run of equally long tasks is cut into eight
 // contiguous pieces, one per XCD (neighbouring tiles share operand panels), while
 // the list as a whole stays longest first.
-static void xcd_order(std::vector<SgemmTask>& tasks, int n) {
+static void xcd_order(std::vector<SgemmTask>& all, int begin, int n, int n_prob) {
   constexpr int X = 8;
-  std::vector<SgemmTask> q[X];
+  std::vector<SgemmTask> q[X], tasks(all.begin() + begin, all.begin() + begin + n);
   for (int i = 0, turn = 0; i < n; ++turn) {
     int j = i;
-    while (j < n && tasks[j].klen == tasks[i].klen) ++j;
+    while (j < n && tasks[j].klen == tasks[i].klen && tasks[j].prob / n_prob == tasks[i].prob / n_prob) ++j;
     for (int x = 0; x < X; ++x) {
       const int lo = i + (int)((long)(j - i) * x / X), hi = i + (int)((long)(j - i) * (x + 1) / X);
       std::vector<SgemmTask>& t = q[(x + turn) % X];
@@ -1338,25 +1401,26 @@ static void xcd_order(std::vector<SgemmTask>& tasks, int n) {
   for (int i = 0; i < n; ++i) {
     int x = i % X;
     for (int k = 0; k < X && at[x] >= q[x].size(); ++k) x = (x + 1) % X;   // that XCD's share is used up
-    tasks[i] = q[x][at[x]++];
+    all[begin + i] = q[x][at[x]++];
   }
 }
 
 // Device lists of an SGEMM launch: block tiles first, longest tasks first (so that
 // the last wave of the launch holds short ones), one reduction entry per 256 outputs.
 void Executor::upload_sgemm(Launch& L) {
+  if (defer_) return;
   std::stable_sort(L.stasks.begin(), L.stasks.end(),
                    [](const SgemmTask& a, const SgemmTask& b) { return sgemm_task_cost(a) > sgemm_task_cost(b); });
   L.n_prob = (int)L.sprobs.size();
   L.d_desc = upload(L.sprobs.data(), sizeof(SgemmProblem) * L.sprobs.size());
   L.n_tasks = (int)L.stasks.size();
-  L.n_tile = 0;
-  L.narrow = false;
+  L.n_square = L.n_narrow = 0;
   for (const SgemmTask& t : L.stasks) {
-    L.n_tile += t.shape >= kTile64x64;
-    L.narrow = L.narrow || t.shape > kTile64x64;
+    L.n_square += t.shape == kTile64x64;
+    L.n_narrow += t.shape > kTile64x64;
   }
-  xcd_order(L.stasks, L.n_tile);
+  xcd_order(L.stasks, 0, L.n_square, (int)probs_.size());
+  xcd_order(L.stasks, L.n_square, L.n_narrow, (int)probs_.size());
   L.d_tasks = upload(L.stasks.data(), sizeof(SgemmTask) * std::max<size_t>(L.stasks.size(), 1));
   std::vector<SgemmReduce> slices;
   for (const SgemmReduce& r : L.sreds)
@@ -1367,7 +1431,8 @@ void Executor::upload_sgemm(Launch& L) {
   L.n_red = (int)slices.size();
   if (L.n_red > 0) L.d_red = upload(slices.data(), sizeof(SgemmReduce) * slices.size());
   L.d_partial = scratch_->tail_ws;
-  L.total = L.n_tile + (L.n_tasks - L.n_tile + 3) / 4;
+  const int blocks = L.n_square + L.n_narrow;
+  L.total = blocks + (L.n_tasks - blocks + 3) / 4;
 }
 
 Launch Executor::merge_sgemm(const std::vector<Launch*>& parts) {
@@ -1435,6 +1500,7 @@ Launch Executor::merge_elem(const std::vector<Launch*>& parts) {
 }
 
 void Executor::fuse_levels(std::vector<Launch>& L) {
+  defer_ = false;
   const int nL = (int)L.size();
   for (Launch& l : L) {
     normalize(l.rd);
@@ -1454,11 +1520,6 @@ void Executor::fuse_levels(std::vector<Launch>& L) {
   for (int i = 0; i < nL; ++i) at[level[i]].push_back(i);
   const long ws_tiles = scratch_ && scratch_->tail_ws ? (long)(scratch_->tail_ws_doubles / 256) : 0;
   std::vector<Launch> out;
-  std::vector<void*> freed;
-  auto retire = [&](Launch& l) {
-    for (void* d : {l.d_desc, l.d_tasks, l.d_red, l.d_bfirst, l.d_src})
-      if (d) freed.push_back(d);
-  };
   for (const std::vector<int>& lv : at) {
     std::vector<Launch*> sg, el;
     for (int i : lv) {
@@ -1471,7 +1532,6 @@ void Executor::fuse_levels(std::vector<Launch>& L) {
       out.push_back(std::move(*el[0]));
     } else if (el.size() > 1) {
       out.push_back(merge_elem(el));
-      for (Launch* l : el) retire(*l);
     }
     // blocked contractions: one launch while their partial tiles fit the workspace
     size_t k = 0;
@@ -1489,12 +1549,12 @@ void Executor::fuse_levels(std::vector<Launch>& L) {
         out.push_back(std::move(*grp[0]));
       } else {
         out.push_back(merge_sgemm(grp));
-        for (Launch* l : grp) retire(*l);
       }
     }
   }
-  release(freed);
-  for (Launch& l : out) {   // host copies no longer needed
+  for (Launch& l : out) {   // upload what was not merged; the host copies are no longer needed
+    if (l.kind == Launch::SGEMM && !l.d_desc) upload_sgemm(l);
+    if (l.kind == Launch::ELEM && !l.d_desc) upload_elem(l);
     std::vector<SgemmProblem>().swap(l.sprobs);
     std::vector<SgemmTask>().swap(l.stasks);
     std::vector<SgemmReduce>().swap(l.sreds);
@@ -1680,6 +1740,18 @@ void Executor::build(const Program* prog, const std::vector<ProblemRef>& probs, 
   const_alloc_ = const_alloc;
   if (!mom_.empty()) infer_laws();
   plan_packing(want_backward);
+  {
+    const char* fz = std::getenv("FTCC_FUSE");
+    defer_ = !mom_.empty() && !(fz && fz[0] == '0');
+  }
+  same_labels_.clear();
+  for (size_t i = 0; i < mom_.size(); ++i) {
+    size_t j = 0;
+    while (j < i && !(mom_[j] && mom_[i] && mom_[j]->dims == mom_[i]->dims && mom_[j]->modulus == mom_[i]->modulus &&
+                      mom_[j]->labels == mom_[i]->labels))
+      ++j;
+    same_labels_.push_back((int)j);
+  }
   const int zero = 0;
   d_zero_ = (int*)upload(&zero, sizeof(int));
   const int np = (int)probs.size();
@@ -1834,6 +1906,7 @@ void Executor::build(const Program* prog, const std::vector<ProblemRef>& probs, 
       fuse_levels(setup_);
       fuse_levels(fwd_);
     }
+    flush_uploads();
     dump_plan();
     return;
   }
@@ -1871,6 +1944,7 @@ void Executor::build(const Program* prog, const std::vector<ProblemRef>& probs, 
     fuse_levels(fwd_);
     fuse_levels(bwd_);
   }
+  flush_uploads();
   dump_plan();
 }
 
@@ -1999,7 +2073,7 @@ void Executor::run(const std::vector<Launch>& L, hipStream_t s) const {
         launch_dot((const DotProblem*)l.d_desc, l.n_prob, l.dot_blocks, l.d_partial, s);
         break;
       case Launch::SGEMM:
-        launch_sgemm((const SgemmProblem*)l.d_desc, (const SgemmTask*)l.d_tasks, l.n_tile, l.narrow, l.n_tasks,
+        launch_sgemm((const SgemmProblem*)l.d_desc, (const SgemmTask*)l.d_tasks, l.n_square, l.n_narrow, l.n_tasks,
                      l.d_partial,
                      (const SgemmReduce*)l.d_red, l.n_red, s);
         break;
@@ -2095,7 +2169,7 @@ long Executor::dispatches(const std::vector<Launch>& L) const {
         k += (l.total > 0) + (t.splits > 1 && t.dp_tiles < l.total) + (l.splitk_blocks > 0);
         break;
       }
-      case Launch::SGEMM: k += (l.n_tile > 0) + (l.n_tasks > l.n_tile) + (l.n_tasks > 0 && l.n_red > 0); break;
+      case Launch::SGEMM: k += (l.n_square > 0) + (l.n_narrow > 0) + (l.n_tasks > l.n_square + l.n_narrow) + (l.n_tasks > 0 && l.n_red > 0); break;
       case Launch::DOT: k += 2; break;
       case Launch::DOTB: k += 1 + (l.n_elem > 0 && l.n_tasks > 0); break;
       case Launch::ELEM: k += (l.n_tasks > 0 && l.n_elem > 0); break;

@@ -133,9 +133,9 @@ struct SgemmReduce {
 // Inner ranges longer than this are split into chunks of kSgemmChunk (or a
 // power-of-two multiple of it when the partial tiles would not fit the workspace).
 constexpr int kSgemmChunk = 64;
-// tasks [0, n_tile) are block tiles (one block each; narrow: not all of them 64 x 64),
-// the rest one wave each
-void launch_sgemm(const SgemmProblem* d_probs, const SgemmTask* d_tasks, int n_tile, bool narrow, int n_tasks,
+// the first n_square tasks are 64 x 64 block tiles, the next n_narrow the other block
+// tiles (one block each), the rest one wave each
+void launch_sgemm(const SgemmProblem* d_probs, const SgemmTask* d_tasks, int n_square, int n_narrow, int n_tasks,
                   double* ws, const SgemmReduce* d_red, int n_red, hipStream_t s);
 
 // Momentum-blocked elementwise sum over the allowed elements of Y only:
