@@ -101,6 +101,7 @@ struct Launch {
   std::vector<ElemTask> etasks;
   void* d_src = nullptr;            // ELEM: source list
   long long n_elem = 0;             // ELEM: elements, problems padded to whole blocks
+  int elem_per = 1;                 // ELEM: elements per thread
   int dot_blocks = 0;
   void* d_desc = nullptr;
   int* d_prefix = nullptr;

@@ -170,15 +170,15 @@ static bool ordered(const Launch& a, const Launch& b) {
   return overlaps(a.wr, b.rd) || overlaps(a.wr, b.wr) || overlaps(a.rd, b.wr);
 }
 
-// Task of the first element of every 256-element block of an element-task list
+// Task of the first element of every `per`-element block of an element-task list
 // (the largest task index whose first element is at or before it), and the last
 // task after the final block: the kernels search only between two neighbours.
-static std::vector<int> block_first_tasks(const std::vector<ElemTask>& tasks, long long total) {
-  const long long nb = (total + 255) / 256;
+static std::vector<int> block_first_tasks(const std::vector<ElemTask>& tasks, long long total, int per) {
+  const long long nb = (total + per - 1) / per;
   std::vector<int> bf((size_t)nb + 1);
   int t = 0;
   for (long long b = 0; b < nb; ++b) {
-    while (t + 1 < (int)tasks.size() && tasks[t + 1].first <= b * 256) ++t;
+    while (t + 1 < (int)tasks.size() && tasks[t + 1].first <= b * per) ++t;
     bf[(size_t)b] = t;
   }
   bf[(size_t)nb] = tasks.empty() ? 0 : (int)tasks.size() - 1;
@@ -1101,7 +1101,11 @@ bool Executor::contract_blocked(std::vector<Launch>& dst, const PerProb& out, co
       if (kl == 0 && acc) continue;   // nothing to add; a set writes its zeros
       const int m0 = blk.second.first, ml = blk.second.second;
       const int n0 = nb->second.first, nl = nb->second.second;
-      int shape = sgemm_tile_shape(ml, nl, kl);
+      // With one orbital per momentum the few blocks large enough for tiles gather every
+      // element from a line of its own, which the tiles do not change, and their blocks
+      // only delay the level (81 orbitals, forward: 40.8 ms with tiles, 38.3 without; 57:
+      // no difference).
+      int shape = one_per_label_ ? 0 : sgemm_tile_shape(ml, nl, kl);
       int R, C;
       if (shape) {
         R = sgemm_tile_rows(shape);
@@ -1263,7 +1267,6 @@ bool Executor::sum_blocked(std::vector<Launch>& dst, const std::vector<SumTerm>&
       add_range(L.rd, q.X, sizeof(double) * (size_t)ipow_l(n, (int)yi.size() - (xpk ? 1 : 0)));
       if (q.scale) add_range(L.rd, q.scale, sizeof(double));
     }
-    L.n_elem = (L.n_elem + 255) / 256 * 256;   // every problem starts on a block boundary
     const InstMomentum& Mm = *mom_[inst];
     for (const auto& blk : T1.blocks) {
       std::vector<int> q(Mm.dims);
@@ -1295,10 +1298,26 @@ void Executor::upload_elem(Launch& L) {
   L.d_desc = upload(L.eprobs.data(), sizeof(ElemProblem) * L.eprobs.size());
   L.d_src = upload(L.esrcs.data(), sizeof(ElemSource) * L.esrcs.size());
   L.n_tasks = (int)L.etasks.size();
+  // Four elements a thread where the launch's tasks fill blocks of that many on average
+  // (dense orbitals: the task is then uniform over a block) and give every CU one; one
+  // where the tasks are smaller (labels: a block of 1024 spans tasks, every thread
+  // searches for each of its elements in turn and a problem's last block is mostly
+  // padding; 10 orbitals, 12 instances: 32.6 ms a step with four, 27.0 with one) or the
+  // launch is (6 dense orbitals: 19.2 against 18.6).
+  L.elem_per = L.n_elem >= std::max(1024LL * L.n_tasks, 1024LL * 256) ? 4 : 1;
+  const long long block = 256 * L.elem_per;
+  long long first = 0;
+  for (size_t t = 0; t < L.etasks.size(); ++t) {
+    ElemTask& T = L.etasks[t];
+    if (t && T.prob != L.etasks[t - 1].prob) first = (first + block - 1) / block * block;   // a block, one problem
+    T.first = first;
+    first += (long long)T.ulen * T.vlen;
+  }
+  L.n_elem = first;
   L.d_tasks = upload(L.etasks.data(), sizeof(ElemTask) * L.etasks.size());
-  const std::vector<int> bf = block_first_tasks(L.etasks, L.n_elem);
+  const std::vector<int> bf = block_first_tasks(L.etasks, L.n_elem, (int)block);
   L.d_bfirst = upload(bf.data(), sizeof(int) * bf.size());
-  L.total = (int)std::min<long long>((L.n_elem + 255) / 256, 1 << 30);
+  L.total = (int)std::min<long long>((L.n_elem + block - 1) / block, 1 << 30);
 }
 
 bool Executor::dot_blocked(std::vector<Launch>& dst, const PerProb& A, const std::string& ai, const PerProb& B,
@@ -1362,7 +1381,7 @@ bool Executor::dot_blocked(std::vector<Launch>& dst, const PerProb& A, const std
   L.n_tasks = (int)tasks.size();
   L.d_tasks = upload(tasks.data(), sizeof(ElemTask) * std::max<size_t>(tasks.size(), 1));
   {
-    const std::vector<int> bf = block_first_tasks(tasks, total);
+    const std::vector<int> bf = block_first_tasks(tasks, total, 256);
     L.d_bfirst = upload(bf.data(), sizeof(int) * bf.size());
   }
   L.n_elem = total;
@@ -1476,7 +1495,6 @@ Launch Executor::merge_elem(const std::vector<Launch*>& parts) {
   M.ranged = true;
   for (const Launch* l : parts) {
     const int po = (int)M.eprobs.size(), so = (int)M.esrcs.size();
-    M.n_elem = (M.n_elem + 255) / 256 * 256;
     for (ElemProblem q : l->eprobs) {
       q.src += so;
       M.eprobs.push_back(q);
@@ -1484,7 +1502,6 @@ Launch Executor::merge_elem(const std::vector<Launch*>& parts) {
     M.esrcs.insert(M.esrcs.end(), l->esrcs.begin(), l->esrcs.end());
     for (ElemTask t : l->etasks) {
       t.prob += po;
-      t.first += M.n_elem;
       M.etasks.push_back(t);
     }
     M.n_elem += l->n_elem;
@@ -2084,7 +2101,7 @@ void Executor::run(const std::vector<Launch>& L, hipStream_t s) const {
         break;
       case Launch::ELEM:
         launch_elem((const ElemProblem*)l.d_desc, (const ElemSource*)l.d_src, (const ElemTask*)l.d_tasks,
-                    (const int*)l.d_bfirst, l.n_tasks, l.n_elem, s);
+                    (const int*)l.d_bfirst, l.n_tasks, l.n_elem, l.elem_per, s);
         break;
     }
   }

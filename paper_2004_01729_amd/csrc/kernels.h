@@ -159,14 +159,14 @@ struct ElemProblem {
   int src, n_src;        // the problem's entries of the source list
 };
 struct ElemTask {
-  long long first;       // elements of the tasks before this one (each problem starts at a multiple of 256)
+  long long first;       // elements of the tasks before this one (each problem starts on a block boundary)
   int prob;
   int u0, ulen, v0, vlen;
 };
-// d_bfirst: per 256-element block the task of its first element, then the last
-// task (total / 256 rounded up, plus one entries)
+// per: elements per thread (1 or 4), a block holds 256 per; d_bfirst: the task of each
+// block's first element, then the last task
 void launch_elem(const ElemProblem* d_probs, const ElemSource* d_src, const ElemTask* d_tasks, const int* d_bfirst,
-                 int n_tasks, long long total, hipStream_t s);
+                 int n_tasks, long long total, int per, hipStream_t s);
 
 // Momentum-blocked full contraction: out = alpha * sum X[ox1[u] + ox2[v]] * Y[oy1[u] + oy2[v]]
 // + beta * out over the allowed elements (task list as for elem_kernel).  Each

@@ -68,3 +68,27 @@ def test_step_both_paths(F, monkeypatch, spin):
         out.append([om, parts, *lam, r["mu"], r["beta"], *r["h"], *r["eps"]])
     for a, b in zip(*out):
         assert _close(a, b, 1e-11)   # the sweeps stop at 1e-13 of the amplitudes
+
+
+@pytest.mark.parametrize("split", [(15, 15), (8, 14), (22, 11)])
+def test_two_label_blocks(F, split):
+    """Two labels (p + q + r + s even): blocks of unequal, odd sizes whose elements share
+    the four-wide elementwise kernel's blocks, against the same problem without labels."""
+    n = sum(split)
+    lab = np.arange(n) % 2 if split[0] == split[1] else np.repeat([0, 1], split)
+    h, eri, eps = fi.random_hamiltonian(n, seed=n, scale=0.1)
+    t1, t2 = fi.random_amplitudes(n, seed=n + 1, scale=0.05)
+    even2 = (lab[:, None] + lab[None, :]) % 2 == 0
+    even4 = (lab[:, None, None, None] + lab[:, None, None] + lab[:, None] + lab) % 2 == 0
+    h, t1, eri, t2 = h * even2, t1 * even2, eri * even4, t2 * even4
+    out = []
+    for labelled in (True, False):
+        print(f"[levels] two labels {split} labelled={labelled}", flush=True)
+        ctx = F.Context(1, n_tau=6, nodes_per_panel=3)
+        ctx.set_hamiltonian(0, h, eri, eps)
+        if labelled:
+            ctx.set_momentum(0, lab, [2])
+        out.append(ctx.eval_residual(0, 0.1, 2.0, t1, t2))
+        ctx.close()
+    for a, b in zip(*out):
+        assert _close(a, b)
