@@ -93,6 +93,7 @@ struct Launch {
   void* d_tasks = nullptr;          // SGEMM / ELEM: task list
   int n_tasks = 0;
   int n_square = 0, n_narrow = 0;   // SGEMM: leading tasks that are 64 x 64 block tiles, then the other block tiles
+  bool wide = false;                // SGEMM: some tasks are 32 x 32 wave tiles
   void* d_bfirst = nullptr;         // ELEM / DOTB: per 256-element block, the task of its first element
   void* d_red = nullptr;            // SGEMM: reductions of split inner ranges
   int n_red = 0;

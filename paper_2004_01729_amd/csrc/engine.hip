@@ -997,7 +997,7 @@ static int part_units(int shape) { return shape >= kTile64x64 ? 16 : 1; }
 // block tiles stand before every wave task, longest first
 static long sgemm_task_cost(const SgemmTask& t) {
   if (t.shape >= kTile64x64) return (t.shape == kTile64x64 ? 2000000000L : 1000000000L) + t.klen;
-  const long per = t.shape ? (8L << ((t.shape >> 6) & 7)) : 32L;
+  const long per = t.shape == kWave32x32 ? 16L : t.shape ? (8L << ((t.shape >> 6) & 7)) : 32L;
   return 3 + 2 * std::max(1L, (t.klen + per - 1) / per);
 }
 
@@ -1082,6 +1082,11 @@ bool Executor::contract_blocked(std::vector<Launch>& dst, const PerProb& out, co
     P.b_inner = has(K, unit_letter(bi, t_b)) ? 1 : 0;
     pinst[p] = p;
     const InstMomentum& Mm = *mom_[inst];
+    struct Block {
+      int m0, ml, k0, kl, n0, nl;
+    };
+    std::vector<Block> blocks;
+    long n_wave = 0;   // 16 x 16 tiles of the problem
     for (const auto& blk : TM.blocks) {
       std::vector<int> q(Mm.dims), qk(Mm.dims), qn(Mm.dims);
       for (int c = 0; c < Mm.dims; ++c) {
@@ -1099,8 +1104,15 @@ bool Executor::contract_blocked(std::vector<Launch>& dst, const PerProb& out, co
       const int k0 = kb == TK.blocks.end() ? 0 : kb->second.first;
       const int kl = kb == TK.blocks.end() ? 0 : kb->second.second;
       if (kl == 0 && acc) continue;   // nothing to add; a set writes its zeros
-      const int m0 = blk.second.first, ml = blk.second.second;
-      const int n0 = nb->second.first, nl = nb->second.second;
+      blocks.push_back(Block{blk.second.first, blk.second.second, k0, kl, nb->second.first, nb->second.second});
+      n_wave += (long)((blk.second.second + 15) / 16) * ((nb->second.second + 15) / 16);
+    }
+    // Waves of 32 x 32 gather each operand element half as often; they pay where a
+    // problem alone still has a wave for every CU (81 labelled orbitals, forward: 38.4 ->
+    // 35.3 ms; 57, step: 48.0 -> 47.0), not where its parallelism is short (33: 216 -> 223).
+    const bool wide = n_wave >= 256;
+    for (const Block& b : blocks) {
+      const int m0 = b.m0, ml = b.ml, k0 = b.k0, kl = b.kl, n0 = b.n0, nl = b.nl;
       // With one orbital per momentum the few blocks large enough for tiles gather every
       // element from a line of its own, which the tiles do not change, and their blocks
       // only delay the level (81 orbitals, forward: 40.8 ms with tiles, 38.3 without; 57:
@@ -1114,6 +1126,10 @@ bool Executor::contract_blocked(std::vector<Launch>& dst, const PerProb& out, co
         shape = thin_ok ? sgemm_shape(ml, nl, kl, thin_cap) : 0;
         R = shape ? 1 << (shape & 7) : 16;
         C = shape ? 1 << ((shape >> 3) & 7) : 16;
+        if (wide && !shape && std::min(ml, nl) > 16 && kl <= kSgemmChunk + kSgemmChunk / 2) {
+          shape = kWave32x32;
+          R = C = 32;
+        }
       }
       // bands of 8 tile rows, down the rows first, so that neighbouring tiles share both
       // operands' panels (see upload_sgemm)
@@ -1434,8 +1450,10 @@ void Executor::upload_sgemm(Launch& L) {
   L.d_desc = upload(L.sprobs.data(), sizeof(SgemmProblem) * L.sprobs.size());
   L.n_tasks = (int)L.stasks.size();
   L.n_square = L.n_narrow = 0;
+  L.wide = false;
   for (const SgemmTask& t : L.stasks) {
     L.n_square += t.shape == kTile64x64;
+    L.wide = L.wide || t.shape == kWave32x32;
     L.n_narrow += t.shape > kTile64x64;
   }
   xcd_order(L.stasks, 0, L.n_square, (int)probs_.size());
@@ -2091,7 +2109,7 @@ void Executor::run(const std::vector<Launch>& L, hipStream_t s) const {
         break;
       case Launch::SGEMM:
         launch_sgemm((const SgemmProblem*)l.d_desc, (const SgemmTask*)l.d_tasks, l.n_square, l.n_narrow, l.n_tasks,
-                     l.d_partial,
+                     l.wide, l.d_partial,
                      (const SgemmReduce*)l.d_red, l.n_red, s);
         break;
       case Launch::DOTB:

@@ -111,11 +111,13 @@ struct SgemmTask {
   int part;              // -1: write C; else the 16 x 16 partial tile goes to ws[part * 256 ...]
   int shape;             // 0: one 16 x 16 MFMA tile (rows, columns <= 16); else a lane-mapped tile of
                          // 2^lr rows x 2^lc columns whose inner range is split over 2^ls lanes
-                         // (lr | lc << 3 | ls << 6, lr + lc + ls = 6; never split into parts); or a
-                         // kTile* code: a tile of 4096 outputs computed by one block through LDS
+                         // (lr | lc << 3 | ls << 6, lr + lc + ls = 6; never split into parts);
+                         // kWave32x32: 2 x 2 MFMA tiles of one wave (never split); or a kTile*
+                         // code: a tile of 4096 outputs computed by one block through LDS
 };
 // block tiles (rows x columns); part counts units of 256 doubles, a block tile takes 16
 constexpr int kTile64x64 = 1 << 12, kTile128x32 = 2 << 12, kTile32x128 = 3 << 12;
+constexpr int kWave32x32 = 1 << 10;
 constexpr int sgemm_tile_rows(int shape) { return shape == kTile64x64 ? 64 : shape == kTile128x32 ? 128 : 32; }
 constexpr int kTileBK = 16;   // inner indices of one step of a block tile
 // shape code of a lane-mapped tile
@@ -134,8 +136,8 @@ struct SgemmReduce {
 // power-of-two multiple of it when the partial tiles would not fit the workspace).
 constexpr int kSgemmChunk = 64;
 // the first n_square tasks are 64 x 64 block tiles, the next n_narrow the other block
-// tiles (one block each), the rest one wave each
-void launch_sgemm(const SgemmProblem* d_probs, const SgemmTask* d_tasks, int n_square, int n_narrow, int n_tasks,
+// tiles (one block each), the rest one wave each; wide: 32 x 32 wave tiles among them
+void launch_sgemm(const SgemmProblem* d_probs, const SgemmTask* d_tasks, int n_square, int n_narrow, int n_tasks, bool wide,
                   double* ws, const SgemmReduce* d_red, int n_red, hipStream_t s);
 
 // Momentum-blocked elementwise sum over the allowed elements of Y only:

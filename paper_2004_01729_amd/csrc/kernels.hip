@@ -371,8 +371,10 @@ __global__ void __launch_bounds__(256) gemm_tail_reduce_kernel(const GemmProblem
 // long inner range (its partial tile then goes to the workspace and
 // sgemm_reduce_kernel adds the chunks); operands are gathered through the
 // block's offset lists straight into MFMA fragments (the blocks are small, so
-// nothing is staged in LDS).  No barriers: waves leave independently.
-__global__ void __launch_bounds__(256) sgemm_kernel(const SgemmProblem* __restrict__ probs,
+// nothing is staged in LDS).  No barriers: waves leave independently.  WIDE: the
+// launch has 32 x 32 tiles too (the others run with fewer registers without them).
+template <bool WIDE>
+__global__ void __launch_bounds__(256, WIDE ? 4 : 1) sgemm_kernel(const SgemmProblem* __restrict__ probs,
                                                     const SgemmTask* __restrict__ tasks, int n_tasks,
                                                     double* __restrict__ ws) {
   const int lane = threadIdx.x & 63;
@@ -387,6 +389,78 @@ __global__ void __launch_bounds__(256) sgemm_kernel(const SgemmProblem* __restri
   const gptr<const double> __restrict__ B = gview(P.B);
   const gptr<const unsigned> __restrict__ offAK = gview(P.offAK) + T.kb;
   const gptr<const unsigned> __restrict__ offBK = gview(P.offBK) + T.kb;
+  if (WIDE && T.shape == kWave32x32) {
+    // 2 x 2 MFMA tiles: each gathered element feeds two products.  The gathers of
+    // scattered elements are what a launch of large blocks waits for (one 64-byte
+    // sector each through the vector cache), so halving them outweighs the fewer waves.
+    const int r = lane & 15, q = lane >> 4;
+    unsigned am[2], bn[2];
+    bool rok[2], cok[2];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      rok[h] = 16 * h + r < T.mlen;
+      cok[h] = 16 * h + r < T.nlen;
+      am[h] = gview(P.offAM)[T.mb + (rok[h] ? 16 * h + r : 0)];
+      bn[h] = gview(P.offBN)[T.nb + (cok[h] ? 16 * h + r : 0)];
+    }
+    double4_t acc[2][2];
+#pragma unroll
+    for (int h = 0; h < 4; ++h) acc[h >> 1][h & 1] = (double4_t){0.0, 0.0, 0.0, 0.0};
+    auto step = [&](auto g_c, int k0) {
+      constexpr int G = decltype(g_c)::value;
+      unsigned ak[G], bk[G];
+      double a[2][G], b[2][G];
+#pragma unroll
+      for (int u = 0; u < G; ++u) {
+        const int k = k0 + 4 * u + q;
+        const int kk = k < T.klen ? k : 0;
+        ak[u] = offAK[kk];
+        bk[u] = offBK[kk];
+      }
+#pragma unroll
+      for (int u = 0; u < G; ++u)
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          a[h][u] = A[am[h] + ak[u]];
+          b[h][u] = B[bk[u] + bn[h]];
+        }
+#pragma unroll
+      for (int u = 0; u < G; ++u) {
+        const bool ok = k0 + 4 * u + q < T.klen;
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          a[h][u] = (ok && rok[h]) ? a[h][u] : 0.0;
+          b[h][u] = (ok && cok[h]) ? b[h][u] : 0.0;
+        }
+#pragma unroll
+        for (int h = 0; h < 4; ++h)
+          acc[h >> 1][h & 1] =
+              __builtin_amdgcn_mfma_f64_16x16x4f64(a[h >> 1][u], b[h & 1][u], acc[h >> 1][h & 1], 0, 0, 0);
+      }
+    };
+    int k0 = 0;
+    for (; T.klen - k0 > 8; k0 += 16) step(std::integral_constant<int, 4>{}, k0);
+    if (T.klen - k0 > 4) step(std::integral_constant<int, 2>{}, k0);
+    else if (T.klen - k0 > 0) step(std::integral_constant<int, 1>{}, k0);
+    const gptr<double> C = gview(P.C);
+    size_t cn[2], cm[8];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) cn[h] = gview(P.offCN)[T.nb + min(16 * h + r, T.nlen - 1)];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) cm[i] = gview(P.offCM)[T.mb + min(4 * i + q, T.mlen - 1)];
+    double cv[16];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) cv[i] = 0.0;
+    if (P.beta != 0.0) {
+#pragma unroll
+      for (int i = 0; i < 16; ++i) cv[i] = C[cm[i >> 1] + cn[i & 1]];
+    }
+#pragma unroll
+    for (int i = 0; i < 16; ++i)
+      if (4 * (i >> 1) + q < T.mlen && 16 * (i & 1) + r < T.nlen)
+        C[cm[i >> 1] + cn[i & 1]] = P.alpha * acc[i >> 3][i & 1][(i >> 1) & 3] + P.beta * cv[i];
+    return;
+  }
   if (T.shape) {
     // Lane-mapped tile of a thin block (a single row or column, or a long inner
     // range on a few outputs): lane = (row, column, inner slice); each lane adds its
@@ -1191,7 +1265,7 @@ void launch_splitk_reduce(const GemmProblem* d_probs, const int* d_prefix, int n
                      total_blocks);
 }
 
-void launch_sgemm(const SgemmProblem* d_probs, const SgemmTask* d_tasks, int n_square, int n_narrow, int n_tasks,
+void launch_sgemm(const SgemmProblem* d_probs, const SgemmTask* d_tasks, int n_square, int n_narrow, int n_tasks, bool wide,
                   double* ws, const SgemmReduce* d_red, int n_red, hipStream_t s) {
   if (n_tasks <= 0) return;
   if (n_square > 0)
@@ -1200,7 +1274,8 @@ void launch_sgemm(const SgemmProblem* d_probs, const SgemmTask* d_tasks, int n_s
     hipLaunchKernelGGL(sgemm_tile_kernel<true>, dim3(n_narrow), dim3(256), 0, s, d_probs, d_tasks + n_square, ws);
   const int first = n_square + n_narrow, waves = n_tasks - first;
   if (waves > 0)
-    hipLaunchKernelGGL(sgemm_kernel, dim3((waves + 3) / 4), dim3(256), 0, s, d_probs, d_tasks + first, waves, ws);
+    hipLaunchKernelGGL(wide ? sgemm_kernel<true> : sgemm_kernel<false>, dim3((waves + 3) / 4), dim3(256), 0, s, d_probs,
+                       d_tasks + first, waves, ws);
   if (n_red > 0)
     hipLaunchKernelGGL(sgemm_reduce_kernel, dim3(n_red), dim3(256), 0, s, d_probs, d_red, (const double*)ws);
 }

@@ -92,3 +92,26 @@ def test_two_label_blocks(F, split):
         ctx.close()
     for a, b in zip(*out):
         assert _close(a, b)
+
+
+@pytest.mark.parametrize("L", [32, 33, 40])
+def test_wide_wave_tiles(F, L):
+    """Rings with a label per orbital: L blocks of L x L outputs over L inner indices, in
+    32 x 32 wave tiles (whole ones, remainders of 1 and of 8), against the same ring
+    without labels."""
+    s = fi.hubbard_config(L=L, U=2.0, T=1.0)
+    lab = np.arange(L)
+    t1, t2 = fi.random_amplitudes(L, seed=L, scale=0.05)
+    t1 = np.diag(np.diag(t1))
+    t2 = t2 * ((lab[:, None, None, None] + lab[:, None, None] - lab[:, None] - lab) % L == 0)
+    out = []
+    for labelled in (True, False):
+        print(f"[levels] ring of {L} labelled={labelled}", flush=True)
+        ctx = F.Context(1, n_tau=6, nodes_per_panel=3)
+        if labelled:
+            ctx.set_momentum(0, *s.momentum)
+        ctx.set_hamiltonian(0, s.h, s.eri, s.eps)
+        out.append(ctx.eval_residual(0, s.mu, s.beta, t1, t2))
+        ctx.close()
+    for a, b in zip(*out):
+        assert _close(a, b)
