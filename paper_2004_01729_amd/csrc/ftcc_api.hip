@@ -745,7 +745,9 @@ void build(ftcc_ctx* c) {
       c->scratch.c[q] = c->dalloc(n4);
       c->scratch.part[q] = c->dalloc(n4);
     }
-  c->scratch.dot_partial = c->dalloc((size_t)nn * 64 + 64);
+  // 64 partial sums for each dot of one launch: one per node, or the two Gram entries of
+  // every stored DIIS residual
+  c->scratch.dot_partial = c->dalloc((size_t)std::max(nn, c->opt.diis_depth ? 2 * kMaxDiis : 0) * 64 + 64);
   {
     // workspace for partial tiles: 128 MiB, or an eighth of a memory cap below 1 GiB
     size_t ws = kTailWorkspaceDoubles;

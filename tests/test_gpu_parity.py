@@ -132,3 +132,20 @@ def test_forward_and_adjoint_with_diis(ftcc):
     assert abs(om[0] - sol.omega) < 1e-10 * abs(sol.omega)
     ref = S.d_omega(model, gr, sol, adj, "mu")
     assert abs(r["mu"][0] - ref) < 1e-8 * max(1.0, abs(ref))
+
+
+@pytest.mark.parametrize("depth", [2, 8])
+def test_diis_one_node_per_panel(ftcc, depth):
+    """The deepest history on the fewest nodes (16 Gram dots for one node, the most dots
+    per node there are): the fixed point of the plain sweeps, both ends of a march to
+    1e-13; the energies amplify that by less than 1e3."""
+    s = fi.hubbard_config(L=3, U=2.0, T=1.0)
+    om = []
+    for d in (depth, 0):
+        _say(f"[diis] hubbard L=3 n_tau=3 nodes_per_panel=1 diis_depth={d}")
+        ctx = ftcc.Context(1, n_tau=3, nodes_per_panel=1, tol=1e-13, diis_depth=d)
+        ctx.set_hamiltonian(0, s.h, s.eri, s.eps)
+        ctx.solve(s.mu, s.beta)
+        om.append(ctx.grand_potential()[0][0])
+        ctx.close()
+    assert abs(om[0] - om[1]) < 1e-10 * abs(om[1])
