@@ -144,6 +144,8 @@ struct ftcc_ctx {
   std::vector<std::array<double*, 4>> ugrad;
   Scratch scratch;
   unsigned long long* d_maxbits = nullptr;    // [B][2]
+  unsigned long long* h_maxbits = nullptr;    // their values at the last post_maxbits (pinned host memory)
+  hipEvent_t maxbits_posted = nullptr;
   double* d_partial = nullptr;                // TAU_BETA partial sums
   std::vector<int> tau_prefix_host;
   int* d_active = nullptr;                    // [B] propagator step flags
@@ -325,6 +327,8 @@ void set_active(ftcc_ctx* c, const std::vector<bool>& active);
 void set_run(ftcc_ctx* c, const std::vector<bool>& run);
 void run_all(ftcc_ctx* c);
 void reset_maxbits(ftcc_ctx* c);
+void post_maxbits(ftcc_ctx* c);
+std::vector<double> wait_maxbits(ftcc_ctx* c);
 std::vector<double> read_maxbits(ftcc_ctx* c);
 void copy_d(ftcc_ctx* c, double* dst, const double* src, long count);
 void zero_d(ftcc_ctx* c, double* dst, long count);
