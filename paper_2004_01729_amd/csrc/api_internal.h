@@ -81,6 +81,7 @@ struct Instance {
   double* rk_tmp[2] = {nullptr, nullptr};   // differential form: reverse-pass temporaries
   double* gacc[12] = {};                    // two-body density: accumulated gradients of the 12 weighted blocks
   double* rk_hbar = nullptr;                // d Omega_CC / d(step) at fixed integrals
+  double* rk_ugrad[4] = {nullptr, nullptr, nullptr, nullptr};   // u-block gradients summed by the reverse march
   // orbital-energy response (allocated on first request): per-orbital accumulators of
   // the thermal-integral part, dL/dDelta of every amplitude element and the assembled vector
   double *deps_acc = nullptr, *deps_delta = nullptr, *deps_out = nullptr;
@@ -175,8 +176,10 @@ struct ftcc_ctx {
   std::map<long, SpLaunch> sp_cache;          // its exponential-sum descriptor sets (until the next solve)
   double gdeg = 2.0;                          // electrons per orbital and occupation: 2 restricted, 1 spin orbitals
   std::vector<double> rk_a, rk_b;
-  double* d_rkw = nullptr;                    // [P + 1] Simpson weight / beta of each grid point
+  double* d_rkw = nullptr;                    // [P + 2] Simpson weight / beta of each grid point, then 0
   int* d_bad = nullptr;                       // flag of the conservation-law checks
+  double* d_rkh = nullptr;                    // [B] step length of each instance
+  std::vector<double> rkh_host;
   std::map<std::tuple<int, int, int>, std::pair<RKProblem*, int*>> rk_cache;
   std::map<std::tuple<int, int, int>, int> rk_blocks;
   std::map<std::tuple<int, int, int>, DotProblem*> rk_dots;
@@ -210,10 +213,21 @@ struct ftcc_ctx {
   // launch descriptors and other small tables: the library's own, outside the caller's
   // allocator and the cap, kept until the context is destroyed
   std::vector<void*> descs;
+  char* desc_at = nullptr;        // the free part of the last chunk
+  size_t desc_left = 0;
   void* desc(const void* host, size_t nbytes) {
-    void* p = nullptr;
-    FTCC_HIP(hipMalloc(&p, std::max<size_t>(nbytes, 8)));
-    descs.push_back(p);
+    constexpr size_t kChunk = size_t(1) << 20;
+    const size_t need = (std::max<size_t>(nbytes, 8) + 255) / 256 * 256;
+    if (need > desc_left) {
+      void* chunk = nullptr;
+      FTCC_HIP(hipMalloc(&chunk, std::max(need, kChunk)));
+      descs.push_back(chunk);
+      desc_at = (char*)chunk;
+      desc_left = std::max(need, kChunk);
+    }
+    void* p = desc_at;
+    desc_at += need;
+    desc_left -= need;
     if (host) FTCC_HIP(hipMemcpy(p, host, nbytes, hipMemcpyHostToDevice));
     else FTCC_HIP(hipMemset(p, 0, nbytes));
     return p;
@@ -266,7 +280,9 @@ using NodeBufs = std::function<double*(int inst, int x)>;
 
 // one Runge-Kutta combination of the differential form: out = x0 * base +
 // sum_l coef[l] * (-Delta Y_l + sigma S_l) over the stage buffers Y_l, S_l
+// per_x0, per_coef: x0 and coef count in units of the step length
 struct RKSpec {
+  bool per_x0 = false, per_coef = false;
   const double* base = nullptr;
   double x0 = 0.0;
   int nst = 0;
@@ -311,11 +327,20 @@ void run_bwd_slots(ftcc_ctx* c);
 long node_len(ftcc_ctx* c, int i);
 void dcopy(ftcc_ctx* c, double* dst, const double* src, long count);
 void node_copy(ftcc_ctx* c, int i, double* dst, const double* src);
-// one launch for a set of whole node states: (instance, dst, src or null for zero) per entry, fixed
-// per (kind, panel) once the context is built
-enum StateSet { ST_SAVE = 0, ST_LOAD = 1, ST_ZERO_COT = 2, ST_ZERO_START = 3, ST_ZERO_END = 4 };
-void state_set(ftcc_ctx* c, int kind, int panel,
-               const std::function<void(std::function<void(int, double*, const double*)>)>& list);
+// One launch for a set of copies, fixed per (kind, panel) once the context is built.  An
+// entry is a whole node state of an instance (src null: zeros) or `len` values; `add`
+// adds them.  From ST_STAGE_IN on an entry is skipped while its instance does not run.
+enum StateSet {
+  ST_SAVE, ST_LOAD, ST_ZERO_COT, ST_ZERO_START, ST_ZERO_END,
+  ST_STAGE_IN, ST_STAGE_OUT, ST_STAGE_D_OUT, ST_REVERSE_IN, ST_REVERSE_S, ST_REVERSE_OUT
+};
+struct StateList {
+  std::function<void(int, double*, const double*, long, bool)> put;
+  void operator()(int i, double* dst, const double* src, long len = 0, bool add = false) const {
+    put(i, dst, src, len, add);
+  }
+};
+void state_set(ftcc_ctx* c, int kind, int panel, const std::function<void(StateList)>& list);
 void forward(ftcc_ctx* c);
 void backward(ftcc_ctx* c);
 void d_forward(ftcc_ctx* c);
@@ -340,12 +365,11 @@ void load_panel(ftcc_ctx* c, int p);
 
 // rk_march.hip: the differential form
 void forward_one(ftcc_ctx* c, int x);
-void backward_one(ftcc_ctx* c, int x);
+void d_stage(ftcc_ctx* c, int x);
 void d_forward_one(ftcc_ctx* c, int x);
 void rk_combine(ftcc_ctx* c, int kind, int p, int x, double sigma, bool track,
                 const std::function<RKSpec(int)>& spec);
 void rk_dot(ftcc_ctx* c, int kind, int p, int x, const std::function<std::array<const double*, 3>(int)>& xyz);
-double rk_h(const ftcc_ctx* c, int i);
 double rk_a(const ftcc_ctx* c, int j, int l);
 void rk_stage_state(ftcc_ctx* c, int p, int x);
 void rk_recompute_stages(ftcc_ctx* c, int p);

@@ -647,13 +647,17 @@ void build(ftcc_ctx* c) {
       I.rk_tmp[1] = c->dalloc(len);
       I.rk_hbar = c->dalloc(1);
     }
+    if (c->rk)
+      for (int k = 0; k < 4; ++k) I.rk_ugrad[k] = c->dalloc((size_t)I.n * I.n);
   }
   if (c->rk || c->simpson) {
     // (1/beta) g_k of Simpson's rule on the uniform grid: w_k / (3 n_g), w = 1 4 2 ... 4 1
     std::vector<double> w(P + 1);
     for (int k = 0; k <= P; ++k) w[k] = ((k == 0 || k == P) ? 1.0 : (k % 2 ? 4.0 : 2.0)) / (3.0 * P);
-    c->d_rkw = c->dalloc(P + 1);
-    FTCC_HIP(hipMemcpy(c->d_rkw, w.data(), sizeof(double) * (P + 1), hipMemcpyHostToDevice));
+    w.push_back(0.0);
+    c->d_rkw = c->dalloc(P + 2);
+    c->d_rkh = c->dalloc(B);
+    FTCC_HIP(hipMemcpy(c->d_rkw, w.data(), sizeof(double) * (P + 2), hipMemcpyHostToDevice));
   }
   trace_mem(c, "integrals, panel states and Lambda storage");
   // Executor slots per instance: every node of a panel evaluated in one grouped
@@ -1009,21 +1013,22 @@ void forward(ftcc_ctx* c) {
   }
 }
 
-void state_set(ftcc_ctx* c, int kind, int panel,
-               const std::function<void(std::function<void(int, double*, const double*)>)>& list) {
+void state_set(ftcc_ctx* c, int kind, int panel, const std::function<void(StateList)>& list) {
   const auto key = std::make_pair(kind, panel);
   auto it = c->state_copies.find(key);
   if (it == c->state_copies.end()) {
     std::vector<StateCopy> cs;
     std::vector<int> prefix;
     int total = 0;
-    list([&](int i, double* dst, const double* src) {
+    list(StateList{[&](int i, double* dst, const double* src, long len, bool add) {
       const Instance& I = c->inst[i];
       StateCopy k{};
       k.src = src;
       k.dst = dst;
-      k.len = node_len(c, i);
-      if (I.d_allowed[0] && I.d_allowed[1]) {
+      k.len = len ? len : node_len(c, i);
+      k.active = kind >= ST_STAGE_IN ? c->d_run + i * c->slots : nullptr;
+      k.add = add;
+      if (!len && I.d_allowed[0] && I.d_allowed[1]) {
         k.a = I.d_allowed[0];
         k.na = I.n_allowed[0];
         k.b = I.d_allowed[1];
@@ -1034,7 +1039,7 @@ void state_set(ftcc_ctx* c, int kind, int panel,
       prefix.push_back(total);
       total += (int)((k.len + kStateCopyBlock - 1) / kStateCopyBlock);
       cs.push_back(k);
-    });
+    }});
     ftcc_ctx::StateCopies t;
     t.n = (int)cs.size();
     t.blocks = total;
@@ -1137,14 +1142,6 @@ void clear_tau_cache(ftcc_ctx* c) {
   }
   c->tau_cache.clear();
   c->tau_shape.clear();
-  for (auto& kv : c->rk_cache) {
-    (void)hipFree(kv.second.first);
-    (void)hipFree(kv.second.second);
-  }
-  c->rk_cache.clear();
-  c->rk_blocks.clear();
-  for (auto& kv : c->rk_dots) (void)hipFree(kv.second);
-  c->rk_dots.clear();
   for (auto& kv : c->sp_cache) (void)hipFree(kv.second.buf);
   c->sp_cache.clear();
 }
@@ -2138,6 +2135,12 @@ int ftcc_response(ftcc_ctx* c, double* dO_dmu, double* dO_dbeta, double* dO_dh, 
       std::vector<bool> ok(B);
       for (int i = 0; i < B; ++i) ok[i] = c->inst[i].status == 0 && c->inst[i].lam_status == 0;
       set_run(c, ok);
+      // the reverse march has summed the gradients of the u blocks over the same stages
+      if (dO_dh)
+        for (int i = 0; i < B; ++i)
+          for (int q = 0; q < 4; ++q)
+            launch_axpby((long)c->inst[i].n * c->inst[i].n, 1.0, c->inst[i].rk_ugrad[q], 1.0, c->inst[i].ugrad_acc[q],
+                         c->stream);
       for (int k = 0; k <= P; ++k) {
         const int ns = k < P ? m : 1;
         const double wk = ((k == 0 || k == P) ? 1.0 : (k % 2 ? 4.0 : 2.0)) / (3.0 * P);
@@ -2156,64 +2159,56 @@ int ftcc_response(ftcc_ctx* c, double* dO_dmu, double* dO_dbeta, double* dO_dh, 
             for (int i = 0; i < B; ++i)
               if (ok[i]) zero_d(c, c->cot[i * m], node_len(c, i));
           }
-          set_ebar(c, x, x == 0 ? k : -1);
-          if (dO_dh) {
-            backward_one(c, x);
+          // the slopes' Delta dependence, d k / d Delta = -Y, weighted by the slope
+          // cotangent: cot = -kbar, so dL/dDelta += cot * Y (stage state in amp)
+          if (dO_deps && k < P)
             for (int i = 0; i < B; ++i) {
               if (!ok[i]) continue;
-              const long n = c->inst[i].n;
-              for (int q = 0; q < 4; ++q)
-                launch_axpby(n * n, 1.0, c->ugrad[i * m + x][q], 1.0, c->inst[i].ugrad_acc[q], c->stream);
+              const long len = node_len(c, i);
+              hipLaunchKernelGGL(mul_acc_kernel, dim3((unsigned)std::min<long>((len + 255) / 256, 65536)),
+                                 dim3(256), 0, c->stream, len, c->cot[i * m + x], c->amp[i * m + x],
+                                 c->inst[i].deps_delta);
             }
-          }
-          for (int which = 0; which < 3; ++which) {
-            if (which == 0 && !dO_dmu) continue;
-            if (which == 1 && !dO_dbeta) continue;
-            if (which == 2 && !want_theta) continue;
-            deriv_setup(c, which);
-            c->ex_d->run_setup(c->stream);
-            d_forward_one(c, x);
+        }
+        // a direction's integrals once for all stages of the step
+        for (int which = 0; which < 3; ++which) {
+          if (which == 0 && !dO_dmu) continue;
+          if (which == 1 && !dO_dbeta) continue;
+          if (which == 2 && !want_theta) continue;
+          deriv_setup(c, which);
+          c->ex_d->run_setup(c->stream);
+          for (int x = 0; x < ns; ++x) {
+            d_stage(c, x);
             rk_dot(c, 2 + which, k, x, [c, x, which](int i) {
-              return std::array<const double*, 3>{c->cot[i * c->m + x], c->dS[i * c->m + x],
-                                                  c->inst[i].acc + which};
+              return std::array<const double*, 3>{c->cot[i * c->m + x], c->s_dS[i], c->inst[i].acc + which};
             });
             if (x == 0)
               for (int i = 0; i < B; ++i)
-                if (ok[i]) launch_axpby(1, wk, c->de[i * m], 1.0, c->inst[i].acc + which, c->stream);
+                if (ok[i]) launch_axpby(1, wk, c->s_de[i], 1.0, c->inst[i].acc + which, c->stream);
           }
-          if (dO_deps) {
-            // the slopes' Delta dependence, d k / d Delta = -Y, weighted by the slope
-            // cotangent: cot = -kbar, so dL/dDelta += cot * Y (stage state in amp)
-            if (k < P)
-              for (int i = 0; i < B; ++i) {
-                if (!ok[i]) continue;
-                const long len = node_len(c, i);
-                hipLaunchKernelGGL(mul_acc_kernel, dim3((unsigned)std::min<long>((len + 255) / 256, 65536)),
-                                   dim3(256), 0, c->stream, len, c->cot[i * m + x], c->amp[i * m + x],
-                                   c->inst[i].deps_delta);
-              }
-            for (int q = 0; q < nmax; ++q) {
-              deriv_setup(c, SETUP_EPS, q);
-              c->ex_d->run_setup(c->stream);
-              d_forward_one(c, x);
-              for (int i = 0; i < B; ++i) {
-                if (!ok[i] || q >= c->inst[i].n) continue;
-                const long n = c->inst[i].n;
-                DotProblem d{};
-                d.X = c->cot[i * m + x];
-                d.Y = c->dS[i * m + x];
-                d.out = c->inst[i].deps_acc + q;
-                d.len = n * n + n * n * n * n;
-                list_allowed(c, i, d);
-                d.alpha = 1.0;
-                d.beta = 1.0;
-                DotProblem* dd = nullptr;
-                FTCC_HIP(hipMallocAsync((void**)&dd, sizeof(DotProblem), c->stream));
-                FTCC_HIP(hipMemcpyAsync(dd, &d, sizeof(DotProblem), hipMemcpyHostToDevice, c->stream));
-                launch_dot(dd, 1, 64, c->scratch.dot_partial, c->stream);
-                FTCC_HIP(hipFreeAsync(dd, c->stream));
-                if (x == 0) launch_axpby(1, wk, c->de[i * m], 1.0, c->inst[i].deps_acc + q, c->stream);
-              }
+        }
+        for (int q = 0; dO_deps && q < nmax; ++q) {
+          deriv_setup(c, SETUP_EPS, q);
+          c->ex_d->run_setup(c->stream);
+          for (int x = 0; x < ns; ++x) {
+            d_stage(c, x);
+            for (int i = 0; i < B; ++i) {
+              if (!ok[i] || q >= c->inst[i].n) continue;
+              const long n = c->inst[i].n;
+              DotProblem d{};
+              d.X = c->cot[i * m + x];
+              d.Y = c->s_dS[i];
+              d.out = c->inst[i].deps_acc + q;
+              d.len = n * n + n * n * n * n;
+              list_allowed(c, i, d);
+              d.alpha = 1.0;
+              d.beta = 1.0;
+              DotProblem* dd = nullptr;
+              FTCC_HIP(hipMallocAsync((void**)&dd, sizeof(DotProblem), c->stream));
+              FTCC_HIP(hipMemcpyAsync(dd, &d, sizeof(DotProblem), hipMemcpyHostToDevice, c->stream));
+              launch_dot(dd, 1, 64, c->scratch.dot_partial, c->stream);
+              FTCC_HIP(hipFreeAsync(dd, c->stream));
+              if (x == 0) launch_axpby(1, wk, c->s_de[i], 1.0, c->inst[i].deps_acc + q, c->stream);
             }
           }
         }

@@ -15,58 +15,74 @@ namespace host {
 // gradient.  Grid states s_k live in sb[k] (k = 0..n_g), their cotangents in
 // abuf[k], and the slope cotangents kbar of step p, stage x in lam[p m + x].
 
+// the state of stage x into the executor slot
+static void stage_in(ftcc_ctx* c, int x) {
+  state_set(c, ST_STAGE_IN, x, [c, x](auto put) {
+    for (int i = 0; i < c->B; ++i) put(i, c->s_amp[i], c->amp[i * c->m + x]);
+  });
+}
+
 // stage x of every running instance: amp[x] -> S[x], e[x]
 void forward_one(ftcc_ctx* c, int x) {
-  for (int i = 0; i < c->B; ++i)
-    if (c->run_host[i]) node_copy(c, i, c->s_amp[i], c->amp[i * c->m + x]);
+  stage_in(c, x);
   run_fwd_slots(c);
   c->resid_evals += n_running(c);
-  for (int i = 0; i < c->B; ++i) {
-    if (!c->run_host[i]) continue;
-    node_copy(c, i, c->S[i * c->m + x], c->s_S[i]);
-    dcopy(c, c->e[i * c->m + x], c->s_e[i], 1);
-  }
+  state_set(c, ST_STAGE_OUT, x, [c, x](auto put) {
+    for (int i = 0; i < c->B; ++i) {
+      put(i, c->S[i * c->m + x], c->s_S[i]);
+      put(i, c->e[i * c->m + x], c->s_e[i], 1);
+    }
+  });
 }
 
-// reverse pass of stage x (tape recomputed first): cot[x], ebar[x] -> gr[x], ugrad[x]; also S[x]
-void backward_one(ftcc_ctx* c, int x) {
-  for (int i = 0; i < c->B; ++i)
-    if (c->run_host[i]) node_copy(c, i, c->s_amp[i], c->amp[i * c->m + x]);
+// Reverse pass of stage x (tape recomputed first), the cotangent of its residual in the
+// slot (s_cot) and the energy's the Simpson weight of grid_point (-1: none): -> gr[x], and
+// the gradients of the u blocks added to rk_ugrad; with_S: also S[x].
+static void backward_one(ftcc_ctx* c, int x, int grid_point, bool with_S) {
+  const int e = grid_point >= 0 ? grid_point : c->P + 1;
+  state_set(c, ST_REVERSE_IN, x * (c->P + 2) + e, [c, x, e](auto put) {
+    for (int i = 0; i < c->B; ++i) {
+      put(i, c->s_amp[i], c->amp[i * c->m + x]);
+      put(i, c->s_ebar[i], c->d_rkw + e, 1);
+    }
+  });
   run_fwd_slots(c);
   c->resid_evals += n_running(c);
-  for (int i = 0; i < c->B; ++i) {
-    if (!c->run_host[i]) continue;
-    const int q = i * c->m + x;
-    node_copy(c, i, c->S[q], c->s_S[i]);
-    node_copy(c, i, c->s_cot[i], c->cot[q]);
-    dcopy(c, c->s_ebar[i], c->ebar[q], 1);
-  }
+  if (with_S)
+    state_set(c, ST_REVERSE_S, x, [c, x](auto put) {
+      for (int i = 0; i < c->B; ++i) put(i, c->S[i * c->m + x], c->s_S[i]);
+    });
   run_bwd_slots(c);
   c->vjp_evals += n_running(c);
-  for (int i = 0; i < c->B; ++i) {
-    if (!c->run_host[i]) continue;
-    const int q = i * c->m + x;
-    const long n = c->inst[i].n;
-    node_copy(c, i, c->gr[q], c->s_gr[i]);
-    for (int k = 0; k < 4; ++k) dcopy(c, c->ugrad[q][k], c->s_ugrad[i][k], n * n);
-  }
+  state_set(c, ST_REVERSE_OUT, x, [c, x](auto put) {
+    for (int i = 0; i < c->B; ++i) {
+      const long n = c->inst[i].n;
+      put(i, c->gr[i * c->m + x], c->s_gr[i]);
+      for (int k = 0; k < 4; ++k) put(i, c->inst[i].rk_ugrad[k], c->s_ugrad[i][k], n * n, true);
+    }
+  });
 }
 
-// derivative-integral residual of stage x: amp[x] -> dS[x], de[x]
-void d_forward_one(ftcc_ctx* c, int x) {
-  for (int i = 0; i < c->B; ++i)
-    if (c->run_host[i]) node_copy(c, i, c->s_amp[i], c->amp[i * c->m + x]);
+// derivative-integral residual of stage x in the slot: amp[x] -> s_dS, s_de
+void d_stage(ftcc_ctx* c, int x) {
+  stage_in(c, x);
   c->ex_d->run_forward(c->stream);
-  for (int i = 0; i < c->B; ++i) {
-    if (!c->run_host[i]) continue;
-    node_copy(c, i, c->dS[i * c->m + x], c->s_dS[i]);
-    dcopy(c, c->de[i * c->m + x], c->s_de[i], 1);
-  }
+}
+
+// the same into dS[x], de[x]
+void d_forward_one(ftcc_ctx* c, int x) {
+  d_stage(c, x);
+  state_set(c, ST_STAGE_D_OUT, x, [c, x](auto put) {
+    for (int i = 0; i < c->B; ++i) {
+      put(i, c->dS[i * c->m + x], c->s_dS[i]);
+      put(i, c->de[i * c->m + x], c->s_de[i], 1);
+    }
+  });
 }
 
 // out = x0 base + sum_l coef_l (-Delta Y_l + sigma S_l) for every instance (both
-// amplitude segments); descriptors cached under (kind, step, stage) until the
-// next solve.  track: max |out| into maxbits[2 i + 1].
+// amplitude segments); descriptors kept under (kind, step, stage): the buffers are fixed
+// once the context is built, and the step length comes from device memory.  track: max |out| into maxbits[2 i + 1].
 void rk_combine(ftcc_ctx* c, int kind, int p, int x, double sigma, bool track,
                 const std::function<RKSpec(int)>& spec) {
   const auto key = std::make_tuple(kind, p, x);
@@ -90,6 +106,8 @@ void rk_combine(ftcc_ctx* c, int kind, int p, int x, double sigma, bool track,
         r.idx = I.d_allowed[seg];
         r.base = sp.base ? sp.base + off : nullptr;
         r.x0 = sp.x0;
+        r.h_x0 = sp.per_x0 ? c->d_rkh + i : nullptr;
+        r.h_coef = sp.per_coef ? c->d_rkh + i : nullptr;
         r.nst = sp.nst;
         for (int l = 0; l < sp.nst; ++l) {
           r.coef[l] = sp.coef[l];
@@ -101,16 +119,12 @@ void rk_combine(ftcc_ctx* c, int kind, int p, int x, double sigma, bool track,
         r.maxbits = track ? c->d_maxbits + 2 * i + 1 : nullptr;
         r.active = c->d_run + i * c->slots;
         prefix.push_back(total);
-        total += (int)((r.len + 1023) / 1024);
+        total += (int)((r.len + kRKBlock - 1) / kRKBlock);
         ps.push_back(r);
       }
     }
-    RKProblem* d_ps = nullptr;
-    int* d_pre = nullptr;
-    FTCC_HIP(hipMalloc((void**)&d_ps, sizeof(RKProblem) * ps.size()));
-    FTCC_HIP(hipMalloc((void**)&d_pre, sizeof(int) * prefix.size()));
-    FTCC_HIP(hipMemcpy(d_ps, ps.data(), sizeof(RKProblem) * ps.size(), hipMemcpyHostToDevice));
-    FTCC_HIP(hipMemcpy(d_pre, prefix.data(), sizeof(int) * prefix.size(), hipMemcpyHostToDevice));
+    RKProblem* d_ps = (RKProblem*)c->desc(ps.data(), sizeof(RKProblem) * ps.size());
+    int* d_pre = (int*)c->desc(prefix.data(), sizeof(int) * prefix.size());
     it = c->rk_cache.emplace(key, std::make_pair(d_ps, d_pre)).first;
     c->rk_blocks[key] = total;
   }
@@ -134,16 +148,13 @@ void rk_dot(ftcc_ctx* c, int kind, int p, int x, const std::function<std::array<
       list_allowed(c, i, d);
       d.alpha = 1.0;
       d.beta = 1.0;
-      DotProblem* dd = nullptr;
-      FTCC_HIP(hipMalloc((void**)&dd, sizeof(DotProblem)));
-      FTCC_HIP(hipMemcpy(dd, &d, sizeof(DotProblem), hipMemcpyHostToDevice));
+      DotProblem* dd = (DotProblem*)c->desc(&d, sizeof(DotProblem));
       it = c->rk_dots.emplace(key, dd).first;
     }
     launch_dot(it->second, 1, 64, c->scratch.dot_partial, c->stream);
   }
 }
 
-double rk_h(const ftcc_ctx* c, int i) { return c->inst[i].beta / c->P; }
 double rk_a(const ftcc_ctx* c, int j, int l) { return c->rk_a[j * c->m + l]; }
 
 // stage state Y_x of step p: sb[p] + h sum_{l<x} a_xl k_l, k_l = -(Delta Y_l + S_l)
@@ -157,8 +168,9 @@ void rk_stage_state(ftcc_ctx* c, int p, int x) {
     RKSpec sp;
     sp.base = c->inst[i].sb[p];
     sp.x0 = 1.0;
+    sp.per_coef = true;
     for (int l = 0; l < x; ++l) {
-      sp.coef[sp.nst] = rk_h(c, i) * rk_a(c, x, l);
+      sp.coef[sp.nst] = rk_a(c, x, l);
       sp.Y[sp.nst] = c->amp[i * c->m + l];
       sp.S[sp.nst] = c->S[i * c->m + l];
       ++sp.nst;
@@ -192,6 +204,9 @@ void rk_solve(ftcc_ctx* c, std::vector<int>& status) {
   std::vector<double> ebuf((size_t)B * (P + 1), 0.0);
   std::vector<bool> ok(B);
   const auto wall0 = std::chrono::steady_clock::now();
+  c->rkh_host.assign(B, 0.0);
+  for (int i = 0; i < B; ++i) c->rkh_host[i] = c->inst[i].beta / P;
+  FTCC_HIP(hipMemcpyAsync(c->d_rkh, c->rkh_host.data(), sizeof(double) * B, hipMemcpyHostToDevice, c->stream));
   auto energy_to_host = [&](int k) {
     for (int i = 0; i < B; ++i)
       if (c->run_host[i])
@@ -211,8 +226,9 @@ void rk_solve(ftcc_ctx* c, std::vector<int>& status) {
       RKSpec sp;
       sp.base = c->inst[i].sb[p];
       sp.x0 = 1.0;
+      sp.per_coef = true;
       for (int l = 0; l < c->m; ++l) {
-        sp.coef[sp.nst] = rk_h(c, i) * c->rk_b[l];
+        sp.coef[sp.nst] = c->rk_b[l];
         sp.Y[sp.nst] = c->amp[i * c->m + l];
         sp.S[sp.nst] = c->S[i * c->m + l];
         ++sp.nst;
@@ -258,10 +274,12 @@ void rk_lambda(ftcc_ctx* c, std::vector<int>& status) {
   const auto wall0 = std::chrono::steady_clock::now();
   // final grid point: only the energy term
   rk_stage_state(c, P, 0);
-  for (int i = 0; i < B; ++i)
-    if (ok[i]) zero_d(c, c->cot[i * m], node_len(c, i));
-  set_ebar(c, 0, P);
-  backward_one(c, 0);
+  for (int i = 0; i < B; ++i) {
+    if (!ok[i]) continue;
+    zero_d(c, c->s_cot[i], node_len(c, i));
+    for (int k = 0; k < 4; ++k) zero_d(c, c->inst[i].rk_ugrad[k], (long)c->inst[i].n * c->inst[i].n);
+  }
+  backward_one(c, 0, P, true);
   for (int i = 0; i < B; ++i)
     if (ok[i]) node_copy(c, i, c->inst[i].abuf[P], c->gr[i * m]);
   for (int p = P - 1; p >= 0; --p) {
@@ -270,12 +288,12 @@ void rk_lambda(ftcc_ctx* c, std::vector<int>& status) {
       rk_combine(c, 2, p, x, +1.0, false, [c, p, x](int i) {
         RKSpec sp;
         const Instance& I = c->inst[i];
-        const double h = rk_h(c, i);
         sp.base = I.abuf[p + 1];
-        sp.x0 = h * c->rk_b[x];
+        sp.x0 = c->rk_b[x];
+        sp.per_x0 = sp.per_coef = true;
         for (int y = x + 1; y < c->m; ++y) {
           if (rk_a(c, y, x) == 0.0) continue;
-          sp.coef[sp.nst] = h * rk_a(c, y, x);
+          sp.coef[sp.nst] = rk_a(c, y, x);
           sp.Y[sp.nst] = I.lam[p * c->m + y];
           sp.S[sp.nst] = c->gr[i * c->m + y];
           ++sp.nst;
@@ -283,15 +301,14 @@ void rk_lambda(ftcc_ctx* c, std::vector<int>& status) {
         sp.out = I.lam[p * c->m + x];
         return sp;
       });
-      rk_combine(c, 7, p, x, 0.0, false, [c, p, x](int i) {   // cotangent of S at the stage: -kbar
+      rk_combine(c, 9, p, x, 0.0, false, [c, p, x](int i) {   // cotangent of S at the stage: -kbar
         RKSpec sp;
         sp.base = c->inst[i].lam[p * c->m + x];
         sp.x0 = -1.0;
-        sp.out = c->cot[i * c->m + x];
+        sp.out = c->s_cot[i];
         return sp;
       });
-      set_ebar(c, x, x == 0 ? p : -1);
-      backward_one(c, x);
+      backward_one(c, x, x == 0 ? p : -1, x == m - 1);   // the other stages' S: rk_recompute_stages
     }
     rk_combine(c, 3, p, 0, +1.0, false, [c, p](int i) {
       RKSpec sp;

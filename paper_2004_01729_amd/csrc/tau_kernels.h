@@ -80,11 +80,14 @@ struct RKProblem {
   const double* Y[kMaxStages];
   const double* S[kMaxStages];
   double sigma;
+  const double* h_x0;            // optional device factor of x0, of every coef
+  const double* h_coef;
   double* out;
   unsigned long long* maxbits;
   const int* active;             // instance runs (nullptr: always)
 };
-// blocks: 1024 elements each, per problem
+constexpr int kRKBlock = 256;   // elements per block
+// blocks: kRKBlock elements each, per problem
 void launch_rk_combine(const RKProblem* d_probs, const int* d_prefix, int n_prob, int total_blocks, hipStream_t s);
 
 // Implicit integral form generated by Simpson's rule (Section III): sums of
@@ -136,6 +139,8 @@ struct StateCopy {
   const unsigned* a;
   const unsigned* b;
   long na, nb, second;
+  const int* active;   // optional run flag (0: skip)
+  int add;             // dst += src
 };
 constexpr long kStateCopyBlock = 1024;   // elements per block
 void launch_state_copies(const StateCopy* d_copies, const int* d_prefix, int n, int blocks, hipStream_t s);
