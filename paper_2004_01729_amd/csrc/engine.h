@@ -353,10 +353,17 @@ class Executor {
                         const std::string& tag, int t_out, int t_a, int t_b);
   // edge > 0: the tuples of a block ordered for the two tensors' contiguous letters
   // (patches of edge x edge where they differ), else lexicographically
-  // edge > 0: the tuples of a block ordered for the two tensors' contiguous letters
-  // (patches of edge x edge where they differ), else lexicographically
   const GroupTable& group_table(int inst, long n, const std::string& letters, const std::string& xi, bool xp,
                                 const std::string& yi, bool yp, const std::vector<int>& signs, int edge = 0);
+  // allowed tuples (one byte per letter), and element offsets of such a list in one tensor
+  std::map<std::string, std::vector<unsigned>> tuple_cache_;
+  std::map<std::string, const unsigned*> list_cache_;
+  const unsigned* zero_offset_ = nullptr;
+  const std::vector<unsigned>& allowed_tuples(int inst, long n, const std::vector<int>& signs);
+  const unsigned* offset_list(int inst, long n, const std::string& letters, const std::vector<int>& signs,
+                              const std::string& xi, bool xp);
+  const unsigned* zero_offset();
+  bool flat_lists(int rank) const;
   std::vector<char> packed_;               // per tensor: stored packed (n^(rank-1) doubles)
   bool pack_on_ = false;                   // packing applies to this executor's problems
   bool one_per_label_ = false;             // every orbital of every instance has its own label

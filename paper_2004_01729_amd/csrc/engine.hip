@@ -944,6 +944,113 @@ const Executor::GroupTable& Executor::group_table(int inst, long n, const std::s
   return group_cache_.emplace(key, std::move(T)).first->second;
 }
 
+// Every orbital with a label of its own: the tuples (one byte per index) with
+// sum_l signs[l] k(index_l) = 0, lexicographically; the last index follows from the
+// others.  At most four letters.
+const std::vector<unsigned>& Executor::allowed_tuples(int inst, long n, const std::vector<int>& signs) {
+  inst = same_labels_[inst];
+  std::string key = std::to_string(inst) + "|";
+  for (int v : signs) key += v == signs[0] ? '+' : '-';   // a common sign does not matter
+  auto it = tuple_cache_.find(key);
+  if (it != tuple_cache_.end()) return it->second;
+  const InstMomentum& M = *mom_[inst];
+  const int g = (int)signs.size(), D = M.dims;
+  auto reduced = [&](int v, int c) { return M.modulus[c] > 0 ? ((v % M.modulus[c]) + M.modulus[c]) % M.modulus[c] : v; };
+  // orbital of a label, over the box that the labels span
+  std::vector<int> lo(D), len(D);
+  std::vector<int> lab((size_t)n * D);
+  for (long p = 0; p < n; ++p)
+    for (int c = 0; c < D; ++c) lab[p * D + c] = reduced(M.labels[p * D + c], c);
+  long box = 1;
+  for (int c = 0; c < D; ++c) {
+    int mn = lab[c], mx = lab[c];
+    for (long p = 1; p < n; ++p) {
+      mn = std::min(mn, lab[p * D + c]);
+      mx = std::max(mx, lab[p * D + c]);
+    }
+    lo[c] = mn;
+    len[c] = mx - mn + 1;
+    box *= len[c];
+  }
+  // wide label ranges (any integers are allowed) are looked up in a map instead
+  const bool dense = box <= (1L << 22);
+  std::vector<int> at(dense ? box : 0, -1);
+  std::unordered_map<long, int> far;
+  auto slot = [&](const int* v) -> long {
+    long o = 0;
+    for (int c = 0; c < D; ++c) {
+      if (v[c] < lo[c] || v[c] >= lo[c] + len[c]) return -1;
+      o = o * len[c] + (v[c] - lo[c]);
+    }
+    return o;
+  };
+  for (long p = 0; p < n; ++p) {
+    const long o = slot(&lab[p * D]);
+    if (dense) at[o] = (int)p; else far[o] = (int)p;
+  }
+  std::vector<unsigned> out;
+  std::vector<int> idx(g, 0), v(D);
+  const long count = ipow(n, g - 1);
+  for (long t = 0; t < count; ++t) {
+    unsigned packed = 0;
+    std::fill(v.begin(), v.end(), 0);
+    for (int l = 0; l + 1 < g; ++l) {
+      packed |= (unsigned)idx[l] << (8 * l);
+      for (int c = 0; c < D; ++c) v[c] += signs[l] * M.labels[(size_t)idx[l] * D + c];
+    }
+    for (int c = 0; c < D; ++c) v[c] = reduced(-signs[g - 1] * v[c], c);
+    const long o = slot(v.data());
+    int last = -1;
+    if (o >= 0) {
+      if (dense) {
+        last = at[o];
+      } else {
+        auto f = far.find(o);
+        if (f != far.end()) last = f->second;
+      }
+    }
+    if (last >= 0) out.push_back(packed | (unsigned)last << (8 * (g - 1)));
+    for (int l = g - 2; l >= 0; --l) {
+      if (++idx[l] < n) break;
+      idx[l] = 0;
+    }
+  }
+  return tuple_cache_.emplace(key, std::move(out)).first->second;
+}
+
+// Element offsets, in a tensor indexed by xi, of the allowed tuples of `letters`.
+const unsigned* Executor::offset_list(int inst, long n, const std::string& letters, const std::vector<int>& signs,
+                                      const std::string& xi, bool xp) {
+  inst = same_labels_[inst];
+  const int g = (int)letters.size();
+  std::string key = std::to_string(inst) + "|";
+  for (int v : signs) key += v == signs[0] ? '+' : '-';
+  unsigned long stride[4] = {0, 0, 0, 0};
+  for (int l = 0; l < g; ++l) {
+    const int pos = (int)xi.find(letters[l]);
+    key += (char)('0' + pos);
+    stride[l] = !xp ? (unsigned long)ipow(n, g - 1 - pos) : pos == g - 1 ? 0ul : (unsigned long)ipow(n, g - 2 - pos);
+  }
+  if (xp) key += '#';
+  auto it = list_cache_.find(key);
+  if (it != list_cache_.end()) return it->second;
+  const std::vector<unsigned>& T = allowed_tuples(inst, n, signs);
+  std::vector<unsigned> off(T.size());
+  for (size_t t = 0; t < T.size(); ++t) {
+    unsigned long o = 0;
+    for (int l = 0; l < g; ++l) o += ((T[t] >> (8 * l)) & 255u) * stride[l];
+    off[t] = (unsigned)o;
+  }
+  const unsigned* d = (const unsigned*)upload(off.data(), sizeof(unsigned) * off.size());
+  return list_cache_.emplace(key, d).first->second;
+}
+
+const unsigned* Executor::zero_offset() {
+  const unsigned z = 0;
+  if (!zero_offset_) zero_offset_ = (const unsigned*)upload(&z, sizeof z);
+  return zero_offset_;
+}
+
 // Tile shape of one block of a blocked contraction (ml rows, nl columns, kl inner):
 // 0 (16 x 16 MFMA tiles) or a lane-mapped shape code, whichever needs fewer wave
 // latencies by a simple count: a wave costs 3 dependent memory latencies (task,
@@ -1228,6 +1335,11 @@ bool Executor::elem_blocked(std::vector<Launch>& dst, const PerProb& X, const st
   return sum_blocked(dst, terms, Y, yi, beta, t_y, tag, yp);
 }
 
+// Elementwise launches address their elements through one list per tensor where every
+// orbital has its own label: the pairs of index groups would be a task of a few elements
+// each, and finding an element's task took longer than its value.
+bool Executor::flat_lists(int rank) const { return one_per_label_ && rank >= 2 && rank <= 4; }
+
 // Y[yi] = beta Y + sum_s alpha_s X_s[xi_s] over the allowed elements of Y (its law known):
 // Y's letters split into two halves whose momentum blocks q and -q pair up.
 // Returns false (dense lowering) when a law is unknown.
@@ -1251,16 +1363,20 @@ bool Executor::sum_blocked(std::vector<Launch>& dst, const std::vector<SumTerm>&
   const int np = (int)probs_.size();
   Launch L;
   double elements = 0.0;
+  const bool flat = flat_lists((int)yi.size());
   for (int p = 0; p < np; ++p) {
     const int inst = probs_[p].inst;
     const long n = probs_[p].n;
     if (ipow(n, (int)yi.size()) >= (1L << 32)) throw std::runtime_error("tensor exceeds 2^32 elements: " + tag);
-    const GroupTable& T1 = group_table(inst, n, G1, yi, ypk, yi, ypk, s1);
-    const GroupTable& T2 = group_table(inst, n, G2, yi, ypk, yi, ypk, s2);
     ElemProblem P;
     P.Y = Y[p];
-    P.oy1 = (const unsigned*)T1.off2;
-    P.oy2 = (const unsigned*)T2.off2;
+    if (flat) {
+      P.oy1 = zero_offset();
+      P.oy2 = offset_list(inst, n, yi, ly, yi, ypk);
+    } else {
+      P.oy1 = (const unsigned*)group_table(inst, n, G1, yi, ypk, yi, ypk, s1).off2;
+      P.oy2 = (const unsigned*)group_table(inst, n, G2, yi, ypk, yi, ypk, s2).off2;
+    }
     P.beta = beta;
     P.active = gate_for(dst, p);
     P.src = (int)L.esrcs.size();
@@ -1273,7 +1389,10 @@ bool Executor::sum_blocked(std::vector<Launch>& dst, const std::vector<SumTerm>&
       ElemSource q;
       q.X = s.X[p];
       q.ox1 = q.ox2 = nullptr;
-      if (s.xi != yi || xpk != ypk) {   // the same tuples in the same order, X's offsets
+      if (flat && (s.xi != yi || xpk != ypk)) {
+        q.ox1 = zero_offset();
+        q.ox2 = offset_list(inst, n, yi, ly, s.xi, xpk);
+      } else if (s.xi != yi || xpk != ypk) {   // the same tuples in the same order, X's offsets
         q.ox1 = (const unsigned*)group_table(inst, n, G1, s.xi, xpk, yi, ypk, s1).off1;
         q.ox2 = (const unsigned*)group_table(inst, n, G2, s.xi, xpk, yi, ypk, s2).off1;
       }
@@ -1283,6 +1402,16 @@ bool Executor::sum_blocked(std::vector<Launch>& dst, const std::vector<SumTerm>&
       add_range(L.rd, q.X, sizeof(double) * (size_t)ipow_l(n, (int)yi.size() - (xpk ? 1 : 0)));
       if (q.scale) add_range(L.rd, q.scale, sizeof(double));
     }
+    L.eprobs.push_back(P);
+    if (flat) {
+      const int count = (int)allowed_tuples(inst, n, ly).size();
+      if (count) L.etasks.push_back(ElemTask{L.n_elem, p, 0, 1, 0, count});
+      L.n_elem += count;
+      elements += (double)count;
+      continue;
+    }
+    const GroupTable& T1 = group_table(inst, n, G1, yi, ypk, yi, ypk, s1);
+    const GroupTable& T2 = group_table(inst, n, G2, yi, ypk, yi, ypk, s2);
     const InstMomentum& Mm = *mom_[inst];
     for (const auto& blk : T1.blocks) {
       std::vector<int> q(Mm.dims);
@@ -1297,7 +1426,6 @@ bool Executor::sum_blocked(std::vector<Launch>& dst, const std::vector<SumTerm>&
       L.n_elem += (long long)blk.second.second * b2->second.second;
       elements += (double)blk.second.second * b2->second.second;
     }
-    L.eprobs.push_back(P);
   }
   L.ranged = true;
   L.kind = Launch::ELEM;
@@ -1345,28 +1473,40 @@ bool Executor::dot_blocked(std::vector<Launch>& dst, const PerProb& A, const std
   const std::vector<int> s1(la.begin(), la.begin() + G1.size()), s2(la.begin() + G1.size(), la.end());
   const int np = (int)probs_.size();
   std::vector<DotbProblem> ps(np);
+  const bool flat = flat_lists((int)ai.size());
   std::vector<ElemTask> tasks;
   long long total = 0;
   for (int p = 0; p < np; ++p) {
     const int inst = probs_[p].inst;
     const long n = probs_[p].n;
     if (ipow(n, (int)ai.size()) >= (1L << 32)) throw std::runtime_error("tensor exceeds 2^32 elements: " + tag);
-    // A's allowed elements: index groups G1 of momentum q with G2 of momentum -q
-    const GroupTable& T1 = group_table(inst, n, G1, ai, is_packed(t_a), bi, is_packed(t_b), s1);
-    const GroupTable& T2 = group_table(inst, n, G2, ai, is_packed(t_a), bi, is_packed(t_b), s2);
     DotbProblem& P = ps[p];
     P.X = A[p];
     P.Y = B[p];
-    P.ox1 = (const unsigned*)T1.off1;
-    P.oy1 = (const unsigned*)T1.off2;
-    P.ox2 = (const unsigned*)T2.off1;
-    P.oy2 = (const unsigned*)T2.off2;
     P.out = out[p];
     P.alpha = alpha;
     P.beta = beta;
     P.active = gate_for(dst, p);
     total = (total + 255) / 256 * 256;     // every problem starts on a block boundary
     const long long start = total;
+    P.first_block = (int)(start / 256);
+    if (flat) {
+      const int count = (int)allowed_tuples(inst, n, la).size();
+      P.ox1 = P.oy1 = zero_offset();
+      P.ox2 = offset_list(inst, n, ai, la, ai, is_packed(t_a));
+      P.oy2 = offset_list(inst, n, ai, la, bi, is_packed(t_b));
+      if (count) tasks.push_back(ElemTask{total, p, 0, 1, 0, count});
+      total += count;
+      P.n_blocks = (count + 255) / 256;
+      continue;
+    }
+    // A's allowed elements: index groups G1 of momentum q with G2 of momentum -q
+    const GroupTable& T1 = group_table(inst, n, G1, ai, is_packed(t_a), bi, is_packed(t_b), s1);
+    const GroupTable& T2 = group_table(inst, n, G2, ai, is_packed(t_a), bi, is_packed(t_b), s2);
+    P.ox1 = (const unsigned*)T1.off1;
+    P.oy1 = (const unsigned*)T1.off2;
+    P.ox2 = (const unsigned*)T2.off1;
+    P.oy2 = (const unsigned*)T2.off2;
     const InstMomentum& Mm = *mom_[inst];
     for (const auto& blk : T1.blocks) {
       std::vector<int> q(Mm.dims);
@@ -1379,7 +1519,6 @@ bool Executor::dot_blocked(std::vector<Launch>& dst, const PerProb& A, const std
       tasks.push_back(ElemTask{total, p, blk.second.first, blk.second.second, b2->second.first, b2->second.second});
       total += (long long)blk.second.second * b2->second.second;
     }
-    P.first_block = (int)(start / 256);
     P.n_blocks = (int)((total - start + 255) / 256);
   }
   if ((total + 255) / 256 > (long long)scratch_->tail_ws_doubles) return false;

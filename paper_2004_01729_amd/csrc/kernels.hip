@@ -838,8 +838,10 @@ __global__ void __launch_bounds__(256) elem_kernel(const ElemProblem* __restrict
   const long long e = (long long)blockIdx.x * 256 + threadIdx.x;
   if (e >= total) return;
   int lo = bfirst[blockIdx.x], hi = bfirst[blockIdx.x + 1];
-  const ElemProblem& P = probs[tasks[lo].prob];
+  const int prob = tasks[lo].prob;
+  const ElemProblem& P = probs[prob];
   if (P.active && *gview(P.active) == 0) return;
+  if (lo < hi && tasks[lo + 1].prob != prob) hi = lo;   // the rest of the block is padding
   while (lo < hi) {
     const int mid = (lo + hi + 1) >> 1;
     if (tasks[mid].first <= e) lo = mid; else hi = mid - 1;
@@ -981,7 +983,8 @@ __global__ void __launch_bounds__(256) dotb_partial_kernel(const DotbProblem* __
   const long long e = (long long)blockIdx.x * 256 + threadIdx.x;
   double v = 0.0;
   if (e < total) {
-    int lo = gview(bfirst)[blockIdx.x], hi = gview(bfirst)[blockIdx.x + 1];
+    int lo = bfirst[blockIdx.x], hi = bfirst[blockIdx.x + 1];
+    if (lo < hi && tasks[lo + 1].prob != tasks[lo].prob) hi = lo;   // the rest of the block is padding
     while (lo < hi) {
       const int mid = (lo + hi + 1) >> 1;
       if (tasks[mid].first <= e) lo = mid; else hi = mid - 1;
