@@ -367,6 +367,106 @@ __global__ void __launch_bounds__(256) gemm_tail_reduce_kernel(const GemmProblem
   }
 }
 
+// One wave's tile of H x H MFMA tiles (16 x 16 each).  What a task waits for is its
+// chain of dependent loads, so all of its offsets are loaded at once: each lane holds
+// those of one row, one column and one inner index (two loads give 64 inner indices,
+// handed to the lanes that need them through the LDS crossbar), the output's with them,
+// and all gathers of up to 4 G inner indices are in flight together.  G: groups of 4
+// inner indices; a step has no more groups than the range needs (rounded up to a power
+// of two).  Lanes past an edge read the last row, column or inner index (in bounds),
+// and their products are zeroed.
+template <int H, int G>
+__device__ __forceinline__ void wave_tile(const SgemmProblem& P, const SgemmTask& T, double* ws, int lane) {
+  const gptr<const double> __restrict__ A = gview(P.A);
+  const gptr<const double> __restrict__ B = gview(P.B);
+  const gptr<const unsigned> __restrict__ offAK = gview(P.offAK) + T.kb;
+  const gptr<const unsigned> __restrict__ offBK = gview(P.offBK) + T.kb;
+  const int r = lane & 15, q = lane >> 4;
+  const int klen = T.klen;
+  unsigned ka = offAK[max(min(lane, klen - 1), 0)], kb = offBK[max(min(lane, klen - 1), 0)];
+  unsigned am[H], bn[H];
+  size_t cn[H], cm[4 * H];
+  bool rok[H], cok[H];
+#pragma unroll
+  for (int h = 0; h < H; ++h) {
+    rok[h] = 16 * h + r < T.mlen;
+    cok[h] = 16 * h + r < T.nlen;
+    am[h] = gview(P.offAM)[T.mb + min(16 * h + r, T.mlen - 1)];
+    bn[h] = gview(P.offBN)[T.nb + min(16 * h + r, T.nlen - 1)];
+    cn[h] = gview(P.offCN)[T.nb + min(16 * h + r, T.nlen - 1)];
+  }
+#pragma unroll
+  for (int i = 0; i < 4 * H; ++i) cm[i] = gview(P.offCM)[T.mb + min(4 * i + q, T.mlen - 1)];
+  double4_t acc[H][H];
+#pragma unroll
+  for (int h = 0; h < H * H; ++h) acc[h / H][h % H] = (double4_t){0.0, 0.0, 0.0, 0.0};
+  // inner indices j .. j + 4 N - 1 of the 64 whose offsets the lanes hold (from `base`)
+  auto step = [&](auto n_c, int base, int j) {
+    constexpr int N = decltype(n_c)::value;
+    double a[H][N], b[H][N];
+#pragma unroll
+    for (int u = 0; u < N; ++u) {
+      const int src = 4 * (j + 4 * u + q);
+      const unsigned ak = (unsigned)__builtin_amdgcn_ds_bpermute(src, (int)ka);
+      const unsigned bk = (unsigned)__builtin_amdgcn_ds_bpermute(src, (int)kb);
+#pragma unroll
+      for (int h = 0; h < H; ++h) {
+        a[h][u] = A[am[h] + ak];   // A fragment: row r, inner q
+        b[h][u] = B[bk + bn[h]];   // B fragment: inner q, column r
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < N; ++u) {
+      const bool ok = base + j + 4 * u + q < klen;
+#pragma unroll
+      for (int h = 0; h < H; ++h) {
+        a[h][u] = (ok && rok[h]) ? a[h][u] : 0.0;
+        b[h][u] = (ok && cok[h]) ? b[h][u] : 0.0;
+      }
+#pragma unroll
+      for (int h = 0; h < H * H; ++h)
+        acc[h / H][h % H] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[h / H][u], b[h % H][u], acc[h / H][h % H], 0, 0, 0);
+    }
+  };
+  for (int base = 0; base < klen; base += 64) {
+    if (base) {
+      ka = offAK[min(base + lane, klen - 1)];
+      kb = offBK[min(base + lane, klen - 1)];
+    }
+    const int len = min(64, klen - base);
+    int j = 0;
+    for (; len - j > 2 * G; j += 4 * G) step(std::integral_constant<int, G>{}, base, j);
+    if (G > 8 && len - j > 16) {
+      step(std::integral_constant<int, 8>{}, base, j);
+      j += 32;
+    }
+    if (G > 4 && len - j > 8) {
+      step(std::integral_constant<int, 4>{}, base, j);
+      j += 16;
+    }
+    if (len - j > 4) step(std::integral_constant<int, 2>{}, base, j);
+    else if (len - j > 0) step(std::integral_constant<int, 1>{}, base, j);
+  }
+  if (H == 1 && T.part >= 0) {   // one chunk of a split inner range: the whole tile, row-major
+    const gptr<double> w = gview(ws) + (size_t)T.part * 256;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) w[i * 64 + lane] = acc[0][0][i];   // (4 i + q) * 16 + r
+    return;
+  }
+  const gptr<double> C = gview(P.C);
+  double cv[4 * H * H];
+#pragma unroll
+  for (int i = 0; i < 4 * H * H; ++i) cv[i] = 0.0;
+  if (P.beta != 0.0) {
+#pragma unroll
+    for (int i = 0; i < 4 * H * H; ++i) cv[i] = C[cm[i / H] + cn[i % H]];
+  }
+#pragma unroll
+  for (int i = 0; i < 4 * H * H; ++i)
+    if (4 * (i / H) + q < T.mlen && cok[i % H])
+      C[cm[i / H] + cn[i % H]] = P.alpha * acc[i / (4 * H)][i % H][(i / H) & 3] + P.beta * cv[i];
+}
+
 // Momentum-blocked tiles: one wave per 16 x 16 output tile, or per chunk of a
 // long inner range (its partial tile then goes to the workspace and
 // sgemm_reduce_kernel adds the chunks); operands are gathered through the
@@ -393,72 +493,7 @@ __global__ void __launch_bounds__(256, WIDE ? 4 : 1) sgemm_kernel(const SgemmPro
     // 2 x 2 MFMA tiles: each gathered element feeds two products.  The gathers of
     // scattered elements are what a launch of large blocks waits for (one 64-byte
     // sector each through the vector cache), so halving them outweighs the fewer waves.
-    const int r = lane & 15, q = lane >> 4;
-    unsigned am[2], bn[2];
-    bool rok[2], cok[2];
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      rok[h] = 16 * h + r < T.mlen;
-      cok[h] = 16 * h + r < T.nlen;
-      am[h] = gview(P.offAM)[T.mb + (rok[h] ? 16 * h + r : 0)];
-      bn[h] = gview(P.offBN)[T.nb + (cok[h] ? 16 * h + r : 0)];
-    }
-    double4_t acc[2][2];
-#pragma unroll
-    for (int h = 0; h < 4; ++h) acc[h >> 1][h & 1] = (double4_t){0.0, 0.0, 0.0, 0.0};
-    auto step = [&](auto g_c, int k0) {
-      constexpr int G = decltype(g_c)::value;
-      unsigned ak[G], bk[G];
-      double a[2][G], b[2][G];
-#pragma unroll
-      for (int u = 0; u < G; ++u) {
-        const int k = k0 + 4 * u + q;
-        const int kk = k < T.klen ? k : 0;
-        ak[u] = offAK[kk];
-        bk[u] = offBK[kk];
-      }
-#pragma unroll
-      for (int u = 0; u < G; ++u)
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-          a[h][u] = A[am[h] + ak[u]];
-          b[h][u] = B[bk[u] + bn[h]];
-        }
-#pragma unroll
-      for (int u = 0; u < G; ++u) {
-        const bool ok = k0 + 4 * u + q < T.klen;
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-          a[h][u] = (ok && rok[h]) ? a[h][u] : 0.0;
-          b[h][u] = (ok && cok[h]) ? b[h][u] : 0.0;
-        }
-#pragma unroll
-        for (int h = 0; h < 4; ++h)
-          acc[h >> 1][h & 1] =
-              __builtin_amdgcn_mfma_f64_16x16x4f64(a[h >> 1][u], b[h & 1][u], acc[h >> 1][h & 1], 0, 0, 0);
-      }
-    };
-    int k0 = 0;
-    for (; T.klen - k0 > 8; k0 += 16) step(std::integral_constant<int, 4>{}, k0);
-    if (T.klen - k0 > 4) step(std::integral_constant<int, 2>{}, k0);
-    else if (T.klen - k0 > 0) step(std::integral_constant<int, 1>{}, k0);
-    const gptr<double> C = gview(P.C);
-    size_t cn[2], cm[8];
-#pragma unroll
-    for (int h = 0; h < 2; ++h) cn[h] = gview(P.offCN)[T.nb + min(16 * h + r, T.nlen - 1)];
-#pragma unroll
-    for (int i = 0; i < 8; ++i) cm[i] = gview(P.offCM)[T.mb + min(4 * i + q, T.mlen - 1)];
-    double cv[16];
-#pragma unroll
-    for (int i = 0; i < 16; ++i) cv[i] = 0.0;
-    if (P.beta != 0.0) {
-#pragma unroll
-      for (int i = 0; i < 16; ++i) cv[i] = C[cm[i >> 1] + cn[i & 1]];
-    }
-#pragma unroll
-    for (int i = 0; i < 16; ++i)
-      if (4 * (i >> 1) + q < T.mlen && 16 * (i & 1) + r < T.nlen)
-        C[cm[i >> 1] + cn[i & 1]] = P.alpha * acc[i >> 3][i & 1][(i >> 1) & 3] + P.beta * cv[i];
+    wave_tile<2, 4>(P, T, ws, lane);
     return;
   }
   if (T.shape) {
@@ -518,67 +553,7 @@ __global__ void __launch_bounds__(256, WIDE ? 4 : 1) sgemm_kernel(const SgemmPro
     }
     return;
   }
-  const int r = lane & 15, q = lane >> 4;
-  const bool row_ok = r < T.mlen, col_ok = r < T.nlen;
-  const unsigned am = row_ok ? gview(P.offAM)[T.mb + r] : 0u;
-  const unsigned bn = col_ok ? gview(P.offBN)[T.nb + r] : 0u;
-  double4_t acc = (double4_t){0.0, 0.0, 0.0, 0.0};
-  // G groups of 4 inner indices per step: the offset loads of all groups are
-  // issued together, then all operand gathers, then the MFMAs, so one step
-  // waits for two memory latencies instead of two per group.  Loads past the
-  // end of the range read the range's first entry (in bounds) and are zeroed;
-  // a step has no more groups than the range needs (rounded up to 1, 2, 4 or 8:
-  // most blocks of a plane-wave gas have an inner range of 4 to 16, and the
-  // scattered gathers are what the kernel waits for).
-  auto step = [&](auto g_c, int k0) {
-    constexpr int G = decltype(g_c)::value;
-    unsigned ak[G], bk[G];
-    double a[G], b[G];
-#pragma unroll
-    for (int u = 0; u < G; ++u) {
-      const int k = k0 + 4 * u + q;
-      const int kk = k < T.klen ? k : 0;
-      ak[u] = offAK[kk];
-      bk[u] = offBK[kk];
-    }
-#pragma unroll
-    for (int u = 0; u < G; ++u) {
-      const bool ok = k0 + 4 * u + q < T.klen;
-      const double va = A[am + ak[u]];     // A fragment: row r, inner q
-      const double vb = B[bk[u] + bn];     // B fragment: inner q, column r
-      a[u] = (ok && row_ok) ? va : 0.0;
-      b[u] = (ok && col_ok) ? vb : 0.0;
-    }
-#pragma unroll
-    for (int u = 0; u < G; ++u) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a[u], b[u], acc, 0, 0, 0);
-  };
-  int k0 = 0;
-  for (; T.klen - k0 > 16; k0 += 32) step(std::integral_constant<int, 8>{}, k0);
-  if (T.klen - k0 > 8) step(std::integral_constant<int, 4>{}, k0);
-  else if (T.klen - k0 > 4) step(std::integral_constant<int, 2>{}, k0);
-  else if (T.klen - k0 > 0) step(std::integral_constant<int, 1>{}, k0);
-  if (T.part >= 0) {   // one chunk of a split inner range: the whole tile, row-major
-    const gptr<double> w = gview(ws) + (size_t)T.part * 256;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) w[i * 64 + lane] = acc[i];   // (4 i + q) * 16 + r
-    return;
-  }
-  // the offsets of the lane's four elements (clamped into the tile), then the
-  // target loads together, then the stores: one memory latency per stage
-  // instead of a chain per element
-  const size_t cn = gview(P.offCN)[T.nb + max(min(r, T.nlen - 1), 0)];
-  size_t cm[4];
-#pragma unroll
-  for (int i = 0; i < 4; ++i) cm[i] = gview(P.offCM)[T.mb + max(min(4 * i + q, T.mlen - 1), 0)];
-  const gptr<double> C = gview(P.C);
-  double cv[4] = {0.0, 0.0, 0.0, 0.0};
-  if (P.beta != 0.0) {
-#pragma unroll
-    for (int i = 0; i < 4; ++i) cv[i] = C[cm[i] + cn];
-  }
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-    if (4 * i + q < T.mlen && r < T.nlen) C[cm[i] + cn] = P.alpha * acc[i] + P.beta * cv[i];
+  wave_tile<1, 8>(P, T, ws, lane);
 }
 
 // Large blocks: one 256-thread block per tile of 4096 outputs (64 x 64, 128 x 32 or
