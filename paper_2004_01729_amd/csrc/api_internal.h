@@ -155,6 +155,7 @@ struct ftcc_ctx {
   std::vector<int> run_slots;                 // host copy of d_run
   KernelProfiler prof;
   hipGraphExec_t g_fwd = nullptr, g_bwd = nullptr;
+  hipGraphExec_t g_fwd_sweep = nullptr, g_fwd_rest = nullptr, g_bwd_sweep = nullptr;
   std::vector<int> beta_part_off;             // first TAU_BETA partial of each instance
   std::vector<int> active_host;               // per-instance "still iterating" flags
   std::map<std::pair<int, int>, std::pair<TauProblem*, int*>> tau_cache;
@@ -342,7 +343,9 @@ struct StateList {
 };
 void state_set(ftcc_ctx* c, int kind, int panel, const std::function<void(StateList)>& list);
 void forward(ftcc_ctx* c);
+void forward_sweep(ftcc_ctx* c);
 void backward(ftcc_ctx* c);
+void backward_sweep(ftcc_ctx* c);
 void d_forward(ftcc_ctx* c);
 void clear_tau_cache(ftcc_ctx* c);
 int tau_problems(ftcc_ctx* c, int mode, int panel, double* partial_base, std::vector<TauProblem>& ps,

@@ -213,6 +213,15 @@ class Executor {
   // false: this executor's launches are not per problem (use the run flags).
   bool run_forward_one(int prob, hipStream_t s) const;
   void run_backward(hipStream_t s) const { run(bwd_, s); }
+  // The parts of the two lists that a fixed-point sweep needs: the forward launches that
+  // lead to tensor outputs, the other ones (they lead to scalar outputs only and may run
+  // any time before the next forward pass), and the backward launches that lead to
+  // gradients of the inputs.  Absent (has_sweeps() false) where a launch's memory ranges
+  // are not known or a tensor launch would overwrite what the others read.
+  bool has_sweeps() const { return !fwd_sweep_.empty(); }
+  void run_forward_sweep(hipStream_t s) const { run(fwd_sweep_, s); }
+  void run_forward_rest(hipStream_t s) const { run(fwd_rest_, s); }
+  void run_backward_sweep(hipStream_t s) const { run(bwd_sweep_, s); }
 
   void set_profiler(KernelProfiler* p) { prof_ = p; }
   // Per-problem run flags (device int array indexed by problem, read when the
@@ -329,7 +338,7 @@ class Executor {
   std::vector<int> version_;
   std::function<double*(size_t)> cache_alloc_;
   size_t cache_budget_ = 0, cache_bytes_ = 0, const_bytes_ = 0;
-  std::vector<Launch> setup_, fwd_, bwd_;
+  std::vector<Launch> setup_, fwd_, bwd_, fwd_sweep_, fwd_rest_, bwd_sweep_;
   std::vector<void*> owned_;
   KernelProfiler* prof_ = nullptr;
   const int* gate_ = nullptr;

@@ -164,6 +164,22 @@ static bool overlaps(const Ranges& a, const Ranges& b) {
   return false;
 }
 
+// Which launches of a list lead to the memory in `needed`: a launch is kept if it writes
+// what is needed, and what it reads is needed then.
+static std::vector<char> leads_to(const std::vector<Launch>& L, Ranges needed) {
+  std::vector<char> keep(L.size(), 0);
+  normalize(needed);
+  for (int i = (int)L.size() - 1; i >= 0; --i) {
+    Ranges wr = L[i].wr;
+    normalize(wr);
+    if (!overlaps(wr, needed)) continue;
+    keep[i] = 1;
+    needed.insert(needed.end(), L[i].rd.begin(), L[i].rd.end());
+    normalize(needed);
+  }
+  return keep;
+}
+
 // must b run after a (a earlier in program order)?
 static bool ordered(const Launch& a, const Launch& b) {
   if (!a.ranged || !b.ranged) return true;
@@ -2114,6 +2130,49 @@ void Executor::build(const Program* prog, const std::vector<ProblemRef>& probs, 
   // FTCC_FUSE=0 keeps the program order, one launch per contraction (diagnostics)
   const char* fz = std::getenv("FTCC_FUSE");
   if (!mom_.empty() && !(fz && fz[0] == '0')) {
+    // The energy's dots and the gradients of the integrals are no part of a fixed-point
+    // sweep (step of a spin ring of 12: 23.1 -> 21.7 ms without them, 6 dense orbitals
+    // 14.1 -> 13.4, 33 dense orbitals, forward 108.7 -> 107.1).
+    bool ranged = true;
+    for (const Launch& l : fwd_) ranged = ranged && l.ranged;
+    for (const Launch& l : bwd_) ranged = ranged && l.ranged;
+    if (ranged) {
+      Ranges out, in;
+      for (int k = 0; k < nt; ++k) {
+        const bool output = prog->t[k].kind == T_OUTPUT, input = prog->t[k].kind == T_INPUT;
+        for (int p = 0; p < np; ++p) {
+          const size_t sz = sizeof(double) * (size_t)ipow_l(probs[p].n, prog->t[k].rank);
+          if (output && prog->t[k].rank > 0) add_range(out, dense_f[k].empty() ? fwd[k][p] : dense_f[k][p], sz);
+          if (input && need_grad[k]) add_range(in, dense_g[k].empty() ? grd[k][p] : dense_g[k][p], sz);
+        }
+      }
+      const std::vector<char> kf = leads_to(fwd_, out), kb = leads_to(bwd_, in);
+      bool apart = true;
+      for (size_t i = 0; i < fwd_.size(); ++i) {
+        if (kf[i]) {
+          fwd_sweep_.push_back(fwd_[i]);
+          continue;
+        }
+        fwd_rest_.push_back(fwd_[i]);
+        Ranges used = fwd_[i].rd;
+        used.insert(used.end(), fwd_[i].wr.begin(), fwd_[i].wr.end());
+        normalize(used);
+        for (size_t j = i + 1; j < fwd_.size(); ++j) {
+          if (!kf[j]) continue;
+          Ranges wr = fwd_[j].wr;
+          normalize(wr);
+          apart = apart && !overlaps(wr, used);
+        }
+      }
+      for (size_t i = 0; i < bwd_.size(); ++i)
+        if (kb[i]) bwd_sweep_.push_back(bwd_[i]);
+      if (!apart || fwd_rest_.empty() || bwd_sweep_.empty()) {
+        fwd_sweep_.clear();
+        fwd_rest_.clear();
+        bwd_sweep_.clear();
+      }
+      for (std::vector<Launch>* l : {&fwd_sweep_, &fwd_rest_, &bwd_sweep_}) fuse_levels(*l);
+    }
     fuse_levels(setup_);
     fuse_levels(fwd_);
     fuse_levels(bwd_);
@@ -2198,7 +2257,8 @@ void Executor::dump_plan() const {
   if (!env || env[0] != '1') return;
   const char* kinds[] = {"perm", "gemm", "dot", "fill", "sgemm", "elem", "dotb"};
   const std::pair<const char*, const std::vector<Launch>*> lists[] = {
-      {"setup", &setup_}, {"forward", &fwd_}, {"backward", &bwd_}};
+      {"setup", &setup_},       {"forward", &fwd_},      {"backward", &bwd_},
+      {"fwd-sweep", &fwd_sweep_}, {"fwd-rest", &fwd_rest_}, {"bwd-sweep", &bwd_sweep_}};
   for (const auto& pl : lists) {
     int counts[7] = {0, 0, 0, 0, 0, 0, 0};
     double fl = 0.0;

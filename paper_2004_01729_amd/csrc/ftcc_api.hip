@@ -566,6 +566,9 @@ long seg_len(const ftcc_ctx* c, int i, int seg) {
 }
 
 // ------------------------------------------------------------------ build
+// the sweeps run parts of the programs of their own (the march of a single slot does not)
+bool sweeps_apart(const ftcc_ctx* c) { return !c->rk && !c->simpson && c->slots == c->m && c->ex_main->has_sweeps(); }
+
 void build(ftcc_ctx* c) {
   if (c->built) return;
   for (int i = 0; i < c->B; ++i)
@@ -933,18 +936,22 @@ void build(ftcc_ctx* c) {
   FTCC_HIP(hipStreamSynchronize(c->stream));
   const char* genv = std::getenv("FTCC_GRAPH");
   if (!(genv && genv[0] == '0')) {
-    // the forward and backward launch lists are static: capture each once as a graph
-    hipGraph_t g;
-    FTCC_HIP(hipStreamBeginCapture(c->stream, hipStreamCaptureModeThreadLocal));
-    c->ex_main->run_forward(c->stream);
-    FTCC_HIP(hipStreamEndCapture(c->stream, &g));
-    FTCC_HIP(hipGraphInstantiate(&c->g_fwd, g, nullptr, nullptr, 0));
-    FTCC_HIP(hipGraphDestroy(g));
-    FTCC_HIP(hipStreamBeginCapture(c->stream, hipStreamCaptureModeThreadLocal));
-    c->ex_main->run_backward(c->stream);
-    FTCC_HIP(hipStreamEndCapture(c->stream, &g));
-    FTCC_HIP(hipGraphInstantiate(&c->g_bwd, g, nullptr, nullptr, 0));
-    FTCC_HIP(hipGraphDestroy(g));
+    // the launch lists are static: capture each once as a graph
+    auto capture = [c](hipGraphExec_t* exec, const std::function<void()>& run) {
+      hipGraph_t g;
+      FTCC_HIP(hipStreamBeginCapture(c->stream, hipStreamCaptureModeThreadLocal));
+      run();
+      FTCC_HIP(hipStreamEndCapture(c->stream, &g));
+      FTCC_HIP(hipGraphInstantiate(exec, g, nullptr, nullptr, 0));
+      FTCC_HIP(hipGraphDestroy(g));
+    };
+    capture(&c->g_fwd, [c] { c->ex_main->run_forward(c->stream); });
+    capture(&c->g_bwd, [c] { c->ex_main->run_backward(c->stream); });
+    if (sweeps_apart(c)) {
+      capture(&c->g_fwd_sweep, [c] { c->ex_main->run_forward_sweep(c->stream); });
+      capture(&c->g_fwd_rest, [c] { c->ex_main->run_forward_rest(c->stream); });
+      capture(&c->g_bwd_sweep, [c] { c->ex_main->run_backward_sweep(c->stream); });
+    }
   }
 
   c->prof.enabled = prof_on;
@@ -967,6 +974,27 @@ void run_fwd_slots(ftcc_ctx* c) {
 void run_bwd_slots(ftcc_ctx* c) {
   if (c->g_bwd && !c->prof.enabled) FTCC_HIP(hipGraphLaunch(c->g_bwd, c->stream));
   else c->ex_main->run_backward(c->stream);
+}
+
+// A fixed-point sweep's part of the two programs, all nodes at once: residuals without
+// the energies (forward_rest then gives those of the last amplitudes), gradients of the
+// amplitudes without those of the integrals.  Else the whole programs.
+void forward_sweep(ftcc_ctx* c) {
+  if (!sweeps_apart(c)) forward(c);
+  else if (c->g_fwd_sweep && !c->prof.enabled) FTCC_HIP(hipGraphLaunch(c->g_fwd_sweep, c->stream));
+  else c->ex_main->run_forward_sweep(c->stream);
+}
+
+void forward_rest(ftcc_ctx* c) {
+  if (!sweeps_apart(c)) return;
+  if (c->g_fwd_rest && !c->prof.enabled) FTCC_HIP(hipGraphLaunch(c->g_fwd_rest, c->stream));
+  else c->ex_main->run_forward_rest(c->stream);
+}
+
+void backward_sweep(ftcc_ctx* c) {
+  if (!sweeps_apart(c)) backward(c);
+  else if (c->g_bwd_sweep && !c->prof.enabled) FTCC_HIP(hipGraphLaunch(c->g_bwd_sweep, c->stream));
+  else c->ex_main->run_backward_sweep(c->stream);
 }
 
 long node_len(ftcc_ctx* c, int i) {
@@ -1405,14 +1433,14 @@ std::vector<int> panel_solve(ftcc_ctx* c, int panel, std::vector<int>& status) {
   set_run(c, active);   // converged or failed instances stop costing residual evaluations
   std::vector<DivergenceWatch> watch(B);
   reset_maxbits(c);
-  forward(c);
+  forward_sweep(c);
   for (int it = 1; it <= c->opt.max_iter; ++it) {
     c->resid_evals += n_running(c) * c->m;
     set_active(c, active);
     if (diis) diis_before(c, amp_of, active);
     tau_run(c, TAU_STEP, panel);
     post_maxbits(c);
-    if (!diis) forward(c);
+    if (!diis) forward_sweep(c);
     std::vector<double> mb = wait_maxbits(c);
     trace_sweep("forward", panel, it, mb);
     bool any = false;
@@ -1443,14 +1471,15 @@ std::vector<int> panel_solve(ftcc_ctx* c, int panel, std::vector<int>& status) {
         if (active[i]) status[i] = FTCC_ENOCONV;
     if (diis) {
       diis_after(c, amp_of, active);
-      if (it < c->opt.max_iter) forward(c);
+      if (it < c->opt.max_iter) forward_sweep(c);
     }
   }
-  // residuals at the final amplitudes of every instance still in good standing
+  // residuals and energies at the final amplitudes of every instance still in good standing
   std::vector<bool> ok(B);
   for (int i = 0; i < B; ++i) ok[i] = status[i] == 0;
   set_run(c, ok);
-  if (diis) forward(c);
+  if (diis) forward_sweep(c);
+  forward_rest(c);
   c->resid_evals += n_running(c) * c->m;
   run_all(c);
   return its;
@@ -1562,6 +1591,8 @@ int ftcc_destroy(ftcc_ctx* c) {
     clear_tau_cache(c);
     if (c->g_fwd) (void)hipGraphExecDestroy(c->g_fwd);
     if (c->g_bwd) (void)hipGraphExecDestroy(c->g_bwd);
+    for (hipGraphExec_t g : {c->g_fwd_sweep, c->g_fwd_rest, c->g_bwd_sweep})
+      if (g) (void)hipGraphExecDestroy(g);
     c->ex_main.reset();
     c->ex_d.reset();
     c->ex_g.reset();
@@ -1836,7 +1867,7 @@ int ftcc_lambda(ftcc_ctx* c, int* iters_out, int* status_out) {
       state_set(c, ST_ZERO_COT, 0, [c](auto add) {
         for (int q = 0; q < c->B * c->m; ++q) add(q / c->m, c->cot[q], nullptr);
       });
-      backward(c);
+      backward_sweep(c);
       c->vjp_evals += n_running(c) * m;
       reset_maxbits(c);
       std::vector<bool> active(B);
@@ -1856,7 +1887,7 @@ int ftcc_lambda(ftcc_ctx* c, int* iters_out, int* status_out) {
       for (int it = 1; it <= c->opt.max_iter; ++it) {
         if (!queued) {
           tau_run(c, TAU_LAMT, p);
-          backward(c);
+          backward_sweep(c);
         }
         c->vjp_evals += n_running(c) * m;
         set_active(c, active);
@@ -1866,7 +1897,7 @@ int ftcc_lambda(ftcc_ctx* c, int* iters_out, int* status_out) {
         queued = likely && !diis && c->slots == m && it < c->opt.max_iter;
         if (queued) {
           tau_run(c, TAU_LAMT, p);
-          backward(c);
+          backward_sweep(c);
         }
         std::vector<double> mb = wait_maxbits(c);
         likely = false;
