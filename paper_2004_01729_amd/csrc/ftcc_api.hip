@@ -760,9 +760,9 @@ void build(ftcc_ctx* c) {
       c->scratch.c[q] = c->dalloc(n4);
       c->scratch.part[q] = c->dalloc(n4);
     }
-  // 64 partial sums for each dot of one launch: one per node, or the two Gram entries of
+  // partial sums of each dot of one launch: one dot per node, or the two Gram entries of
   // every stored DIIS residual
-  c->scratch.dot_partial = c->dalloc((size_t)std::max(nn, c->opt.diis_depth ? 2 * kMaxDiis : 0) * 64 + 64);
+  c->scratch.dot_partial = c->dalloc((size_t)std::max(nn, c->opt.diis_depth ? 2 * kMaxDiis : 0) * kMaxDotBlocks);
   {
     // workspace for partial tiles: 128 MiB, or an eighth of a memory cap below 1 GiB
     size_t ws = kTailWorkspaceDoubles;

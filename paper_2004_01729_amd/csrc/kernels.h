@@ -194,6 +194,7 @@ void launch_splitk_reduce(const GemmProblem* d_probs, const int* d_prefix, int n
                           hipStream_t s);
 void launch_permute(const PermProblem* d_probs, const int* d_prefix, int n_prob, int total_blocks,
                     hipStream_t s);
+constexpr int kMaxDotBlocks = 256;   // blocks of one problem's dot
 void launch_dot(const DotProblem* d_probs, int n_prob, int blocks_per, double* d_partial, hipStream_t s);
 
 // GEMM tile configurations: 0: 128x128 BK 16, 1: 64x64 BK 16, 2: 128x128 BK 32

@@ -1040,26 +1040,34 @@ __global__ void __launch_bounds__(256) dotb_final_kernel(const DotbProblem* __re
   *out = v;
 }
 
-// C = alpha * sum_s partial[s] + beta * C for split-K problems
-__global__ void splitk_reduce_kernel(const GemmProblem* __restrict__ probs, const int* __restrict__ prefix,
-                                     int n_prob, int total) {
+// C = alpha * sum_s partial[s] + beta * C for split-K problems: 64 outputs per block,
+// the splits dealt to its four waves, whose sums are added in wave order.  (A thread
+// adding every split of its outputs, 1024 outputs a block, left 57 x 57 outputs of 180
+// splits to four blocks: 127 us.)
+__global__ void __launch_bounds__(256) splitk_reduce_kernel(const GemmProblem* __restrict__ probs,
+                                                            const int* __restrict__ prefix, int n_prob, int total) {
   const int pi = find_problem(prefix, n_prob, blockIdx.x);
   const GemmProblem P = probs[pi];
-  if (P.ksplit <= 1 || (P.active && *gview(P.active) == 0)) return;
+  if (P.ksplit <= 1 || (P.active && *gview(P.active) == 0)) return;   // uniform per block
   const long mn = (long)P.M * P.N;
-  const long chunk = (long)(blockIdx.x - prefix[pi]) * 256 * 4;
-  for (int u = 0; u < 4; ++u) {
-    long e = chunk + u * 256 + threadIdx.x;
-    if (e >= mn) return;
-    double s = 0.0;
-    for (int k = 0; k < P.ksplit; ++k) s += gview(P.partial)[k * mn + e];
-    long gm = e / P.N, gn = e % P.N;
-    const long off = P.offM ? (long)gview(P.offM)[gm] + gview(P.offN)[gn] : gm * P.ldc + gn;
-    const gptr<double> c = gview(P.C) + off;
-    double v = P.alpha * s;
-    if (P.beta != 0.0) v += P.beta * (*c);
-    *c = v;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const long e = (long)(blockIdx.x - prefix[pi]) * 64 + lane;
+  double s = 0.0;
+  if (e < mn) {
+#pragma unroll 8
+    for (int k = wave; k < P.ksplit; k += 4) s += gview(P.partial)[k * mn + e];
   }
+  __shared__ double part[256];
+  part[threadIdx.x] = s;
+  __syncthreads();
+  if (wave || e >= mn) return;
+  s = ((part[lane] + part[64 + lane]) + part[128 + lane]) + part[192 + lane];
+  const long gm = e / P.N, gn = e % P.N;
+  const long off = P.offM ? (long)gview(P.offM)[gm] + gview(P.offN)[gn] : gm * P.ldc + gn;
+  const gptr<double> c = gview(P.C) + off;
+  double v = P.alpha * s;
+  if (P.beta != 0.0) v += P.beta * (*c);
+  *c = v;
 }
 
 // ------------------------------------------------------------------ permute
@@ -1159,11 +1167,13 @@ __global__ void dot_partial_kernel(const DotProblem* __restrict__ probs, int blo
   double s = 0.0;
   if (P.ia) {
     const long cnt = P.na + P.nb;
+#pragma unroll 4
     for (long t = (long)bi * 256 + threadIdx.x; t < cnt; t += (long)blocks_per * 256) {
       const long e = t < P.na ? (long)gview(P.ia)[t] : P.second + (long)gview(P.ib)[t - P.na];
       s += gview(P.X)[e] * gview(P.Y)[e];
     }
   } else {
+#pragma unroll 8
     for (long e = (long)bi * 256 + threadIdx.x; e < P.len; e += (long)blocks_per * 256)
       s += gview(P.X)[e] * gview(P.Y)[e];
   }
@@ -1177,14 +1187,16 @@ __global__ void dot_partial_kernel(const DotProblem* __restrict__ probs, int blo
   if (threadIdx.x == 0) partial[blockIdx.x] = red[0];
 }
 
-__global__ void dot_final_kernel(const DotProblem* __restrict__ probs, int n_prob, int blocks_per,
-                                 const double* partial) {
-  const int pi = blockIdx.x * blockDim.x + threadIdx.x;
-  if (pi >= n_prob) return;
-  const DotProblem P = probs[pi];
+// One wave per problem: each lane adds every 64th partial sum, then a butterfly.
+__global__ void __launch_bounds__(64) dot_final_kernel(const DotProblem* __restrict__ probs, int blocks_per,
+                                                       const double* partial) {
+  const int pi = blockIdx.x;
+  const DotProblem& P = probs[pi];
   if (P.active && *gview(P.active) == 0) return;
   double s = 0.0;
-  for (int b = 0; b < blocks_per; ++b) s += partial[pi * blocks_per + b];
+  for (int b = threadIdx.x; b < blocks_per; b += 64) s += partial[pi * blocks_per + b];
+  for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
+  if (threadIdx.x) return;
   double v = P.alpha * s;
   const gptr<double> out = gview(P.out);
   if (P.beta != 0.0) v += P.beta * (*out);
@@ -1324,8 +1336,7 @@ void launch_dot(const DotProblem* d_probs, int n_prob, int blocks_per, double* d
   if (n_prob <= 0) return;
   hipLaunchKernelGGL(dot_partial_kernel, dim3(n_prob * blocks_per), dim3(256), 0, s, d_probs, blocks_per,
                      d_partial);
-  hipLaunchKernelGGL(dot_final_kernel, dim3((n_prob + 63) / 64), dim3(64), 0, s, d_probs, n_prob, blocks_per,
-                     d_partial);
+  hipLaunchKernelGGL(dot_final_kernel, dim3(n_prob), dim3(64), 0, s, d_probs, blocks_per, d_partial);
 }
 
 }  // namespace ftcc
