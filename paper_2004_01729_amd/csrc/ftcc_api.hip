@@ -889,12 +889,12 @@ void build(ftcc_ctx* c) {
   // Optional buffers: reused permuted copies of value operands (GEMM path), private
   // copies of accumulated outputs (blocked path).  One is taken only while it leaves a
   // reserve for what the executors must still allocate (the second executor's
-  // intermediates and permuted constants: 16 n^4 doubles per instance, plus 1 GiB), and
+  // intermediates and permuted constants: 24 n^4 doubles per instance, plus 1 GiB), and
   // an allocation that fails leaves the operand uncached or the writes serial.  The
   // blocked path's stay within an eighth of the memory available here, and a capped
   // context takes none.
   double reserve = 1073741824.0;
-  for (int i = 0; i < B; ++i) reserve += 16.0 * std::pow((double)c->inst[i].n, 4) * sizeof(double);
+  for (int i = 0; i < B; ++i) reserve += 24.0 * std::pow((double)c->inst[i].n, 4) * sizeof(double);
   double copies_left = blocked ? (c->opt.mem_cap_bytes ? 0.0 : c->available() / 8.0) : INFINITY;
   auto vcache = [c, reserve, &copies_left](size_t count) -> double* {
     const double bytes = (double)count * sizeof(double);
@@ -908,9 +908,10 @@ void build(ftcc_ctx* c) {
       return nullptr;
     }
   };
-  // reuse budget for permuted operand copies: a quarter of the memory still available
+  // reuse budget for permuted operand copies: an eighth of the memory still available (at
+  // 123 orbitals a quarter left the derivative executor short of its permuted constants)
   // (the blocked contractions address their operands in place: no permuted copies)
-  const size_t budget = blocked ? 0 : (size_t)(c->available() / 4);
+  const size_t budget = blocked ? 0 : (size_t)(c->available() / 8);
   std::vector<const InstMomentum*> by_inst;
   if (mom)
     for (const Instance& I : c->inst) by_inst.push_back(&I.mom);
