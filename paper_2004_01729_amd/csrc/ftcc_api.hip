@@ -1201,7 +1201,7 @@ int tau_problems(ftcc_ctx* c, int mode, int panel, double* partial_base, std::ve
         t.idx = I.d_allowed[seg];
         t.h = I.beta / c->P;
         t.maxbits = c->d_maxbits + 2 * i;
-        t.active = (mode == TAU_STEP || mode == TAU_LSTEP) ? c->d_active + i : nullptr;
+        t.active = (mode == TAU_STEP || mode == TAU_LSTEP || mode == TAU_LSWEEP) ? c->d_active + i : nullptr;
         for (int x = 0; x < m; ++x) {
           const int p = i * m + x;
           switch (mode) {
@@ -1217,7 +1217,10 @@ int tau_problems(ftcc_ctx* c, int mode, int panel, double* partial_base, std::ve
               t.S[x] = I.lam[panel * m + x] + off;
               t.s[x] = c->cot[p] + off;
               break;
-            case TAU_LSTEP:     // s = lambda (node storage), R = gradient
+            case TAU_LSWEEP:    // s = lambda (node storage), R = gradient
+              t.lamt[x] = c->cot[p] + off;
+              [[fallthrough]];
+            case TAU_LSTEP:
               t.s[x] = I.lam[panel * m + x] + off;
               t.R[x] = c->gr[p] + off;
               break;
@@ -1234,7 +1237,7 @@ int tau_problems(ftcc_ctx* c, int mode, int panel, double* partial_base, std::ve
         if (mode == TAU_INIT || mode == TAU_STEP || mode == TAU_END || mode == TAU_BETA || mode == TAU_DEPS)
           t.sb = I.sb[panel] + off;
         if (mode == TAU_END) t.out = I.sb[panel + 1] + off;
-        if (mode == TAU_LAMT || mode == TAU_APREV) t.sb = I.abuf[panel + 1] + off;
+        if (mode == TAU_LAMT || mode == TAU_LSWEEP || mode == TAU_APREV) t.sb = I.abuf[panel + 1] + off;
         if (mode == TAU_APREV) t.out = I.abuf[panel] + off;
         if (mode == TAU_BETA || mode == TAU_DEPS) t.lam_a = I.abuf[panel + 1] + off;
         if (mode == TAU_DEPS) t.out = I.deps_delta + off;
@@ -1874,8 +1877,11 @@ int ftcc_lambda(ftcc_ctx* c, int* iters_out, int* status_out) {
       std::vector<bool> active(B);
       for (int i = 0; i < B; ++i) active[i] = c->inst[i].status == 0;
       set_active(c, active);
-      tau_run(c, TAU_LSTEP, p);
+      // A step writes the next sweep's lambda-tilde with it: both are elementwise over the
+      // panel's nodes (DIIS replaces lambda in between).
       const bool diis = c->opt.diis_depth > 0;
+      const int step = diis ? TAU_LSTEP : TAU_LSWEEP;
+      tau_run(c, step, p);
       NodeBufs lam_of = [c, p](int i, int x) { return c->inst[i].lam[p * c->m + x]; };
       if (diis) diis_reset(c);
       std::vector<DivergenceWatch> watch(B);
@@ -1886,20 +1892,15 @@ int ftcc_lambda(ftcc_ctx* c, int* iters_out, int* status_out) {
       std::vector<double> last(B, 0.0);
       bool queued = false, likely = false;
       for (int it = 1; it <= c->opt.max_iter; ++it) {
-        if (!queued) {
-          tau_run(c, TAU_LAMT, p);
-          backward_sweep(c);
-        }
+        if (diis) tau_run(c, TAU_LAMT, p);
+        if (!queued) backward_sweep(c);
         c->vjp_evals += n_running(c) * m;
         set_active(c, active);
         if (diis) diis_before(c, lam_of, active);
-        tau_run(c, TAU_LSTEP, p);
+        tau_run(c, step, p);
         post_maxbits(c);
         queued = likely && !diis && c->slots == m && it < c->opt.max_iter;
-        if (queued) {
-          tau_run(c, TAU_LAMT, p);
-          backward_sweep(c);
-        }
+        if (queued) backward_sweep(c);
         std::vector<double> mb = wait_maxbits(c);
         likely = false;
         trace_sweep("lambda", p, it, mb);

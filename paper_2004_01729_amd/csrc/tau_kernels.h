@@ -31,6 +31,7 @@ enum TauMode {
   TAU_LSTEP = 6,    // s_x (lambda) = -R_x (gradient), with max|change|, max|lambda|
   TAU_DEPS = 7,     // out[e] += sum_x S_x(lam) (-dE_x sb + sum_y dW_xy R_y) + a (-dEe sb + sum dWe_y R_y),
                     // d/dDelta at fixed h (the orbital-energy response through the propagator)
+  TAU_LSWEEP = 8,   // TAU_LSTEP, then lamt_x = TAU_LAMT's sum of the new lambda
 };
 
 // One amplitude segment of one instance (t1: n^2 elements, t2: n^4 elements).
@@ -44,6 +45,7 @@ struct TauProblem {
   const double* S[kMaxNodes];   // residuals (or lambda)
   const double* R[kMaxNodes];   // residuals for TAU_BETA / gradients for TAU_LSTEP
   double* s[kMaxNodes];         // node amplitudes (or lambda-tilde / lambda)
+  double* lamt[kMaxNodes];      // lambda-tilde for TAU_LSWEEP
   double* out;                  // end state / previous adjoint state / TAU_DEPS accumulator
   const double* lam_a;          // a_{p+1} for TAU_BETA and TAU_DEPS
   unsigned long long* maxbits;  // [0] max |change|, [1] max |value| (bit patterns of doubles >= 0)

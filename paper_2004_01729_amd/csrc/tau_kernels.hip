@@ -174,14 +174,16 @@ __global__ void __launch_bounds__(256) tau_kernel(const PanelRule* __restrict__ 
       Sv[y] = P.S[y] ? gview(P.S[y])[e] : 0.0;
       any = any || (Sv[y] != 0.0);
     }
-    if (mode == TAU_LSTEP) {
+    if (mode == TAU_LSTEP || mode == TAU_LSWEEP) {
       for (int x = 0; x < m; ++x) {
         const double nv = -gview(P.R[x])[e];
         mchg = nan_max(mchg, fabs(nv - gview(P.s[x])[e]));
         mval = nan_max(mval, fabs(nv));
         gview(P.s[x])[e] = nv;
+        Sv[x] = nv;
+        any = any || nv != 0.0;
       }
-      continue;
+      if (mode == TAU_LSTEP) continue;   // TAU_LSWEEP: lambda-tilde of the new lambda below
     }
     if ((IT == 4 && mode == TAU_BETA) || (IT == 1 && mode == TAU_DEPS)) {
       double Rv[M];
@@ -213,7 +215,9 @@ __global__ void __launch_bounds__(256) tau_kernel(const PanelRule* __restrict__ 
     if (IT == 4) continue;   // TAU_BETA only
     if (!any) {
       // structurally zero (dropped slots, or zero start): outputs stay zero
-      if (mode == TAU_INIT || mode == TAU_LAMT) {
+      if (mode == TAU_LSWEEP) {
+        for (int x = 0; x < m; ++x) gview(P.lamt[x])[e] = 0.0;
+      } else if (mode == TAU_INIT || mode == TAU_LAMT) {
         for (int x = 0; x < m; ++x) gview(P.s[x])[e] = 0.0;
       } else if (mode == TAU_STEP) {
         for (int x = 0; x < m; ++x) {
@@ -243,12 +247,12 @@ __global__ void __launch_bounds__(256) tau_kernel(const PanelRule* __restrict__ 
       for (int y = 0; y < m; ++y)
         if (Sv[y] != 0.0) v -= w.We[y] * Sv[y];
       gview(P.out)[e] = v;
-    } else if (mode == TAU_LAMT) {
+    } else if (mode == TAU_LAMT || mode == TAU_LSWEEP) {
       for (int x = 0; x < m; ++x) {
         double v = (sb != 0.0) ? w.We[x] * sb : 0.0;
         for (int y = 0; y < m; ++y)
           if (Sv[y] != 0.0) v += w.W[y][x] * Sv[y];
-        gview(P.s[x])[e] = v;
+        gview(mode == TAU_LAMT ? P.s[x] : P.lamt[x])[e] = v;
       }
     } else if (mode == TAU_APREV) {
       double v = (sb != 0.0) ? w.Ee * sb : 0.0;
@@ -259,7 +263,7 @@ __global__ void __launch_bounds__(256) tau_kernel(const PanelRule* __restrict__ 
   }
   // block reductions
   __shared__ double r0[256], r1[256];
-  if (mode == TAU_STEP || mode == TAU_LSTEP) {
+  if (mode == TAU_STEP || mode == TAU_LSTEP || mode == TAU_LSWEEP) {
     r0[threadIdx.x] = mchg;
     r1[threadIdx.x] = mval;
     __syncthreads();
