@@ -103,6 +103,8 @@ struct Launch {
   void* d_src = nullptr;            // ELEM: source list
   long long n_elem = 0;             // ELEM: elements, problems padded to whole blocks
   int elem_per = 1;                 // ELEM: elements per thread
+  bool flat = false;                // ELEM: every problem's elements are one list; d_tasks: its n_flat blocks
+  int n_flat = 0;
   int dot_blocks = 0;
   void* d_desc = nullptr;
   int* d_prefix = nullptr;

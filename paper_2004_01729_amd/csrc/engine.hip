@@ -1448,6 +1448,7 @@ bool Executor::sum_blocked(std::vector<Launch>& dst, const std::vector<SumTerm>&
     }
   }
   L.ranged = true;
+  L.flat = flat;
   L.kind = Launch::ELEM;
   L.bytes = sizeof(double) * elements * ((double)terms.size() + (beta != 0.0) + 1);
   L.tag = tag + "(blocked)";
@@ -1469,6 +1470,15 @@ void Executor::upload_elem(Launch& L) {
   // padding; 10 orbitals, 12 instances: 32.6 ms a step with four, 27.0 with one) or the
   // launch is (6 dense orbitals: 19.2 against 18.6).
   L.elem_per = L.n_elem >= std::max(1024LL * L.n_tasks, 1024LL * 256) ? 4 : 1;
+  L.n_flat = 0;
+  if (L.flat && L.elem_per == 1) {
+    std::vector<ElemBlock> blocks;
+    for (const ElemTask& T : L.etasks)
+      for (int k = 0; k < T.vlen; k += 256) blocks.push_back(ElemBlock{T.prob, k, T.vlen});
+    L.n_flat = L.total = (int)blocks.size();
+    L.d_tasks = upload(blocks.data(), sizeof(ElemBlock) * blocks.size());
+    return;
+  }
   const long long block = 256 * L.elem_per;
   long long first = 0;
   for (size_t t = 0; t < L.etasks.size(); ++t) {
@@ -1669,7 +1679,7 @@ Launch Executor::merge_sgemm(const std::vector<Launch*>& parts) {
 Launch Executor::merge_elem(const std::vector<Launch*>& parts) {
   Launch M;
   M.kind = Launch::ELEM;
-  M.ranged = true;
+  M.ranged = M.flat = true;
   for (const Launch* l : parts) {
     const int po = (int)M.eprobs.size(), so = (int)M.esrcs.size();
     for (ElemProblem q : l->eprobs) {
@@ -1682,6 +1692,7 @@ Launch Executor::merge_elem(const std::vector<Launch*>& parts) {
       M.etasks.push_back(t);
     }
     M.n_elem += l->n_elem;
+    M.flat = M.flat && l->flat;
     M.bytes += l->bytes;
     M.rd.insert(M.rd.end(), l->rd.begin(), l->rd.end());
     M.wr.insert(M.wr.end(), l->wr.begin(), l->wr.end());
@@ -2321,7 +2332,11 @@ void Executor::run(const std::vector<Launch>& L, hipStream_t s) const {
                     l.d_partial, s);
         break;
       case Launch::ELEM:
-        launch_elem((const ElemProblem*)l.d_desc, (const ElemSource*)l.d_src, (const ElemTask*)l.d_tasks,
+        if (l.n_flat > 0)
+          launch_elem_flat((const ElemProblem*)l.d_desc, (const ElemSource*)l.d_src, (const ElemBlock*)l.d_tasks,
+                           l.n_flat, s);
+        else
+          launch_elem((const ElemProblem*)l.d_desc, (const ElemSource*)l.d_src, (const ElemTask*)l.d_tasks,
                     (const int*)l.d_bfirst, l.n_tasks, l.n_elem, l.elem_per, s);
         break;
     }

@@ -165,6 +165,13 @@ struct ElemTask {
   int prob;
   int u0, ulen, v0, vlen;
 };
+// 256 elements of one problem whose allowed elements are one list (ElemProblem::oy2 of
+// `count`, a source's in ox2): the blocks of launch_elem_flat
+struct ElemBlock {
+  int prob, first, count;
+};
+void launch_elem_flat(const ElemProblem* d_probs, const ElemSource* d_src, const ElemBlock* d_blocks, int n_blocks,
+                      hipStream_t s);
 // per: elements per thread (1 or 4), a block holds 256 per; d_bfirst: the task of each
 // block's first element, then the last task
 void launch_elem(const ElemProblem* d_probs, const ElemSource* d_src, const ElemTask* d_tasks, const int* d_bfirst,
