@@ -65,6 +65,7 @@ struct Instance {
   std::vector<double> eps_host;
   InstMomentum mom;                // dims == 0: no momentum labels
   unsigned* d_allowed[2] = {nullptr, nullptr};   // momentum-allowed elements of the t1 / t2 segments
+  unsigned* d_where[2] = {nullptr, nullptr};     // where they lie in a node state (packed states; else d_allowed)
   long n_allowed[2] = {0, 0};
   int* d_labels = nullptr;         // device copies for the conservation checks
   int* d_modulus = nullptr;
@@ -149,6 +150,15 @@ struct ftcc_ctx {
   hipEvent_t maxbits_posted = nullptr;
   double* d_partial = nullptr;                // TAU_BETA partial sums
   std::vector<int> tau_prefix_host;
+  // Node states (amplitudes, residuals, lambda ...) without the last index of t1 and t2,
+  // which momentum fixes: every orbital of every instance has its own label.  The
+  // segments still begin at 0 and n^2; dense_node: one dense state for the interface.
+  // Against dense states, whose allowed elements lie n apart (a 64-byte sector each) and
+  // which every pass gathered and scattered: 81 orbitals, forward 32.4 -> 28.9 ms (the
+  // propagator 56 -> 26 us a sweep); 57, step 40.8 -> 35.7; 33, Runge-Kutta 121.5 -> 107.7.
+  bool packed_states = false;
+  double* dense_node = nullptr;
+  std::vector<double*> g_amp, g_cot;          // the density's dense node amplitudes and cotangents
   int* d_active = nullptr;                    // [B] propagator step flags
   int* d_run = nullptr;                       // [B slots] residual-program run flags (executor gate)
   std::vector<int> run_host;                  // [B] which instances run
@@ -328,6 +338,8 @@ void run_bwd_slots(ftcc_ctx* c);
 long node_len(ftcc_ctx* c, int i);
 void dcopy(ftcc_ctx* c, double* dst, const double* src, long count);
 void node_copy(ftcc_ctx* c, int i, double* dst, const double* src);
+void dense_state(ftcc_ctx* c, int i, double* dense, const double* state);
+void state_to_host(ftcc_ctx* c, int i, const double* state, double* t1, double* t2);
 // One launch for a set of copies, fixed per (kind, panel) once the context is built.  An
 // entry is a whole node state of an instance (src null: zeros) or `len` values; `add`
 // adds them.  From ST_STAGE_IN on an entry is skipped while its instance does not run.

@@ -206,6 +206,11 @@ class Executor {
   // to the integrals).  Call before build().
   void set_inline_setup(bool on) { inline_setup_ = on; }
 
+  // The rank >= 2 inputs, outputs and their gradients are bound to packed buffers (else to
+  // dense ones).  Only where io_packable() says so for the same program, problems, labels.
+  void set_packed_io(bool on) { packed_io_ = on; }
+  bool io_packable(const Program* prog, const std::vector<ProblemRef>& probs);
+
   // time the candidate GEMM tile configurations of every large GEMM launch and keep the best
   void autotune(hipStream_t s);
   void run_setup(hipStream_t s) const { run(setup_, s); }
@@ -321,6 +326,7 @@ class Executor {
   std::vector<ProblemRef> probs_;
   Scratch* scratch_ = nullptr;
   bool inline_setup_ = false;
+  bool packed_io_ = false;
   // Momentum-blocked lists: every launch moves to the earliest dependency level
   // its byte ranges allow, and the blocked contractions (and the blocked
   // elementwise ops) of one level become one launch each.  Every buffer sees its
@@ -382,8 +388,7 @@ class Executor {
   // constants (and derived constants) read through packed copies: no gradient asked
   // for them, and every op that reads them lowers to blocked kernels
   std::vector<int> plan_const_packing(const std::vector<int>& const_grads) const;
-  // inputs and outputs of rank >= 2 worked on through packed shadows: gathered from
-  // their dense buffers at the start of a pass, scattered back at its end
+  // inputs and outputs of rank >= 2 that every op lets be packed
   std::vector<int> plan_io_packing() const;
   bool is_packed(int t) const { return t >= 0 && t < (int)packed_.size() && packed_[t]; }
   size_t elems(int t, long n, int rank) const { return (size_t)ipow_l(n, is_packed(t) ? rank - 1 : rank); }

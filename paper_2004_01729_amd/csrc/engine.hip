@@ -805,6 +805,17 @@ std::vector<int> Executor::plan_io_packing() const {
   return out;
 }
 
+bool Executor::io_packable(const Program* prog, const std::vector<ProblemRef>& probs) {
+  if (mom_.empty()) return false;
+  prog_ = prog;
+  probs_ = probs;
+  infer_laws();
+  plan_packing(true);
+  int n_io = 0;
+  for (const TensorDecl& d : prog->t) n_io += (d.kind == T_INPUT || d.kind == T_OUTPUT) && d.rank >= 2;
+  return (int)plan_io_packing().size() == n_io;
+}
+
 void Executor::infer_laws() {
   const int nt = (int)prog_->t.size();
   law_.assign(nt, {});
@@ -2054,44 +2065,9 @@ void Executor::build(const Program* prog, const std::vector<ProblemRef>& probs, 
     probs_ = probs;
     scratch_ = scratch;
   }
-  // Packed shadows of the rank >= 2 inputs and outputs (and of their gradients):
-  // the ops work on the shadows, the inputs are gathered into them first and the
-  // outputs scattered back last (over the allowed elements; the dense buffers'
-  // forbidden elements stay zero).
-  const std::vector<int> io = plan_io_packing();
-  std::vector<PerProb> dense_f(nt), dense_g(nt);
-  auto shadows = [&](int k) {
-    PerProb s(np);
-    for (int p = 0; p < np; ++p) {
-      const size_t cnt = (size_t)ipow_l(probs[p].n, prog->t[k].rank - 1);
-      s[p] = const_alloc_(probs[p].inst, cnt);
-      const_bytes_ += sizeof(double) * cnt;
-    }
-    return s;
-  };
-  auto letters = [](int r) {
-    std::string ix;
-    for (int a = 0; a < r; ++a) ix.push_back((char)('p' + a));
-    return ix;
-  };
-  for (int k : io) {
-    dense_f[k] = fwd[k];
-    fwd[k] = shadows(k);
-    if (need_grad[k]) {
-      dense_g[k] = grd[k];
-      grd[k] = shadows(k);
-    }
-    packed_[k] = 1;
-  }
-  auto move_packed = [&](std::vector<Launch>& dst, const PerProb& X, const PerProb& Y, int k, bool to_packed,
-                         const std::string& what) {
-    const std::string ix = letters(prog->t[k].rank);
-    if (!elem_blocked(dst, X, ix, Y, ix, 1.0, 0.0, k, k, what + prog->t[k].name, nullptr, to_packed ? 0 : 1,
-                      to_packed ? 1 : 0))
-      throw std::runtime_error("no packed shadow of " + prog->t[k].name);
-  };
-  for (int k : io)
-    if (prog->t[k].kind == T_INPUT) move_packed(fwd_, dense_f[k], fwd[k], k, true, "gather:");
+  // rank >= 2 inputs, outputs and their gradients in packed buffers
+  if (packed_io_)
+    for (int k : plan_io_packing()) packed_[k] = 1;
   version_.assign(nt, 0);
   auto vidx = [&](int k) { return (k >= 0 && cidx(k) < 0) ? k : -1; };
   // buffer keys of the op lists: a tensor's values k, its gradient nt + k
@@ -2103,8 +2079,6 @@ void Executor::build(const Program* prog, const std::vector<ProblemRef>& probs, 
                          prog->t[o.out].name});
   }
   lower(fwd_, ops, {}, {});
-  for (int k : io)
-    if (prog->t[k].kind == T_OUTPUT) move_packed(fwd_, fwd[k], dense_f[k], k, false, "scatter:");
   if (!want_backward) {
     const char* fz = std::getenv("FTCC_FUSE");
     if (!mom_.empty() && !(fz && fz[0] == '0')) {
@@ -2115,8 +2089,6 @@ void Executor::build(const Program* prog, const std::vector<ProblemRef>& probs, 
     dump_plan();
     return;
   }
-  for (int k : io)
-    if (need_grad[k] && prog->t[k].kind == T_OUTPUT) move_packed(bwd_, dense_g[k], grd[k], k, true, "gather:d");
   // every gradient buffer except the cotangents of the outputs starts at zero
   std::vector<int> zeroed;
   std::vector<PerProb> zero_bufs;
@@ -2140,8 +2112,6 @@ void Executor::build(const Program* prog, const std::vector<ProblemRef>& probs, 
                            true, cidx(o.a), -1, vidx(o.a), -1, o.b, o.a, o.out, tag + ":dB"});
   }
   lower(bwd_, ops, zeroed, zero_bufs);
-  for (int k : io)
-    if (need_grad[k] && prog->t[k].kind == T_INPUT) move_packed(bwd_, grd[k], dense_g[k], k, false, "scatter:d");
   // FTCC_FUSE=0 keeps the program order, one launch per contraction (diagnostics)
   const char* fz = std::getenv("FTCC_FUSE");
   if (!mom_.empty() && !(fz && fz[0] == '0')) {
@@ -2157,8 +2127,8 @@ void Executor::build(const Program* prog, const std::vector<ProblemRef>& probs, 
         const bool output = prog->t[k].kind == T_OUTPUT, input = prog->t[k].kind == T_INPUT;
         for (int p = 0; p < np; ++p) {
           const size_t sz = sizeof(double) * (size_t)ipow_l(probs[p].n, prog->t[k].rank);
-          if (output && prog->t[k].rank > 0) add_range(out, dense_f[k].empty() ? fwd[k][p] : dense_f[k][p], sz);
-          if (input && need_grad[k]) add_range(in, dense_g[k].empty() ? grd[k][p] : dense_g[k][p], sz);
+          if (output && prog->t[k].rank > 0) add_range(out, fwd[k][p], sz);
+          if (input && need_grad[k]) add_range(in, grd[k][p], sz);
         }
       }
       const std::vector<char> kf = leads_to(fwd_, out), kb = leads_to(bwd_, in);

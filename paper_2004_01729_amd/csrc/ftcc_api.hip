@@ -485,9 +485,9 @@ void deriv_setup(ftcc_ctx* c, int which, int q) {
 void list_allowed(const ftcc_ctx* c, int i, DotProblem& d) {
   const Instance& I = c->inst[i];
   if (!I.d_allowed[0]) return;
-  d.ia = I.d_allowed[0];
+  d.ia = I.d_where[0];
   d.na = I.n_allowed[0];
-  d.ib = I.d_allowed[1];
+  d.ib = I.d_where[1];
   d.nb = I.n_allowed[1];
   d.second = (long)I.n * I.n;
 }
@@ -554,6 +554,14 @@ void allowed_elements(ftcc_ctx* c, int i) {
     I.d_allowed[seg] = (unsigned*)c->dalloc(l.size() / 2 + 1);
     if (!l.empty())
       FTCC_HIP(hipMemcpy(I.d_allowed[seg], l.data(), sizeof(unsigned) * l.size(), hipMemcpyHostToDevice));
+    I.d_where[seg] = I.d_allowed[seg];
+    if (c->packed_states) {
+      std::vector<unsigned> w(l);
+      for (unsigned& e : w) e /= (unsigned)n;
+      I.d_where[seg] = (unsigned*)c->dalloc(w.size() / 2 + 1);
+      if (!w.empty())
+        FTCC_HIP(hipMemcpy(I.d_where[seg], w.data(), sizeof(unsigned) * w.size(), hipMemcpyHostToDevice));
+    }
   }
 }
 
@@ -576,6 +584,20 @@ void build(ftcc_ctx* c) {
   const int m = c->m, P = c->P, B = c->B;
   c->prog = c->opt.spin_orbital ? build_spin_orbital_program() : build_residual_program();
   const bool mom = momentum_on(c);
+  if (mom) {
+    std::vector<const InstMomentum*> labels;
+    std::vector<ProblemRef> one;
+    long longest = 0;
+    for (int i = 0; i < B; ++i) {
+      labels.push_back(&c->inst[i].mom);
+      one.push_back({i, 0, c->inst[i].n});
+      longest = std::max(longest, node_len_of(c->inst[i].n));
+    }
+    Executor probe;
+    probe.set_momentum(labels);
+    c->packed_states = probe.io_packable(&c->prog, one);
+    if (c->packed_states) c->dense_node = c->dalloc(longest);
+  }
   if (mom)
     for (int i = 0; i < B; ++i) {
       Instance& I = c->inst[i];
@@ -919,11 +941,13 @@ void build(ftcc_ctx* c) {
     for (const InstMomentum& t : c->one_block) by_inst.push_back(&t);
   c->ex_main.reset(new Executor());
   c->ex_main->set_gate(c->d_run, c->run_slots.data());
+  c->ex_main->set_packed_io(c->packed_states);
   if (blocked) c->ex_main->set_momentum(by_inst);
   c->ex_main->build(&prog, probs, bind_main, &c->scratch, calloc_, true, ugrads, vcache, budget);
   c->ex_main->set_profiler(&c->prof);
   trace_executor(c, "main", *c->ex_main);
   c->ex_d.reset(new Executor());
+  c->ex_d->set_packed_io(c->packed_states);
   if (blocked) c->ex_d->set_momentum(by_inst);
   c->ex_d->build(&prog, probs, bind_d, &c->scratch, calloc_, false, {}, vcache, budget / 2);
   c->ex_d->set_profiler(&c->prof);
@@ -1017,9 +1041,37 @@ void node_copy(ftcc_ctx* c, int i, double* dst, const double* src) {
     dcopy(c, dst, src, node_len(c, i));
     return;
   }
-  launch_copy_listed(I.d_allowed[0], I.n_allowed[0], I.d_allowed[1], I.n_allowed[1], (long)I.n * I.n, src, dst,
+  launch_copy_listed(I.d_where[0], I.n_allowed[0], I.d_where[1], I.n_allowed[1], (long)I.n * I.n, src, dst,
                      c->stream);
   FTCC_HIP(hipGetLastError());
+}
+
+// a node state of instance i in dense storage (forbidden elements zero)
+void dense_state(ftcc_ctx* c, int i, double* dense, const double* state) {
+  const Instance& I = c->inst[i];
+  if (!c->packed_states) {
+    dcopy(c, dense, state, node_len(c, i));
+    return;
+  }
+  const long n2 = (long)I.n * I.n;
+  zero_d(c, dense, node_len(c, i));
+  for (int seg = 0; seg < 2; ++seg)
+    launch_repack(I.d_allowed[seg], I.n_allowed[seg], I.n, dense + (seg ? n2 : 0),
+                  const_cast<double*>(state) + (seg ? n2 : 0), false, c->stream);
+  FTCC_HIP(hipGetLastError());
+}
+
+// t1 and t2 (either may be null) of a node state to the caller's arrays
+void state_to_host(ftcc_ctx* c, int i, const double* state, double* t1, double* t2) {
+  const long n2 = (long)c->inst[i].n * c->inst[i].n;
+  if (!t1 && !t2) return;
+  if (c->packed_states) {
+    dense_state(c, i, c->dense_node, state);
+    state = c->dense_node;
+  }
+  if (t1) FTCC_HIP(hipMemcpyAsync(t1, state, sizeof(double) * n2, hipMemcpyDeviceToHost, c->stream));
+  if (t2) FTCC_HIP(hipMemcpyAsync(t2, state + n2, sizeof(double) * n2 * n2, hipMemcpyDeviceToHost, c->stream));
+  sync(c);
 }
 
 constexpr int kEvalGateMinN = 12;
@@ -1058,9 +1110,9 @@ void state_set(ftcc_ctx* c, int kind, int panel, const std::function<void(StateL
       k.active = kind >= ST_STAGE_IN ? c->d_run + i * c->slots : nullptr;
       k.add = add;
       if (!len && I.d_allowed[0] && I.d_allowed[1]) {
-        k.a = I.d_allowed[0];
+        k.a = I.d_where[0];
         k.na = I.n_allowed[0];
-        k.b = I.d_allowed[1];
+        k.b = I.d_where[1];
         k.nb = I.n_allowed[1];
         k.second = (long)I.n * I.n;
         k.len = k.na + k.nb;
@@ -1199,6 +1251,7 @@ int tau_problems(ftcc_ctx* c, int mode, int panel, double* partial_base, std::ve
         t.rank = seg ? 4 : 2;
         t.len = seg_len(c, i, seg);
         t.idx = I.d_allowed[seg];
+        t.pack = c->packed_states ? (unsigned)n : 0u;
         t.h = I.beta / c->P;
         t.maxbits = c->d_maxbits + 2 * i;
         t.active = (mode == TAU_STEP || mode == TAU_LSTEP || mode == TAU_LSWEEP) ? c->d_active + i : nullptr;
@@ -1797,12 +1850,10 @@ int ftcc_get_amplitudes(ftcc_ctx* c, int i, int k, double* t1, double* t2) {
     if (c->opt.checkpoint && !uniform) fail(FTCC_ESTATE, "amplitudes are not kept with checkpoint = 1");
     // uniform-grid forms: the grid states s(tau_k), k = 0..n_tau
     if (i < 0 || i >= c->B || k < 0 || k >= c->opt.n_tau + (uniform ? 1 : 0)) fail(FTCC_EINVAL, "index out of range");
-    const long n = c->inst[i].n, n2 = n * n;
     FTCC_HIP(hipSetDevice(c->device));
     sync(c);
     const double* src = uniform ? c->inst[i].sb[k] : c->inst[i].grid[k];
-    FTCC_HIP(hipMemcpy(t1, src, sizeof(double) * n2, hipMemcpyDeviceToHost));
-    FTCC_HIP(hipMemcpy(t2, src + n2, sizeof(double) * n2 * n2, hipMemcpyDeviceToHost));
+    state_to_host(c, i, src, t1, t2);
   });
 }
 
@@ -1974,42 +2025,33 @@ int ftcc_get_lambda(ftcc_ctx* c, int i, int k, double* l1, double* l2, double* l
     if (c->simpson) {
       // Simpson integral form: lambda of grid point k, k = 0..n_tau (lambda_0 = 0)
       if (i < 0 || i >= c->B || k < 0 || k > c->opt.n_tau) fail(FTCC_EINVAL, "index out of range");
-      const long n = c->inst[i].n, n2 = n * n;
       FTCC_HIP(hipSetDevice(c->device));
       if (lt1 || lt2) {
         run_all(c);
         simpson_lamt(c, k);
       }
       sync(c);
-      if (l1) FTCC_HIP(hipMemcpy(l1, c->inst[i].lam[k], sizeof(double) * n2, hipMemcpyDeviceToHost));
-      if (l2) FTCC_HIP(hipMemcpy(l2, c->inst[i].lam[k] + n2, sizeof(double) * n2 * n2, hipMemcpyDeviceToHost));
-      if (lt1) FTCC_HIP(hipMemcpy(lt1, c->cot[i * c->m], sizeof(double) * n2, hipMemcpyDeviceToHost));
-      if (lt2) FTCC_HIP(hipMemcpy(lt2, c->cot[i * c->m] + n2, sizeof(double) * n2 * n2, hipMemcpyDeviceToHost));
+      state_to_host(c, i, c->inst[i].lam[k], l1, l2);
+      state_to_host(c, i, c->cot[i * c->m], lt1, lt2);
       return;
     }
     if (c->rk) {
       // differential form: the cotangent of the grid state s(tau_k), k = 0..n_tau
       if (i < 0 || i >= c->B || k < 0 || k > c->opt.n_tau) fail(FTCC_EINVAL, "index out of range");
       if (lt1 || lt2) fail(FTCC_EINVAL, "the differential form has no lambda-tilde");
-      const long n = c->inst[i].n, n2 = n * n;
       FTCC_HIP(hipSetDevice(c->device));
       sync(c);
-      if (l1) FTCC_HIP(hipMemcpy(l1, c->inst[i].abuf[k], sizeof(double) * n2, hipMemcpyDeviceToHost));
-      if (l2) FTCC_HIP(hipMemcpy(l2, c->inst[i].abuf[k] + n2, sizeof(double) * n2 * n2, hipMemcpyDeviceToHost));
+      state_to_host(c, i, c->inst[i].abuf[k], l1, l2);
       return;
     }
     if (i < 0 || i >= c->B || k < 0 || k >= c->opt.n_tau) fail(FTCC_EINVAL, "index out of range");
-    const long n = c->inst[i].n, n2 = n * n;
     FTCC_HIP(hipSetDevice(c->device));
     sync(c);
-    if (l1) FTCC_HIP(hipMemcpy(l1, c->inst[i].lam[k], sizeof(double) * n2, hipMemcpyDeviceToHost));
-    if (l2) FTCC_HIP(hipMemcpy(l2, c->inst[i].lam[k] + n2, sizeof(double) * n2 * n2, hipMemcpyDeviceToHost));
+    state_to_host(c, i, c->inst[i].lam[k], l1, l2);
     if (lt1 || lt2) {
       tau_run(c, TAU_LAMT, k / c->m);
       sync(c);
-      const double* src = c->cot[i * c->m + k % c->m];
-      if (lt1) FTCC_HIP(hipMemcpy(lt1, src, sizeof(double) * n2, hipMemcpyDeviceToHost));
-      if (lt2) FTCC_HIP(hipMemcpy(lt2, src + n2, sizeof(double) * n2 * n2, hipMemcpyDeviceToHost));
+      state_to_host(c, i, c->cot[i * c->m + k % c->m], lt1, lt2);
     }
   });
 }
@@ -2433,7 +2475,12 @@ int ftcc_response(ftcc_ctx* c, double* dO_dmu, double* dO_dbeta, double* dO_dh, 
         hipLaunchKernelGGL(deps_meanfield_kernel, dim3((n + 63) / 64), dim3(64), 0, c->stream, n, I.eps, I.occ,
                            I.fock, I.mu, I.beta, c->gdeg, I.deps_out);
         launch_axpby(n, 1.0, I.deps_acc, 1.0, I.deps_out, c->stream);
-        hipLaunchKernelGGL(deps_reduce_kernel, dim3(n), dim3(256), 0, c->stream, n, I.deps_delta, I.deps_out);
+        const double* delta = I.deps_delta;
+        if (c->packed_states) {
+          dense_state(c, i, c->dense_node, delta);
+          delta = c->dense_node;
+        }
+        hipLaunchKernelGGL(deps_reduce_kernel, dim3(n), dim3(256), 0, c->stream, n, delta, I.deps_out);
         FTCC_HIP(hipGetLastError());
         FTCC_HIP(hipMemcpyAsync(dO_deps + off, I.deps_out, sizeof(double) * n, hipMemcpyDeviceToHost, c->stream));
         off += n;
@@ -2466,17 +2513,21 @@ int ftcc_eval_residual(ftcc_ctx* c, int i, double mu, double beta, const double*
     c->ex_main->run_setup(c->stream);
     // every node slot gets the amplitudes (ftcc_time_residual evaluates them all)
     const int q = i * c->m;
-    FTCC_HIP(hipMemcpyAsync(c->amp[q], t1, sizeof(double) * n2, hipMemcpyHostToDevice, c->stream));
-    FTCC_HIP(hipMemcpyAsync(c->amp[q] + n2, t2, sizeof(double) * n4, hipMemcpyHostToDevice, c->stream));
-    for (int x = 1; x < c->m; ++x) node_copy(c, i, c->amp[q + x], c->amp[q]);
+    double* in = c->packed_states ? c->dense_node : c->amp[q];
+    FTCC_HIP(hipMemcpyAsync(in, t1, sizeof(double) * n2, hipMemcpyHostToDevice, c->stream));
+    FTCC_HIP(hipMemcpyAsync(in + n2, t2, sizeof(double) * n4, hipMemcpyHostToDevice, c->stream));
     if (I.d_allowed[0]) {   // the blocked path keeps every forbidden element of a state at zero
-      check_momentum(c, i, c->amp[q], 2, "t1");
-      check_momentum(c, i, c->amp[q] + n2, 4, "t2");
+      check_momentum(c, i, in, 2, "t1");
+      check_momentum(c, i, in + n2, 4, "t2");
     }
+    if (c->packed_states)
+      for (int seg = 0; seg < 2; ++seg)
+        launch_repack(I.d_allowed[seg], I.n_allowed[seg], I.n, in + (seg ? n2 : 0), c->amp[q] + (seg ? n2 : 0), true,
+                      c->stream);
+    for (int x = 1; x < c->m; ++x) node_copy(c, i, c->amp[q + x], c->amp[q]);
     eval_one(c, i);
     if (S2) touch_pages(S2, sizeof(double) * n4);   // while the GPU works
-    if (S1) FTCC_HIP(hipMemcpyAsync(S1, c->S[q], sizeof(double) * n2, hipMemcpyDeviceToHost, c->stream));
-    if (S2) FTCC_HIP(hipMemcpyAsync(S2, c->S[q] + n2, sizeof(double) * n4, hipMemcpyDeviceToHost, c->stream));
+    state_to_host(c, i, c->S[q], S1, S2);
     if (E) FTCC_HIP(hipMemcpyAsync(E, c->e[q], sizeof(double), hipMemcpyDeviceToHost, c->stream));
     sync(c);
     c->solved = false;

@@ -890,7 +890,8 @@ __global__ void __launch_bounds__(256) elem_kernel(const ElemProblem* __restrict
 
 // elem_kernel where a problem's elements are one list: the block says which problem and
 // where, nothing is searched or divided.  What bounds these launches is the chain of
-// dependent loads (33 labelled orbitals: 5.1 us by elem_kernel, 3.9 here).
+// dependent loads (33 labelled orbitals: 5.9 us a launch over pairs of index groups by
+// elem_kernel, 4.8 here).
 __global__ void __launch_bounds__(256) elem_flat_kernel(const ElemProblem* __restrict__ probs,
                                                         const ElemSource* __restrict__ srcs,
                                                         const ElemBlock* __restrict__ blocks) {

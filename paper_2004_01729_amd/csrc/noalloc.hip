@@ -131,9 +131,9 @@ int ftcc_response_noalloc(ftcc_ctx* c, double* dO_dmu, double* dO_dbeta) {
             d.out = I.acc + which;
             d.len = n * n + n * n * n * n;
             if (I.d_allowed[0]) {
-              d.ia = I.d_allowed[0];
+              d.ia = I.d_where[0];
               d.na = I.n_allowed[0];
-              d.ib = I.d_allowed[1];
+              d.ib = I.d_where[1];
               d.nb = I.n_allowed[1];
               d.second = n * n;
             }

@@ -104,6 +104,7 @@ void rk_combine(ftcc_ctx* c, int kind, int p, int x, double sigma, bool track,
         r.rank = seg ? 4 : 2;
         r.len = seg_len(c, i, seg);
         r.idx = I.d_allowed[seg];
+        r.pack = c->packed_states ? (unsigned)I.n : 0u;
         r.base = sp.base ? sp.base + off : nullptr;
         r.x0 = sp.x0;
         r.h_x0 = sp.per_x0 ? c->d_rkh + i : nullptr;

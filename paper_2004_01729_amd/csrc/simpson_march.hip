@@ -54,6 +54,7 @@ void expsum_run(ftcc_ctx* c, long key, const std::function<ExpSpec(int)>& spec) 
         p.rank = seg ? 4 : 2;
         p.len = seg_len(c, i, seg);
         p.idx = I.d_allowed[seg];
+        p.pack = c->packed_states ? (unsigned)I.n : 0u;
         p.h = I.beta / c->P;
         p.mode = sp.mode;
         p.base = sp.base ? sp.base + off : nullptr;

@@ -53,6 +53,8 @@ struct TauProblem {
   double* partial;              // TAU_BETA: one partial sum per block
   const unsigned* idx;          // optional: the elements to visit (momentum-allowed ones), len of them;
                                 // nullptr: every element 0..len-1
+  unsigned pack;                // 0, or n: element e lies at e / n of the segments (the last index,
+                                // fixed by the others, is not stored)
 };
 
 // elements per block of a launch (per problem); d_rule is a device copy of the rule
@@ -82,6 +84,7 @@ struct RKProblem {
   const double* Y[kMaxStages];
   const double* S[kMaxStages];
   double sigma;
+  unsigned pack;                 // as in TauProblem
   const double* h_x0;            // optional device factor of x0, of every coef
   const double* h_coef;
   double* out;
@@ -107,6 +110,7 @@ struct ExpTerm {
   double k;
 };
 struct ExpSumProblem {
+  unsigned pack;         // as in TauProblem
   const double* eps;
   int n;
   int rank;                      // 2 or 4
@@ -146,6 +150,9 @@ struct StateCopy {
 };
 constexpr long kStateCopyBlock = 1024;   // elements per block
 void launch_state_copies(const StateCopy* d_copies, const int* d_prefix, int n, int blocks, hipStream_t s);
+
+void launch_repack(const unsigned* list, long count, int n, double* dense, double* packed, bool to_packed,
+                   hipStream_t s);
 
 // One instance's thermal set-up: occupations and weights from (mu, beta), the Fock
 // operator f_pq = h_pq + sum_r (g <pr|qr> - <pr|rq>) n_r (g = 2: spin-restricted

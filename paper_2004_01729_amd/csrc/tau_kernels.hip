@@ -166,20 +166,21 @@ __global__ void __launch_bounds__(256) tau_kernel(const PanelRule* __restrict__ 
   for (int u = 0; u < IT; ++u) {
     const long ei = base + u * 256 + threadIdx.x;
     if (ei >= P.len) break;
-    const long e = P.idx ? (long)gview(P.idx)[ei] : ei;   // element offset in the segment
-    const double sb = P.sb ? gview(P.sb)[e] : 0.0;
+    const long e = P.idx ? (long)gview(P.idx)[ei] : ei;   // element of the segment, and where it lies
+    const long at = P.pack ? (long)((unsigned)e / P.pack) : e;
+    const double sb = P.sb ? gview(P.sb)[at] : 0.0;
     double Sv[M];
     bool any = (sb != 0.0);
     for (int y = 0; y < m; ++y) {
-      Sv[y] = P.S[y] ? gview(P.S[y])[e] : 0.0;
+      Sv[y] = P.S[y] ? gview(P.S[y])[at] : 0.0;
       any = any || (Sv[y] != 0.0);
     }
     if (mode == TAU_LSTEP || mode == TAU_LSWEEP) {
       for (int x = 0; x < m; ++x) {
-        const double nv = -gview(P.R[x])[e];
-        mchg = nan_max(mchg, fabs(nv - gview(P.s[x])[e]));
+        const double nv = -gview(P.R[x])[at];
+        mchg = nan_max(mchg, fabs(nv - gview(P.s[x])[at]));
         mval = nan_max(mval, fabs(nv));
-        gview(P.s[x])[e] = nv;
+        gview(P.s[x])[at] = nv;
         Sv[x] = nv;
         any = any || nv != 0.0;
       }
@@ -187,9 +188,9 @@ __global__ void __launch_bounds__(256) tau_kernel(const PanelRule* __restrict__ 
     }
     if ((IT == 4 && mode == TAU_BETA) || (IT == 1 && mode == TAU_DEPS)) {
       double Rv[M];
-      bool anyb = any || (P.lam_a && gview(P.lam_a)[e] != 0.0);
+      bool anyb = any || (P.lam_a && gview(P.lam_a)[at] != 0.0);
       for (int y = 0; y < m; ++y) {
-        Rv[y] = gview(P.R[y])[e];
+        Rv[y] = gview(P.R[y])[at];
         anyb = anyb || (Rv[y] != 0.0);
       }
       if (!anyb) continue;
@@ -206,59 +207,59 @@ __global__ void __launch_bounds__(256) tau_kernel(const PanelRule* __restrict__ 
         double f = (sb != 0.0) ? -w.Ee * sb : 0.0;
         for (int y = 0; y < m; ++y)
           if (Rv[y] != 0.0) f += w.We[y] * Rv[y];
-        val += gview(P.lam_a)[e] * f;
+        val += gview(P.lam_a)[at] * f;
       }
       if (mode == TAU_BETA) acc += val;
-      else gview(P.out)[e] += val;
+      else gview(P.out)[at] += val;
       continue;
     }
     if (IT == 4) continue;   // TAU_BETA only
     if (!any) {
       // structurally zero (dropped slots, or zero start): outputs stay zero
       if (mode == TAU_LSWEEP) {
-        for (int x = 0; x < m; ++x) gview(P.lamt[x])[e] = 0.0;
+        for (int x = 0; x < m; ++x) gview(P.lamt[x])[at] = 0.0;
       } else if (mode == TAU_INIT || mode == TAU_LAMT) {
-        for (int x = 0; x < m; ++x) gview(P.s[x])[e] = 0.0;
+        for (int x = 0; x < m; ++x) gview(P.s[x])[at] = 0.0;
       } else if (mode == TAU_STEP) {
         for (int x = 0; x < m; ++x) {
-          mchg = nan_max(mchg, fabs(gview(P.s[x])[e]));
-          gview(P.s[x])[e] = 0.0;
+          mchg = nan_max(mchg, fabs(gview(P.s[x])[at]));
+          gview(P.s[x])[at] = 0.0;
         }
       } else {
-        gview(P.out)[e] = 0.0;
+        gview(P.out)[at] = 0.0;
       }
       continue;
     }
     Weights<M> w;
     weights<M>(R, delta_of(P, e), P.h, w, 0, mode != TAU_INIT && mode != TAU_STEP);
     if (mode == TAU_INIT) {
-      for (int x = 0; x < m; ++x) gview(P.s[x])[e] = (sb != 0.0) ? w.E[x] * sb : 0.0;
+      for (int x = 0; x < m; ++x) gview(P.s[x])[at] = (sb != 0.0) ? w.E[x] * sb : 0.0;
     } else if (mode == TAU_STEP) {
       for (int x = 0; x < m; ++x) {
         double v = (sb != 0.0) ? w.E[x] * sb : 0.0;
         for (int y = 0; y < m; ++y)
           if (Sv[y] != 0.0) v -= w.W[x][y] * Sv[y];
-        mchg = nan_max(mchg, fabs(v - gview(P.s[x])[e]));
+        mchg = nan_max(mchg, fabs(v - gview(P.s[x])[at]));
         mval = nan_max(mval, fabs(v));
-        gview(P.s[x])[e] = v;
+        gview(P.s[x])[at] = v;
       }
     } else if (mode == TAU_END) {
       double v = (sb != 0.0) ? w.Ee * sb : 0.0;
       for (int y = 0; y < m; ++y)
         if (Sv[y] != 0.0) v -= w.We[y] * Sv[y];
-      gview(P.out)[e] = v;
+      gview(P.out)[at] = v;
     } else if (mode == TAU_LAMT || mode == TAU_LSWEEP) {
       for (int x = 0; x < m; ++x) {
         double v = (sb != 0.0) ? w.We[x] * sb : 0.0;
         for (int y = 0; y < m; ++y)
           if (Sv[y] != 0.0) v += w.W[y][x] * Sv[y];
-        gview(mode == TAU_LAMT ? P.s[x] : P.lamt[x])[e] = v;
+        gview(mode == TAU_LAMT ? P.s[x] : P.lamt[x])[at] = v;
       }
     } else if (mode == TAU_APREV) {
       double v = (sb != 0.0) ? w.Ee * sb : 0.0;
       for (int x = 0; x < m; ++x)
         if (Sv[x] != 0.0) v += w.E[x] * Sv[x];
-      gview(P.out)[e] = v;
+      gview(P.out)[at] = v;
     }
   }
   // block reductions
@@ -331,15 +332,16 @@ __global__ void __launch_bounds__(256) rk_combine_kernel(const RKProblem* __rest
   double vmax = 0.0;
   if (ei < P.len) {
     const long e = P.idx ? (long)gview(P.idx)[ei] : ei;
+    const long at = P.pack ? (long)((unsigned)e / P.pack) : e;
     const double d = seg_delta(P.eps, P.n, P.rank, e);
     const double hx = P.h_x0 ? *gview(P.h_x0) : 1.0, hc = P.h_coef ? *gview(P.h_coef) : 1.0;
-    double v = P.base ? hx * P.x0 * gview(P.base)[e] : 0.0;
+    double v = P.base ? hx * P.x0 * gview(P.base)[at] : 0.0;
     for (int l = 0; l < P.nst; ++l) {
-      const double y = P.Y[l] ? gview(P.Y[l])[e] : 0.0;
-      const double sv = P.S[l] ? gview(P.S[l])[e] : 0.0;
+      const double y = P.Y[l] ? gview(P.Y[l])[at] : 0.0;
+      const double sv = P.S[l] ? gview(P.S[l])[at] : 0.0;
       v += hc * P.coef[l] * (-d * y + P.sigma * sv);
     }
-    gview(P.out)[e] = v;
+    gview(P.out)[at] = v;
     vmax = fabs(v);
   }
   if (!P.maxbits) return;   // uniform per launch problem
@@ -374,11 +376,12 @@ __global__ void __launch_bounds__(256) expsum_kernel(const ExpSumProblem* __rest
     const long ei = first + u * 256 + threadIdx.x;
     if (ei >= P.len) break;
     const long e = P.idx ? (long)gview(P.idx)[ei] : ei;
+    const long at = P.pack ? (long)((unsigned)e / P.pack) : e;
     const double d = seg_delta(P.eps, P.n, P.rank, e);
     double acc = 0.0;
     for (int l = 0; l < P.nterms; ++l) {
       const ExpTerm t = P.terms[l];
-      const double x = gview(t.X)[e];
+      const double x = gview(t.X)[at];
       if (x == 0.0) continue;
       const double z = d * P.h * t.k;
       const double ex = exp(-z);
@@ -386,10 +389,10 @@ __global__ void __launch_bounds__(256) expsum_kernel(const ExpSumProblem* __rest
                                    : (P.mode == 1 ? t.C * ex * (1.0 - z) : -P.h * P.h * t.C * t.k * ex);
       acc += f * x;
     }
-    if (P.prod) acc *= gview(P.prod)[e];
-    const double v = (P.base ? P.x0 * gview(P.base)[e] : 0.0) + acc;
-    if (P.maxbits) cmax = nan_max(cmax, fabs(v - gview(P.out)[e]));
-    gview(P.out)[e] = v;
+    if (P.prod) acc *= gview(P.prod)[at];
+    const double v = (P.base ? P.x0 * gview(P.base)[at] : 0.0) + acc;
+    if (P.maxbits) cmax = nan_max(cmax, fabs(v - gview(P.out)[at]));
+    gview(P.out)[at] = v;
     vmax = nan_max(vmax, fabs(v));
   }
   if (!P.maxbits) return;   // uniform per launch problem
@@ -430,6 +433,25 @@ void launch_copy_listed(const unsigned* a, long na, const unsigned* b, long nb, 
   if (total <= 0) return;
   hipLaunchKernelGGL(copy_listed_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s, a, na, b, nb,
                      second, src, dst);
+}
+
+// A segment between dense storage and storage without the last index: the allowed
+// elements `list`, dense element e against packed element e / n.
+__global__ void __launch_bounds__(256) repack_kernel(const unsigned* __restrict__ list, long count, unsigned n,
+                                                     double* __restrict__ dense, double* __restrict__ packed,
+                                                     bool to_packed) {
+  const long k = (long)blockIdx.x * 256 + threadIdx.x;
+  if (k >= count) return;
+  const unsigned e = gview(list)[k];
+  if (to_packed) gview(packed)[e / n] = gview(dense)[e];
+  else gview(dense)[e] = gview(packed)[e / n];
+}
+
+void launch_repack(const unsigned* list, long count, int n, double* dense, double* packed, bool to_packed,
+                   hipStream_t s) {
+  if (count <= 0) return;
+  hipLaunchKernelGGL(repack_kernel, dim3((unsigned)((count + 255) / 256)), dim3(256), 0, s, list, count, (unsigned)n,
+                     dense, packed, to_packed);
 }
 
 // ------------------------------------------------------------------ thermal quantities

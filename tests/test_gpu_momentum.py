@@ -219,3 +219,30 @@ def test_packed_storage_changes_no_result(F, monkeypatch):
     for key in ("h", "eps"):
         for x, y in zip(r0[key], r1[key]):
             assert np.array_equal(x, y)
+
+
+@pytest.mark.parametrize("propagator", [0, 3, 4, 5])
+def test_packed_states_change_no_result(F, monkeypatch, propagator):
+    """Node states without the last index (labels all distinct) against dense ones
+    (FTCC_PACK=0), every form of the march: the same elements in the same order, so the
+    bits of amplitudes, Lambda, response and two-body density are the same."""
+    s = fi.hubbard_config(L=5, U=2.0, T=1.0)
+    out = []
+    for pack in ("1", "0"):
+        monkeypatch.setenv("FTCC_PACK", pack)
+        print(f"[momentum] packed states propagator={propagator} FTCC_PACK={pack}", flush=True)
+        ctx = _ctx(F, [s], n_tau=6, nodes_per_panel=3, propagator=propagator, tol=1e-12)
+        ctx.solve(s.mu, s.beta)
+        res = [ctx.grand_potential()[0], *ctx.amplitudes(0, 4)]
+        ctx.lam()
+        res += [x for x in ctx.get_lambda(0, 3, tilde=propagator in (0, 5)) if x is not None]
+        r = ctx.response(want_mu=True, want_beta=True, want_h=True, want_eps=True)
+        res += [r["mu"], r["beta"], *r["h"], *r["eps"]]
+        if propagator != 5:
+            res += list(ctx.two_body_density())
+        t1, t2 = res[1], res[2]
+        res += list(ctx.eval_residual(0, s.mu, s.beta, t1, t2))
+        ctx.close()
+        out.append(res)
+    for a, b in zip(*out):
+        assert np.array_equal(a, b)
