@@ -367,6 +367,12 @@ __global__ void __launch_bounds__(256) gemm_tail_reduce_kernel(const GemmProblem
   }
 }
 
+// Momentum-blocked tiles: one wave per 16 x 16 output tile (32 x 32 in launches of many
+// blocks), or per chunk of a long inner range (its partial tile then goes to the
+// workspace and sgemm_reduce_kernel adds the chunks); operands are gathered through the
+// block's offset lists straight into MFMA fragments (the blocks are small, so nothing
+// is staged in LDS).  No barriers: waves leave independently.
+
 // One wave's tile of H x H MFMA tiles (16 x 16 each).  What a task waits for is its
 // chain of dependent loads, so all of its offsets are loaded at once: each lane holds
 // those of one row, one column and one inner index (two loads give 64 inner indices,
@@ -467,12 +473,7 @@ __device__ __forceinline__ void wave_tile(const SgemmProblem& P, const SgemmTask
       C[cm[i / H] + cn[i % H]] = P.alpha * acc[i / (4 * H)][i % H][(i / H) & 3] + P.beta * cv[i];
 }
 
-// Momentum-blocked tiles: one wave per 16 x 16 output tile, or per chunk of a
-// long inner range (its partial tile then goes to the workspace and
-// sgemm_reduce_kernel adds the chunks); operands are gathered through the
-// block's offset lists straight into MFMA fragments (the blocks are small, so
-// nothing is staged in LDS).  No barriers: waves leave independently.  WIDE: the
-// launch has 32 x 32 tiles too (the others run with fewer registers without them).
+// WIDE: the launch has 32 x 32 tiles too (the others run with fewer registers without them).
 template <bool WIDE>
 __global__ void __launch_bounds__(256, WIDE ? 4 : 1) sgemm_kernel(const SgemmProblem* __restrict__ probs,
                                                     const SgemmTask* __restrict__ tasks, int n_tasks,

@@ -144,3 +144,31 @@ def test_rk_option_errors(F):
     with pytest.raises(F.FTCCError):
         ctx.amplitudes(0, 5)
     ctx.close()
+
+
+@pytest.mark.parametrize("propagator", [0, 2, 4, 5])
+@pytest.mark.parametrize("labels", [False, True])
+def test_second_solve_at_another_temperature(propagator, labels):
+    """Descriptors and launch lists outlive a solve; the step length does not: a second
+    solve at another beta and mu gives the bits of a fresh context's first."""
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2004_01729_amd import ftcc as F
+    s = fi.hubbard_config(L=4, U=2.0, T=1.0)
+    out = []
+    for points in ([(s.mu, s.beta), (s.mu + 0.1, 0.7 * s.beta)], [(s.mu + 0.1, 0.7 * s.beta)]):
+        print(f"[rk] propagator={propagator} labels={labels} points={len(points)}", flush=True)
+        ctx = F.Context(1, n_tau=6, nodes_per_panel=3, propagator=propagator, tol=1e-12)
+        if labels:
+            ctx.set_momentum(0, *s.momentum)
+        ctx.set_hamiltonian(0, s.h, s.eri, s.eps)
+        for mu, beta in points:
+            ctx.solve(mu, beta)
+            om = ctx.grand_potential()[0]
+            ctx.lam()
+            r = ctx.response(want_mu=True, want_beta=True, want_h=True)
+        out.append([om, r["mu"], r["beta"], *r["h"], *ctx.amplitudes(0, 2)])
+        ctx.close()
+    for a, b in zip(*out):
+        assert np.array_equal(a, b)
