@@ -1798,8 +1798,9 @@ void Executor::lower_one(std::vector<Launch>& dst, const OpInst& o, const PerPro
 // is taken together: contractions write private copies (the first one the buffer
 // itself), and one elementwise sum adds the copies and the elementwise terms in op
 // order.  A contraction whose operands are ready later than everything else
-// accumulates in place after that sum.  27 -> 13 dispatches per forward pass of the
-// restricted program, 40 -> 21 per reverse pass.  Copies are taken only while memory
+// accumulates in place after that sum.  27 -> 14 launches per forward pass of the
+// restricted program at 6 orbitals (6 sums, 6 contraction levels, 2 dots), 40 -> 13 per
+// reverse pass.  Copies are taken only while memory
 // is plentiful (cache_alloc); without them the writes are serial.
 void Executor::lower(std::vector<Launch>& dst, const std::vector<OpInst>& ops, const std::vector<int>& zeroed,
                      const std::vector<PerProb>& zero_bufs) {

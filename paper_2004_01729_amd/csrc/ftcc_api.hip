@@ -891,9 +891,10 @@ void build(ftcc_ctx* c) {
   auto calloc_ = [c](int, size_t count) { return c->dalloc(count); };
   // Small dense problems take the blocked executor's path as well, everything in one
   // block: no operand or output is permuted and independent contractions share
-  // launches.  Four nodes' residuals, GEMM path against this one: n = 8 0.401 / 0.106
-  // ms, 16 0.646 / 0.248, 24 1.40 / 0.80, 32 3.23 / 2.68, 40 8.81 / 8.77, 44 13.7 /
-  // 15.2, 57 50.7 / 64.5: beyond 40 the 128 x 128 tiles of the GEMM path win.
+  // launches.  Four nodes' residuals, GEMM path against this one: n = 8 0.409 / 0.119
+  // ms, 16 0.633 / 0.265, 24 1.21 / 0.72, 32 2.61 / 2.26, 40 7.88 / 6.83, 48 18.2 / 17.7,
+  // 50 22.8 / 23.9; one node alone (41: 6.4 / 8.5 with the copies) wins on the 128 x 128
+  // tiles of the GEMM path, whose launches take one problem, so the line lies at 40.
   // FTCC_DENSE_LEVELS=N: up to n = N (diagnostics; 0: never).
   int nmax = 0;
   for (const Instance& I : c->inst) nmax = std::max(nmax, I.n);
