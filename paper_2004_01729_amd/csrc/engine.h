@@ -381,6 +381,7 @@ class Executor {
                               const std::string& xi, bool xp);
   const unsigned* zero_offset();
   bool flat_lists(int rank) const;
+  bool flat_sums(int rank, const std::vector<int>& signs);
   std::vector<char> packed_;               // per tensor: stored packed (n^(rank-1) doubles)
   bool pack_on_ = false;                   // packing applies to this executor's problems
   bool one_per_label_ = false;             // every orbital of every instance has its own label

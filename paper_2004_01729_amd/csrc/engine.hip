@@ -975,9 +975,9 @@ const Executor::GroupTable& Executor::group_table(int inst, long n, const std::s
   return group_cache_.emplace(key, std::move(T)).first->second;
 }
 
-// Every orbital with a label of its own: the tuples (one byte per index) with
-// sum_l signs[l] k(index_l) = 0, lexicographically; the last index follows from the
-// others.  At most four letters.
+// The tuples (one byte per index) with sum_l signs[l] k(index_l) = 0,
+// lexicographically: the last index runs over the orbitals of the label that the others
+// leave.  At most four letters.
 const std::vector<unsigned>& Executor::allowed_tuples(int inst, long n, const std::vector<int>& signs) {
   inst = same_labels_[inst];
   std::string key = std::to_string(inst) + "|";
@@ -1005,8 +1005,8 @@ const std::vector<unsigned>& Executor::allowed_tuples(int inst, long n, const st
   }
   // wide label ranges (any integers are allowed) are looked up in a map instead
   const bool dense = box <= (1L << 22);
-  std::vector<int> at(dense ? box : 0, -1);
-  std::unordered_map<long, int> far;
+  std::vector<std::vector<int>> at(dense ? box : 0);   // orbitals of each label, ascending
+  std::unordered_map<long, std::vector<int>> far;
   auto slot = [&](const int* v) -> long {
     long o = 0;
     for (int c = 0; c < D; ++c) {
@@ -1017,7 +1017,8 @@ const std::vector<unsigned>& Executor::allowed_tuples(int inst, long n, const st
   };
   for (long p = 0; p < n; ++p) {
     const long o = slot(&lab[p * D]);
-    if (dense) at[o] = (int)p; else far[o] = (int)p;
+    if (dense) at[o].push_back((int)p);
+    else far[o].push_back((int)p);
   }
   std::vector<unsigned> out;
   std::vector<int> idx(g, 0), v(D);
@@ -1031,16 +1032,17 @@ const std::vector<unsigned>& Executor::allowed_tuples(int inst, long n, const st
     }
     for (int c = 0; c < D; ++c) v[c] = reduced(-signs[g - 1] * v[c], c);
     const long o = slot(v.data());
-    int last = -1;
+    const std::vector<int>* last = nullptr;
     if (o >= 0) {
       if (dense) {
-        last = at[o];
+        last = &at[o];
       } else {
         auto f = far.find(o);
-        if (f != far.end()) last = f->second;
+        if (f != far.end()) last = &f->second;
       }
     }
-    if (last >= 0) out.push_back(packed | (unsigned)last << (8 * (g - 1)));
+    if (last)
+      for (int p : *last) out.push_back(packed | (unsigned)p << (8 * (g - 1)));
     for (int l = g - 2; l >= 0; --l) {
       if (++idx[l] < n) break;
       idx[l] = 0;
@@ -1371,6 +1373,18 @@ bool Executor::elem_blocked(std::vector<Launch>& dst, const PerProb& X, const st
 // each, and finding an element's task took longer than its value.
 bool Executor::flat_lists(int rank) const { return one_per_label_ && rank >= 2 && rank <= 4; }
 
+// Sums do so for other problems of at most kFlatElements elements too: their launches are
+// as much bound by the chain of dependent loads (6 dense orbitals, a step: 13.35 -> 12.9 ms; a
+// spin ring of 12 21.4 -> 20.8); larger ones would read as many offsets as values.
+constexpr size_t kFlatElements = 1 << 17;
+bool Executor::flat_sums(int rank, const std::vector<int>& signs) {
+  if (flat_lists(rank)) return true;
+  if (rank < 2 || rank > 4) return false;
+  for (const ProblemRef& p : probs_)
+    if (ipow(p.n, rank) > (1L << 20) || allowed_tuples(p.inst, p.n, signs).size() > kFlatElements) return false;
+  return true;
+}
+
 // Y[yi] = beta Y + sum_s alpha_s X_s[xi_s] over the allowed elements of Y (its law known):
 // Y's letters split into two halves whose momentum blocks q and -q pair up.
 // Returns false (dense lowering) when a law is unknown.
@@ -1394,7 +1408,7 @@ bool Executor::sum_blocked(std::vector<Launch>& dst, const std::vector<SumTerm>&
   const int np = (int)probs_.size();
   Launch L;
   double elements = 0.0;
-  const bool flat = flat_lists((int)yi.size());
+  const bool flat = flat_sums((int)yi.size(), ly);
   for (int p = 0; p < np; ++p) {
     const int inst = probs_[p].inst;
     const long n = probs_[p].n;
