@@ -8,9 +8,13 @@
 //   permute4       grouped 4-index transpose-accumulate Y[perm] = alpha X + beta Y,
 //                  LDS-tiled when the fastest index moves
 //   dot            grouped full contractions (two-pass, deterministic)
-//   sgemm, elem,   momentum-blocked contractions over element-offset lists (one wave
-//   dotb           per 16x16 MFMA tile), unary ops and full contractions over the
-//                  momentum-allowed elements
+//   sgemm_tile     contractions over element-offset lists, large blocks: one block per
+//                  64x64, 128x32 or 32x128 outputs, operands gathered into LDS
+//   sgemm          the same, smaller blocks: a wave per 16x16 or 32x32 MFMA tile or per
+//                  lane-mapped thin tile; sgemm_reduce adds the parts of split ranges
+//   elem, elem4,   elementwise sums over the allowed elements: tasks of index-group
+//   elem_flat      pairs, four elements a thread, one element list per problem
+//   dotb           full contractions over the allowed elements
 //
 // The imaginary-time kernels (thermal blocks, propagator, adjoint) are in
 // tau_kernels.hip.
