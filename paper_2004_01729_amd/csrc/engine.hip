@@ -1250,6 +1250,8 @@ bool Executor::contract_blocked(std::vector<Launch>& dst, const PerProb& out, co
     // Waves of 32 x 32 gather each operand element half as often; they pay where a
     // problem alone still has a wave for every CU (81 labelled orbitals, forward: 38.4 ->
     // 35.3 ms; 57, step: 48.0 -> 47.0), not where its parallelism is short (33: 216 -> 223).
+    // They take inner ranges of up to 192 whole: 16 x 16 tiles in parts of 64 and their sum
+    // cost a step of 123 labelled orbitals 750 ms against 716.
     const bool wide = n_wave >= 256;
     for (const Block& b : blocks) {
       const int m0 = b.m0, ml = b.ml, k0 = b.k0, kl = b.kl, n0 = b.n0, nl = b.nl;
@@ -1266,7 +1268,7 @@ bool Executor::contract_blocked(std::vector<Launch>& dst, const PerProb& out, co
         shape = thin_ok ? sgemm_shape(ml, nl, kl, thin_cap) : 0;
         R = shape ? 1 << (shape & 7) : 16;
         C = shape ? 1 << ((shape >> 3) & 7) : 16;
-        if (wide && !shape && std::min(ml, nl) > 16 && kl <= kSgemmChunk + kSgemmChunk / 2) {
+        if (wide && !shape && std::min(ml, nl) > 16 && kl <= 3 * kSgemmChunk) {
           shape = kWave32x32;
           R = C = 32;
         }
