@@ -2214,7 +2214,7 @@ int ftcc_response(ftcc_ctx* c, double* dO_dmu, double* dO_dbeta, double* dO_dh, 
       // the reverse march has summed the gradients of the u blocks over the same stages
       if (dO_dh)
         for (int i = 0; i < B; ++i)
-          for (int q = 0; q < 4; ++q)
+          for (int q = 0; q < 4 && ok[i]; ++q)
             launch_axpby((long)c->inst[i].n * c->inst[i].n, 1.0, c->inst[i].rk_ugrad[q], 1.0, c->inst[i].ugrad_acc[q],
                          c->stream);
       for (int k = 0; k <= P; ++k) {

@@ -276,9 +276,9 @@ void rk_lambda(ftcc_ctx* c, std::vector<int>& status) {
   // final grid point: only the energy term
   rk_stage_state(c, P, 0);
   for (int i = 0; i < B; ++i) {
-    if (!ok[i]) continue;
-    zero_d(c, c->s_cot[i], node_len(c, i));
+    // an instance that does not run keeps nothing of an earlier solve
     for (int k = 0; k < 4; ++k) zero_d(c, c->inst[i].rk_ugrad[k], (long)c->inst[i].n * c->inst[i].n);
+    if (ok[i]) zero_d(c, c->s_cot[i], node_len(c, i));
   }
   backward_one(c, 0, P, true);
   for (int i = 0; i < B; ++i)

@@ -172,3 +172,29 @@ def test_second_solve_at_another_temperature(propagator, labels):
         ctx.close()
     for a, b in zip(*out):
         assert np.array_equal(a, b)
+
+
+@pytest.mark.parametrize("propagator", [3, 4])
+def test_failed_instance_holds_nothing_of_an_earlier_solve(F, propagator):
+    """A second solve in which one instance diverges: its dOmega/dh is the mean-field part,
+    bit for bit that of a context that never solved before (the gradients that the first
+    solve's reverse march summed are gone), and the good instance's is unaffected."""
+    h, eri, eps = fi.random_hamiltonian(11, seed=4, scale=0.05)
+    bad = fi.System("random11", h, eri, eps, 0.1, 2.0)
+    good = fi.hubbard_config(L=4, U=2.0, T=1.0)
+    out = []
+    for betas in ([0.1, 20.0], [20.0]):
+        ctx = F.Context(2, n_tau=6, propagator=propagator)
+        for i, s in enumerate((bad, good)):
+            ctx.set_hamiltonian(i, s.h, s.eri, s.eps)
+        for beta in betas:
+            print(f"[rk] random n=11 beta={beta} + hubbard L=4 propagator={propagator}", flush=True)
+            _, st = ctx.solve([bad.mu, good.mu], [beta, good.beta], raise_on_status=False)
+            assert st[1] == 0 and (st[0] == 0) == (beta == 0.1)
+            ctx.lam(raise_on_status=False)
+            r = ctx.response(want_h=True)
+        ctx.close()
+        out.append(r["h"])
+    for a, b in zip(*out):
+        assert np.array_equal(a, b)
+    assert np.isfinite(out[0][0]).all() and np.count_nonzero(out[0][0] - np.diag(np.diag(out[0][0]))) == 0
