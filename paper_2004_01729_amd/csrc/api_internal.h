@@ -222,7 +222,8 @@ struct ftcc_ctx {
   }
 
   // launch descriptors and other small tables: the library's own, outside the caller's
-  // allocator and the cap, kept until the context is destroyed
+  // allocator and the cap, kept until the context is destroyed.  host null: not written
+  // here (a clear on the null stream would not be ordered before the work of c->stream).
   std::vector<void*> descs;
   char* desc_at = nullptr;        // the free part of the last chunk
   size_t desc_left = 0;
@@ -240,7 +241,6 @@ struct ftcc_ctx {
     desc_at += need;
     desc_left -= need;
     if (host) FTCC_HIP(hipMemcpy(p, host, nbytes, hipMemcpyHostToDevice));
-    else FTCC_HIP(hipMemset(p, 0, nbytes));
     return p;
   }
 

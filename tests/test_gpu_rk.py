@@ -198,3 +198,20 @@ def test_failed_instance_holds_nothing_of_an_earlier_solve(F, propagator):
     for a, b in zip(*out):
         assert np.array_equal(a, b)
     assert np.isfinite(out[0][0]).all() and np.count_nonzero(out[0][0] - np.diag(np.diag(out[0][0]))) == 0
+
+
+@pytest.mark.parametrize("propagator", [0, 4, 5])
+def test_first_response_of_a_context_equals_the_second(F, propagator):
+    """The buffers that the first response allocates are written in full before they are
+    read: the second response, which finds them there, gives the same bits."""
+    s = fi.hubbard_config(L=4, U=2.0, T=1.0)
+    print(f"[rk] two responses propagator={propagator}", flush=True)
+    ctx = F.Context(1, n_tau=6, nodes_per_panel=3, propagator=propagator)
+    ctx.set_hamiltonian(0, s.h, s.eri, s.eps)
+    ctx.solve(s.mu, s.beta)
+    ctx.lam()
+    out = [ctx.response(want_mu=True, want_beta=True, want_h=True) for _ in range(2)]
+    ctx.close()
+    for key in ("mu", "beta"):
+        assert np.array_equal(out[0][key], out[1][key])
+    assert np.array_equal(out[0]["h"][0], out[1]["h"][0]) and np.abs(out[0]["h"][0]).max() > 0.1
