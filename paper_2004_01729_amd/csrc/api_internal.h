@@ -158,7 +158,6 @@ struct ftcc_ctx {
   // propagator 56 -> 26 us a sweep); 57, step 40.8 -> 35.7; 33, Runge-Kutta 121.5 -> 107.7.
   bool packed_states = false;
   double* dense_node = nullptr;
-  std::vector<double*> g_amp, g_cot;          // the density's dense node amplitudes and cotangents
   int* d_active = nullptr;                    // [B] propagator step flags
   int* d_run = nullptr;                       // [B slots] residual-program run flags (executor gate)
   std::vector<int> run_host;                  // [B] which instances run

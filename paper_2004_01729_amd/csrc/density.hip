@@ -71,12 +71,6 @@ void build_gamma_executor(ftcc_ctx* c) {
     for (int x = 0; x < SL; ++x) probs.push_back({i, x, c->inst[i].n});
   const int id_t1 = prog.id("t1"), id_t2 = prog.id("t2"), id_S1 = prog.id("S1"), id_S2 = prog.id("S2"),
             id_E = prog.id("E");
-  std::vector<double*> g_gr = c->s_gr, g_S = c->s_S;
-  c->g_amp = c->s_amp;
-  c->g_cot = c->s_cot;
-  if (c->packed_states)
-    for (size_t p = 0; p < probs.size(); ++p)
-      for (double** q : {&c->g_amp[p], &c->g_cot[p], &g_gr[p], &g_S[p]}) *q = c->dalloc(node_len(c, probs[p].inst));
   auto buf = [c](std::map<std::pair<int, int>, double*>& store, int t, int key, long count) {
     return shared_buf(c, store, t, key, count);
   };
@@ -84,11 +78,10 @@ void build_gamma_executor(ftcc_ctx* c) {
     const TensorDecl& d = prog.t[t];
     const int i = probs[p].inst;
     const long n = probs[p].n, n2 = n * n, cnt = ipow(n, d.rank);
-    // dense storage, whatever the node states have
-    if (t == id_t1) return grad ? g_gr[p] : c->g_amp[p];
-    if (t == id_t2) return grad ? g_gr[p] + n2 : c->g_amp[p] + n2;
-    if (t == id_S1) return grad ? c->g_cot[p] : g_S[p];
-    if (t == id_S2) return grad ? c->g_cot[p] + n2 : g_S[p] + n2;
+    if (t == id_t1) return grad ? c->s_gr[p] : c->s_amp[p];
+    if (t == id_t2) return grad ? c->s_gr[p] + n2 : c->s_amp[p] + n2;
+    if (t == id_S1) return grad ? c->s_cot[p] : c->s_S[p];
+    if (t == id_S2) return grad ? c->s_cot[p] + n2 : c->s_S[p] + n2;
     if (t == id_E) return grad ? c->s_ebar[p] : c->s_e[p];
     if (d.kind == T_CONST) return grad ? buf(c->g_cgrad, t, p, cnt) : c->inst[i].blk[d.name];
     if (d.derived) return buf(grad ? c->g_cgrad : c->g_derived, t, p, cnt);
@@ -107,6 +100,7 @@ void build_gamma_executor(ftcc_ctx* c) {
   };
   std::unique_ptr<Executor> ex(new Executor());
   ex->set_inline_setup(true);
+  ex->set_packed_io(c->packed_states);
   ex->set_gate(c->d_run, c->run_slots.data());
   if (momentum_on(c)) {
     std::vector<const InstMomentum*> by_inst;
@@ -128,11 +122,6 @@ void build_gamma_executor(ftcc_ctx* c) {
 // ugrad_acc, g blocks into gacc)
 void gamma_pass(ftcc_ctx* c) {
   const Program& prog = c->prog;
-  if (c->packed_states)
-    for (int q = 0; q < c->B * c->slots; ++q) {
-      dense_state(c, q / c->slots, c->g_amp[q], c->s_amp[q]);
-      dense_state(c, q / c->slots, c->g_cot[q], c->s_cot[q]);
-    }
   c->ex_g->run_forward(c->stream);
   c->ex_g->run_backward(c->stream);
   const int SL = c->slots;

@@ -790,7 +790,7 @@ std::vector<int> Executor::plan_const_packing(const std::vector<int>& const_grad
 
 std::vector<int> Executor::plan_io_packing() const {
   std::vector<int> out;
-  if (!pack_on_ || inline_setup_) return out;
+  if (!pack_on_) return out;
   const int nt = (int)prog_->t.size();
   for (int k = 0; k < nt; ++k) {
     const TensorDecl& d = prog_->t[k];
