@@ -115,3 +115,27 @@ def test_wide_wave_tiles(F, L):
         ctx.close()
     for a, b in zip(*out):
         assert _close(a, b)
+
+
+@pytest.mark.parametrize("L", [64, 66, 98])
+def test_wide_wave_tiles_over_long_inner_ranges(F, L):
+    """The same with one panel node: L ceil(L / 16)^2 >= 256 tiles of 16 x 16, so the 32 x 32
+    wave tiles are taken; whole tiles over one batch of 64 inner indices, remainders of 2 in
+    both, and three tiles and a remainder over a range that 16 x 16 tiles would split."""
+    assert L * ((L + 15) // 16) ** 2 >= 256
+    s = fi.hubbard_config(L=L, U=2.0, T=1.0)
+    lab = np.arange(L)
+    t1, t2 = fi.random_amplitudes(L, seed=L, scale=0.05)
+    t1 = np.diag(np.diag(t1))
+    t2 *= (lab[:, None, None, None] + lab[:, None, None] - lab[:, None] - lab) % L == 0
+    out = []
+    for labelled in (True, False):
+        print(f"[levels] ring of {L}, one node, labelled={labelled}", flush=True)
+        ctx = F.Context(1, n_tau=1, nodes_per_panel=1)
+        if labelled:
+            ctx.set_momentum(0, *s.momentum)
+        ctx.set_hamiltonian(0, s.h, s.eri, s.eps)
+        out.append(ctx.eval_residual(0, s.mu, s.beta, t1, t2))
+        ctx.close()
+    for a, b in zip(*out):
+        assert _close(a, b)
