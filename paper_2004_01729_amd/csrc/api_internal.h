@@ -16,6 +16,7 @@
 #include <functional>
 #include <map>
 #include <memory>
+#include <set>
 #include <string>
 #include <tuple>
 #include <vector>
@@ -97,7 +98,15 @@ struct ftcc_ctx {
   PanelRule rule;
   PanelRule* d_rule = nullptr;
   std::vector<Instance> inst;
-  std::vector<void*> allocs;
+  // device buffers, and what each belongs to: what an executor took can be given back
+  enum Owner { OF_CONTEXT, OF_DENSITY };
+  struct Alloc {
+    void* p;
+    size_t bytes;
+    Owner owner;
+  };
+  std::vector<Alloc> allocs;
+  Owner alloc_for = OF_CONTEXT;               // of the buffers allocated now
   Program prog;
   std::vector<InstMomentum> one_block;        // small dense problems: labels that put everything into one block
   std::unique_ptr<Executor> ex_main, ex_d, ex_g;   // ex_g: integral gradients (built on first use)
@@ -216,9 +225,13 @@ struct ftcc_ctx {
     // allowed blocks of their outputs and rely on the forbidden elements being 0
     if (hipMemset(p, 0, nb) != hipSuccess) fail(FTCC_EDEVICE, "hipMemset of a new buffer failed");
     bytes += nb;
-    allocs.push_back(p);
+    allocs.push_back(Alloc{p, nb, alloc_for});
     return (double*)p;
   }
+
+  // Gives the buffers of `owner` back and forgets them wherever they are shared.  A caller's
+  // allocator without a free function reclaims them itself: they only leave the lists.
+  void release(Owner owner);
 
   // launch descriptors and other small tables: the library's own, outside the caller's
   // allocator and the cap, kept until the context is destroyed.  host null: not written
@@ -310,6 +323,7 @@ bool trace_on();
 // a later request for more elements than it holds is an error (executors that
 // share intermediates must agree on their storage)
 double* shared_buf(ftcc_ctx* c, std::map<std::pair<int, int>, double*>& store, int t, int key, long count);
+double* optional_alloc(ftcc_ctx* c, size_t count);
 // FTCC_TRACE=2: a line per sweep as well (the largest change over the batch)
 void trace_sweep(const char* phase, int panel, int it, const std::vector<double>& maxbits);
 void trace(ftcc_ctx* c, const char* phase, int panel, int n_panels, const std::vector<int>& sweeps,
@@ -317,6 +331,13 @@ void trace(ftcc_ctx* c, const char* phase, int panel, int n_panels, const std::v
 void trace_mem(ftcc_ctx* c, const char* stage);
 void trace_executor(ftcc_ctx* c, const char* which, const Executor& ex);
 void sync(ftcc_ctx* c);
+// buffers allocated while it lives belong to `owner`
+struct AllocFor {
+  ftcc_ctx* c;
+  ftcc_ctx::Owner before;
+  AllocFor(ftcc_ctx* ctx, ftcc_ctx::Owner owner) : c(ctx), before(ctx->alloc_for) { c->alloc_for = owner; }
+  ~AllocFor() { c->alloc_for = before; }
+};
 // thermal quantities of every instance, or of one (i >= 0), at its mu and beta
 void thermal_setup(ftcc_ctx* c, int i = -1);
 // derivative blocks of every instance along `which` (SetupDeriv; SETUP_DIR: the directions of

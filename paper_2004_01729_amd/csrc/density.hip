@@ -61,9 +61,10 @@ namespace host {
 // gradients with respect to every constant block (the u and g blocks): the
 // constant combinations are evaluated inside the forward pass so that their
 // gradients reach the raw blocks.  Built on first use; its intermediates share
-// the main executor's buffers (the two never run interleaved).
-void build_gamma_executor(ftcc_ctx* c) {
-  if (c->ex_g) return;
+// the main executor's buffers (the two never run interleaved).  copies: with the
+// optional private copies of accumulated outputs, while memory is plentiful.
+static void build_gamma(ftcc_ctx* c, bool copies) {
+  const AllocFor owner(c, ftcc_ctx::OF_DENSITY);
   const Program& prog = c->prog;
   const int SL = c->slots;
   std::vector<ProblemRef> probs;
@@ -91,12 +92,11 @@ void build_gamma_executor(ftcc_ctx* c) {
   for (int k = 0; k < (int)prog.t.size(); ++k)
     if (prog.t[k].kind == T_CONST) cgrads.push_back(k);
   auto calloc_ = [c](int, size_t count) { return c->dalloc(count); };
-  // private copies of accumulated outputs are optional: only while memory is plentiful
   double reserve = 1073741824.0;
   for (const Instance& I : c->inst) reserve += 16.0 * std::pow((double)I.n, 4) * sizeof(double);
-  auto vcache = [c, reserve](size_t count) -> double* {
-    if (c->opt.mem_cap_bytes || c->available() < 4.0 * reserve + (double)count * sizeof(double)) return nullptr;
-    return c->dalloc(count);
+  auto vcache = [c, copies, reserve](size_t count) -> double* {
+    if (!copies || c->available() < 4.0 * reserve + (double)count * sizeof(double)) return nullptr;
+    return optional_alloc(c, count);
   };
   std::unique_ptr<Executor> ex(new Executor());
   ex->set_inline_setup(true);
@@ -108,12 +108,26 @@ void build_gamma_executor(ftcc_ctx* c) {
     ex->set_momentum(by_inst);
   }
   ex->build(&prog, probs, bind, &c->scratch, calloc_, true, cgrads, vcache, 0);
-  c->ex_g = std::move(ex);
   for (int i = 0; i < c->B; ++i) {
     Instance& I = c->inst[i];
     const long n2 = (long)I.n * I.n;
     for (int k = 0; k < 12; ++k)
       if (!I.gacc[k]) I.gacc[k] = c->dalloc(n2 * n2);
+  }
+  c->ex_g = std::move(ex);
+}
+
+// The optional copies must not cost the call its memory (the free memory of the device
+// says nothing about what a caller's allocator still holds): where something fails to
+// fit, all of it is given back and built again without them.
+void build_gamma_executor(ftcc_ctx* c) {
+  for (bool copies = !c->opt.mem_cap_bytes; !c->ex_g; copies = false) {
+    try {
+      build_gamma(c, copies);
+    } catch (const Fail& f) {
+      c->release(ftcc_ctx::OF_DENSITY);
+      if (f.code != FTCC_ENOMEM || !copies) throw;
+    }
   }
 }
 

@@ -223,6 +223,30 @@ __global__ void post_u64_kernel(unsigned long long* p, unsigned long long* host,
 
 }  // namespace
 
+void ftcc_ctx::release(Owner owner) {
+  FTCC_HIP(hipStreamSynchronize(stream));
+  std::set<const double*> gone;
+  std::vector<Alloc> kept;
+  for (const Alloc& a : allocs) {
+    if (a.owner != owner) {
+      kept.push_back(a);
+      continue;
+    }
+    gone.insert((const double*)a.p);
+    bytes -= a.bytes;
+    if (ufree) ufree(a.p, uuser);
+    else if (!ualloc) (void)hipFree(a.p);
+  }
+  allocs.swap(kept);
+  for (auto* m : {&inter, &inter_grad, &derived, &dderived, &g_derived, &g_cgrad})
+    for (auto it = m->begin(); it != m->end();) it = gone.count(it->second) ? m->erase(it) : std::next(it);
+  for (auto it = buf_elems.begin(); it != buf_elems.end();)
+    it = gone.count(it->first) ? buf_elems.erase(it) : std::next(it);
+  for (Instance& I : inst)
+    for (double*& g : I.gacc)
+      if (gone.count(g)) g = nullptr;
+}
+
 namespace ftcc {
 namespace host {
 
@@ -347,6 +371,16 @@ double* shared_buf(ftcc_ctx* c, std::map<std::pair<int, int>, double*>& store, i
   store[k] = p;
   c->buf_elems[p] = count;
   return p;
+}
+
+// A buffer the plan can do without: null where it does not fit.
+double* optional_alloc(ftcc_ctx* c, size_t count) {
+  try {
+    return c->dalloc(count);
+  } catch (const Fail& f) {
+    if (f.code != FTCC_ENOMEM) throw;
+    return nullptr;
+  }
 }
 
 // Progress lines on stderr (one per panel of each phase, and one per sweep at
@@ -922,14 +956,9 @@ void build(ftcc_ctx* c) {
   auto vcache = [c, reserve, &copies_left](size_t count) -> double* {
     const double bytes = (double)count * sizeof(double);
     if (bytes > copies_left || c->available() < reserve + bytes) return nullptr;
-    try {
-      double* q = c->dalloc(count);
-      copies_left -= bytes;
-      return q;
-    } catch (const Fail& f) {
-      if (f.code != FTCC_ENOMEM) throw;
-      return nullptr;
-    }
+    double* q = optional_alloc(c, count);
+    if (q) copies_left -= bytes;
+    return q;
   };
   // reuse budget for permuted operand copies: an eighth of the memory still available (at
   // 123 orbitals a quarter left the derivative executor short of its permuted constants)
@@ -1655,9 +1684,9 @@ int ftcc_destroy(ftcc_ctx* c) {
     c->ex_d.reset();
     c->ex_g.reset();
     for (void* p : c->descs) (void)hipFree(p);
-    for (void* p : c->allocs) {
-      if (c->ufree) c->ufree(p, c->uuser);
-      else if (!c->ualloc) (void)hipFree(p);
+    for (const ftcc_ctx::Alloc& a : c->allocs) {
+      if (c->ufree) c->ufree(a.p, c->uuser);
+      else if (!c->ualloc) (void)hipFree(a.p);
     }
     if (c->h_maxbits) (void)hipHostFree(c->h_maxbits);
     if (c->maxbits_posted) (void)hipEventDestroy(c->maxbits_posted);
