@@ -952,12 +952,14 @@ void build(ftcc_ctx* c) {
   // context takes none.
   double reserve = 1073741824.0;
   for (int i = 0; i < B; ++i) reserve += 24.0 * std::pow((double)c->inst[i].n, 4) * sizeof(double);
-  double copies_left = blocked ? (c->opt.mem_cap_bytes ? 0.0 : c->available() / 8.0) : INFINITY;
-  auto vcache = [c, reserve, &copies_left](size_t count) -> double* {
+  // (shared by the two executors, which keep the function)
+  const auto copies_left = std::make_shared<double>(
+      blocked ? (c->opt.mem_cap_bytes ? 0.0 : c->available() / 8.0) : INFINITY);
+  auto vcache = [c, reserve, copies_left](size_t count) -> double* {
     const double bytes = (double)count * sizeof(double);
-    if (bytes > copies_left || c->available() < reserve + bytes) return nullptr;
+    if (bytes > *copies_left || c->available() < reserve + bytes) return nullptr;
     double* q = optional_alloc(c, count);
-    if (q) copies_left -= bytes;
+    if (q) *copies_left -= bytes;
     return q;
   };
   // reuse budget for permuted operand copies: an eighth of the memory still available (at
