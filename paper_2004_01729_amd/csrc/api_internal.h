@@ -99,7 +99,7 @@ struct ftcc_ctx {
   PanelRule* d_rule = nullptr;
   std::vector<Instance> inst;
   // device buffers, and what each belongs to: what an executor took can be given back
-  enum Owner { OF_CONTEXT, OF_DENSITY };
+  enum Owner { OF_CONTEXT, OF_EXECUTORS, OF_DENSITY };
   struct Alloc {
     void* p;
     size_t bytes;

@@ -121,7 +121,7 @@ static void build_gamma(ftcc_ctx* c, bool copies) {
 // says nothing about what a caller's allocator still holds): where something fails to
 // fit, all of it is given back and built again without them.
 void build_gamma_executor(ftcc_ctx* c) {
-  for (bool copies = !c->opt.mem_cap_bytes; !c->ex_g; copies = false) {
+  for (bool copies = !c->opt.mem_cap_bytes && !(c->ualloc && !c->ufree); !c->ex_g; copies = false) {
     try {
       build_gamma(c, copies);
     } catch (const Fail& f) {

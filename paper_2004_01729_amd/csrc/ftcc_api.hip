@@ -440,6 +440,7 @@ void setup_tables(ftcc_ctx* c) {
   std::vector<SetupProblem> ps;
   std::vector<int> prefix;
   int total = 0;
+  c->setup_blocks.clear();
   for (Instance& I : c->inst) {
     SetupProblem p{};
     p.n = I.n;
@@ -611,6 +612,177 @@ long seg_len(const ftcc_ctx* c, int i, int seg) {
 // the sweeps run parts of the programs of their own (the march of a single slot does not)
 bool sweeps_apart(const ftcc_ctx* c) { return !c->rk && !c->simpson && c->slots == c->m && c->ex_main->has_sweeps(); }
 
+// The main and the derivative executor over the context's node slots, and their graphs.
+// copies: with optional buffers (permuted operand copies, private copies of accumulated
+// outputs).
+static void build_executors(ftcc_ctx* c, bool copies) {
+  const AllocFor owner(c, ftcc_ctx::OF_EXECUTORS);
+  const int B = c->B;
+  const Program& prog = c->prog;
+  const bool mom = momentum_on(c);
+  std::vector<ProblemRef> probs;
+  for (int i = 0; i < B; ++i)
+    for (int x = 0; x < c->slots; ++x) probs.push_back({i, x, c->inst[i].n});
+  std::vector<int> ugrads;
+  for (int k = 0; k < 4; ++k) ugrads.push_back(prog.id(kU[k]));
+  const int id_t1 = prog.id("t1"), id_t2 = prog.id("t2"), id_S1 = prog.id("S1"), id_S2 = prog.id("S2"),
+            id_E = prog.id("E");
+
+  auto tensor_buf = [c, &probs](std::map<std::pair<int, int>, double*>& store, int t, int key, long count) {
+    return shared_buf(c, store, t, key, count);
+  };
+  // intermediates take the element count the executor addresses (packed or dense)
+  auto bind_common = [&, c](int t, int p, bool grad, size_t count) -> double* {
+    const TensorDecl& d = prog.t[t];
+    const long n = probs[p].n, n2 = n * n;
+    const long cnt = (long)count;
+    if (t == id_t1) return grad ? c->s_gr[p] : c->s_amp[p];
+    if (t == id_t2) return grad ? c->s_gr[p] + n2 : c->s_amp[p] + n2;
+    if (grad) {
+      if (t == id_S1) return c->s_cot[p];
+      if (t == id_S2) return c->s_cot[p] + n2;
+      if (t == id_E) return c->s_ebar[p];
+      if (d.kind == T_CONST) {
+        for (int k = 0; k < 4; ++k)
+          if (d.name == kU[k]) return c->s_ugrad[p][k];
+        fail(FTCC_EINVAL, "no gradient buffer for " + d.name);
+      }
+      return tensor_buf(c->inter_grad, t, p, cnt);
+    }
+    if (d.kind == T_INTER && !d.derived) return tensor_buf(c->inter, t, p, cnt);
+    return nullptr;
+  };
+  Binder bind_main = [&, c](int t, int p, bool grad, size_t count) -> double* {
+    const TensorDecl& d = prog.t[t];
+    if (double* q = bind_common(t, p, grad, count)) return q;
+    const int i = probs[p].inst;
+    const long n = probs[p].n, n2 = n * n;
+    if (d.kind == T_CONST) return c->inst[i].blk[d.name];
+    if (d.derived) return tensor_buf(c->derived, t, i, ipow(n, d.rank));
+    if (t == id_S1) return c->s_S[p];
+    if (t == id_S2) return c->s_S[p] + n2;
+    if (t == id_E) return c->s_e[p];
+    fail(FTCC_EINVAL, "unbound tensor " + d.name);
+  };
+  Binder bind_d = [&, c](int t, int p, bool grad, size_t count) -> double* {
+    const TensorDecl& d = prog.t[t];
+    if (double* q = bind_common(t, p, grad, count)) return q;
+    const int i = probs[p].inst;
+    const long n = probs[p].n, n2 = n * n;
+    if (d.kind == T_CONST) return c->inst[i].dblk[d.name];
+    if (d.derived) return tensor_buf(c->dderived, t, i, ipow(n, d.rank));
+    if (t == id_S1) return c->s_dS[p];
+    if (t == id_S2) return c->s_dS[p] + n2;
+    if (t == id_E) return c->s_de[p];
+    fail(FTCC_EINVAL, "unbound tensor " + d.name);
+  };
+  auto calloc_ = [c](int, size_t count) { return c->dalloc(count); };
+  // Small dense problems take the blocked executor's path as well, everything in one
+  // block: no operand or output is permuted and independent contractions share
+  // launches.  Four nodes' residuals, GEMM path against this one: n = 8 0.409 / 0.119
+  // ms, 16 0.633 / 0.265, 24 1.21 / 0.72, 32 2.61 / 2.26, 40 7.88 / 6.83, 48 18.2 / 17.7,
+  // 50 22.8 / 23.9; one node alone (41: 6.4 / 8.5 with the copies) wins on the 128 x 128
+  // tiles of the GEMM path, whose launches take one problem, so the line lies at 40.
+  // FTCC_DENSE_LEVELS=N: up to n = N (diagnostics; 0: never).
+  int nmax = 0;
+  for (const Instance& I : c->inst) nmax = std::max(nmax, I.n);
+  const char* lenv = std::getenv("FTCC_DENSE_LEVELS");
+  const bool trivial = !mom && nmax <= (lenv ? std::atoi(lenv) : 40);
+  c->one_block.clear();
+  if (trivial)
+    for (const Instance& I : c->inst) {
+      InstMomentum t;
+      t.dims = 1;
+      t.modulus = {1};
+      t.labels.assign(I.n, 0);
+      c->one_block.push_back(t);
+    }
+  const bool blocked = mom || trivial;
+  // Optional buffers: reused permuted copies of value operands (GEMM path), private
+  // copies of accumulated outputs (blocked path).  One is taken only while it leaves a
+  // reserve for what the executors must still allocate (the second executor's
+  // intermediates and permuted constants: 24 n^4 doubles per instance, plus 1 GiB), and
+  // an allocation that fails leaves the operand uncached or the writes serial.  The
+  // blocked path's stay within an eighth of the memory available here; a capped context
+  // takes none, nor one that could not give them back (an allocator without a free function).
+  double reserve = 1073741824.0;
+  for (int i = 0; i < B; ++i) reserve += 24.0 * std::pow((double)c->inst[i].n, 4) * sizeof(double);
+  // (shared by the two executors, which keep the function)
+  const bool keeps = c->ualloc && !c->ufree;
+  const auto copies_left = std::make_shared<double>(
+      !copies || (blocked && (c->opt.mem_cap_bytes || keeps)) ? 0.0 : blocked ? c->available() / 8.0 : INFINITY);
+  auto vcache = [c, reserve, copies_left](size_t count) -> double* {
+    const double bytes = (double)count * sizeof(double);
+    if (bytes > *copies_left || c->available() < reserve + bytes) return nullptr;
+    double* q = optional_alloc(c, count);
+    if (q) *copies_left -= bytes;
+    return q;
+  };
+  // reuse budget for permuted operand copies: an eighth of the memory still available (at
+  // 123 orbitals a quarter left the derivative executor short of its permuted constants)
+  // (the blocked contractions address their operands in place: no permuted copies)
+  const size_t budget = blocked || !copies ? 0 : (size_t)(c->available() / 8);
+  std::vector<const InstMomentum*> by_inst;
+  if (mom)
+    for (const Instance& I : c->inst) by_inst.push_back(&I.mom);
+  else
+    for (const InstMomentum& t : c->one_block) by_inst.push_back(&t);
+  c->ex_main.reset(new Executor());
+  c->ex_main->set_gate(c->d_run, c->run_slots.data());
+  c->ex_main->set_packed_io(c->packed_states);
+  if (blocked) c->ex_main->set_momentum(by_inst);
+  c->ex_main->build(&prog, probs, bind_main, &c->scratch, calloc_, true, ugrads, vcache, budget);
+  c->ex_main->set_profiler(&c->prof);
+  trace_executor(c, "main", *c->ex_main);
+  c->ex_d.reset(new Executor());
+  c->ex_d->set_packed_io(c->packed_states);
+  if (blocked) c->ex_d->set_momentum(by_inst);
+  c->ex_d->build(&prog, probs, bind_d, &c->scratch, calloc_, false, {}, vcache, budget / 2);
+  c->ex_d->set_profiler(&c->prof);
+  trace_executor(c, "derivative", *c->ex_d);
+  trace_mem(c, "executors");
+  // no kernel-profiler events inside the autotuner or a graph capture
+  const bool prof_on = c->prof.enabled;
+  c->prof.enabled = false;
+  c->ex_main->autotune(c->stream);
+  c->ex_d->autotune(c->stream);
+  FTCC_HIP(hipStreamSynchronize(c->stream));
+  const char* genv = std::getenv("FTCC_GRAPH");
+  if (!(genv && genv[0] == '0')) {
+    // the launch lists are static: capture each once as a graph
+    auto capture = [c](hipGraphExec_t* exec, const std::function<void()>& run) {
+      hipGraph_t g;
+      FTCC_HIP(hipStreamBeginCapture(c->stream, hipStreamCaptureModeThreadLocal));
+      run();
+      FTCC_HIP(hipStreamEndCapture(c->stream, &g));
+      FTCC_HIP(hipGraphInstantiate(exec, g, nullptr, nullptr, 0));
+      FTCC_HIP(hipGraphDestroy(g));
+    };
+    capture(&c->g_fwd, [c] { c->ex_main->run_forward(c->stream); });
+    capture(&c->g_bwd, [c] { c->ex_main->run_backward(c->stream); });
+    if (sweeps_apart(c)) {
+      capture(&c->g_fwd_sweep, [c] { c->ex_main->run_forward_sweep(c->stream); });
+      capture(&c->g_fwd_rest, [c] { c->ex_main->run_forward_rest(c->stream); });
+      capture(&c->g_bwd_sweep, [c] { c->ex_main->run_backward_sweep(c->stream); });
+    }
+  }
+
+  c->prof.enabled = prof_on;
+}
+
+static void drop_executors(ftcc_ctx* c) {
+  FTCC_HIP(hipStreamSynchronize(c->stream));
+  for (hipGraphExec_t* g : {&c->g_fwd, &c->g_bwd, &c->g_fwd_sweep, &c->g_fwd_rest, &c->g_bwd_sweep}) {
+    if (*g) (void)hipGraphExecDestroy(*g);
+    *g = nullptr;
+  }
+  c->ex_main.reset();
+  c->ex_d.reset();
+  c->ex_g.reset();
+  c->release(ftcc_ctx::OF_DENSITY);
+  c->release(ftcc_ctx::OF_EXECUTORS);
+}
+
 void build(ftcc_ctx* c) {
   if (c->built) return;
   for (int i = 0; i < c->B; ++i)
@@ -644,8 +816,6 @@ void build(ftcc_ctx* c) {
       check_momentum(c, i, I.eri, 4, "<pq|rs>");
       allowed_elements(c, i);
     }
-  const Program& prog = c->prog;
-
   for (int i = 0; i < B; ++i) {
     Instance& I = c->inst[i];
     const int n = I.n;
@@ -782,13 +952,11 @@ void build(ftcc_ctx* c) {
   c->s_dS.resize(np);
   c->s_de.resize(np);
   c->s_ugrad.resize(np);
-  std::vector<ProblemRef> probs;
   for (int i = 0; i < B; ++i)
     for (int x = 0; x < SL; ++x) {
       const int q = i * SL + x;
       const int n = c->inst[i].n;
       const long n2 = (long)n * n, n4 = n2 * n2, len = n2 + n4;
-      probs.push_back({i, x, n});
       if (SL == m) {
         const int p = i * m + x;
         c->s_amp[q] = c->amp[p];
@@ -827,8 +995,9 @@ void build(ftcc_ctx* c) {
     c->scratch.tail_ws_doubles = ws;
   }
   c->d_maxbits = (unsigned long long*)c->dalloc(2 * B);
-  FTCC_HIP(hipHostMalloc((void**)&c->h_maxbits, sizeof(unsigned long long) * 2 * B, hipHostMallocCoherent));
-  FTCC_HIP(hipEventCreateWithFlags(&c->maxbits_posted, hipEventDisableTiming));
+  if (!c->h_maxbits)
+    FTCC_HIP(hipHostMalloc((void**)&c->h_maxbits, sizeof(unsigned long long) * 2 * B, hipHostMallocCoherent));
+  if (!c->maxbits_posted) FTCC_HIP(hipEventCreateWithFlags(&c->maxbits_posted, hipEventDisableTiming));
   c->d_active = (int*)c->dalloc(B);
   c->d_run = (int*)c->dalloc(B * SL);
   c->run_host.assign(B, 1);
@@ -869,149 +1038,18 @@ void build(ftcc_ctx* c) {
   }
 
   trace_mem(c, "node and slot buffers");
-  std::vector<int> ugrads;
-  for (int k = 0; k < 4; ++k) ugrads.push_back(prog.id(kU[k]));
-  const int id_t1 = prog.id("t1"), id_t2 = prog.id("t2"), id_S1 = prog.id("S1"), id_S2 = prog.id("S2"),
-            id_E = prog.id("E");
-
-  auto tensor_buf = [c, &probs](std::map<std::pair<int, int>, double*>& store, int t, int key, long count) {
-    return shared_buf(c, store, t, key, count);
-  };
-  // intermediates take the element count the executor addresses (packed or dense)
-  auto bind_common = [&, c](int t, int p, bool grad, size_t count) -> double* {
-    const TensorDecl& d = prog.t[t];
-    const long n = probs[p].n, n2 = n * n;
-    const long cnt = (long)count;
-    if (t == id_t1) return grad ? c->s_gr[p] : c->s_amp[p];
-    if (t == id_t2) return grad ? c->s_gr[p] + n2 : c->s_amp[p] + n2;
-    if (grad) {
-      if (t == id_S1) return c->s_cot[p];
-      if (t == id_S2) return c->s_cot[p] + n2;
-      if (t == id_E) return c->s_ebar[p];
-      if (d.kind == T_CONST) {
-        for (int k = 0; k < 4; ++k)
-          if (d.name == kU[k]) return c->s_ugrad[p][k];
-        fail(FTCC_EINVAL, "no gradient buffer for " + d.name);
-      }
-      return tensor_buf(c->inter_grad, t, p, cnt);
-    }
-    if (d.kind == T_INTER && !d.derived) return tensor_buf(c->inter, t, p, cnt);
-    return nullptr;
-  };
-  Binder bind_main = [&, c](int t, int p, bool grad, size_t count) -> double* {
-    const TensorDecl& d = prog.t[t];
-    if (double* q = bind_common(t, p, grad, count)) return q;
-    const int i = probs[p].inst;
-    const long n = probs[p].n, n2 = n * n;
-    if (d.kind == T_CONST) return c->inst[i].blk[d.name];
-    if (d.derived) return tensor_buf(c->derived, t, i, ipow(n, d.rank));
-    if (t == id_S1) return c->s_S[p];
-    if (t == id_S2) return c->s_S[p] + n2;
-    if (t == id_E) return c->s_e[p];
-    fail(FTCC_EINVAL, "unbound tensor " + d.name);
-  };
-  Binder bind_d = [&, c](int t, int p, bool grad, size_t count) -> double* {
-    const TensorDecl& d = prog.t[t];
-    if (double* q = bind_common(t, p, grad, count)) return q;
-    const int i = probs[p].inst;
-    const long n = probs[p].n, n2 = n * n;
-    if (d.kind == T_CONST) return c->inst[i].dblk[d.name];
-    if (d.derived) return tensor_buf(c->dderived, t, i, ipow(n, d.rank));
-    if (t == id_S1) return c->s_dS[p];
-    if (t == id_S2) return c->s_dS[p] + n2;
-    if (t == id_E) return c->s_de[p];
-    fail(FTCC_EINVAL, "unbound tensor " + d.name);
-  };
-  auto calloc_ = [c](int, size_t count) { return c->dalloc(count); };
-  // Small dense problems take the blocked executor's path as well, everything in one
-  // block: no operand or output is permuted and independent contractions share
-  // launches.  Four nodes' residuals, GEMM path against this one: n = 8 0.409 / 0.119
-  // ms, 16 0.633 / 0.265, 24 1.21 / 0.72, 32 2.61 / 2.26, 40 7.88 / 6.83, 48 18.2 / 17.7,
-  // 50 22.8 / 23.9; one node alone (41: 6.4 / 8.5 with the copies) wins on the 128 x 128
-  // tiles of the GEMM path, whose launches take one problem, so the line lies at 40.
-  // FTCC_DENSE_LEVELS=N: up to n = N (diagnostics; 0: never).
-  int nmax = 0;
-  for (const Instance& I : c->inst) nmax = std::max(nmax, I.n);
-  const char* lenv = std::getenv("FTCC_DENSE_LEVELS");
-  const bool trivial = !mom && nmax <= (lenv ? std::atoi(lenv) : 40);
-  if (trivial)
-    for (const Instance& I : c->inst) {
-      InstMomentum t;
-      t.dims = 1;
-      t.modulus = {1};
-      t.labels.assign(I.n, 0);
-      c->one_block.push_back(t);
-    }
-  const bool blocked = mom || trivial;
-  // Optional buffers: reused permuted copies of value operands (GEMM path), private
-  // copies of accumulated outputs (blocked path).  One is taken only while it leaves a
-  // reserve for what the executors must still allocate (the second executor's
-  // intermediates and permuted constants: 24 n^4 doubles per instance, plus 1 GiB), and
-  // an allocation that fails leaves the operand uncached or the writes serial.  The
-  // blocked path's stay within an eighth of the memory available here, and a capped
-  // context takes none.
-  double reserve = 1073741824.0;
-  for (int i = 0; i < B; ++i) reserve += 24.0 * std::pow((double)c->inst[i].n, 4) * sizeof(double);
-  // (shared by the two executors, which keep the function)
-  const auto copies_left = std::make_shared<double>(
-      blocked ? (c->opt.mem_cap_bytes ? 0.0 : c->available() / 8.0) : INFINITY);
-  auto vcache = [c, reserve, copies_left](size_t count) -> double* {
-    const double bytes = (double)count * sizeof(double);
-    if (bytes > *copies_left || c->available() < reserve + bytes) return nullptr;
-    double* q = optional_alloc(c, count);
-    if (q) *copies_left -= bytes;
-    return q;
-  };
-  // reuse budget for permuted operand copies: an eighth of the memory still available (at
-  // 123 orbitals a quarter left the derivative executor short of its permuted constants)
-  // (the blocked contractions address their operands in place: no permuted copies)
-  const size_t budget = blocked ? 0 : (size_t)(c->available() / 8);
-  std::vector<const InstMomentum*> by_inst;
-  if (mom)
-    for (const Instance& I : c->inst) by_inst.push_back(&I.mom);
-  else
-    for (const InstMomentum& t : c->one_block) by_inst.push_back(&t);
-  c->ex_main.reset(new Executor());
-  c->ex_main->set_gate(c->d_run, c->run_slots.data());
-  c->ex_main->set_packed_io(c->packed_states);
-  if (blocked) c->ex_main->set_momentum(by_inst);
-  c->ex_main->build(&prog, probs, bind_main, &c->scratch, calloc_, true, ugrads, vcache, budget);
-  c->ex_main->set_profiler(&c->prof);
-  trace_executor(c, "main", *c->ex_main);
-  c->ex_d.reset(new Executor());
-  c->ex_d->set_packed_io(c->packed_states);
-  if (blocked) c->ex_d->set_momentum(by_inst);
-  c->ex_d->build(&prog, probs, bind_d, &c->scratch, calloc_, false, {}, vcache, budget / 2);
-  c->ex_d->set_profiler(&c->prof);
-  trace_executor(c, "derivative", *c->ex_d);
-  trace_mem(c, "executors");
-  // no kernel-profiler events inside the autotuner or a graph capture
-  const bool prof_on = c->prof.enabled;
-  c->prof.enabled = false;
-  c->ex_main->autotune(c->stream);
-  c->ex_d->autotune(c->stream);
-  FTCC_HIP(hipStreamSynchronize(c->stream));
-  const char* genv = std::getenv("FTCC_GRAPH");
-  if (!(genv && genv[0] == '0')) {
-    // the launch lists are static: capture each once as a graph
-    auto capture = [c](hipGraphExec_t* exec, const std::function<void()>& run) {
-      hipGraph_t g;
-      FTCC_HIP(hipStreamBeginCapture(c->stream, hipStreamCaptureModeThreadLocal));
-      run();
-      FTCC_HIP(hipStreamEndCapture(c->stream, &g));
-      FTCC_HIP(hipGraphInstantiate(exec, g, nullptr, nullptr, 0));
-      FTCC_HIP(hipGraphDestroy(g));
-    };
-    capture(&c->g_fwd, [c] { c->ex_main->run_forward(c->stream); });
-    capture(&c->g_bwd, [c] { c->ex_main->run_backward(c->stream); });
-    if (sweeps_apart(c)) {
-      capture(&c->g_fwd_sweep, [c] { c->ex_main->run_forward_sweep(c->stream); });
-      capture(&c->g_fwd_rest, [c] { c->ex_main->run_forward_rest(c->stream); });
-      capture(&c->g_bwd_sweep, [c] { c->ex_main->run_backward_sweep(c->stream); });
+  // The optional buffers must not cost the context its memory (the free memory of the
+  // device says nothing about what a caller's allocator still holds): where something
+  // fails to fit, the executors give all of theirs back and are built without them.
+  for (bool copies = true;; copies = false) {
+    try {
+      build_executors(c, copies);
+      break;
+    } catch (const Fail& f) {
+      drop_executors(c);
+      if (f.code != FTCC_ENOMEM || !copies) throw;
     }
   }
-
-  c->prof.enabled = prof_on;
   c->built = true;
 }
 
@@ -1678,9 +1716,7 @@ int ftcc_destroy(ftcc_ctx* c) {
     (void)hipSetDevice(c->device);
     (void)hipStreamSynchronize(c->stream);
     clear_tau_cache(c);
-    if (c->g_fwd) (void)hipGraphExecDestroy(c->g_fwd);
-    if (c->g_bwd) (void)hipGraphExecDestroy(c->g_bwd);
-    for (hipGraphExec_t g : {c->g_fwd_sweep, c->g_fwd_rest, c->g_bwd_sweep})
+    for (hipGraphExec_t g : {c->g_fwd, c->g_bwd, c->g_fwd_sweep, c->g_fwd_rest, c->g_bwd_sweep})
       if (g) (void)hipGraphExecDestroy(g);
     c->ex_main.reset();
     c->ex_d.reset();

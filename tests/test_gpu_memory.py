@@ -82,6 +82,31 @@ def _close(out, ref, tol=1e-11):
         assert np.abs(a - b).max() <= tol * max(np.abs(b).max(), 1e-3)
 
 
+def _run(F, kind, limit=None, after_solve=False, **opt):
+    """A step with at most `limit` bytes; after_solve: no more than the solve took."""
+    s, pool = _system(kind), Pool()
+    pool.limit = limit
+    print(f"[memory] {kind} limit={limit} after_solve={after_solve} {opt}", flush=True)
+    ctx = _context(F, s, pool, **opt)
+    try:
+        if after_solve:
+            ctx.solve(s[3], s[4])
+            pool.limit = pool.held
+        out = _step(ctx, s)
+        held = pool.held
+    finally:
+        ctx.close()
+    assert pool.held == 0
+    return out, held
+
+
+@pytest.mark.parametrize("kind", ["ring6", "pair10", "dense10", "dense41"])
+def test_step_without_room_for_optional_copies(F, kind):
+    ref, held = _run(F, kind, mem_cap_bytes=NO_COPIES)
+    out, _ = _run(F, kind, limit=held)
+    _close(out, ref)
+
+
 def _density(F, kind, room=None, monkeypatch=None, **opt):
     """The density with `room` bytes beyond what solve, lambda and response hold."""
     s, pool = _system(kind), Pool()
