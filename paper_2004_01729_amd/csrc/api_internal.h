@@ -111,7 +111,8 @@ struct ftcc_ctx {
   std::vector<InstMomentum> one_block;        // small dense problems: labels that put everything into one block
   std::unique_ptr<Executor> ex_main, ex_d, ex_g;   // ex_g: integral gradients (built on first use)
   std::map<std::pair<int, int>, double*> g_derived, g_cgrad;   // (tensor, problem) buffers of ex_g
-  bool built = false, solved = false, have_lambda = false;
+  bool buffers = false, built = false, solved = false, have_lambda = false;
+  bool lean = false;   // the executors without optional buffers and over the residual's lean form
   // thermal set-up of all instances in one launch per stage
   SetupProblem* d_setup = nullptr;            // [B]
   int* d_setup_prefix = nullptr;              // [B] first block of each instance, [B] a 0
@@ -324,6 +325,8 @@ bool trace_on();
 // share intermediates must agree on their storage)
 double* shared_buf(ftcc_ctx* c, std::map<std::pair<int, int>, double*>& store, int t, int key, long count);
 double* optional_alloc(ftcc_ctx* c, size_t count);
+void shrink_executors(ftcc_ctx* c);
+void with_room(ftcc_ctx* c, const std::function<void()>& allocate);
 // FTCC_TRACE=2: a line per sweep as well (the largest change over the batch)
 void trace_sweep(const char* phase, int panel, int it, const std::vector<double>& maxbits);
 void trace(ftcc_ctx* c, const char* phase, int panel, int n_panels, const std::vector<int>& sweeps,

@@ -119,14 +119,18 @@ static void build_gamma(ftcc_ctx* c, bool copies) {
 
 // The optional copies must not cost the call its memory (the free memory of the device
 // says nothing about what a caller's allocator still holds): where something fails to
-// fit, all of it is given back and built again without them.
+// fit, all of it is given back and built again without them, in the end beside the lean
+// form of the other executors.
 void build_gamma_executor(ftcc_ctx* c) {
-  for (bool copies = !c->opt.mem_cap_bytes && !(c->ualloc && !c->ufree); !c->ex_g; copies = false) {
+  bool copies = !c->opt.mem_cap_bytes && !c->lean && !(c->ualloc && !c->ufree);
+  while (!c->ex_g) {
     try {
       build_gamma(c, copies);
     } catch (const Fail& f) {
       c->release(ftcc_ctx::OF_DENSITY);
-      if (f.code != FTCC_ENOMEM || !copies) throw;
+      if (f.code != FTCC_ENOMEM || (!copies && c->lean)) throw;
+      if (!copies) shrink_executors(c);
+      copies = false;
     }
   }
 }

@@ -79,7 +79,7 @@ class Program {
 };
 
 // The spin-restricted FT-CCSD kernels E, S1, S2 as a Program.
-Program build_residual_program();
+Program build_residual_program(bool lean);   // lean: nine O(n^6) contractions, fewer arrays
 Program build_spin_orbital_program();
 
 struct Launch {

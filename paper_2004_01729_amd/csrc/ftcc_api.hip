@@ -612,10 +612,13 @@ long seg_len(const ftcc_ctx* c, int i, int seg) {
 // the sweeps run parts of the programs of their own (the march of a single slot does not)
 bool sweeps_apart(const ftcc_ctx* c) { return !c->rk && !c->simpson && c->slots == c->m && c->ex_main->has_sweeps(); }
 
+static void set_program(ftcc_ctx* c, bool lean) {
+  c->lean = lean;
+  c->prog = c->opt.spin_orbital ? build_spin_orbital_program() : build_residual_program(lean);
+}
+
 // The main and the derivative executor over the context's node slots, and their graphs.
-// copies: with optional buffers (permuted operand copies, private copies of accumulated
-// outputs).
-static void build_executors(ftcc_ctx* c, bool copies) {
+static void build_executors(ftcc_ctx* c) {
   const AllocFor owner(c, ftcc_ctx::OF_EXECUTORS);
   const int B = c->B;
   const Program& prog = c->prog;
@@ -704,13 +707,14 @@ static void build_executors(ftcc_ctx* c, bool copies) {
   // intermediates and permuted constants: 24 n^4 doubles per instance, plus 1 GiB), and
   // an allocation that fails leaves the operand uncached or the writes serial.  The
   // blocked path's stay within an eighth of the memory available here; a capped context
-  // takes none, nor one that could not give them back (an allocator without a free function).
+  // takes none, nor one that could not give them back (an allocator without a free
+  // function), nor the lean form.
   double reserve = 1073741824.0;
   for (int i = 0; i < B; ++i) reserve += 24.0 * std::pow((double)c->inst[i].n, 4) * sizeof(double);
   // (shared by the two executors, which keep the function)
   const bool keeps = c->ualloc && !c->ufree;
   const auto copies_left = std::make_shared<double>(
-      !copies || (blocked && (c->opt.mem_cap_bytes || keeps)) ? 0.0 : blocked ? c->available() / 8.0 : INFINITY);
+      c->lean || (blocked && (c->opt.mem_cap_bytes || keeps)) ? 0.0 : blocked ? c->available() / 8.0 : INFINITY);
   auto vcache = [c, reserve, copies_left](size_t count) -> double* {
     const double bytes = (double)count * sizeof(double);
     if (bytes > *copies_left || c->available() < reserve + bytes) return nullptr;
@@ -721,7 +725,7 @@ static void build_executors(ftcc_ctx* c, bool copies) {
   // reuse budget for permuted operand copies: an eighth of the memory still available (at
   // 123 orbitals a quarter left the derivative executor short of its permuted constants)
   // (the blocked contractions address their operands in place: no permuted copies)
-  const size_t budget = blocked || !copies ? 0 : (size_t)(c->available() / 8);
+  const size_t budget = blocked || c->lean ? 0 : (size_t)(c->available() / 8);
   std::vector<const InstMomentum*> by_inst;
   if (mom)
     for (const Instance& I : c->inst) by_inst.push_back(&I.mom);
@@ -783,12 +787,38 @@ static void drop_executors(ftcc_ctx* c) {
   c->release(ftcc_ctx::OF_EXECUTORS);
 }
 
-void build(ftcc_ctx* c) {
-  if (c->built) return;
-  for (int i = 0; i < c->B; ++i)
-    if (!c->inst[i].has_ham) fail(FTCC_ESTATE, "instance " + std::to_string(i) + " has no Hamiltonian");
+// Makes room in a context whose executors are built: they give everything back and are
+// built again in their lean form.  Integrals, amplitudes and Lambda stay as they are.
+void shrink_executors(ftcc_ctx* c) {
+  c->built = false;
+  drop_executors(c);
+  set_program(c, true);
+  try {
+    build_executors(c);
+  } catch (...) {
+    drop_executors(c);
+    c->solved = c->have_lambda = false;
+    throw;
+  }
+  c->built = true;
+  if (c->solved) c->ex_main->run_setup(c->stream);
+}
+
+// What a later call allocates first of all: where it does not fit, once more beside the
+// lean executors.
+void with_room(ftcc_ctx* c, const std::function<void()>& allocate) {
+  try {
+    allocate();
+  } catch (const Fail& f) {
+    if (f.code != FTCC_ENOMEM || c->lean) throw;
+    shrink_executors(c);
+    allocate();
+  }
+}
+
+// integrals, states, node and slot buffers, and the schedule that fits them
+static void build_buffers(ftcc_ctx* c) {
   const int m = c->m, P = c->P, B = c->B;
-  c->prog = c->opt.spin_orbital ? build_spin_orbital_program() : build_residual_program();
   const bool mom = momentum_on(c);
   if (mom) {
     std::vector<const InstMomentum*> labels;
@@ -892,8 +922,8 @@ void build(ftcc_ctx* c) {
   // Executor slots per instance: every node of a panel evaluated in one grouped
   // launch (slots = m) unless the per-slot working set would take more than half
   // of the free device memory; then the nodes go through one slot in turn.  The
-  // working set is about 40 n^4 doubles (intermediates, their gradients,
-  // scratch), or, when the momentum-blocked intermediates are stored packed
+  // working set is at most 40 n^4 doubles (14 intermediates and their gradients, 4 of
+  // scratch, 5 node states: 37), or, when the momentum-blocked intermediates are stored packed
   // (n^3 each), the scratch and the derivative residual of each slot, 5 n^4.
   {
     bool packed = momentum_on(c) && packing_enabled();
@@ -1038,16 +1068,26 @@ void build(ftcc_ctx* c) {
   }
 
   trace_mem(c, "node and slot buffers");
-  // The optional buffers must not cost the context its memory (the free memory of the
-  // device says nothing about what a caller's allocator still holds): where something
-  // fails to fit, the executors give all of theirs back and are built without them.
-  for (bool copies = true;; copies = false) {
+  c->buffers = true;
+}
+
+void build(ftcc_ctx* c) {
+  if (c->built) return;
+  for (int i = 0; i < c->B; ++i)
+    if (!c->inst[i].has_ham) fail(FTCC_ESTATE, "instance " + std::to_string(i) + " has no Hamiltonian");
+  set_program(c, false);
+  if (!c->buffers) build_buffers(c);
+  // What is optional must not cost the context its memory (the free memory of the device
+  // says nothing about what a caller's allocator still holds): where something fails to
+  // fit, the executors give all of theirs back and are built in the lean form.
+  for (;;) {
     try {
-      build_executors(c, copies);
+      build_executors(c);
       break;
     } catch (const Fail& f) {
       drop_executors(c);
-      if (f.code != FTCC_ENOMEM || !copies) throw;
+      if (f.code != FTCC_ENOMEM || c->lean) throw;
+      set_program(c, true);
     }
   }
   c->built = true;
@@ -2162,7 +2202,6 @@ static void ensure_resp_groups(ftcc_ctx* c) {
     FTCC_HIP(hipMemcpy(d, h, bytes, hipMemcpyHostToDevice));
     return (void*)d;
   };
-  c->d_resp_dots = (DotProblem*)up(ds.data(), sizeof(DotProblem) * ds.size());
   c->d_resp_w = (double*)up(w.data(), sizeof(double) * w.size());
   c->d_de_ptrs = (const double**)up(de.data(), sizeof(double*) * de.size());
   c->d_acc_ptrs = (double**)up(acc.data(), sizeof(double*) * acc.size());
@@ -2177,6 +2216,7 @@ static void ensure_resp_groups(ftcc_ctx* c) {
   for (long v : n2) total_n2 += v;
   c->d_dh_out = (double*)c->desc(nullptr, sizeof(double) * total_n2);
   c->d_acc_all = (double*)c->desc(nullptr, sizeof(double) * 13 * B);   // the accumulators (8) and mean-field sums (5), gathered for the host
+  c->d_resp_dots = (DotProblem*)up(ds.data(), sizeof(DotProblem) * ds.size());   // last: the set is complete
 }
 
 int ftcc_response(ftcc_ctx* c, double* dO_dmu, double* dO_dbeta, double* dO_dh, double* dO_deps,
@@ -2188,18 +2228,18 @@ int ftcc_response(ftcc_ctx* c, double* dO_dmu, double* dO_dbeta, double* dO_dh, 
     const int B = c->B, m = c->m, P = c->P;
     int nmax = 0;
     for (int i = 0; i < B; ++i) nmax = std::max(nmax, c->inst[i].n);
-    if (dO_deps) {
-      for (int i = 0; i < B; ++i) {
+    with_room(c, [&] {
+      ensure_resp_groups(c);
+      for (int i = 0; dO_deps && i < B; ++i) {
         Instance& I = c->inst[i];
-        const long n = I.n;
-        if (!I.deps_acc) {
-          I.deps_acc = c->dalloc(n);
-          I.deps_out = c->dalloc(n);
-          I.deps_delta = c->dalloc(node_len(c, i));
-        }
-        zero_d(c, I.deps_acc, n);
-        zero_d(c, I.deps_delta, node_len(c, i));
+        if (!I.deps_acc) I.deps_acc = c->dalloc(I.n);
+        if (!I.deps_out) I.deps_out = c->dalloc(I.n);
+        if (!I.deps_delta) I.deps_delta = c->dalloc(node_len(c, i));
       }
+    });
+    for (int i = 0; dO_deps && i < B; ++i) {
+      zero_d(c, c->inst[i].deps_acc, c->inst[i].n);
+      zero_d(c, c->inst[i].deps_delta, node_len(c, i));
     }
     const bool want_theta = dO_dtheta && (deri_dtheta || dh_dtheta);
     // device copies of the theta directions
@@ -2241,7 +2281,6 @@ int ftcc_response(ftcc_ctx* c, double* dO_dmu, double* dO_dbeta, double* dO_dh, 
     // dot launches: <lamt_x, dS_x> and (g_x/beta) dE_x accumulated into acc[slot]
     // all (instance, node) dots in one launch, then the node sums per instance
     auto accumulate = [&](int slot) {
-      ensure_resp_groups(c);
       launch_dot(c->d_resp_dots, B * m, 64, c->scratch.dot_partial, c->stream);
       hipLaunchKernelGGL(resp_combine_kernel, dim3((B + 63) / 64), dim3(64), 0, c->stream, B, m,
                          (const double*)c->d_resp_vals, c->d_de_ptrs, (const double*)c->d_resp_w, c->d_acc_ptrs, slot);
@@ -2486,7 +2525,6 @@ int ftcc_response(ftcc_ctx* c, double* dO_dmu, double* dO_dbeta, double* dO_dh, 
       // beta: explicit dependence of the propagator weights (needs S at converged s)
       if (dO_dbeta) {
         tau_run(c, TAU_BETA, p);
-        ensure_resp_groups(c);
         launch_partial_sums(B, c->d_partial, c->d_beta_off, 1.0 / P, c->d_acc_ptrs, 3, c->stream);
         FTCC_HIP(hipGetLastError());
       }
@@ -2517,7 +2555,6 @@ int ftcc_response(ftcc_ctx* c, double* dO_dmu, double* dO_dbeta, double* dO_dh, 
     hipLaunchKernelGGL(meanfield_kernel, dim3(B), dim3(256), 0, c->stream, (const SetupProblem*)c->d_setup,
                        (const double*)c->d_mubeta, want_theta ? (const double* const*)c->d_dirs : nullptr, c->gdeg);
     FTCC_HIP(hipGetLastError());
-    ensure_resp_groups(c);
     hipLaunchKernelGGL(gather_acc_kernel, dim3((13 * B + 255) / 256), dim3(256), 0, c->stream, B, c->d_acc_ptrs,
                        (const SetupProblem*)c->d_setup, c->d_acc_all);
     FTCC_HIP(hipGetLastError());

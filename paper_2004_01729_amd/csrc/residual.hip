@@ -34,12 +34,14 @@
 // 2 W1 + W3 of the usual ring intermediate W1_mbej = g_mbej + t_jf Z_mbef - t_nb g_mnej
 // + t2_njfb L_mnef / 2 - t2_jnfb g_mnef / 2: with it the ring terms
 // (2 t2_imae - t2_imea) W1_mbej + t2_imae W3_mbej are the two above and the two t2
-// products of W1 are one, for any t2 (8 O(n^6) contractions instead of 9).
+// products of W1 are one, for any t2 (8 O(n^6) contractions instead of 9).  T2y, Zs and
+// their gradients are four more arrays of n^4 per slot, and Lo4 one per executor: where
+// they do not fit, the lean form has W1 in the place of Ws.
 #include "engine.h"
 
 namespace ftcc {
 
-Program build_residual_program() {
+Program build_residual_program(bool lean) {
   Program P;
   P.tensor("t1", 2, T_INPUT);
   P.tensor("t2", 4, T_INPUT);
@@ -48,8 +50,11 @@ Program build_residual_program() {
                         "g_vvvo", "g_ovoo", "g_vvoo"})
     P.tensor(g, 4, T_CONST);
   for (const char* x : {"L", "Lo3", "Lo4", "Lvo", "Lov3", "tt", "tau", "taut", "T2x", "T2y", "Wmnij", "Wabef", "Z", "Zs",
-                        "Ws", "W3", "P1", "Q2", "X"})
-    P.tensor(x, 4, T_INTER);
+                        "Ws", "W3", "P1", "Q2", "X"}) {
+    const std::string name = x;
+    if (lean && (name == "Lo4" || name == "T2y" || name == "Zs")) continue;
+    P.tensor(lean && name == "Ws" ? "W1" : x, 4, T_INTER);
+  }
   for (const char* x : {"Fme", "Fae", "Fmi", "Fpbe", "Fpmj"}) P.tensor(x, 2, T_INTER);
   P.tensor("S1", 2, T_OUTPUT);
   P.tensor("S2", 4, T_OUTPUT);
@@ -69,8 +74,10 @@ Program build_residual_program() {
   P.add("L", "mnef", -1.0, "g_oovv", "mnfe");
   P.set("Lo3", "mnie", 2.0, "g_ooov", "mnie");
   P.add("Lo3", "mnie", -1.0, "g_oovo", "mnei");
-  P.set("Lo4", "mnej", 2.0, "g_oovo", "mnej");
-  P.add("Lo4", "mnej", -1.0, "g_ooov", "mnje");
+  if (!lean) {
+    P.set("Lo4", "mnej", 2.0, "g_oovo", "mnej");
+    P.add("Lo4", "mnej", -1.0, "g_ooov", "mnje");
+  }
   P.set("Lvo", "nafi", 2.0, "g_ovvo", "nafi");
   P.add("Lvo", "nafi", -1.0, "g_ovov", "naif");
   P.set("Lov3", "mafe", 2.0, "g_ovvv", "mafe");
@@ -84,8 +91,10 @@ Program build_residual_program() {
   P.add("taut", "ijab", 0.5, "tt", "ijab");
   P.set("T2x", "imae", 2.0, "t2", "imae");
   P.add("T2x", "imae", -1.0, "t2", "imea");
-  P.set("T2y", "njfb", 2.0, "t2", "njfb");
-  P.add("T2y", "njfb", -1.0, "t2", "jnfb");
+  if (!lean) {
+    P.set("T2y", "njfb", 2.0, "t2", "njfb");
+    P.add("T2y", "njfb", -1.0, "t2", "jnfb");
+  }
 
   // one-body intermediates
   P.set("Fme", "me", 1.0, "u_ov", "me");
@@ -113,12 +122,20 @@ Program build_residual_program() {
   P.add("Wabef", "abef", -1.0, "t1", "ma", "g_ovvv", "mbef");
   P.set("Z", "mbef", 1.0, "g_ovvv", "mbef");
   P.add("Z", "mbef", -1.0, "t1", "nb", "g_oovv", "mnef");
-  P.set("Zs", "mbef", 1.0, "Lov3", "mbef");
-  P.add("Zs", "mbef", -1.0, "t1", "nb", "L", "mnef");
-  P.set("Ws", "mbej", 1.0, "Lvo", "mbej");
-  P.add("Ws", "mbej", 1.0, "t1", "jf", "Zs", "mbef");
-  P.add("Ws", "mbej", -1.0, "t1", "nb", "Lo4", "mnej");
-  P.add("Ws", "mbej", 0.5, "T2y", "njfb", "L", "mnef");
+  if (lean) {
+    P.set("W1", "mbej", 1.0, "g_ovvo", "mbej");
+    P.add("W1", "mbej", 1.0, "t1", "jf", "Z", "mbef");
+    P.add("W1", "mbej", -1.0, "t1", "nb", "g_oovo", "mnej");
+    P.add("W1", "mbej", 0.5, "t2", "njfb", "L", "mnef");
+    P.add("W1", "mbej", -0.5, "t2", "jnfb", "g_oovv", "mnef");
+  } else {
+    P.set("Zs", "mbef", 1.0, "Lov3", "mbef");
+    P.add("Zs", "mbef", -1.0, "t1", "nb", "L", "mnef");
+    P.set("Ws", "mbej", 1.0, "Lvo", "mbej");
+    P.add("Ws", "mbej", 1.0, "t1", "jf", "Zs", "mbef");
+    P.add("Ws", "mbej", -1.0, "t1", "nb", "Lo4", "mnej");
+    P.add("Ws", "mbej", 0.5, "T2y", "njfb", "L", "mnef");
+  }
   P.set("W3", "mbej", -1.0, "g_ovov", "mbje");
   P.add("W3", "mbej", -1.0, "t1", "jf", "Z", "mbfe");
   P.add("W3", "mbej", 1.0, "t1", "nb", "g_ooov", "mnje");
@@ -133,8 +150,13 @@ Program build_residual_program() {
   P.add("X", "ijab", -1.0, "t2", "imab", "Fpmj", "mj");
   P.add("X", "ijab", 0.5, "tau", "mnab", "Wmnij", "mnij");
   P.add("X", "ijab", 0.5, "tau", "ijef", "Wabef", "abef");
-  P.add("X", "ijab", 0.5, "T2x", "imae", "Ws", "mbej");
-  P.add("X", "ijab", 0.5, "t2", "imea", "W3", "mbej");
+  if (lean) {
+    P.add("X", "ijab", 1.0, "T2x", "imae", "W1", "mbej");
+    P.add("X", "ijab", 1.0, "t2", "imae", "W3", "mbej");
+  } else {
+    P.add("X", "ijab", 0.5, "T2x", "imae", "Ws", "mbej");
+    P.add("X", "ijab", 0.5, "t2", "imea", "W3", "mbej");
+  }
   P.add("X", "ijab", 1.0, "t2", "mjae", "W3", "mbei");
   P.add("X", "ijab", 1.0, "t1", "ie", "P1", "abej");
   P.add("X", "ijab", -1.0, "t1", "je", "Q2", "abie");

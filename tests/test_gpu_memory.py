@@ -1,8 +1,9 @@
 """Contexts whose device memory is limited: a caller's allocator that returns NULL beyond
-a limit.  What is optional (private copies of accumulated outputs) never fails a call
-that fits without it.  Results agree with an unlimited context's to the difference of
-the summation orders: the sweeps stop at 1e-13 of the amplitudes, 1e-11 of the largest
-element is allowed."""
+a limit.  What is optional (private copies of accumulated outputs, permuted operand
+copies) and what the eight-contraction form of the residual takes beyond the
+nine-contraction one never fails a call that fits without it.  Results agree with an
+unlimited context's to the difference of the summation orders: the sweeps stop at
+1e-13 of the amplitudes, 1e-11 of the largest element is allowed."""
 import numpy as np
 import pytest
 
@@ -107,6 +108,22 @@ def test_step_without_room_for_optional_copies(F, kind):
     _close(out, ref)
 
 
+@pytest.mark.parametrize("kind", ["ring6", "pair10", "dense10", "dense41"])
+def test_step_with_less_room_than_the_eight_contraction_form(F, kind):
+    """One byte less than the form with eight contractions takes."""
+    ref, held = _run(F, kind, mem_cap_bytes=NO_COPIES)
+    out, less = _run(F, kind, limit=held - 1)
+    _close(out, ref)
+    assert less < held
+
+
+@pytest.mark.parametrize("kind", ["ring6", "pair10", "dense10"])
+def test_response_without_room_after_the_solve(F, kind):
+    ref, _ = _run(F, kind)
+    out, _ = _run(F, kind, after_solve=True)
+    _close(out, ref)
+
+
 def _density(F, kind, room=None, monkeypatch=None, **opt):
     """The density with `room` bytes beyond what solve, lambda and response hold."""
     s, pool = _system(kind), Pool()
@@ -124,11 +141,13 @@ def _density(F, kind, room=None, monkeypatch=None, **opt):
     return gam, took
 
 
+@pytest.mark.parametrize("less", [0, 1])
 @pytest.mark.parametrize("kind", ["ring6", "pair10", "dense10"])
-def test_density_without_room_for_optional_copies(F, kind):
-    """Room for the density's own buffers only."""
+def test_density_without_room_for_optional_copies(F, kind, less):
+    """Room for the density's own buffers only, and one byte less than that (the
+    executors' nine-contraction form makes up for it)."""
     ref, took = _density(F, kind, mem_cap_bytes=NO_COPIES)
-    gam, _ = _density(F, kind, room=took)
+    gam, _ = _density(F, kind, room=took - less)
     _close(gam, ref)
 
 
