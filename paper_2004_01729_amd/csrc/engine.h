@@ -160,8 +160,8 @@ bool packing_enabled();
 
 struct Scratch {
   std::vector<double*> a, b, c, part;   // per problem: n^4 doubles each
-  double* dot_partial = nullptr;        // >= n_prob * kMaxDotBlocks doubles
-  double* tail_ws = nullptr;            // partial tiles of split GEMM tails, blocked GEMM chunks, blocked dots
+  double* dot_partial = nullptr;        // >= n_prob * 64 doubles
+  double* tail_ws = nullptr;            // partial tiles of split GEMM tails, blocked GEMM chunks, blocked and wide dots
   size_t tail_ws_doubles = 0;           // its size (at most kTailWorkspaceDoubles)
 };
 

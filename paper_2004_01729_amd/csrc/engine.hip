@@ -494,10 +494,13 @@ void Executor::contract(std::vector<Launch>& dst, const PerProb& out, const std:
     // from a million elements on 64 blocks of 256 threads read less than the memory delivers
     // (57 orbitals: 281 us with 64)
     L.dot_blocks = 64;
-    for (const DotProblem& d : ds)
-      if (d.len >= (1L << 20)) L.dot_blocks = kMaxDotBlocks;
-    L.d_desc = upload(ds.data(), sizeof(DotProblem) * np);
     L.d_partial = scratch_->dot_partial;
+    for (const DotProblem& d : ds)
+      if (d.len >= (1L << 20) && (size_t)np * kMaxDotBlocks <= scratch_->tail_ws_doubles) {
+        L.dot_blocks = kMaxDotBlocks;
+        L.d_partial = scratch_->tail_ws;
+      }
+    L.d_desc = upload(ds.data(), sizeof(DotProblem) * np);
     L.tag = tag;
     dst.push_back(L);
     return;

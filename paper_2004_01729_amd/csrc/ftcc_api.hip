@@ -823,16 +823,13 @@ static void build_buffers(ftcc_ctx* c) {
   if (mom) {
     std::vector<const InstMomentum*> labels;
     std::vector<ProblemRef> one;
-    long longest = 0;
     for (int i = 0; i < B; ++i) {
       labels.push_back(&c->inst[i].mom);
       one.push_back({i, 0, c->inst[i].n});
-      longest = std::max(longest, node_len_of(c->inst[i].n));
     }
     Executor probe;
     probe.set_momentum(labels);
     c->packed_states = probe.io_packable(&c->prog, one);
-    if (c->packed_states) c->dense_node = c->dalloc(longest);
   }
   if (mom)
     for (int i = 0; i < B; ++i) {
@@ -906,8 +903,6 @@ static void build_buffers(ftcc_ctx* c) {
       I.rk_tmp[1] = c->dalloc(len);
       I.rk_hbar = c->dalloc(1);
     }
-    if (c->rk)
-      for (int k = 0; k < 4; ++k) I.rk_ugrad[k] = c->dalloc((size_t)I.n * I.n);
   }
   if (c->rk || c->simpson) {
     // (1/beta) g_k of Simpson's rule on the uniform grid: w_k / (3 n_g), w = 1 4 2 ... 4 1
@@ -915,7 +910,7 @@ static void build_buffers(ftcc_ctx* c) {
     for (int k = 0; k <= P; ++k) w[k] = ((k == 0 || k == P) ? 1.0 : (k % 2 ? 4.0 : 2.0)) / (3.0 * P);
     w.push_back(0.0);
     c->d_rkw = c->dalloc(P + 2);
-    c->d_rkh = c->dalloc(B);
+    if (c->rk) c->d_rkh = c->dalloc(B);
     FTCC_HIP(hipMemcpy(c->d_rkw, w.data(), sizeof(double) * (P + 2), hipMemcpyHostToDevice));
   }
   trace_mem(c, "integrals, panel states and Lambda storage");
@@ -960,8 +955,9 @@ static void build_buffers(ftcc_ctx* c) {
       c->gr[p] = c->dalloc(len);
       c->cot[p] = c->dalloc(len);
       c->ebar[p] = c->dalloc(1);
-      // with one slot the derivative residuals reuse the gradient buffers (never live together)
-      c->dS[p] = (SL == m) ? c->dalloc(len) : c->gr[p];
+      // with one slot, and in the differential form, the derivative residuals reuse the
+      // gradient buffers (never live together)
+      c->dS[p] = (SL == m && !c->rk) ? c->dalloc(len) : c->gr[p];
       c->de[p] = c->de_all + p;
       for (int k = 0; k < 4; ++k) c->ugrad[p][k] = c->dalloc(n2);
       const double eb = c->rule.b[x] / P;   // (1/beta) g_x
@@ -982,6 +978,7 @@ static void build_buffers(ftcc_ctx* c) {
   c->s_dS.resize(np);
   c->s_de.resize(np);
   c->s_ugrad.resize(np);
+  int widest = 0;
   for (int i = 0; i < B; ++i)
     for (int x = 0; x < SL; ++x) {
       const int q = i * SL + x;
@@ -1009,14 +1006,21 @@ static void build_buffers(ftcc_ctx* c) {
         c->s_de[q] = c->dalloc(1);
         for (int k = 0; k < 4; ++k) c->s_ugrad[q][k] = c->dalloc(n2);
       }
-      c->scratch.a[q] = c->dalloc(n4);
+      // (with packed states: the largest also holds the interface's dense node state)
+      c->scratch.a[q] = c->dalloc(c->packed_states ? len : n4);
+      if (c->packed_states && n > widest) {
+        widest = n;
+        c->dense_node = c->scratch.a[q];
+      }
       c->scratch.b[q] = c->dalloc(n4);
       c->scratch.c[q] = c->dalloc(n4);
       c->scratch.part[q] = c->dalloc(n4);
     }
-  // partial sums of each dot of one launch: one dot per node, or the two Gram entries of
-  // every stored DIIS residual
-  c->scratch.dot_partial = c->dalloc((size_t)std::max(nn, c->opt.diis_depth ? 2 * kMaxDiis : 0) * kMaxDotBlocks);
+  // sums of the u blocks' gradients: the node buffers that the stages leave unused, if any
+  for (int i = 0; i < B && c->rk; ++i)
+    for (int k = 0; k < 4; ++k)
+      c->inst[i].rk_ugrad[k] = SL != m ? c->ugrad[i * m][k] : c->dalloc((size_t)c->inst[i].n * c->inst[i].n);
+  c->scratch.dot_partial = c->dalloc((size_t)nn * 64 + 64);   // partial sums of one dot per node
   {
     // workspace for partial tiles: 128 MiB, or an eighth of a memory cap below 1 GiB
     size_t ws = kTailWorkspaceDoubles;
@@ -1552,7 +1556,8 @@ void diis_after(ftcc_ctx* c, const NodeBufs& it, const std::vector<bool>& active
     DotProblem* dd = nullptr;
     FTCC_HIP(hipMallocAsync((void**)&dd, sizeof(DotProblem) * ds.size(), c->stream));
     FTCC_HIP(hipMemcpyAsync(dd, ds.data(), sizeof(DotProblem) * ds.size(), hipMemcpyHostToDevice, c->stream));
-    launch_dot(dd, (int)ds.size(), 64, c->scratch.dot_partial, c->stream);
+    // (up to 16 dots, whatever the number of nodes: more than dot_partial is sized for)
+    launch_dot(dd, (int)ds.size(), 64, c->scratch.tail_ws, c->stream);
     FTCC_HIP(hipFreeAsync(dd, c->stream));
   }
   if (!any) return;

@@ -46,8 +46,8 @@ class Pool:
 
 def _system(kind):
     """(h, eri, eps, mu, beta, labels or None)"""
-    if kind == "ring6":         # a label per orbital
-        s = fi.hubbard_config(L=6, U=2.0, T=1.0)
+    if kind.startswith("ring"):   # a label per orbital
+        s = fi.hubbard_config(L=int(kind[4:]), U=2.0, T=1.0)
         return s.h, s.eri, s.eps, s.mu, s.beta, s.momentum
     n = int(kind.lstrip("dense").lstrip("pair"))
     h, eri, eps = fi.random_hamiltonian(n, seed=n, scale=0.2 / n)
@@ -159,3 +159,24 @@ def test_density_takes_no_more_with_packed_states(F, monkeypatch):
         monkeypatch.setenv("FTCC_PACK", pack)
         took.append(_density(F, "ring6", mem_cap_bytes=NO_COPIES)[1])
     assert took[0] <= took[1]
+
+
+# the least that solve, Lambda, the response (mu, beta, h, eps) and the density (but
+# propagator 5) ran in before the node states were packed
+LEAST = [("ring10", 0, 0, 144829184), ("ring10", 2, 0, 142078976), ("ring10", 4, 0, 144284160),
+         ("ring10", 5, 0, 139591680), ("ring10", 0, 4, 146124544), ("pair14", 0, 0, 186715136),
+         ("pair14", 4, 0, 178135296), ("dense12", 0, 0, 181944576)]
+
+
+@pytest.mark.parametrize("kind,propagator,diis,limit", LEAST)
+def test_runs_in_the_memory_it_ran_in(F, kind, propagator, diis, limit):
+    s, pool = _system(kind), Pool()
+    pool.limit = limit
+    print(f"[memory] {kind} propagator={propagator} diis={diis} limit={limit}", flush=True)
+    ctx = _context(F, s, pool, propagator=propagator, diis_depth=diis)
+    try:
+        _step(ctx, s)
+        if propagator != 5:
+            ctx.two_body_density()
+    finally:
+        ctx.close()
