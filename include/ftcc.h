@@ -99,11 +99,13 @@ typedef struct {
   int diis_depth;       /* 0: plain fixed-point sweeps; 2..8: DIIS (Anderson) extrapolation over
                            this many sweeps, forward and adjoint (needs 2 * depth * m * (n^2 + n^4)
                            doubles per instance) */
-  size_t mem_cap_bytes; /* 0: no cap.  Otherwise an upper bound on the device memory the context
-                           allocates; the schedule is chosen to fit it: checkpointing is switched
-                           on when the stored tau grid would take more than half the cap, and the
-                           nodes of a panel share one executor slot when the per-node working set
-                           would not fit.  An allocation beyond the cap fails with FTCC_ENOMEM. */
+  size_t mem_cap_bytes; /* 0: no cap.  Otherwise an upper bound on the context's bulk buffers (see
+                           ftcc_set_allocator); the schedule is chosen to fit it: checkpointing is
+                           switched on when the stored tau grid would take more than half the cap,
+                           the nodes of a panel share one executor slot when the per-node working
+                           set would not fit, and the residual takes nine O(n^6) contractions
+                           instead of eight when their arrays would not.  An allocation beyond the
+                           cap fails with FTCC_ENOMEM. */
   int spin_orbital;     /* 0: spin-restricted spatial orbitals (closed-shell amplitudes);
                            1: general spin orbitals (unrestricted references such as the Neel
                            state or UHF, Section IV.A): h is N x N, <pq|rs> N^4 over spin orbitals
@@ -133,8 +135,10 @@ int ftcc_set_stream(ftcc_ctx* ctx, void* hip_stream);
  *   free(ptr, user) is called once for every pointer alloc returned, in
  *   ftcc_destroy (free may be NULL when the caller reclaims the memory itself).
  * Must be called before the first ftcc_set_hamiltonian (FTCC_ESTATE otherwise).
- * NULL alloc restores hipMalloc / hipFree.  Launch descriptors (a few KB) are
- * always the library's own hipMalloc. */
+ * NULL alloc restores hipMalloc / hipFree.  Launch descriptors and the index
+ * lists of blocked contractions are always the library's own hipMalloc, and
+ * beside mem_cap_bytes (a few MB for tens of orbitals; with labels a list
+ * takes 4 bytes per element of a packed tensor). */
 typedef void* (*ftcc_alloc_fn)(size_t bytes, void* user);
 typedef void (*ftcc_free_fn)(void* ptr, void* user);
 int ftcc_set_allocator(ftcc_ctx* ctx, ftcc_alloc_fn alloc, ftcc_free_fn free_fn, void* user);

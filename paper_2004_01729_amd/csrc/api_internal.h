@@ -241,14 +241,14 @@ struct ftcc_ctx {
   char* desc_at = nullptr;        // the free part of the last chunk
   size_t desc_left = 0;
   void* desc(const void* host, size_t nbytes) {
-    constexpr size_t kChunk = size_t(1) << 20;
     const size_t need = (std::max<size_t>(nbytes, 8) + 255) / 256 * 256;
-    if (need > desc_left) {
+    if (need > desc_left) {   // the next chunk: 64 KiB, then twice the one before, up to 1 MiB
+      const size_t size = std::max(need, size_t(65536) << std::min<size_t>(descs.size(), 4));
       void* chunk = nullptr;
-      FTCC_HIP(hipMalloc(&chunk, std::max(need, kChunk)));
+      FTCC_HIP(hipMalloc(&chunk, size));
       descs.push_back(chunk);
       desc_at = (char*)chunk;
-      desc_left = std::max(need, kChunk);
+      desc_left = size;
     }
     void* p = desc_at;
     desc_at += need;

@@ -311,8 +311,10 @@ class Executor {
   // over at the end of build() (flush_uploads), one transfer per chunk.
   void* upload(const void* host, size_t bytes);
   void flush_uploads();
+  void end_uploads();
   struct Chunk {
     char* dev = nullptr;
+    size_t size = 0;
     std::vector<char> host;
     size_t flushed = 0;
   };

@@ -101,8 +101,8 @@ Executor::~Executor() {
 }
 
 void* Executor::upload(const void* host, size_t bytes) {
-  constexpr size_t kChunk = (size_t)4 << 20, kAlign = 256;
-  if (bytes > kChunk / 4) {
+  constexpr size_t kFirst = (size_t)64 << 10, kLast = (size_t)4 << 20, kAlign = 256;
+  if (bytes > kLast / 4) {
     void* d = nullptr;
     FTCC_HIP(hipMalloc(&d, bytes));
     owned_.push_back(d);
@@ -110,14 +110,16 @@ void* Executor::upload(const void* host, size_t bytes) {
     return d;
   }
   const size_t need = (std::max<size_t>(bytes, 8) + kAlign - 1) / kAlign * kAlign;
-  if (chunks_.empty() || chunks_.back().host.size() + need > kChunk) {
+  if (chunks_.empty() || chunks_.back().host.size() + need > chunks_.back().size) {
     flush_uploads();
     Chunk c;
+    // each twice the one before: at most half of a plan's chunks is left unused
+    c.size = std::max(need, chunks_.empty() ? kFirst : std::min(kLast, 2 * chunks_.back().size));
     void* d = nullptr;
-    FTCC_HIP(hipMalloc(&d, kChunk));
+    FTCC_HIP(hipMalloc(&d, c.size));
     owned_.push_back(d);
     c.dev = (char*)d;
-    c.host.reserve(kChunk);
+    c.host.reserve(c.size);
     chunks_.push_back(std::move(c));
   }
   Chunk& c = chunks_.back();
@@ -134,6 +136,13 @@ void Executor::flush_uploads() {
                          hipMemcpyHostToDevice));
     c.flushed = c.host.size();
   }
+}
+
+// The plan is complete: its tables are on the device, the host images are not needed.
+void Executor::end_uploads() {
+  flush_uploads();
+  chunks_.clear();
+  tuple_cache_.clear();
 }
 
 using Ranges = std::vector<std::pair<uintptr_t, uintptr_t>>;
@@ -2105,7 +2114,7 @@ void Executor::build(const Program* prog, const std::vector<ProblemRef>& probs, 
       fuse_levels(setup_);
       fuse_levels(fwd_);
     }
-    flush_uploads();
+    end_uploads();
     dump_plan();
     return;
   }
@@ -2182,7 +2191,7 @@ void Executor::build(const Program* prog, const std::vector<ProblemRef>& probs, 
     fuse_levels(fwd_);
     fuse_levels(bwd_);
   }
-  flush_uploads();
+  end_uploads();
   dump_plan();
 }
 

@@ -180,3 +180,28 @@ def test_runs_in_the_memory_it_ran_in(F, kind, propagator, diis, limit):
             ctx.two_body_density()
     finally:
         ctx.close()
+
+
+def test_descriptors_of_a_small_context_are_small(F):
+    """What a context of a 4-site ring takes beside the caller's allocator.  Descriptor
+    chunks of fixed sizes (1 MiB, and 4 MiB per executor) took at least 9 MiB; the plan
+    itself is below 1 MiB, and the stream and the graphs took 2.25 beside those chunks."""
+    import torch
+    s, pools = _system("ring4"), []
+    warm = torch.empty(1 << 32, dtype=torch.uint8, device="cuda")   # the pools' memory: held by torch
+    del warm
+
+    def one():
+        pools.append(Pool())
+        ctx = _context(F, s, pools[-1])
+        _step(ctx, s)
+        return ctx
+    ctxs = [one()]
+    torch.cuda.synchronize()
+    free, reserved = torch.cuda.mem_get_info()[0], torch.cuda.memory_reserved()
+    ctxs += [one() for _ in range(8)]
+    torch.cuda.synchronize()
+    own = free - torch.cuda.mem_get_info()[0] - (torch.cuda.memory_reserved() - reserved)
+    for c in ctxs:
+        c.close()
+    assert own / 8 < 6 << 20
