@@ -213,6 +213,14 @@ __global__ void zero_u64_kernel(unsigned long long* p, int count) {
   if (i < count) p[i] = 0ull;
 }
 
+// run flags: only `one` runs, the flags as they were go to `saved`
+__global__ void only_flag_kernel(int* flags, int* saved, int count, int one) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= count) return;
+  saved[i] = flags[i];
+  flags[i] = i == one;
+}
+
 // the sweep's maxima to host memory, cleared for the next sweep
 __global__ void post_u64_kernel(unsigned long long* p, unsigned long long* host, int count) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
@@ -1033,7 +1041,7 @@ static void build_buffers(ftcc_ctx* c) {
     FTCC_HIP(hipHostMalloc((void**)&c->h_maxbits, sizeof(unsigned long long) * 2 * B, hipHostMallocCoherent));
   if (!c->maxbits_posted) FTCC_HIP(hipEventCreateWithFlags(&c->maxbits_posted, hipEventDisableTiming));
   c->d_active = (int*)c->dalloc(B);
-  c->d_run = (int*)c->dalloc(B * SL);
+  c->d_run = (int*)c->dalloc(B * SL);   // and as many saved ones (eval_one)
   c->run_host.assign(B, 1);
   c->run_slots.assign(B * SL, 1);
   FTCC_HIP(hipMemcpy(c->d_run, c->run_slots.data(), sizeof(int) * B * SL, hipMemcpyHostToDevice));
@@ -1188,8 +1196,6 @@ void state_to_host(ftcc_ctx* c, int i, const double* state, double* t1, double* 
   sync(c);
 }
 
-constexpr int kEvalGateMinN = 12;
-
 // forward residuals of every node of the panel slots (node amplitudes -> S, E)
 void forward(ftcc_ctx* c) {
   if (c->slots == c->m) {
@@ -1270,19 +1276,15 @@ void eval_one(ftcc_ctx* c, int i) {
     return;
   }
   if (!c->prof.enabled && c->ex_main->run_forward_one(i * c->m, c->stream)) return;
-  // The blocked launches hold every problem: the others' tasks return at once.  Below
-  // this size a pass of all nodes costs no more than switching the flags.
-  if (c->B == 1 && c->inst[i].n < kEvalGateMinN) {
-    run_fwd_slots(c);
-    return;
-  }
-  std::vector<int> only(c->run_slots.size(), 0);
-  only[i * c->m] = 1;
-  FTCC_HIP(hipMemcpyAsync(c->d_run, only.data(), sizeof(int) * only.size(), hipMemcpyHostToDevice, c->stream));
+  // The launches hold every problem: the others' tasks return at once (at 6 orbitals a pass of
+  // four nodes costs no less, 170 us either way; at 24, 1070 us against 860).  On the stream
+  // alone, so that the caller's thread goes on while the GPU works.
+  const int count = (int)c->run_slots.size(), q = i * c->m;
+  int* saved = c->d_run + count;
+  hipLaunchKernelGGL(only_flag_kernel, dim3((count + 255) / 256), dim3(256), 0, c->stream, c->d_run, saved, count, q);
+  FTCC_HIP(hipGetLastError());
   run_fwd_slots(c);
-  FTCC_HIP(hipMemcpyAsync(c->d_run, c->run_slots.data(), sizeof(int) * c->run_slots.size(), hipMemcpyHostToDevice,
-                          c->stream));
-  FTCC_HIP(hipStreamSynchronize(c->stream));   // both host arrays are read by then
+  FTCC_HIP(hipMemcpyAsync(c->d_run, saved, sizeof(int) * count, hipMemcpyDeviceToDevice, c->stream));
 }
 
 // reverse pass of every node (cotangents cot, E weights ebar -> gradients gr, ugrad).
@@ -2636,7 +2638,7 @@ int ftcc_eval_residual(ftcc_ctx* c, int i, double mu, double beta, const double*
                       c->stream);
     for (int x = 1; x < c->m; ++x) node_copy(c, i, c->amp[q + x], c->amp[q]);
     eval_one(c, i);
-    if (S2) touch_pages(S2, sizeof(double) * n4);   // while the GPU works
+    if (S2) touch_pages(S2, sizeof(double) * n4);   // the evaluation is queued: while the GPU works
     state_to_host(c, i, c->S[q], S1, S2);
     if (E) FTCC_HIP(hipMemcpyAsync(E, c->e[q], sizeof(double), hipMemcpyDeviceToHost, c->stream));
     sync(c);

@@ -136,3 +136,45 @@ def test_kernel_profile_enabled_before_first_solve(F):
     ctx.close()
     assert kp["launches"] > 0 and kp["seconds"] > 0.0 and kp["flops"] > 0.0
     assert om0 == om1
+
+
+@pytest.mark.parametrize("labels", [False, True])
+def test_a_residual_leaves_the_other_nodes_and_instances_running(F, labels):
+    """Residuals of both instances of a batch, in between and before a solve: the solve is
+    that of a context that evaluated none, bit for bit, and so is each residual."""
+    systems = [fi.hubbard_config(L=L, U=2.0, T=1.0) for L in (13, 5)]
+    rng = np.random.default_rng(3)
+    amps = []
+    for s in systems:
+        n = s.eps.size
+        k = np.arange(n)
+        t2 = 0.02 * rng.standard_normal((n,) * 4)
+        amps.append((0.02 * np.diag(rng.standard_normal(n)),
+                     t2 * ((k[:, None, None, None] + k[:, None, None] - k[:, None] - k) % n == 0)))
+
+    def context():
+        ctx = F.Context(2, n_tau=4, nodes_per_panel=2, tol=1e-12)
+        for i, s in enumerate(systems):
+            if labels:
+                ctx.set_momentum(i, *s.momentum)
+            ctx.set_hamiltonian(i, s.h, s.eri, s.eps)
+        return ctx
+
+    def residual(ctx, i):
+        print(f"[batch] residual of instance {i}, labels={labels}", flush=True)
+        return ctx.eval_residual(i, systems[i].mu, systems[i].beta, *amps[i])
+
+    def solve(ctx):
+        ctx.solve([s.mu for s in systems], [s.beta for s in systems])
+        return [ctx.grand_potential()[0], *ctx.amplitudes(0, 3), *ctx.amplitudes(1, 3)]
+
+    a, b = context(), context()
+    r0, r1 = residual(a, 0), residual(a, 1)
+    out = solve(a)
+    again = residual(a, 0)
+    ref = solve(b)
+    late = residual(b, 1)
+    a.close()
+    b.close()
+    for x, y in zip(out + list(r0) + list(r1), ref + list(again) + list(late)):
+        assert np.array_equal(x, y)
