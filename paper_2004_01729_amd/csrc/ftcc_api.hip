@@ -1283,7 +1283,10 @@ void eval_one(ftcc_ctx* c, int i) {
   int* saved = c->d_run + count;
   hipLaunchKernelGGL(only_flag_kernel, dim3((count + 255) / 256), dim3(256), 0, c->stream, c->d_run, saved, count, q);
   FTCC_HIP(hipGetLastError());
+  const std::vector<int> before = c->run_slots;   // the host copy counts the flops of what runs
+  for (int p = 0; p < count; ++p) c->run_slots[p] = p == q;
   run_fwd_slots(c);
+  std::copy(before.begin(), before.end(), c->run_slots.begin());
   FTCC_HIP(hipMemcpyAsync(c->d_run, saved, sizeof(int) * count, hipMemcpyDeviceToDevice, c->stream));
 }
 

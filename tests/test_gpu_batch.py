@@ -138,6 +138,25 @@ def test_kernel_profile_enabled_before_first_solve(F):
     assert om0 == om1
 
 
+def test_kernel_profile_counts_the_one_node_of_a_residual(F):
+    """An evaluated residual is one node of the panel's four: under the profiler it counts a
+    quarter of the flops of a pass of all nodes through the same launches."""
+    s = fi.ueg_config(57, 14, 1.0, 0.5)
+    t1, t2 = fi.random_amplitudes(57, seed=1, scale=0.02)
+    print("[profile] ueg 57 PW, one residual and one pass of four nodes", flush=True)
+    ctx = F.Context(1, n_tau=4, nodes_per_panel=4, checkpoint=1)
+    ctx.set_hamiltonian(0, s.h, s.eri, s.eps)
+    ctx.eval_residual(0, s.mu, s.beta, t1, t2)
+    ctx.kernel_profile(1)
+    ctx.time_residual(1)
+    four = ctx.kernel_profile(1)
+    ctx.eval_residual(0, s.mu, s.beta, t1, t2)
+    one = ctx.kernel_profile(0)
+    ctx.close()
+    assert one["launches"] == four["launches"] > 0
+    assert 4 * one["flops"] == four["flops"] > 0.0
+
+
 @pytest.mark.parametrize("labels", [False, True])
 def test_a_residual_leaves_the_other_nodes_and_instances_running(F, labels):
     """Residuals of both instances of a batch, in between and before a solve: the solve is
