@@ -213,12 +213,12 @@ __global__ void zero_u64_kernel(unsigned long long* p, int count) {
   if (i < count) p[i] = 0ull;
 }
 
-// run flags: only `one` runs, the flags as they were go to `saved`
+// run flags: only `one` runs, the flags as they were go to `saved`; one < 0: from there back
 __global__ void only_flag_kernel(int* flags, int* saved, int count, int one) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= count) return;
-  saved[i] = flags[i];
-  flags[i] = i == one;
+  if (one >= 0) saved[i] = flags[i];
+  flags[i] = one >= 0 ? i == one : saved[i];
 }
 
 // the sweep's maxima to host memory, cleared for the next sweep
@@ -1287,7 +1287,8 @@ void eval_one(ftcc_ctx* c, int i) {
   for (int p = 0; p < count; ++p) c->run_slots[p] = p == q;
   run_fwd_slots(c);
   std::copy(before.begin(), before.end(), c->run_slots.begin());
-  FTCC_HIP(hipMemcpyAsync(c->d_run, saved, sizeof(int) * count, hipMemcpyDeviceToDevice, c->stream));
+  hipLaunchKernelGGL(only_flag_kernel, dim3((count + 255) / 256), dim3(256), 0, c->stream, c->d_run, saved, count, -1);
+  FTCC_HIP(hipGetLastError());
 }
 
 // reverse pass of every node (cotangents cot, E weights ebar -> gradients gr, ugrad).
