@@ -129,7 +129,7 @@ __device__ __forceinline__ double seg_delta(const double* eps_ptr, int n, int ra
 
 __device__ __forceinline__ double delta_of(const TauProblem& P, long e) { return seg_delta(P.eps, P.n, P.rank, e); }
 
-// max that propagates NaN as +infinity (fmax would drop it)
+// max that propagates a NaN b as +infinity (fmax would drop it); a is not NaN
 __device__ __forceinline__ double nan_max(double a, double b) {
   if (b != b) return INFINITY;
   return fmax(a, b);
@@ -342,7 +342,7 @@ __global__ void __launch_bounds__(256) rk_combine_kernel(const RKProblem* __rest
       v += hc * P.coef[l] * (-d * y + P.sigma * sv);
     }
     gview(P.out)[at] = v;
-    vmax = fabs(v);
+    vmax = nan_max(0.0, fabs(v));   // a NaN as infinity: nan_max below would drop one on its left
   }
   if (!P.maxbits) return;   // uniform per launch problem
   __shared__ double red[256];

@@ -215,3 +215,27 @@ def test_first_response_of_a_context_equals_the_second(F, propagator):
     for key in ("mu", "beta"):
         assert np.array_equal(out[0][key], out[1][key])
     assert np.array_equal(out[0]["h"][0], out[1]["h"][0]) and np.abs(out[0]["h"][0]).max() > 0.1
+
+
+@pytest.mark.parametrize("propagator", [3, 4])
+@pytest.mark.parametrize("n", [2, 4, 6])
+def test_divergence_of_a_short_segment_is_reported(F, n, propagator):
+    """Amplitudes with n and n^3 allowed elements, fewer than the threads of a block: all of
+    them non-finite beside threads without an element.  The march fails with
+    FTCC_ENONFINITE as it does without labels, and the other instance is unaffected."""
+    bad = fi.hubbard_config(L=n, U=60.0, T=0.02)
+    good = fi.hubbard_config(L=n, U=2.0, T=1.0)
+    out = []
+    for labels in (True, False):
+        print(f"[rk] divergent ring of {n}, propagator={propagator}, labels={labels}", flush=True)
+        ctx = F.Context(2, n_tau=8, propagator=propagator)
+        for i, s in enumerate((bad, good)):
+            if labels:
+                ctx.set_momentum(i, *s.momentum)
+            ctx.set_hamiltonian(i, s.h, s.eri, s.eps)
+        _, st = ctx.solve([bad.mu, good.mu], [bad.beta, good.beta], raise_on_status=False)
+        out.append((list(st), ctx.grand_potential()[0]))
+        ctx.close()
+    for st, om in out:
+        assert st == [F.ENONFINITE, 0] and np.isnan(om[0])
+    assert abs(out[0][1][1] - out[1][1][1]) < 1e-11 * abs(out[1][1][1])
