@@ -175,7 +175,6 @@ struct ftcc_ctx {
   KernelProfiler prof;
   hipGraphExec_t g_fwd = nullptr, g_bwd = nullptr;
   hipGraphExec_t g_fwd_sweep = nullptr, g_fwd_rest = nullptr, g_bwd_sweep = nullptr;
-  std::vector<int> beta_part_off;             // first TAU_BETA partial of each instance
   std::vector<int> active_host;               // per-instance "still iterating" flags
   std::map<std::pair<int, int>, std::pair<TauProblem*, int*>> tau_cache;
   std::map<std::pair<int, int>, std::pair<int, int>> tau_shape;   // (n_prob, blocks)

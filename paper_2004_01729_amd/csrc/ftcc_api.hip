@@ -1071,11 +1071,7 @@ static void build_buffers(ftcc_ctx* c) {
   FTCC_HIP(hipMemcpy(c->d_rule, &c->rule, sizeof(PanelRule), hipMemcpyHostToDevice));
   {
     size_t blocks = 16;
-    c->beta_part_off.assign(B, 0);
-    for (int i = 0; i < B; ++i) {
-      c->beta_part_off[i] = (int)blocks - 16;
-      blocks += (seg_len(c, i, 0) + 1023) / 1024 + (seg_len(c, i, 1) + 1023) / 1024;
-    }
+    for (int i = 0; i < B; ++i) blocks += (seg_len(c, i, 0) + 1023) / 1024 + (seg_len(c, i, 1) + 1023) / 1024;
     c->d_partial = c->dalloc(blocks);
   }
 

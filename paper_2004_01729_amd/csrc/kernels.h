@@ -88,7 +88,7 @@ void launch_gemm(int cfg, bool ta, bool tb, const GemmProblem* d_probs, const in
 // restricted to the blocks allowed by a conserved quantity.  Rows, inner indices
 // and columns of a block are lists of element offsets into the dense operands
 // (the row offset of A plus the inner offset of A addresses A[m, k], and so on),
-// so no operand is permuted.  One task is one 16 x 16 output tile of one block.
+// so no operand is permuted.  One task is one tile of one block's outputs (SgemmTask::shape).
 struct SgemmProblem {
   const double* A;
   const double* B;
@@ -108,7 +108,7 @@ struct SgemmTask {
   int mb, mlen;          // first row (index into offAM / offCM) and rows
   int kb, klen;          // first inner index (into offAK / offBK) and count
   int nb, nlen;          // first column (into offBN / offCN) and columns
-  int part;              // -1: write C; else the 16 x 16 partial tile goes to ws[part * 256 ...]
+  int part;              // -1: write C; else the partial tile goes to ws[part * 256 ...]
   int shape;             // 0: one 16 x 16 MFMA tile (rows, columns <= 16); else a lane-mapped tile of
                          // 2^lr rows x 2^lc columns whose inner range is split over 2^ls lanes
                          // (lr | lc << 3 | ls << 6, lr + lc + ls = 6; never split into parts);
@@ -132,8 +132,9 @@ struct SgemmReduce {
   int shape;             // 0: 16 x 16 tile (parts of 1 unit); kTile*: block tile (parts of 16)
   int slice;             // which 256 outputs of the tile (one entry per slice on the device)
 };
-// Inner ranges longer than this are split into chunks of kSgemmChunk (or a
-// power-of-two multiple of it when the partial tiles would not fit the workspace).
+// 16 x 16 tiles keep inner ranges of up to one and a half chunks whole (32 x 32 wave tiles
+// are taken up to three, lane-mapped tiles of any) and are split into chunks above that;
+// a chunk doubles while the partial tiles would not fit the workspace.
 constexpr int kSgemmChunk = 64;
 // the first n_square tasks are 64 x 64 block tiles, the next n_narrow the other block
 // tiles (one block each), the rest one wave each; wide: 32 x 32 wave tiles among them

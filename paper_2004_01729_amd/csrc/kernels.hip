@@ -446,10 +446,6 @@ __device__ __forceinline__ void wave_tile(const SgemmProblem& P, const SgemmTask
     const int len = min(64, klen - base);
     int j = 0;
     for (; len - j > 2 * G; j += 4 * G) step(std::integral_constant<int, G>{}, base, j);
-    if (G > 8 && len - j > 16) {
-      step(std::integral_constant<int, 8>{}, base, j);
-      j += 32;
-    }
     if (G > 4 && len - j > 8) {
       step(std::integral_constant<int, 4>{}, base, j);
       j += 16;
@@ -1088,7 +1084,7 @@ __global__ void __launch_bounds__(256) dotb_final_kernel(const DotbProblem* __re
 // adding every split of its outputs, 1024 outputs a block, left 57 x 57 outputs of 180
 // splits to four blocks: 127 us.)
 __global__ void __launch_bounds__(256) splitk_reduce_kernel(const GemmProblem* __restrict__ probs,
-                                                            const int* __restrict__ prefix, int n_prob, int total) {
+                                                            const int* __restrict__ prefix, int n_prob) {
   const int pi = find_problem(prefix, n_prob, blockIdx.x);
   const GemmProblem P = probs[pi];
   if (P.ksplit <= 1 || (P.active && *gview(P.active) == 0)) return;   // uniform per block
@@ -1330,8 +1326,7 @@ GemmTail plan_gemm_tail(int cfg, int total_tiles, int min_k, bool any_ksplit, do
 void launch_splitk_reduce(const GemmProblem* d_probs, const int* d_prefix, int n_prob, int total_blocks,
                           hipStream_t s) {
   if (total_blocks <= 0) return;
-  hipLaunchKernelGGL(splitk_reduce_kernel, dim3(total_blocks), dim3(256), 0, s, d_probs, d_prefix, n_prob,
-                     total_blocks);
+  hipLaunchKernelGGL(splitk_reduce_kernel, dim3(total_blocks), dim3(256), 0, s, d_probs, d_prefix, n_prob);
 }
 
 void launch_sgemm(const SgemmProblem* d_probs, const SgemmTask* d_tasks, int n_square, int n_narrow, int n_tasks, bool wide,
