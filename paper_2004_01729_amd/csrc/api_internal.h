@@ -223,7 +223,7 @@ struct ftcc_ctx {
     }
     // every buffer starts zeroed: momentum-blocked contractions write only the
     // allowed blocks of their outputs and rely on the forbidden elements being 0
-    if (hipMemset(p, 0, nb) != hipSuccess) fail(FTCC_EDEVICE, "hipMemset of a new buffer failed");
+    FTCC_LEGACY(hipMemset(p, 0, nb));
     bytes += nb;
     allocs.push_back(Alloc{p, nb, alloc_for});
     return (double*)p;
@@ -252,7 +252,7 @@ struct ftcc_ctx {
     void* p = desc_at;
     desc_at += need;
     desc_left -= need;
-    if (host) FTCC_HIP(hipMemcpy(p, host, nbytes, hipMemcpyHostToDevice));
+    if (host) FTCC_LEGACY(hipMemcpy(p, host, nbytes, hipMemcpyHostToDevice));
     return p;
   }
 

@@ -106,7 +106,7 @@ void* Executor::upload(const void* host, size_t bytes) {
     void* d = nullptr;
     FTCC_HIP(hipMalloc(&d, bytes));
     owned_.push_back(d);
-    FTCC_HIP(hipMemcpy(d, host, bytes, hipMemcpyHostToDevice));
+    FTCC_LEGACY(hipMemcpy(d, host, bytes, hipMemcpyHostToDevice));
     return d;
   }
   const size_t need = (std::max<size_t>(bytes, 8) + kAlign - 1) / kAlign * kAlign;
@@ -132,7 +132,7 @@ void* Executor::upload(const void* host, size_t bytes) {
 void Executor::flush_uploads() {
   for (Chunk& c : chunks_) {
     if (c.flushed < c.host.size())
-      FTCC_HIP(hipMemcpy(c.dev + c.flushed, c.host.data() + c.flushed, c.host.size() - c.flushed,
+      FTCC_LEGACY(hipMemcpy(c.dev + c.flushed, c.host.data() + c.flushed, c.host.size() - c.flushed,
                          hipMemcpyHostToDevice));
     c.flushed = c.host.size();
   }

@@ -516,7 +516,7 @@ void set_directions(ftcc_ctx* c, const std::vector<double*>& d_dh, const std::ve
     d.push_back(d_dh[i]);
     d.push_back(d_deri[i]);
   }
-  FTCC_HIP(hipMemcpy(c->d_dirs, d.data(), sizeof(double*) * d.size(), hipMemcpyHostToDevice));
+  FTCC_LEGACY(hipMemcpy(c->d_dirs, d.data(), sizeof(double*) * d.size(), hipMemcpyHostToDevice));
 }
 
 void deriv_setup(ftcc_ctx* c, int which, int q) {
@@ -596,14 +596,14 @@ void allowed_elements(ftcc_ctx* c, int i) {
     I.n_allowed[seg] = (long)l.size();
     I.d_allowed[seg] = (unsigned*)c->dalloc(l.size() / 2 + 1);
     if (!l.empty())
-      FTCC_HIP(hipMemcpy(I.d_allowed[seg], l.data(), sizeof(unsigned) * l.size(), hipMemcpyHostToDevice));
+      FTCC_LEGACY(hipMemcpy(I.d_allowed[seg], l.data(), sizeof(unsigned) * l.size(), hipMemcpyHostToDevice));
     I.d_where[seg] = I.d_allowed[seg];
     if (c->packed_states) {
       std::vector<unsigned> w(l);
       for (unsigned& e : w) e /= (unsigned)n;
       I.d_where[seg] = (unsigned*)c->dalloc(w.size() / 2 + 1);
       if (!w.empty())
-        FTCC_HIP(hipMemcpy(I.d_where[seg], w.data(), sizeof(unsigned) * w.size(), hipMemcpyHostToDevice));
+        FTCC_LEGACY(hipMemcpy(I.d_where[seg], w.data(), sizeof(unsigned) * w.size(), hipMemcpyHostToDevice));
     }
   }
 }
@@ -763,6 +763,7 @@ static void build_executors(ftcc_ctx* c) {
   if (!(genv && genv[0] == '0')) {
     // the launch lists are static: capture each once as a graph
     auto capture = [c](hipGraphExec_t* exec, const std::function<void()>& run) {
+      std::unique_lock<std::shared_mutex> alone(capture_mutex());
       hipGraph_t g;
       FTCC_HIP(hipStreamBeginCapture(c->stream, hipStreamCaptureModeThreadLocal));
       run();
@@ -844,8 +845,8 @@ static void build_buffers(ftcc_ctx* c) {
       Instance& I = c->inst[i];
       I.d_labels = (int*)c->dalloc(I.mom.labels.size() / 2 + 1);
       I.d_modulus = (int*)c->dalloc(I.mom.modulus.size() / 2 + 1);
-      FTCC_HIP(hipMemcpy(I.d_labels, I.mom.labels.data(), sizeof(int) * I.mom.labels.size(), hipMemcpyHostToDevice));
-      FTCC_HIP(
+      FTCC_LEGACY(hipMemcpy(I.d_labels, I.mom.labels.data(), sizeof(int) * I.mom.labels.size(), hipMemcpyHostToDevice));
+      FTCC_LEGACY(
           hipMemcpy(I.d_modulus, I.mom.modulus.data(), sizeof(int) * I.mom.modulus.size(), hipMemcpyHostToDevice));
       check_momentum(c, i, I.h, 2, "h");
       check_momentum(c, i, I.eri, 4, "<pq|rs>");
@@ -919,7 +920,7 @@ static void build_buffers(ftcc_ctx* c) {
     w.push_back(0.0);
     c->d_rkw = c->dalloc(P + 2);
     if (c->rk) c->d_rkh = c->dalloc(B);
-    FTCC_HIP(hipMemcpy(c->d_rkw, w.data(), sizeof(double) * (P + 2), hipMemcpyHostToDevice));
+    FTCC_LEGACY(hipMemcpy(c->d_rkw, w.data(), sizeof(double) * (P + 2), hipMemcpyHostToDevice));
   }
   trace_mem(c, "integrals, panel states and Lambda storage");
   // Executor slots per instance: every node of a panel evaluated in one grouped
@@ -969,7 +970,7 @@ static void build_buffers(ftcc_ctx* c) {
       c->de[p] = c->de_all + p;
       for (int k = 0; k < 4; ++k) c->ugrad[p][k] = c->dalloc(n2);
       const double eb = c->rule.b[x] / P;   // (1/beta) g_x
-      FTCC_HIP(hipMemcpy(c->ebar[p], &eb, sizeof(double), hipMemcpyHostToDevice));
+      FTCC_LEGACY(hipMemcpy(c->ebar[p], &eb, sizeof(double), hipMemcpyHostToDevice));
       (void)n4;
     }
   const int np = B * SL;
@@ -1044,10 +1045,10 @@ static void build_buffers(ftcc_ctx* c) {
   c->d_run = (int*)c->dalloc(B * SL);   // and as many saved ones (eval_one)
   c->run_host.assign(B, 1);
   c->run_slots.assign(B * SL, 1);
-  FTCC_HIP(hipMemcpy(c->d_run, c->run_slots.data(), sizeof(int) * B * SL, hipMemcpyHostToDevice));
+  FTCC_LEGACY(hipMemcpy(c->d_run, c->run_slots.data(), sizeof(int) * B * SL, hipMemcpyHostToDevice));
   {
     std::vector<int> ones(2 * B, 1);
-    FTCC_HIP(hipMemcpy(c->d_active, ones.data(), sizeof(int) * B, hipMemcpyHostToDevice));
+    FTCC_LEGACY(hipMemcpy(c->d_active, ones.data(), sizeof(int) * B, hipMemcpyHostToDevice));
   }
   const int D = c->opt.diis_depth;
   if (D > 0) {
@@ -1068,7 +1069,7 @@ static void build_buffers(ftcc_ctx* c) {
     c->diis_next.assign(B, 0);
   }
   c->d_rule = (PanelRule*)c->dalloc(sizeof(PanelRule) / sizeof(double) + 1);
-  FTCC_HIP(hipMemcpy(c->d_rule, &c->rule, sizeof(PanelRule), hipMemcpyHostToDevice));
+  FTCC_LEGACY(hipMemcpy(c->d_rule, &c->rule, sizeof(PanelRule), hipMemcpyHostToDevice));
   {
     size_t blocks = 16;
     for (int i = 0; i < B; ++i) blocks += (seg_len(c, i, 0) + 1023) / 1024 + (seg_len(c, i, 1) + 1023) / 1024;
@@ -1431,8 +1432,8 @@ void tau_run(ftcc_ctx* c, int mode, int panel) {
     int* d_pre = nullptr;
     FTCC_HIP(hipMalloc((void**)&d_ps, sizeof(TauProblem) * ps.size()));
     FTCC_HIP(hipMalloc((void**)&d_pre, sizeof(int) * prefix.size()));
-    FTCC_HIP(hipMemcpy(d_ps, ps.data(), sizeof(TauProblem) * ps.size(), hipMemcpyHostToDevice));
-    FTCC_HIP(hipMemcpy(d_pre, prefix.data(), sizeof(int) * prefix.size(), hipMemcpyHostToDevice));
+    FTCC_LEGACY(hipMemcpy(d_ps, ps.data(), sizeof(TauProblem) * ps.size(), hipMemcpyHostToDevice));
+    FTCC_LEGACY(hipMemcpy(d_pre, prefix.data(), sizeof(int) * prefix.size(), hipMemcpyHostToDevice));
     it = c->tau_cache.emplace(key, std::make_pair(d_ps, d_pre)).first;
     c->tau_shape[key] = std::make_pair((int)ps.size(), total);
   }
@@ -1840,9 +1841,9 @@ int ftcc_set_hamiltonian(ftcc_ctx* c, int i, int n, const double* h, const doubl
       I.eri = c->dalloc(n4);
       I.eps = c->dalloc(n);
     }
-    FTCC_HIP(hipMemcpy(I.h, h, sizeof(double) * n2, hipMemcpyHostToDevice));
-    FTCC_HIP(hipMemcpy(I.eri, eri, sizeof(double) * n4, hipMemcpyHostToDevice));
-    FTCC_HIP(hipMemcpy(I.eps, eps, sizeof(double) * n, hipMemcpyHostToDevice));
+    FTCC_LEGACY(hipMemcpy(I.h, h, sizeof(double) * n2, hipMemcpyHostToDevice));
+    FTCC_LEGACY(hipMemcpy(I.eri, eri, sizeof(double) * n4, hipMemcpyHostToDevice));
+    FTCC_LEGACY(hipMemcpy(I.eps, eps, sizeof(double) * n, hipMemcpyHostToDevice));
     I.eps_host.assign(eps, eps + n);
     if (c->built && momentum_on(c)) {   // a new Hamiltonian must keep the declared conservation law
       check_momentum(c, i, I.h, 2, "h");
@@ -1915,7 +1916,7 @@ int ftcc_solve_amplitudes(ftcc_ctx* c, const double* mu, const double* beta, int
     for (int i = 0; i < B; ++i) {
       Instance& I = c->inst[i];
       double mf[5];
-      FTCC_HIP(hipMemcpy(mf, I.mf, sizeof(mf), hipMemcpyDeviceToHost));
+      FTCC_LEGACY(hipMemcpy(mf, I.mf, sizeof(mf), hipMemcpyDeviceToHost));
       I.omega0 = mf[0];
       I.omega1 = mf[1];
       if (!c->rk && !c->simpson) {
@@ -2206,7 +2207,7 @@ static void ensure_resp_groups(ftcc_ctx* c) {
   }
   auto up = [c](const void* h, size_t bytes) {
     double* d = c->dalloc((bytes + 7) / 8);
-    FTCC_HIP(hipMemcpy(d, h, bytes, hipMemcpyHostToDevice));
+    FTCC_LEGACY(hipMemcpy(d, h, bytes, hipMemcpyHostToDevice));
     return (void*)d;
   };
   c->d_resp_w = (double*)up(w.data(), sizeof(double) * w.size());
@@ -2268,13 +2269,13 @@ int ftcc_response(ftcc_ctx* c, double* dO_dmu, double* dO_dbeta, double* dO_dh, 
         if (deri_dtheta && deri_dtheta[i]) {
           FTCC_HIP(hipMalloc((void**)&d_deri[i], sizeof(double) * n4));
           tmp.push_back(d_deri[i]);
-          FTCC_HIP(hipMemcpy(d_deri[i], deri_dtheta[i], sizeof(double) * n4, hipMemcpyHostToDevice));
+          FTCC_LEGACY(hipMemcpy(d_deri[i], deri_dtheta[i], sizeof(double) * n4, hipMemcpyHostToDevice));
           if (momentum_on(c)) check_momentum(c, i, d_deri[i], 4, "deri_dtheta");
         }
         if (dh_dtheta && dh_dtheta[i]) {
           FTCC_HIP(hipMalloc((void**)&d_dh[i], sizeof(double) * n2));
           tmp.push_back(d_dh[i]);
-          FTCC_HIP(hipMemcpy(d_dh[i], dh_dtheta[i], sizeof(double) * n2, hipMemcpyHostToDevice));
+          FTCC_LEGACY(hipMemcpy(d_dh[i], dh_dtheta[i], sizeof(double) * n2, hipMemcpyHostToDevice));
           if (momentum_on(c)) check_momentum(c, i, d_dh[i], 2, "dh_dtheta");
         }
       }

@@ -85,11 +85,11 @@ void expsum_run(ftcc_ctx* c, long key, const std::function<ExpSpec(int)>& spec) 
     for (size_t q = 0; q < ps.size(); ++q) {
       ps[q].terms = d_terms + k;
       if (!terms[q].empty())
-        FTCC_HIP(hipMemcpy(d_terms + k, terms[q].data(), terms[q].size() * sizeof(ExpTerm), hipMemcpyHostToDevice));
+        FTCC_LEGACY(hipMemcpy(d_terms + k, terms[q].data(), terms[q].size() * sizeof(ExpTerm), hipMemcpyHostToDevice));
       k += terms[q].size();
     }
-    FTCC_HIP(hipMemcpy(d_ps, ps.data(), ps.size() * sizeof(ExpSumProblem), hipMemcpyHostToDevice));
-    FTCC_HIP(hipMemcpy(d_pre, prefix.data(), prefix.size() * sizeof(int), hipMemcpyHostToDevice));
+    FTCC_LEGACY(hipMemcpy(d_ps, ps.data(), ps.size() * sizeof(ExpSumProblem), hipMemcpyHostToDevice));
+    FTCC_LEGACY(hipMemcpy(d_pre, prefix.data(), prefix.size() * sizeof(int), hipMemcpyHostToDevice));
     it = c->sp_cache.emplace(key, SpLaunch{buf, (int)ps.size(), total}).first;
   }
   const SpLaunch& L = it->second;

@@ -197,3 +197,44 @@ def test_a_residual_leaves_the_other_nodes_and_instances_running(F, labels):
     b.close()
     for x, y in zip(out + list(r0) + list(r1), ref + list(again) + list(late)):
         assert np.array_equal(x, y)
+
+
+def test_contexts_on_several_threads(F):
+    """Contexts that are built and run on threads at the same time (their plans are captured as
+    graphs while other threads allocate and upload) give the bits of the same contexts one
+    after the other."""
+    import threading
+    jobs = [(fi.hubbard_config(L=7, U=2.0, T=1.0), True, {}), (fi.hubbard_config(L=6, U=2.0, T=1.0), False, {}),
+            (fi.hubbard_config(L=5, U=2.0, T=1.0), True, dict(propagator=4)),
+            (fi.hubbard_config(L=4, U=2.0, T=1.0), False, dict(propagator=5))]
+
+    def run(s, labels, opt):
+        ctx = F.Context(1, n_tau=8, nodes_per_panel=4, **opt)
+        if labels:
+            ctx.set_momentum(0, *s.momentum)
+        ctx.set_hamiltonian(0, s.h, s.eri, s.eps)
+        ctx.solve(s.mu, s.beta)
+        ctx.lam()
+        r = ctx.response(want_mu=True, want_beta=True, want_h=True)
+        out = [ctx.grand_potential()[0], r["mu"], r["beta"], r["h"][0]]
+        ctx.close()
+        return out
+
+    print("[batch] four contexts, one after the other and on threads", flush=True)
+    ref = [run(*j) for j in jobs]
+    for _ in range(3):
+        res = [None] * len(jobs)
+
+        def work(k):
+            try:
+                res[k] = run(*jobs[k])
+            except F.FTCCError as e:
+                res[k] = e
+        threads = [threading.Thread(target=work, args=(k,)) for k in range(len(jobs))]
+        for t in threads:
+            t.start()
+        for t in threads:
+            t.join()
+        for out, want in zip(res, ref):
+            assert isinstance(out, list), out
+            assert all(np.array_equal(a, b) for a, b in zip(out, want))
