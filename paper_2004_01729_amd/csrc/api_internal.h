@@ -111,7 +111,9 @@ struct ftcc_ctx {
   std::vector<InstMomentum> one_block;        // small dense problems: labels that put everything into one block
   std::unique_ptr<Executor> ex_main, ex_d, ex_g;   // ex_g: integral gradients (built on first use)
   std::map<std::pair<int, int>, double*> g_derived, g_cgrad;   // (tensor, problem) buffers of ex_g
-  bool buffers = false, built = false, solved = false, have_lambda = false;
+  // buffers: laid out; built: the executors too; planned: they were once (tables of their
+  // pointers are kept)
+  bool buffers = false, built = false, planned = false, solved = false, have_lambda = false;
   bool lean = false;   // the executors without optional buffers and over the residual's lean form
   // thermal set-up of all instances in one launch per stage
   SetupProblem* d_setup = nullptr;            // [B]

@@ -1099,7 +1099,7 @@ void build(ftcc_ctx* c) {
       set_program(c, true);
     }
   }
-  c->built = true;
+  c->built = c->planned = true;
 }
 
 // number of instances whose residual programs currently run
@@ -1802,7 +1802,7 @@ int ftcc_set_momentum(ftcc_ctx* c, int i, int n, int dims, const int* labels, co
   return run_guarded([&] {
     if (!c || !labels || !modulus) fail(FTCC_EINVAL, "null argument");
     if (i < 0 || i >= c->B) fail(FTCC_EINVAL, "instance index out of range");
-    if (c->built) fail(FTCC_ESTATE, "momentum labels must be set before the first solve");
+    if (c->planned) fail(FTCC_ESTATE, "momentum labels must be set before the first solve");
     if (n < 1 || n > 255) fail(FTCC_EINVAL, "n must be 1..255");
     if (dims < 1 || dims > 3) fail(FTCC_EINVAL, "dims must be 1..3");
     Instance& I = c->inst[i];
@@ -1811,6 +1811,7 @@ int ftcc_set_momentum(ftcc_ctx* c, int i, int n, int dims, const int* labels, co
       if (modulus[d] < 0) fail(FTCC_EINVAL, "modulus must be >= 0");
     for (long k = 0; k < (long)n * dims; ++k)
       if (labels[k] <= -(1 << 16) || labels[k] >= (1 << 16)) fail(FTCC_EINVAL, "labels must lie in (-65536, 65536)");
+    c->buffers = false;   // of a solve that found no memory: laid out for the labels it had
     I.mom.dims = dims;
     I.mom.modulus.assign(modulus, modulus + dims);
     I.mom.labels.assign(labels, labels + (long)n * dims);
@@ -1825,7 +1826,7 @@ int ftcc_set_hamiltonian(ftcc_ctx* c, int i, int n, const double* h, const doubl
     if (n < 1 || n > 256) fail(FTCC_EINVAL, "n must be 1..256");
     FTCC_HIP(hipSetDevice(c->device));
     Instance& I = c->inst[i];
-    if (c->built && n != I.n) fail(FTCC_EINVAL, "n cannot change after the first solve");
+    if (I.h && n != I.n) fail(FTCC_EINVAL, "n cannot change");
     const long n2 = (long)n * n, n4 = n2 * n2;
     for (long k = 0; k < n2; ++k)
       if (!std::isfinite(h[k])) fail(FTCC_EINVAL, "h has a non-finite entry");
@@ -1845,7 +1846,7 @@ int ftcc_set_hamiltonian(ftcc_ctx* c, int i, int n, const double* h, const doubl
     FTCC_LEGACY(hipMemcpy(I.eri, eri, sizeof(double) * n4, hipMemcpyHostToDevice));
     FTCC_LEGACY(hipMemcpy(I.eps, eps, sizeof(double) * n, hipMemcpyHostToDevice));
     I.eps_host.assign(eps, eps + n);
-    if (c->built && momentum_on(c)) {   // a new Hamiltonian must keep the declared conservation law
+    if (c->buffers && momentum_on(c)) {   // a new Hamiltonian must keep the declared conservation law
       check_momentum(c, i, I.h, 2, "h");
       check_momentum(c, i, I.eri, 4, "<pq|rs>");
     }

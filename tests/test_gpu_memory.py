@@ -205,3 +205,43 @@ def test_descriptors_of_a_small_context_are_small(F):
     for c in ctxs:
         c.close()
     assert own / 8 < 6 << 20
+
+
+def test_a_context_goes_on_after_a_solve_without_memory(F):
+    """A solve that finds no memory leaves a context that solves once there is some: with the
+    same labels, with labels set in between, and a Hamiltonian that breaks them is refused."""
+    h, eri, eps, mu, beta, momentum = _system("ring6")
+
+    def omega(labels, late=False, limit=None):
+        pool = Pool()
+        print(f"[memory] labels={labels} late={late} limit={limit}", flush=True)
+        ctx = _context(F, (h, eri, eps, mu, beta, None if late else momentum if labels else None), pool)
+        if limit is not None:
+            pool.limit = limit
+            with pytest.raises(F.FTCCError) as e:
+                ctx.solve(mu, beta)
+            assert e.value.code == F.ENOMEM
+            pool.limit = None
+        if late:
+            ctx.set_momentum(0, *momentum)
+        if limit is not None and labels and not late:
+            bad = eri.copy()
+            bad[0, 0, 0, 1] = 1.0
+            with pytest.raises(F.FTCCError):   # at once where the labels are laid out, else by the solve
+                ctx.set_hamiltonian(0, h, bad, eps)
+                ctx.solve(mu, beta)
+            with pytest.raises(F.FTCCError):
+                ctx.set_hamiltonian(0, h[:5, :5], eri[:5, :5, :5, :5], eps[:5])
+            ctx.set_hamiltonian(0, h, eri, eps)
+        ctx.solve(mu, beta)
+        out = [ctx.grand_potential()[0], *ctx.amplitudes(0, 1)]
+        ctx.close()
+        return out
+
+    for labels in (True, False):
+        ref = omega(labels)
+        # 128 MiB of what a context holds are one workspace: limits before it, and among what
+        # comes after it, the executors' buffers last
+        for limit in (1 << 20, 134_800_000, 135_050_000 if labels else 135_300_000):
+            for late in ((False, True) if labels else (False,)):
+                _close(omega(labels, late, limit), ref)
